@@ -15,6 +15,7 @@ from __future__ import annotations
 import math
 
 import torch
+import torch.utils.checkpoint
 
 import armt_synth as S
 import paper_2506_05229_amd as P
@@ -110,27 +111,28 @@ def _dims(s):
             "wgate": (F, d), "wup": (F, d), "wdown": (d, F), "wm_q": (dm, d), "wm_k": (dm, d), "wm_v": (d, d), "wm_b": (1, d)}
 
 
-def prepare(case, seed):
-    """Inputs and the model a user's program holds: weights ~ N(0, 0.02^2), gains ~ N(1, 0.1^2), embeddings ~ N(0, 1)."""
+def _drawer(seed, dt):
     gen = torch.Generator(device="cuda").manual_seed(int(seed))
-    shape = _shape(case)
-    dt = torch.bfloat16 if shape.dtype == "bf16" else torch.float32
 
     def normal(dims, std=1.0, mean=0.0, dtype=dt):
         return torch.randn(dims, generator=gen, device="cuda", dtype=torch.float32).mul_(std).add_(mean).to(dtype)
 
-    st = {"kind": case["kind"], "case": dict(case), "shape": shape}
-    if case["kind"] in ("prompt", "head"):
-        vocab = case.get("vocab", S.LLAMA3_VOCAB)
-        table = normal((vocab, shape.d_model)) if case["kind"] == "prompt" else torch.zeros((1, shape.d_model), dtype=dt, device="cuda")
-        st["ends"] = P.TokenEnds(shape, table, normal((shape.d_model,), 0.1, 1.0), normal((vocab, shape.d_model), 0.02))
-        if case["kind"] == "head":
-            st["hidden"] = normal((case["rows"], shape.d_model), 3.0)
-            # gradient of a mean loss over the rows
-            st["d_logits"] = normal((case["rows"], vocab), 1.0 / case["rows"], dtype=torch.float32)
-            st["grads"] = (torch.zeros(shape.d_model, device="cuda"), torch.zeros((vocab, shape.d_model), device="cuda"))
-            return st
-        st["ids"] = torch.randint(0, vocab, (shape.n_tokens,), generator=gen, device="cuda", dtype=torch.int32)
+    return gen, normal
+
+
+def _ends(case, shape, normal):
+    """Embedding table (prompts only), final gain and head weight."""
+    vocab = case.get("vocab", S.LLAMA3_VOCAB)
+    table = normal((vocab, shape.d_model)) if case["kind"] == "prompt" else None
+    return table, normal((shape.d_model,), 0.1, 1.0), normal((vocab, shape.d_model), 0.02)
+
+
+def _head_inputs(case, shape, normal):
+    """Hidden states and the gradient of a mean loss over the rows."""
+    return normal((case["rows"], shape.d_model), 3.0), normal((case["rows"], case["vocab"]), 1.0 / case["rows"], dtype=torch.float32)
+
+
+def _weights(shape, normal):
     layers = []
     for _ in range(shape.n_layers):
         lw = {}
@@ -138,18 +140,47 @@ def prepare(case, seed):
             scale = {"wm_k": shape.mem_k_scale, "wm_v": shape.mem_v_scale}.get(f, 1.0)
             lw[f] = normal(dims, 0.1, 1.0) if f.startswith("rms") else normal(dims, 0.02 * scale)
         layers.append(lw)
-    st["model"] = P.Armt(shape, layers, normal((shape.n_mem, shape.d_model), 0.02))
-    if case["kind"] == "prompt":
-        return st
+    return layers, normal((shape.n_mem, shape.d_model), 0.02)
+
+
+def _sequences(case, shape, normal):
+    """Token embeddings; for a carried-in state also the three segments in front of them."""
     B = case.get("batch", 1)
     lead = (B,) if case["kind"] == "batched" or B > 1 else ()
-    st["x"] = normal(lead + (shape.n_tokens, shape.d_model))
-    if case.get("carry"):
+    x = normal(lead + (shape.n_tokens, shape.d_model))
+    first = normal((3 * shape.seg_len, shape.d_model)) if case.get("carry") else None
+    return x, first, normal(lead + (shape.n_tokens, shape.d_model)) if case["kind"] == "train" else None
+
+
+def _act_type(shape):
+    return torch.bfloat16 if shape.dtype == "bf16" else torch.float32
+
+
+def prepare(case, seed):
+    """Inputs and the model a user's program holds: weights ~ N(0, 0.02^2), gains ~ N(1, 0.1^2), embeddings ~ N(0, 1)."""
+    shape = _shape(case)
+    gen, normal = _drawer(seed, _act_type(shape))
+    st = {"kind": case["kind"], "case": dict(case), "shape": shape}
+    if case["kind"] in ("prompt", "head"):
+        table, gain, w_lm = _ends(case, shape, normal)
+        if table is None:
+            table = torch.zeros((1, shape.d_model), dtype=_act_type(shape), device="cuda")
+        st["ends"] = P.TokenEnds(shape, table, gain, w_lm)
+        if case["kind"] == "head":
+            st["hidden"], st["d_logits"] = _head_inputs(case, shape, normal)
+            st["grads"] = (torch.zeros(shape.d_model, device="cuda"), torch.zeros((case["vocab"], shape.d_model), device="cuda"))
+            return st
+        st["ids"] = torch.randint(0, S.LLAMA3_VOCAB, (shape.n_tokens,), generator=gen, device="cuda", dtype=torch.int32)
+    layers, mem_emb = _weights(shape, normal)
+    st["model"] = P.Armt(shape, layers, mem_emb)
+    if case["kind"] == "prompt":
+        return st
+    st["x"], first, d_hidden = _sequences(case, shape, normal)
+    if first is not None:
         # a state as earlier segments leave it: the state after three other segments (one pass of the library itself)
-        first = normal((3 * shape.seg_len, shape.d_model))
         _, st["A"], st["z"] = st["model"].forward(first, diagonal=True)
     if case["kind"] == "train":
-        st["d_hidden"] = normal(lead + (shape.n_tokens, shape.d_model))
+        st["d_hidden"] = d_hidden
         # one buffer per kind of weight over the layers, as an optimizer that works on flat parameters keeps them
         st["flat"] = {f: torch.zeros((shape.n_layers,) + dims, device="cuda") for f, dims in _dims(shape).items()}
         st["d_mem_emb"] = torch.zeros((shape.n_mem, shape.d_model), device="cuda")
@@ -184,6 +215,120 @@ def run(st):
     return hidden, A, z, st["flat"], out["mem_emb"], out["x"]
 
 
+# ---- the same passes from the definition, in 64 bits
+
+def _norm64(x, gain, eps):
+    return x * torch.rsqrt((x * x).mean(-1, keepdim=True) + eps) * gain
+
+
+def _dpfp64(k, nu):
+    r = torch.cat([k.clamp_min(0), (-k).clamp_min(0)], -1)
+    return torch.cat([r * r.roll(j, -1) for j in range(1, nu + 1)], -1)
+
+
+def _attention64(q, k, v):
+    """Causal, grouped heads; q [T, H, dh], a block of query rows at a time."""
+    T, H, dh = q.shape
+    k, v = (t.repeat_interleave(H // t.shape[1], 1).transpose(0, 1).contiguous() for t in (k, v))
+    rows = max(64, int(2 ** 27 / (H * T)))
+    out = []
+    for i in range(0, T, rows):
+        e = min(T, i + rows)
+        score = torch.matmul(q[i:e].transpose(0, 1), k[:, :e].transpose(1, 2).contiguous()) / math.sqrt(dh)
+        ahead = torch.arange(e, device=q.device)[None, :] > torch.arange(i, e, device=q.device)[:, None]
+        out.append(torch.matmul(score.masked_fill_(ahead, float("-inf")).softmax(-1), v[:, :e]).transpose(0, 1))
+    return torch.cat(out).reshape(T, H * dh)
+
+
+def _cell64(s, w, x, A, z, empty):
+    """One (layer, segment) cell: read, decoder block, delta-rule update.  Returns (output rows, A, z)."""
+    T, H, G, dh = x.shape[0], s.n_heads, s.n_kv_heads, s.head_dim
+    w = {f: t.double() for f, t in w.items()}
+    if not empty:
+        f = _dpfp64(x @ w["wm_q"].T, s.dpfp_nu)
+        x = x + (f @ A.T) / (f @ z + s.assoc_eps)[:, None]
+    n = _norm64(x, w["rms1"], s.rms_eps)
+    at = torch.arange(T, device=x.device, dtype=torch.float64)[:, None]
+    angle = at * float(s.rope_theta) ** (-2.0 * torch.arange(dh // 2, device=x.device, dtype=torch.float64) / dh)
+    cos, sin = angle.cos()[:, None], angle.sin()[:, None]
+
+    def rotated(t):
+        a, b = t[..., :dh // 2], t[..., dh // 2:]
+        return torch.cat([a * cos - b * sin, b * cos + a * sin], -1)
+
+    q, k, v = ((n @ w[f].T).reshape(T, heads, dh) for f, heads in (("wq", H), ("wk", G), ("wv", G)))
+    x = x + _attention64(rotated(q), rotated(k), v) @ w["wo"].T
+    n = _norm64(x, w["rms2"], s.rms_eps)
+    x = x + (torch.nn.functional.silu(n @ w["wgate"].T) * (n @ w["wup"].T)) @ w["wdown"].T
+    y = x[s.seg_len:]
+    f, v = _dpfp64(y @ w["wm_k"].T, s.dpfp_nu), y @ w["wm_v"].T
+    zf = f @ z
+    old = 0.0 if empty else (f @ A.T) / (zf + s.assoc_eps)[:, None]
+    beta = torch.sigmoid(y @ w["wm_b"][0])[:, None]
+    return x, A + (beta * (v - old)).T @ f, z + (1.0 - zf / ((f * f).sum(-1) + s.assoc_eps)) @ f
+
+
+def _forward64(s, layers, mem_emb, x, state=None, recompute=False):
+    """(hidden, A [layers], z [layers]); recompute keeps only the cells' inputs for the gradients."""
+    dev, empty = x.device, state is None
+    A, z = state or ([torch.zeros(s.d_model, s.phi, dtype=torch.float64, device=dev)] * s.n_layers,
+                     [torch.zeros(s.phi, dtype=torch.float64, device=dev)] * s.n_layers)
+    A, z, hidden = list(A), list(z), []
+    for i in range(0, x.shape[0], s.seg_len):
+        rows = torch.cat([x[i:i + s.seg_len].double(), mem_emb.double()])
+        for l, w in enumerate(layers):
+            args = (s, w, rows, A[l], z[l], empty and i == 0)
+            rows, A[l], z[l] = torch.utils.checkpoint.checkpoint(_cell64, *args, use_reentrant=False) if recompute else _cell64(*args)
+        hidden.append(rows[:s.seg_len])
+    return torch.cat(hidden), torch.stack(A), torch.stack(z)
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits; None where that would take long."""
+    s = _shape(case)
+    if case["kind"] != "head" and work(case)["flops"] * (4 / 3 if case["kind"] == "train" else 1) > 1.5e14:
+        return None
+    gen, normal = _drawer(seed, _act_type(s))
+    if case["kind"] in ("prompt", "head"):
+        table, gain, w_lm = _ends(case, s, normal)
+    if case["kind"] == "head":
+        hidden, d_logits = _head_inputs(case, s, normal)
+        h, g, w = (t.double().requires_grad_() for t in (hidden, gain, w_lm))
+        logits = _norm64(h, g, s.rms_eps) @ w.T
+        return logits.detach(), torch.autograd.grad(logits, (h, g, w), d_logits.double())
+    if case["kind"] == "prompt":
+        ids = torch.randint(0, S.LLAMA3_VOCAB, (s.n_tokens,), generator=gen, device="cuda", dtype=torch.int32)
+        layers, mem_emb = _weights(s, normal)
+        hidden, A, z = _forward64(s, layers, mem_emb, table[ids.long()])
+        return hidden, A, z, _norm64(hidden[-case["rows"]:], gain.double(), s.rms_eps) @ w_lm.double().T
+    layers, mem_emb = _weights(s, normal)
+    x, first, d_hidden = _sequences(case, s, normal)
+    if case["kind"] == "forward":
+        state = None if first is None else _forward64(s, layers, mem_emb, first)[1:]
+        return _forward64(s, layers, mem_emb, x, state)
+    if case["kind"] == "batched":
+        return tuple(torch.stack(t) for t in zip(*(_forward64(s, layers, mem_emb, xb) for xb in x)))
+    layers = [{f: t.double().requires_grad_() for f, t in w.items()} for w in layers]
+    mem_emb = mem_emb.double().requires_grad_()
+    out, d_x = [], []
+    leaves = [mem_emb] + [t for w in layers for t in w.values()]
+    sums = [torch.zeros_like(t) for t in leaves]
+    for xb, db in zip(x, d_hidden) if x.dim() == 3 else [(x, d_hidden)]:
+        xb = xb.double().requires_grad_()
+        res = _forward64(s, layers, mem_emb, xb, recompute=True)
+        grads = torch.autograd.grad(res[0], leaves + [xb], db.double(), allow_unused=True)
+        for total, g in zip(sums, grads):
+            if g is not None:
+                total += g
+        out.append([t.detach() for t in res])
+        d_x.append(grads[-1])
+    hidden, A, z = (torch.stack(t) if x.dim() == 3 else t[0] for t in zip(*out))
+    flat = {f: torch.stack([sums[1 + l * len(w) + i] for l, w in enumerate(layers)]) for i, f in enumerate(layers[0])}
+    if s.dtype == "bf16":
+        flat["wm_k"] = None     # its denominators are as small as assoc_eps: bf16 operands leave this gradient one digit (0.14 off)
+    return hidden, A, z, flat, sums[0], torch.stack(d_x) if x.dim() == 3 else d_x[0]
+
+
 def work(case):
     """Bytes: weights, inputs, states and results once.  Flops: the products of the definition (causal attention counts the
     lower triangle), times three for a training step."""
@@ -214,5 +359,6 @@ def tolerance(case):
         # plain fp32-FMA kernels on the same bf16 operands against the matrix-core path: 6e-6, largest element 4e-5
         return {"rel": 3e-5, "max": 2e-4}
     # the same comparison for a whole model: hidden states 1.2e-2 (1B) and 2.2e-2 (3B), A 5e-2, largest element 0.7; a
-    # difference of one bf16 rounding in an early layer reaches all later ones.  Stated below what that would allow.
-    return {"rel": 0.03, "max": 0.9}
+    # difference of one bf16 rounding in an early layer reaches all later ones.  Against 64 bits: hidden states 0.8e-2 (1B)
+    # and 1.5e-2 (3B), A 3.5e-2 and 6e-2; gradients 1.5e-2 to 7e-2, that of wm_k 0.14.
+    return {"rel": 0.25, "max": 0.95} if case["kind"] == "train" else {"rel": 0.1, "max": 0.9}
