@@ -16,6 +16,7 @@
 #include "attention_mfma.h"
 #include "backward_kernels.h"
 #include "common.h"
+#include "gemm_f32.h"
 #include "gemm_generic.h"
 #include "gemm_mfma.h"
 #include "rowwise_kernels.h"
@@ -304,6 +305,8 @@ armt_status gemm(hipStream_t st, const GemmGroup* table, int first, int g, const
   const bool timed = prof_start(s.tag, st);
   if (std::is_same<T, bf16>::value && !debug_generic()) {
     HIP_TRY(launch_gemm_mfma(table, first, g, s, st, g_gemm_tile_config));
+  } else if (std::is_same<T, float>::value) {
+    HIP_TRY(launch_gemm_f32(table, first, g, s, st));
   } else {
     HIP_TRY(launch_gemm_generic<T>(table, first, g, s, st));
   }

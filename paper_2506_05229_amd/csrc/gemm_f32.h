@@ -1,0 +1,190 @@
+// Grouped GEMM of the fp32 configurations on the matrix cores: v_mfma_f32_16x16x4_f32 multiplies and adds in fp32.
+//
+// These problems are small (a cell of the fp32 configuration is 72 x 128 ... 512 with K = 128 ... 512) and what bounds a launch is one
+// chain of memory latencies, not arithmetic: with 64 x 64 tiles staged through LDS in k-steps of 16 the down projection (K = 512)
+// went through 32 of them.  Here a workgroup owns a 32 x 32 tile (16 x 32 for at most 16 rows), its four waves a quarter of K each,
+// and a wave loads its operands straight into registers, F32_CH chunks of 16 k ahead: a lane holds four consecutive k of one row, and
+// the i-th of four MFMAs takes element i of either operand (the products of a chunk are summed in that order on both sides).  The four
+// partial tiles are added in wave order through LDS, so a result depends on K alone.
+//
+// Against the plain FMA kernel, us per launch: 4 x (72 x 256, K 128) 19.9 -> 13.9, 4 x (72 x 128, K 512) 61.3 -> 14.4, 4 x (512 x 128,
+// K 2560) 313 -> 51, 1040 x 2048 x 2048 561 -> 226, 4096 x 4096 x 1024 1350 -> 824; error against 64 bits half as large (sums of
+// a quarter of the length).  Only many tiles whose rows cannot be read 16 bytes at a time stay with the other kernel
+// (launch_gemm_f32): 4 x (1000 x 1000, K 333) 127 us there, 144 here.
+#pragma once
+
+#include "common.h"
+#include "gemm_generic.h"
+
+namespace armt {
+
+constexpr int F32_CH = 4;      // chunks of 16 k per batch of loads
+
+// grid: (ceil(N / 32), ceil(M / (16 TM)), g); block: 256.
+template <int TM, bool SWIGLU>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s) {
+  constexpr int TN = 2, NB = SWIGLU ? 2 : 1, BM = 16 * TM, BN = 16 * TN, LD = BN + 4;
+  __shared__ __align__(16) float part[NB][4][BM][LD];
+  const GemmGroup g = table[first + blockIdx.z];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, q = lane >> 4;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  // 16-byte loads need 16-byte aligned rows and a K that ends with one; anything else is read element by element
+  const bool wide = (((uintptr_t)g.A | (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)g.B2) & 15) == 0 &&
+                    ((s.K | s.lda | s.ldb) & 3) == 0;
+  const float* a[TM];
+  const float* b[NB][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) a[i] = (const float*)g.A + (size_t)min(m0 + 16 * i + r16, s.M - 1) * s.lda;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = min(n0 + 16 * j + r16, s.N - 1);       // rows past the edges repeat the last one; masked on store
+    if (SWIGLU) {
+      b[0][j] = (const float*)g.B0 + (size_t)n * s.ldb;
+      b[NB - 1][j] = (const float*)g.B1 + (size_t)n * s.ldb;
+    } else {
+      b[0][j] = weight_row<float>(g, s, n);
+    }
+  }
+  auto load = [&](const float* row, int k) __attribute__((always_inline)) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (wide) {
+      if (k < s.K) v = *(const f32x4*)(row + k);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k + e < s.K) v[e] = row[k + e];
+    }
+    return v;
+  };
+  // this thread's four results, and what their epilogue reads: requested together with the operands
+  const int row = tid >> 3, col = (tid & 7) * 4, m = m0 + row, n = n0 + col;
+  const bool mine = row < BM && m < s.M && n < s.N;
+  const bool wide_out = n + 3 < s.N && ((s.ldc | s.ldr | s.ldc2) & 3) == 0 &&
+                        (((uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.R) & 15) == 0;
+  f32x4 res = {0.f, 0.f, 0.f, 0.f};
+  float rs = 1.f;
+  if (mine) {
+    if (g.rowscale) rs = g.rowscale[m];
+    if (s.epi == EPI_RESID_F32 && g.R) {
+      const float* r = g.R + (size_t)m * s.ldr + n;
+      if (wide_out) {
+        res = *(const f32x4*)r;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < s.N) res[e] = r[e];
+      }
+    }
+  }
+  f32x4 acc[NB][TM][TN];
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[u][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int chunks = (s.K + 15) >> 4, per = (chunks + 3) >> 2;
+  const int c0 = min(wave * per, chunks), c1 = min(c0 + per, chunks);
+  struct Batch { f32x4 a[F32_CH][TM], b[F32_CH][NB][TN]; };
+  auto fetch = [&](Batch& t, int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < F32_CH; ++h) {
+      const int k = c + h < c1 ? 16 * (c + h) + 4 * q : s.K;      // past this wave's share: zeros
+#pragma unroll
+      for (int i = 0; i < TM; ++i) t.a[h][i] = load(a[i], k);
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) t.b[h][u][j] = load(b[u][j], k);
+    }
+  };
+  auto multiply = [&](const Batch& t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < F32_CH; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[u][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.a[h][i][e], t.b[h][u][j][e], acc[u][i][j], 0, 0, 0);
+  };
+  Batch t0, t1;
+  if (c0 < c1) fetch(t0, c0);
+  for (int c = c0; c < c1; c += 2 * F32_CH) {
+    const bool two = c + F32_CH < c1;
+    if (two) fetch(t1, c + F32_CH);
+    multiply(t0);
+    if (c + 2 * F32_CH < c1) fetch(t0, c + 2 * F32_CH);
+    if (two) multiply(t1);
+  }
+  // a 16 x 16 result block has lane = column lane % 16 and registers = rows 4 * (lane / 16) + r
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[u][wave][16 * i + 4 * q + r][16 * j + r16] = acc[u][i][j][r];
+  __syncthreads();
+  if (!mine) return;
+  auto total = [&](int u) {
+    f32x4 v = *(const f32x4*)&part[u][0][row][col];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += *(const f32x4*)&part[u][w][row][col];
+    return v;
+  };
+  f32x4 v = total(0), v2;
+  if (SWIGLU) {
+    const f32x4 up = total(NB - 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float gv = v[e] * rs;
+      v[e] = gv / (1.f + expf(-gv)) * (up[e] * rs);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = res[e] + v[e] * rs;      // res: zeros without a residual
+  }
+  const bool copy = s.epi == EPI_RESID_F32 && g.C2;
+  if (copy) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v2[e] = g.gain ? v[e] * ((const float*)g.gain)[min(n + e, s.N - 1)] : v[e];
+  }
+  float* out = (float*)g.C + (size_t)m * s.ldc + n;
+  float* out2 = (float*)g.C2 + (size_t)m * s.ldc2 + n;
+  if (wide_out) {
+    *(f32x4*)out = v;
+    if (copy) *(f32x4*)out2 = v2;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (n + e >= s.N) break;
+      out[e] = v[e];
+      if (copy) out2[e] = v2[e];
+    }
+  }
+}
+
+inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, const GemmShape& s, hipStream_t st) {
+  if (g <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
+  if (((s.K | s.lda | s.ldb) & 3) && (int64_t)g * ((s.M + 63) / 64) * ((s.N + 63) / 64) >= 512)
+    return launch_gemm_generic<float>(table, first, g, s, st);
+  const bool swiglu = s.epi == EPI_SWIGLU;
+  const int bm = s.M <= 16 ? 16 : 32;
+  const dim3 grid((s.N + 31) / 32, (s.M + bm - 1) / bm, g);
+  if (bm == 16) {
+    if (swiglu) gemm_f32_kernel<1, true><<<grid, 256, 0, st>>>(table, first, s);
+    else gemm_f32_kernel<1, false><<<grid, 256, 0, st>>>(table, first, s);
+  } else {
+    if (swiglu) gemm_f32_kernel<2, true><<<grid, 256, 0, st>>>(table, first, s);
+    else gemm_f32_kernel<2, false><<<grid, 256, 0, st>>>(table, first, s);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace armt

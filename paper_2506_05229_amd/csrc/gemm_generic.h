@@ -1,6 +1,6 @@
 // Grouped GEMM, plain fp32 FMA version: any M, N, K, any activation type.
-// This is the fp32 path (fp32 configurations need true fp32 products, which the bf16 matrix
-// cores cannot give) and the shape-agnostic reference the MFMA kernel is checked against.
+// The shape-agnostic reference the matrix-core kernels are checked against, and the fp32 path of large problems whose
+// rows are not aligned to 16 bytes.
 #pragma once
 
 #include "common.h"

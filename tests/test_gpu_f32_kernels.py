@@ -1,0 +1,60 @@
+"""The fp32 grouped GEMM and the delta rule with fewer than 16 memory tokens at the sizes where their tiles, K shares and
+vector loads end."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+import armt_synth as S
+import paper_2506_05229_amd as P
+from oracle import armt_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("g, M, N, K, shift", [
+    (1, 1, 1, 1, 0),
+    (2, 16, 32, 16, 0),         # 16-row tile, one chunk of K: three waves without work
+    (1, 17, 33, 60, 0),         # one row and column into the next tile, K ends inside a chunk
+    (3, 31, 160, 67, 0),        # K not a multiple of 4: element-wise reads
+    (2, 72, 128, 512, 0),
+    (2, 72, 128, 512, 1),       # rows that start 4 bytes past a 16-byte boundary
+    (1, 33, 40, 2116, 0),       # shares of 33 chunks: several batches and a partial one
+    (4, 700, 1000, 333, 0),     # many tiles of rows that cannot be read 16 bytes at a time
+])
+def test_f32_gemm(g, M, N, K, shift):
+    gen = torch.Generator(device="cuda").manual_seed(M * N + K)
+
+    def mat(r, c):
+        return torch.randn(r * c + shift, device="cuda", generator=gen)[shift:].view(r, c)
+
+    a, b = [mat(M, K) for _ in range(g)], [mat(N, K) for _ in range(g)]
+    out = P.grouped_gemm(a, b, [torch.full((M, N), float("nan"), device="cuda") for _ in range(g)])
+    for i in range(g):
+        want = a[i].double() @ b[i].double().T
+        # K fp32 products and sums: at most (K + 1) 2^-24 of the sum of the products' magnitudes
+        bound = (K + 1) * 2.0 ** -24 * (a[i].double().abs() @ b[i].double().abs().T)
+        assert ((out[i].double() - want).abs() <= bound + 1e-30).all(), i
+
+
+@pytest.mark.parametrize("n_mem, d_mem", [(1, 32), (5, 32), (15, 64), (16, 32)])
+@pytest.mark.parametrize("d_model", [128, 200])
+def test_delta_rule_few_tokens(n_mem, d_mem, d_model):
+    g = 3
+    shape = S.get_shape("tiny").replace(n_layers=g, d_model=d_model, n_heads=4, n_kv_heads=2, head_dim=d_model // 4, n_mem=n_mem,
+                                        d_mem=d_mem)
+    rng = np.random.default_rng(n_mem)
+    w = [{"wm_k": rng.standard_normal((d_mem, d_model)) * 0.05, "wm_v": rng.standard_normal((d_model, d_model)) * 0.1,
+          "wm_b": rng.standard_normal((1, d_model)) * 0.1} for _ in range(g)]
+    ym = rng.standard_normal((g, n_mem, d_model))
+    A, z = rng.standard_normal((g, d_model, shape.phi)) * 0.1, rng.random((g, shape.phi)) + 0.1
+    w = [{k: v.astype(np.float32) for k, v in wi.items()} for wi in w]
+    ym, A, z = (t.astype(np.float32) for t in (ym, A, z))
+    dev = lambda t: torch.as_tensor(t).cuda()
+    Ad, zd = dev(A), dev(z)
+    P.ArmtSteps(shape).assoc_update(dev(ym), *[[dev(w[i][f]) for i in range(g)] for f in ("wm_k", "wm_v", "wm_b")], Ad, zd)
+    for i in range(g):
+        wA, wz = O.assoc_update(*(t[i].astype(np.float64) for t in (ym, A, z)), False,
+                                {k: v.astype(np.float64) for k, v in w[i].items()}, shape.assoc_eps, shape.dpfp_nu)
+        # sums of d_model and Phi fp32 products, squared once by the feature map
+        for got, want in ((Ad[i], wA), (zd[i], wz)):
+            assert np.linalg.norm(got.cpu().numpy() - want) <= 1e-5 * np.linalg.norm(want)
