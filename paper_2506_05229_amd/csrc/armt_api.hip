@@ -368,11 +368,12 @@ armt_status step_assoc_update(hipStream_t st, const GemmGroup* t_mkv, const Gemm
   prof_stop(timed, st, g);
   HIP_TRY(hipGetLastError());
   timed = prof_start(PK_DELTA_RULE, st);
-  if (m == 16 && Phi % 64 == 0 && Phi <= 512) {
-    const int rows_per_block = 32;
+  if (m <= 16 && Phi % 64 == 0 && Phi <= 512) {
+    // A block needs the 4 m Phi bytes of phi(k) once; fewer rows per block while the launch has less than two blocks per CU
+    const int rows_per_block = (int64_t)g * ((d + 31) / 32) >= 2 * MF_CUS ? 32 : 8;
     const dim3 grid((d + rows_per_block - 1) / rows_per_block, g);
 #define ARMT_DELTA16(NPL) \
-  case NPL: delta_rule16_kernel<NPL><<<grid, 256, 0, st>>>(KVm, Fm, Coef, aux, first, d, dm, rows_per_block); break;
+  case NPL: delta_rule16_kernel<NPL><<<grid, 256, 0, st>>>(KVm, Fm, Coef, aux, first, m, d, dm, rows_per_block); break;
     switch (Phi / 64) {
       ARMT_DELTA16(1) ARMT_DELTA16(2) ARMT_DELTA16(3) ARMT_DELTA16(4) ARMT_DELTA16(5) ARMT_DELTA16(6) ARMT_DELTA16(7)
       ARMT_DELTA16(8)

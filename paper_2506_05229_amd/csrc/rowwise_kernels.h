@@ -323,28 +323,29 @@ __device__ __forceinline__ float dr_dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
 
-// Fast path of the delta rule for n_mem = 16 and Phi = 64 * NPL: phi(k_i) lives in registers (lane owns columns
+// Fast path of the delta rule for n_mem <= 16 and Phi = 64 * NPL (tokens past n_mem count as zeros): phi(k_i) lives in registers (lane owns columns
 // lane + 64 k), the 16 dot products of a row are reduced with a transposing butterfly (17 exchanges instead of
 // 16 full wave reductions; afterwards lane L holds the complete dot product for i = (L >> 2) & 15), and the 16
 // coefficients are broadcast through scalar registers.  grid: (ceil(d / rows_per_block), g), block: 256.
 template <int NPL>
 __global__ __launch_bounds__(256) void delta_rule16_kernel(const float* __restrict__ KV, const float* __restrict__ Fm,
                                                            const float* __restrict__ Coef,
-                                                           const LayerAux* __restrict__ aux, int first, int d, int dm,
+                                                           const LayerAux* __restrict__ aux, int first, int m, int d, int dm,
                                                            int rows_per_block) {
   constexpr int M = 16, Phi = 64 * NPL;
   const int l = first + blockIdx.y;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const float* Fl = Fm + (size_t)l * M * Phi;
-  const float* cf = Coef + (size_t)l * M * 4;
+  const float* Fl = Fm + (size_t)l * m * Phi;
+  const float* cf = Coef + (size_t)l * m * 4;
   float f[M][NPL];
 #pragma unroll
   for (int i = 0; i < M; ++i)
 #pragma unroll
-    for (int k = 0; k < NPL; ++k) f[i][k] = Fl[i * Phi + lane + 64 * k];
+    for (int k = 0; k < NPL; ++k) f[i][k] = i < m ? Fl[i * Phi + lane + 64 * k] : 0.f;
   const int mi = (lane >> 2) & 15;                 // the memory token whose dot product this lane ends up with
-  const float beta = cf[mi * 4 + 0], rden = cf[mi * 4 + 2];
-  const float* Vmi = KV + (size_t)l * M * (dm + d) + (size_t)mi * (dm + d) + dm;
+  const bool token = mi < m;
+  const float beta = token ? cf[mi * 4 + 0] : 0.f, rden = token ? cf[mi * 4 + 2] : 0.f;
+  const float* Vmi = KV + (size_t)l * m * (dm + d) + (size_t)(token ? mi : 0) * (dm + d) + dm;
   float* A = aux[l].A;
   bf16* A16 = aux[l].A16;
   const bool b3 = lane & 8, b2 = lane & 4;
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(256) void delta_rule16_kernel(const float* __restri
     float dot = (b2 ? q2[1] : q2[0]) + __shfl_xor(b2 ? q2[0] : q2[1], 4, kWave);
     dot += dr_dpp<0x4E>(dot);      // lane ^ 2
     dot += dr_dpp<0xB1>(dot);      // lane ^ 1
-    const float coef = beta * (vr - dot * rden);      // beta_i (v_i[r] - v_bar_i[r])
+    const float coef = token ? beta * (vr - dot * rden) : 0.f;      // beta_i (v_i[r] - v_bar_i[r])
     float upd[NPL] = {};
 #pragma unroll
     for (int i = 0; i < M; ++i) {
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(256) void delta_rule16_kernel(const float* __restri
     for (int k = 0; k < NPL; ++k) {
       float s = 0.f;
 #pragma unroll
-      for (int i = 0; i < M; ++i) s = fmaf(cf[i * 4 + 1], f[i][k], s);
+      for (int i = 0; i < M; ++i) s = fmaf(i < m ? cf[i * 4 + 1] : 0.f, f[i][k], s);
       z[lane + 64 * k] += s;
     }
   }
