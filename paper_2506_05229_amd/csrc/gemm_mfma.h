@@ -33,7 +33,7 @@ namespace armt {
 constexpr int MF_BK = 64;                 // k-tile (bf16 elements): 128 bytes per tile row
 constexpr int MF_ROW_BYTES = MF_BK * 2;
 constexpr int MF_CUS = 256;            // compute units of the chip: a round of one tile per unit
-constexpr int MF_NUM_CONFIGS = 7;         // tile configuration numbers of launch_gemm_mfma_epi lie below this
+constexpr int MF_NUM_CONFIGS = 9;         // tile configuration numbers of launch_gemm_mfma_epi lie below this
 
 // swizzle of the 16-byte chunk index inside a 128-byte tile row; depends on row bits 0..3 only
 __device__ __forceinline__ int mf_swz(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
@@ -984,7 +984,17 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
   // W_Q of the read with the feature map as its epilogue: one d_mem-wide tile column, so the workgroups are the M-tiles;
   // 32-row tiles put two or more workgroups on a CU, whose waves then fill each other's waits
   if (s.epi == EPI_DPFP_READ && s.M >= 64 && (long)g * ((s.M + 63) / 64) < 1024) return 4;
+  // Launches that leave a CU at most one workgroup wait for the latency of its copies: small tiles with a deep ring.
+  // us per launch, two stages of 128 x 128 -> here (1040 rows): attention output (N = K = 2048) of one cell 30.4 -> 24.8, two cells
+  // 36.4 -> 28.2; down (K = 8192) 108 -> 75, 112 -> 87; with more tiles than CUs the rings of four cost occupancy and
+  // lose (down, three cells: 138 against 154 and 210)
+  const auto tiles_of = [&](int bm) {
+    const long tm = (s.M > bm && s.M % bm == 16) ? s.M / bm : (s.M + bm - 1) / bm, cols = s.epi == EPI_SWIGLU ? 64 : 128;
+    return g * tm * ((s.N + cols - 1) / cols);
+  };
+  if (s.epi != EPI_DPFP_READ && tiles_of(64) <= MF_CUS) return 7;
   if (s.M < 96 || s.N < 96) return 2;
+  if (s.epi != EPI_DPFP_READ && tiles_of(128) <= MF_CUS) return 8;
   const int tm = (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256;
   const int bn_out = (s.epi == EPI_SWIGLU) ? 128 : 256;
   const long tiles = (long)g * tm * ((s.N + bn_out - 1) / bn_out);
@@ -1036,6 +1046,18 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
     case 6:   // as 1, copies addressed by scalar base + lane offset where the shape allows
       if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 2, 2, EPI, true>(table, first, g, s, st);
       return launch_mfma_cfg<128, 128, 2, 2, EPI>(table, first, g, s, st);
+    case 7:   // at most one workgroup per CU: nobody else fills the waits for a copy, so four k-tiles in LDS
+      if constexpr (EPI != EPI_DPFP_READ) {
+        if (mfma_regular_shape<64, 128, EPI>(s)) return launch_mfma_cfg<64, 128, 2, 2, EPI, true, 4>(table, first, g, s, st);
+        return launch_mfma_cfg<64, 128, 2, 2, EPI, false, 4>(table, first, g, s, st);
+      }
+      break;
+    case 8:   // the same for 128 x 128 tiles, eight waves
+      if constexpr (EPI != EPI_DPFP_READ) {
+        if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 4, 2, EPI, true, 4>(table, first, g, s, st);
+        return launch_mfma_cfg<128, 128, 4, 2, EPI, false, 4>(table, first, g, s, st);
+      }
+      break;
     default: break;
   }
   return launch_mfma_cfg<64, 128, 2, 2, EPI>(table, first, g, s, st);
