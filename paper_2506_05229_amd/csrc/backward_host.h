@@ -52,7 +52,7 @@ TrainLayout carve_train(const Dims& D) {
   // L = cells of a step (layers x batch): everything per cell; Lr = layers: weights, their gradients' window operands
   const size_t L = D.L, Lr = D.Lr, B = D.B, T = D.T, d = D.d, e = D.esz, F = D.F, Hd = (size_t)D.H * D.dh;
   o.Tp = round64(D.T); o.mp = round64(D.m); o.dmP = round64(D.dm); o.Kmkv = round64(D.dm + D.d);
-  o.nblk = (D.d + UB_ROWS - 1) / UB_ROWS;
+  o.nblk = (D.d + update_bwd_rows_per_block(D.d) - 1) / update_bwd_rows_per_block(D.d);
   o.Kw = WG_WIN * (int)B * o.Tp; o.Km = WG_WIN * (int)B * o.mp;
   // bf16 GEMM operands with T rows per cell end in padding rows, so that the grouped GEMM may read whole 256-row tiles
   const size_t LT = L * T + (D.bf16 ? padded_rows(D.T) - T : 0);
@@ -453,12 +453,13 @@ armt_status backward_group(const BCtx& c, int lo, int g, int gr, int slot) {
   // ---- memory update (Eq. 3-5)
   {
     const dim3 grid(o.nblk, g);
-    const size_t lds = (size_t)UB_M * (2 * Phi + 2) * 4;
+    const size_t lds = (size_t)UB_M * ((Phi + 63) / 64 * 64 + Phi + 2) * 4;
 #define ARMT_UB(NPL)                                                                                                      \
   case NPL:                                                                                                              \
     update_bwd_rows_kernel<NPL><<<grid, 256, lds, st>>>(c.at<float>(o.KVm), c.at<float>(o.Fm), c.at<float>(o.Coef),      \
                                                         c.at<float>(o.Aw), c.at<float>(o.DA), c.at<float>(o.Upd), c.at<float>(o.DV), \
-                                                        c.at<float>(o.Part), lo, D.m, D.d, D.dm, Phi);                   \
+                                                        c.at<float>(o.Part), lo, D.m, D.d, D.dm, Phi,                    \
+                                                        update_bwd_rows_per_block(D.d));                                       \
     break;
     switch ((Phi + 63) / 64) { ARMT_UB(1) ARMT_UB(2) ARMT_UB(3) ARMT_UB(4) ARMT_UB(5) ARMT_UB(6) ARMT_UB(7) ARMT_UB(8) }
 #undef ARMT_UB

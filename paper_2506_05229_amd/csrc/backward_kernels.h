@@ -5,6 +5,7 @@
 // attention backward and the backward of the delta rule.  Plain fp32 arithmetic throughout.
 #pragma once
 
+#include "attention_generic.h"
 #include "common.h"
 #include "rowwise_kernels.h"
 
@@ -295,6 +296,7 @@ __global__ __launch_bounds__(64) void attention_bwd_q_kernel(const T* __restrict
   const T* kbase = base + H * dh + kvh * dh;
   const T* vbase = base + (H + Hkv) * dh + kvh * dh;
   const size_t orow = ((size_t)l * Trows + i) * (H * dh) + h * dh;
+  const bool quads = quads_of_columns<T>(dh);
   float dsum = 0.f;
   for (int c = lane; c < dh; c += 64) {
     q[c] = to_f32(base[(size_t)i * ldq + h * dh + c]);
@@ -305,10 +307,7 @@ __global__ __launch_bounds__(64) void attention_bwd_q_kernel(const T* __restrict
   __syncthreads();
   float mx = -INFINITY;
   for (int j = lane; j <= i; j += 64) {
-    const T* kr = kbase + (size_t)j * ldq;
-    float s = 0.f;
-    for (int c = 0; c < dh; ++c) s = fmaf(q[c], to_f32(kr[c]), s);
-    s *= scale;
+    const float s = row_dot(q, kbase + (size_t)j * ldq, dh, quads) * scale;
     p[j] = s;
     mx = fmaxf(mx, s);
   }
@@ -318,12 +317,15 @@ __global__ __launch_bounds__(64) void attention_bwd_q_kernel(const T* __restrict
   sum = wave_sum(sum);
   const float lse = mx + logf(sum);
   for (int j = lane; j <= i; j += 64) {
-    const T* vr = vbase + (size_t)j * ldq;
-    float dp = 0.f;
-    for (int c = 0; c < dh; ++c) dp = fmaf(go[c], to_f32(vr[c]), dp);
+    const float dp = row_dot(go, vbase + (size_t)j * ldq, dh, quads);
     p[j] = expf(p[j] - lse) * (dp - dsum) * scale;      // dS_ij
   }
   __syncthreads();
+  if (quads) {
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    add_rows(a, p, (const float*)kbase, ldq, i + 1, dh, lane);
+    if (4 * lane < dh) *(f32x4*)((float*)dQKV + ((size_t)l * Trows + i) * ldq + h * dh + 4 * lane) = a;
+  } else
   for (int c = lane; c < dh; c += 64) {
     float a = 0.f;
     for (int j = 0; j <= i; ++j) a = fmaf(p[j], to_f32(kbase[(size_t)j * ldq + c]), a);
@@ -357,6 +359,8 @@ __global__ __launch_bounds__(64) void attention_bwd_kv_kernel(const T* __restric
     vj[c] = to_f32(base[(size_t)j * ldq + (H + Hkv + kvh) * dh + c]);
   }
   __syncthreads();
+  const bool quads = quads_of_columns<T>(dh);
+  f32x4 dk4 = {0.f, 0.f, 0.f, 0.f}, dv4 = dk4;
   float dk[2] = {0.f, 0.f}, dv[2] = {0.f, 0.f};          // columns lane and lane + 64 (dh <= 128)
   for (int h = kvh * rep; h < (kvh + 1) * rep; ++h) {
     const float* lse = LSE + ((size_t)l * H + h) * Trows;
@@ -367,11 +371,7 @@ __global__ __launch_bounds__(64) void attention_bwd_kv_kernel(const T* __restric
       if (i < Trows) {
         const T* qr = base + (size_t)i * ldq + h * dh;
         const T* gr = dO + ((size_t)l * Trows + i) * (H * dh) + h * dh;
-        float s = 0.f, dp = 0.f;
-        for (int c = 0; c < dh; ++c) {
-          s = fmaf(to_f32(qr[c]), kj[c], s);
-          dp = fmaf(to_f32(gr[c]), vj[c], dp);
-        }
+        const float s = row_dot(kj, qr, dh, quads), dp = row_dot(vj, gr, dh, quads);
         pv = expf(s * scale - lse[i]);
         dsv = pv * (dp - dvec[i]) * scale;
       }
@@ -380,6 +380,11 @@ __global__ __launch_bounds__(64) void attention_bwd_kv_kernel(const T* __restric
       ds[lane] = dsv;
       __syncthreads();
       const int n = min(64, Trows - i0);
+      if (quads) {
+        add_rows(dk4, ds, (const float*)base + (size_t)i0 * ldq + h * dh, ldq, n, dh, lane, false);
+        add_rows(dv4, pp, (const float*)dO + ((size_t)l * Trows + i0) * (H * dh) + h * dh, H * dh, n, dh, lane, false);
+        continue;
+      }
       for (int t = 0; t < n; ++t) {
         const T* qr = base + (size_t)(i0 + t) * ldq + h * dh;
         const T* gr = dO + ((size_t)l * Trows + i0 + t) * (H * dh) + h * dh;
@@ -393,6 +398,16 @@ __global__ __launch_bounds__(64) void attention_bwd_kv_kernel(const T* __restric
         }
       }
     }
+  }
+  if (quads) {
+    add_groups(dk4, dh);
+    add_groups(dv4, dh);
+    if (4 * lane < dh) {
+      float* out = (float*)dQKV + ((size_t)l * Trows + j) * ldq + 4 * lane;
+      *(f32x4*)(out + (H + kvh) * dh) = dk4;
+      *(f32x4*)(out + (H + Hkv + kvh) * dh) = dv4;
+    }
+    return;
   }
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
@@ -484,17 +499,24 @@ __global__ __launch_bounds__(128) void read_bwd_dpfp_kernel(const float* __restr
 // Coef as written by memupd_prep_kernel ({beta, gamma, 1/den (0 = memory empty), z.f}).
 // The memory tokens are taken in chunks of UB_M (their partial feature gradients live in registers); a wave re-reads
 // its rows of A and G for every chunk, carries the running update of G between chunks in Upd and writes G with the last.
-// grid: (ceil(d / UB_ROWS), g), block: 256; Phi <= 64 * NPL; LDS: UB_M * (2 Phi + 2) floats.
-constexpr int UB_ROWS = 32, UB_M = 16;
+// The 16 dot products with either row are reduced by one transposing butterfly each (dr_sum16; 32 full wave reductions one after
+// another were what bounded this kernel), after which a lane holds everything about one token and the two factors
+// of the outer products are broadcast through scalar registers; the next row is requested before the current one is worked on.
+// grid: (ceil(d / rows_per_block), g), block: 256; Phi <= 64 * NPL; LDS: UB_M * (64 NPL + Phi + 2) floats.
+constexpr int UB_M = 16;
+// rows per block: a wave takes a quarter of them one after another, so narrow models, whose launches are few blocks, take fewer
+inline int update_bwd_rows_per_block(int d) { return d >= 512 ? 32 : 8; }
 template <int NPL>
 __global__ __launch_bounds__(256) void update_bwd_rows_kernel(const float* __restrict__ KV, const float* __restrict__ Fm,
                                                               const float* __restrict__ Coef,
                                                               const float* __restrict__ Aold, float* __restrict__ DA,
                                                               float* __restrict__ Upd, float* __restrict__ DV,
-                                                              float* __restrict__ Part, int first, int m, int d, int dm, int Phi) {
+                                                              float* __restrict__ Part, int first, int m, int d, int dm, int Phi,
+                                                              int rows_per_block) {
   extern __shared__ float sm[];
-  float* F = sm;                               // [UB_M][Phi]: the f_i of the current chunk of memory tokens
-  float* acc = sm + (size_t)UB_M * Phi;        // [UB_M][Phi + 2]
+  constexpr int LF = 64 * NPL;
+  float* F = sm;                               // [UB_M][LF]: the f_i of the current chunk of memory tokens, zeros behind
+  float* acc = sm + UB_M * LF;                 // [UB_M][Phi + 2]
   const int l = first + blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const float* Fl = Fm + (size_t)l * m * Phi;
   const float* cf = Coef + (size_t)l * m * 4;
@@ -502,57 +524,73 @@ __global__ __launch_bounds__(256) void update_bwd_rows_kernel(const float* __res
   float* G = DA + (size_t)l * d * Phi;
   float* U = Upd + (size_t)l * d * Phi;        // sum_i w_i[r] f_i over the chunks so far (used only if m > UB_M)
   const float* V = KV + (size_t)l * m * (dm + d) + dm;
-  const int r0 = blockIdx.x * UB_ROWS, r1 = min(d, r0 + UB_ROWS);
+  const int r0 = blockIdx.x * rows_per_block, r1 = min(d, r0 + rows_per_block);
   const int stride = Phi + 2;
   float* out = Part + ((size_t)l * gridDim.x + blockIdx.x) * m * stride;
 
   for (int i0 = 0; i0 < m; i0 += UB_M) {       // memory tokens in chunks of UB_M; every chunk needs the ORIGINAL G
     const int n = min(UB_M, m - i0);
     __syncthreads();                           // the previous chunk's F and acc are no longer read
-    for (int c = threadIdx.x; c < n * Phi; c += blockDim.x) F[c] = Fl[(size_t)i0 * Phi + c];
+    for (int c = threadIdx.x; c < UB_M * LF; c += blockDim.x) {
+      const int i = c / LF, x = c % LF;
+      F[c] = i < n && x < Phi ? Fl[(size_t)(i0 + i) * Phi + x] : 0.f;
+    }
     __syncthreads();
-    float dfp[UB_M][NPL], db[UB_M], dd[UB_M];
+    const int mi = (lane >> 2) & 15, it = i0 + min(mi, n - 1);     // the token this lane ends up with
+    const bool token = mi < n;
+    const float beta = token ? cf[it * 4 + 0] : 0.f, rden = token ? cf[it * 4 + 2] : 0.f;
+    const float* Vi = V + (size_t)it * (dm + d);
+    float dfp[UB_M][NPL], db = 0.f, dd = 0.f;
 #pragma unroll
-    for (int i = 0; i < UB_M; ++i) {
-      db[i] = dd[i] = 0.f;
+    for (int i = 0; i < UB_M; ++i)
 #pragma unroll
       for (int k = 0; k < NPL; ++k) dfp[i][k] = 0.f;
-    }
-    for (int r = r0 + w; r < r1; r += 4) {
-      float a[NPL], g[NPL], upd[NPL];
+    float an[NPL], gn[NPL], vn = 0.f;
+    auto request = [&](int r) {
 #pragma unroll
       for (int k = 0; k < NPL; ++k) {
         const int c = lane + 64 * k;
-        a[k] = c < Phi ? A[(size_t)r * Phi + c] : 0.f;
-        g[k] = c < Phi ? G[(size_t)r * Phi + c] : 0.f;
+        an[k] = c < Phi ? A[(size_t)r * Phi + c] : 0.f;
+        gn[k] = c < Phi ? G[(size_t)r * Phi + c] : 0.f;
+      }
+      vn = Vi[r];
+    };
+    if (r0 + w < r1) request(r0 + w);
+    for (int r = r0 + w; r < r1; r += 4) {
+      float a[NPL], g[NPL], upd[NPL];
+      const float v = vn;
+#pragma unroll
+      for (int k = 0; k < NPL; ++k) {
+        const int c = lane + 64 * k;
+        a[k] = an[k];
+        g[k] = gn[k];
         upd[k] = (i0 > 0 && c < Phi) ? U[(size_t)r * Phi + c] : 0.f;
       }
+      if (r + 4 < r1) request(r + 4);
+      float p[UB_M], pq[UB_M];
 #pragma unroll
       for (int i = 0; i < UB_M; ++i) {
-        if (i >= n) continue;                  // uniform; `continue` keeps the loop unrollable (dfp[][] stays in registers)
-        float pa = 0.f, pg = 0.f;
+        p[i] = pq[i] = 0.f;
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-          const int c = lane + 64 * k;
-          const float f = c < Phi ? F[i * Phi + c] : 0.f;
-          pa = fmaf(a[k], f, pa);
-          pg = fmaf(g[k], f, pg);
+          const float f = F[i * LF + lane + 64 * k];
+          p[i] = fmaf(a[k], f, p[i]);
+          pq[i] = fmaf(g[k], f, pq[i]);
         }
-        pa = wave_sum(pa);
-        pg = wave_sum(pg);
-        const int it = i0 + i;
-        const float beta = cf[it * 4 + 0], rden = cf[it * 4 + 2];
-        const float vbar = pa * rden, e = V[(size_t)it * (dm + d) + r] - vbar;
-        const float wi = -beta * pg * rden;
-        if (lane == 0) DV[((size_t)l * m + it) * d + r] = beta * pg;
-        db[i] = fmaf(e, pg, db[i]);
-        dd[i] = fmaf(beta * vbar * rden, pg, dd[i]);
+      }
+      const float pa = dr_sum16(p, lane), pg = dr_sum16(pq, lane);
+      const float vbar = pa * rden, e = v - vbar;
+      const float wi = token ? -beta * pg * rden : 0.f, be = token ? beta * e : 0.f;
+      if (token && (lane & 3) == 0) DV[((size_t)l * m + it) * d + r] = beta * pg;
+      db = fmaf(e, pg, db);
+      dd = fmaf(beta * vbar * rden, pg, dd);
+#pragma unroll
+      for (int i = 0; i < UB_M; ++i) {
+        const float bi = dr_lane(be, 4 * i), wl = dr_lane(wi, 4 * i);
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-          const int c = lane + 64 * k;
-          const float f = c < Phi ? F[i * Phi + c] : 0.f;
-          dfp[i][k] = fmaf(beta * e, g[k], fmaf(wi, a[k], dfp[i][k]));
-          upd[k] = fmaf(wi, f, upd[k]);
+          dfp[i][k] = fmaf(bi, g[k], fmaf(wl, a[k], dfp[i][k]));
+          upd[k] = fmaf(wl, F[i * LF + lane + 64 * k], upd[k]);
         }
       }
       const bool last = i0 + UB_M >= m;
@@ -576,10 +614,10 @@ __global__ __launch_bounds__(256) void update_bwd_rows_kernel(const float* __res
             const int c = lane + 64 * k;
             if (c < Phi) acc[(size_t)i * stride + c] = (ww ? acc[(size_t)i * stride + c] : 0.f) + dfp[i][k];
           }
-          if (lane == 0) {
-            acc[(size_t)i * stride + Phi] = (ww ? acc[(size_t)i * stride + Phi] : 0.f) + db[i];
-            acc[(size_t)i * stride + Phi + 1] = (ww ? acc[(size_t)i * stride + Phi + 1] : 0.f) + dd[i];
-          }
+        }
+        if (token && (lane & 3) == 0) {
+          acc[(size_t)mi * stride + Phi] = (ww ? acc[(size_t)mi * stride + Phi] : 0.f) + db;
+          acc[(size_t)mi * stride + Phi + 1] = (ww ? acc[(size_t)mi * stride + Phi + 1] : 0.f) + dd;
         }
       }
       __syncthreads();
@@ -617,6 +655,7 @@ __global__ __launch_bounds__(128) void update_bwd_tokens_kernel(const float* __r
   float dg = 0.f, ff = 0.f;
   for (int c = threadIdx.x; c < Phi; c += blockDim.x) {
     float s = 0.f;
+#pragma unroll 16
     for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * m * stride + c];
     df[c] = s;
     dg = fmaf(dz[c], f[c], dg);
@@ -624,12 +663,20 @@ __global__ __launch_bounds__(128) void update_bwd_tokens_kernel(const float* __r
   }
   dg = block_sum(dg, red);
   ff = block_sum(ff, red);
+  // (read by all threads, added in block order by one: a chain of additions, not of memory latencies)
+  __shared__ float pb[2][128];
   float dbeta = 0.f, dden = 0.f;
-  if (threadIdx.x == 0)
-    for (int b = 0; b < nblocks; ++b) {
-      dbeta += part[(size_t)b * m * stride + Phi];
-      dden += part[(size_t)b * m * stride + Phi + 1];
+  for (int b0 = 0; b0 < nblocks; b0 += 128) {
+    const int nb = min(128, nblocks - b0);
+    __syncthreads();
+    if ((int)threadIdx.x < nb) {
+      pb[0][threadIdx.x] = part[(size_t)(b0 + threadIdx.x) * m * stride + Phi];
+      pb[1][threadIdx.x] = part[(size_t)(b0 + threadIdx.x) * m * stride + Phi + 1];
     }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int b = 0; b < nb; ++b) { dbeta += pb[0][b]; dden += pb[1][b]; }
+  }
   const float beta = Coef[mi * 4 + 0], gamma = Coef[mi * 4 + 1], zf = Coef[mi * 4 + 3];
   const float inv = 1.0f / (ff + eps);
   __shared__ float dzf_s;

@@ -323,6 +323,27 @@ __device__ __forceinline__ float dr_dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
 
+// Sums of p[0 .. 15] over the wave, by a transposing butterfly: lane L gets the sum for i = (L >> 2) & 15.  The first two
+// levels are lane-half / lane-row swaps (one instruction exchanges what the two sides of a level send each other), the others
+// data-parallel moves inside a row; 17 exchanges instead of the 96 of 16 wave_sums, added in the same order as these.
+__device__ __forceinline__ float dr_sum16(const float (&p)[16], int lane) {
+  const bool b3 = lane & 8, b2 = lane & 4;
+  float q8[8], q4[4], q2[2];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) q8[j] = dr_swap_add32(p[j], p[j + 8]);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) q4[j] = dr_swap_add16(q8[j], q8[j + 4]);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) q2[j] = (b3 ? q4[j + 2] : q4[j]) + dr_dpp<0x128>(b3 ? q4[j] : q4[j + 2]);   // lane ^ 8
+  float dot = (b2 ? q2[1] : q2[0]) + __shfl_xor(b2 ? q2[0] : q2[1], 4, kWave);
+  dot += dr_dpp<0x4E>(dot);      // lane ^ 2
+  dot += dr_dpp<0xB1>(dot);      // lane ^ 1
+  return dot;
+}
+__device__ __forceinline__ float dr_lane(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
 // Fast path of the delta rule for n_mem <= 16 and Phi = 64 * NPL (tokens past n_mem count as zeros): phi(k_i) lives in registers (lane owns columns
 // lane + 64 k), the 16 dot products of a row are reduced with a transposing butterfly (17 exchanges instead of
 // 16 full wave reductions; afterwards lane L holds the complete dot product for i = (L >> 2) & 15), and the 16
@@ -348,7 +369,6 @@ __global__ __launch_bounds__(256) void delta_rule16_kernel(const float* __restri
   const float* Vmi = KV + (size_t)l * m * (dm + d) + (size_t)(token ? mi : 0) * (dm + d) + dm;
   float* A = aux[l].A;
   bf16* A16 = aux[l].A16;
-  const bool b3 = lane & 8, b2 = lane & 4;
   const int r0 = blockIdx.x * rows_per_block, r1 = min(d, r0 + rows_per_block);
   // the wave's next row is requested before the current one is worked on: with one row of 4 * Phi bytes in flight
   // per wave the pass ran at the latency of HBM, not at its rate
@@ -376,23 +396,12 @@ __global__ __launch_bounds__(256) void delta_rule16_kernel(const float* __restri
       for (int k = 0; k < NPL; ++k) t = fmaf(a[k], f[i][k], t);
       p[i] = t;
     }
-    // transposing butterfly: the first two levels are lane-half / lane-row swaps (one instruction exchanges what the two
-    // sides of a level send each other), the others data-parallel moves inside a row; sums as in the plain exchange
-    float q8[8], q4[4], q2[2];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) q8[j] = dr_swap_add32(p[j], p[j + 8]);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) q4[j] = dr_swap_add16(q8[j], q8[j + 4]);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) q2[j] = (b3 ? q4[j + 2] : q4[j]) + dr_dpp<0x128>(b3 ? q4[j] : q4[j + 2]);   // lane ^ 8
-    float dot = (b2 ? q2[1] : q2[0]) + __shfl_xor(b2 ? q2[0] : q2[1], 4, kWave);
-    dot += dr_dpp<0x4E>(dot);      // lane ^ 2
-    dot += dr_dpp<0xB1>(dot);      // lane ^ 1
+    const float dot = dr_sum16(p, lane);
     const float coef = token ? beta * (vr - dot * rden) : 0.f;      // beta_i (v_i[r] - v_bar_i[r])
     float upd[NPL] = {};
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      const float ci = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, coef), i * 4));
+      const float ci = dr_lane(coef, i * 4);
 #pragma unroll
       for (int k = 0; k < NPL; ++k) upd[k] = fmaf(ci, f[i][k], upd[k]);
     }
