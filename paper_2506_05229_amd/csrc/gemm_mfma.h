@@ -140,9 +140,16 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // per-row scale of the result (1 / rms of a fused RMSNorm, or 1 / denominator of the associative read),
   // fetched once; visible to everybody after the first barrier of the main loop
   float* rs_lds = (float*)(smem + mfma_tile_lds_bytes<BM, BN, WGM, WGN, EPI, TAIL, NS>());
-  for (int r = tid; r < A_ROWS; r += NW * 64) {
+  auto row_scale_of = [&](int r) {
     const int m = r < BM ? m0 + r : m0_strip + r - BM;
-    rs_lds[r] = (g.rowscale && m < s.M) ? g.rowscale[m] : 1.f;
+    return (g.rowscale && m < s.M) ? g.rowscale[m] : 1.f;
+  };
+  // (pipelined: one row per thread, kept in a register until the last k-tile, so that the first copies do not wait for it)
+  float rs_mine = 1.f;
+  if (PIPE) {
+    if (tid < A_ROWS) rs_mine = row_scale_of(tid);
+  } else {
+    for (int r = tid; r < A_ROWS; r += NW * 64) rs_lds[r] = row_scale_of(r);
   }
   const int wm = wave / WGN, wn = wave % WGN;
   const bool tail = tail_blk && wave < (TAIL ? BN / 32 : 0);   // wave-uniform: this wave computes part of the strip
@@ -381,6 +388,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       phase(a0, b0, H0{}, H0{}, integral_constant<int, 4>{}, [&](int q) { read_b(b1, kt, 1, q); },
             [&] { if (LEFT == 2) { copy_a(kt + 2, 0); copy_b(kt + 2, 0); } });
       phase_end(integral_constant<int, W1>{});
+      if (LEFT == 0 && tid < A_ROWS) rs_lds[tid] = rs_mine;
       phase(a0, b1, H0{}, H1{}, integral_constant<int, 8>{}, [&](int q) { read_a(a1, kt, 1, q); },
             [&] { if (LEFT == 2) copy_b(kt + 2, 1); });
       phase_end(integral_constant<int, W2>{});
