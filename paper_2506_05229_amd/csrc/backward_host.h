@@ -33,6 +33,9 @@ enum TKind {
   TK_COUNT
 };
 
+// weight gradients that are accumulated over a window of steps
+constexpr TKind kWindowGrads[] = {TK_WD, TK_WG, TK_WU, TK_WO, TK_WQ, TK_WK, TK_WV, TK_WMQ, TK_WMK, TK_WMV};
+
 struct TrainLayout {
   size_t Xin, X1, Xb, N1, N2, RStd1, RStd2, QKV, Vt, Att, Hres, GU, Uff, Yf, Yb, Qm, Fphi, RDen, KVm, Fm, Coef, Rope;
   size_t Aw, zw, A16w, ATr;
@@ -40,7 +43,7 @@ struct TrainLayout {
   size_t TA, TB, TmA, TmB, CPart, WinA, WinB;
   size_t wa_rows, wb_rows, aDY, aDGU, aDH, aDQKV, aDQR, bU, bN2, bATT, bN1, bX;   // rows of a layer's window operands
   size_t WdT, WguT, WoT, WqkvT, WmqT, WmkvT;
-  size_t Ptrs, Tables, Aux, total;
+  size_t Ptrs, KRange, Tables, Aux, total;
   int Tp, mp, dmP, Kmkv, nblk, Kw, Km;     // Kw, Km: columns of a window row (WG_WIN slots x batch x Tp or mp)
   size_t ta_rows, tb_rows;
 };
@@ -125,6 +128,7 @@ TrainLayout carve_train(const Dims& D) {
   o.WmqT = take(Lr * d * o.dmP * e);
   o.WmkvT = take(Lr * d * o.Kmkv * e);
   o.Ptrs = take(3 * L * sizeof(float*));
+  o.KRange = take(4 * Lr * sizeof(int));
   o.Tables = take((size_t)TK_COUNT * L * sizeof(GemmGroup));
   o.Aux = take(L * sizeof(LayerAux));
   o.total = p;
@@ -197,6 +201,7 @@ void fill_train_shapes(BCtx& c) {
   set(TK_WMQ, D.dm, D.d, Kw, Kw, D.d, EPI_RESID_F32, -1, 0, Kw);
   set(TK_WMK, D.dm, D.d, Km, Km, D.d, EPI_RESID_F32, -1, 0, Km);
   set(TK_WMV, D.d, D.d, Km, Km, D.d, EPI_RESID_F32, -1, 0, Km);
+  for (int k : kWindowGrads) c.shape[k].k_slot = D.B * ((k == TK_WMK || k == TK_WMV) ? o.mp : o.Tp) / 64;
 }
 
 armt_status upload_train_tables(BCtx& c, const armt_layer_weights* W, const armt_layer_grads* G) {
@@ -256,6 +261,7 @@ armt_status upload_train_tables(BCtx& c, const armt_layer_weights* W, const armt
     auto wgrad = [&](int k, char* A, char* Bp, float* C) {
       if (k != TK_DA && l % B != 0) return;
       GemmGroup* q = &tab[(size_t)k * L + (k == TK_DA ? l : lr)]; q->A = A; q->B0 = Bp; q->C = C; q->R = C;
+      if (k != TK_DA) q->krange = (const int*)(ws + o.KRange) + 2 * ((k == TK_WMQ ? D.Lr : 0) + lr);
     };
     wgrad(TK_WD, WA + o.aDY * rowb, WB + o.bU * rowb, gw.wdown);
     wgrad(TK_WG, WA + o.aDGU * rowb, WB + o.bN2 * rowb, gw.wgate);
@@ -568,17 +574,19 @@ armt_status backward_typed(BCtx& c, const armt_layer_weights* W, int64_t N, floa
   {
     const int n = D.T * (D.dh / 2);
     rope_table_kernel<<<(n + 255) / 256, 256, 0, c.st>>>(c.at<float>(o.Rope), D.T, D.dh / 2, (double)D.rope_theta);
-    // zero what is only ever written in part: the reduction padding of the transposed operands, the K padding of
-    // dq and [dk | dv], and the gradient slots
+    // zero what is only ever written in part: the K padding of dq and [dk | dv], the gradient slots and, in fp32, the
+    // reduction padding of the transposed operands (the bf16 transposes write theirs)
     auto zero = [&](size_t off, size_t bytes) {
       fill_f32_kernel<<<ew_blocks(bytes / 4), 256, 0, c.st>>>(c.at<float>(off), bytes / 4, 0.f);
     };
-    zero(o.TA, (size_t)L * o.ta_rows * o.Tp * D.esz);
-    zero(o.TB, (size_t)L * o.tb_rows * o.Tp * D.esz);
-    zero(o.TmA, (size_t)Lr * (D.dm + D.d) * o.Km * D.esz);
-    zero(o.TmB, (size_t)Lr * D.d * o.Km * D.esz);
-    zero(o.WinA, (size_t)Lr * o.wa_rows * o.Kw * D.esz);
-    zero(o.WinB, (size_t)Lr * o.wb_rows * o.Kw * D.esz);
+    if (!D.bf16) {
+      zero(o.TA, (size_t)L * o.ta_rows * o.Tp * D.esz);
+      zero(o.TB, (size_t)L * o.tb_rows * o.Tp * D.esz);
+      zero(o.TmA, (size_t)Lr * (D.dm + D.d) * o.Km * D.esz);
+      zero(o.TmB, (size_t)Lr * D.d * o.Km * D.esz);
+      zero(o.WinA, (size_t)Lr * o.wa_rows * o.Kw * D.esz);
+      zero(o.WinB, (size_t)Lr * o.wb_rows * o.Kw * D.esz);
+    }
     zero(o.DQr, (size_t)L * D.T * o.dmP * D.esz);
     zero(o.DKV, (size_t)L * D.m * o.Kmkv * D.esz);
     zero(o.DX, (size_t)(L + B) * cell * 4);
@@ -592,32 +600,26 @@ armt_status backward_typed(BCtx& c, const armt_layer_weights* W, int64_t N, floa
   struct Slot { int lo, hi, no_read; };        // live layers of the step; the layer whose cell had no read (-1: none)
   Slot slots[WG_WIN];
   int n_slots = 0;
-  auto clear_slot = [&](int l, int p, bool read_only) {
-    // zero slot p of layer l on the A side (then the stale B side of that slot adds nothing)
-    const size_t e = D.esz, rowb = (size_t)o.Kw * e, colb = (size_t)B * o.Tp * e;
-    char* WA = c.ws + o.WinA + (size_t)l * o.wa_rows * rowb + (size_t)p * colb;
-    const size_t r0 = read_only ? o.aDQR : 0, nr = read_only ? (size_t)D.dm : o.wa_rows;
-    zero_columns_kernel<<<dim3((unsigned)nr), 256, 0, c.st>>>(WA + r0 * rowb, rowb, colb);
-    if (!read_only) {
-      const size_t mrow = (size_t)o.Km * e, mcol = (size_t)B * o.mp * e;
-      zero_columns_kernel<<<dim3((unsigned)(D.dm + D.d)), 256, 0, c.st>>>(c.ws + o.TmA + (size_t)l * (D.dm + D.d) * mrow + (size_t)p * mcol,
-                                                                         mrow, mcol);
-    }
-  };
+  // A layer is live in consecutive steps, so its part of the window is one range of slots, and its GEMMs run over that range
+  // (the first segment's cell, which is the layer's last slot, has no read and so no gradient of W_Q^mem).
   auto flush = [&]() -> armt_status {
     if (n_slots == 0) return ARMT_OK;
     int LO = slots[0].lo, HI = slots[0].hi;
-    for (int p = 1; p < n_slots; ++p) { LO = std::min(LO, slots[p].lo); HI = std::max(HI, slots[p].hi); }
+    std::vector<int> range(4 * (size_t)Lr, 0);
     for (int p = 0; p < n_slots; ++p) {
-      for (int l = LO; l <= HI; ++l)
-        if (l < slots[p].lo || l > slots[p].hi) clear_slot(l, p, false);
-      if (slots[p].no_read >= 0) clear_slot(slots[p].no_read, p, true);
+      LO = std::min(LO, slots[p].lo);
+      HI = std::max(HI, slots[p].hi);
+      for (int l = slots[p].lo; l <= slots[p].hi; ++l)
+        for (int k = 0; k < 2; ++k) {      // all kinds, W_Q^mem
+          if (k == 1 && slots[p].no_read == l) continue;
+          int* r = &range[2 * ((size_t)k * Lr + l)];
+          if (r[1]++ == 0) r[0] = p;
+        }
     }
-    HIP_TRY(hipGetLastError());
-    const int kinds[] = {TK_WD, TK_WG, TK_WU, TK_WO, TK_WQ, TK_WK, TK_WV, TK_WMQ, TK_WMK, TK_WMV};
-    for (int k : kinds) {
+    ARMT_TRY(upload_bytes(c.st, c.ws + o.KRange, range.data(), range.size() * sizeof(int)));
+    for (int k : kWindowGrads) {
       GemmShape s = c.shape[k];
-      s.K = n_slots * B * ((k == TK_WMK || k == TK_WMV) ? o.mp : o.Tp);
+      s.K = n_slots * s.k_slot * 64;
       ARMT_TRY(gemm<T>(c.st, c.table(k), LO, HI - LO + 1, s));
     }
     n_slots = 0;

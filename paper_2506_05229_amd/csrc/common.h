@@ -63,7 +63,8 @@ struct GemmGroup {
   const float* rowscale;  // per-row factor applied to the accumulator (or null)
   const void* gain;       // EPI_RESID_F32: C2 = (bf16)(result * gain[col]) instead of (bf16)result (or null)
   float* ssq_out;         // EPI_RESID_F32: [M][tiles_n] per-row sums of squares of the result, one per N-tile (or null)
-  const void* pad_[6];    // keep entries at 128 bytes
+  const int* krange;      // part of the reduction to do: {first, count} in units of GemmShape::k_slot steps of 64 (or null: all of it)
+  const void* pad_[5];    // keep entries at 128 bytes
 };
 static_assert(sizeof(GemmGroup) == 128, "pointer-table entries are 128 bytes");
 
@@ -93,8 +94,21 @@ struct GemmShape {
                         // instead of a strip of the last M-tile (same results up to rounding order)
   int ldb;              // row stride of the weight blocks in elements (>= K); the weights of the model are dense: ldb = K
   float fparam = 0.f;   // EPI_DPFP_READ: assoc_eps
+  int k_slot = 0;       // steps of 64 per unit of GemmGroup::krange
   int a_rows = 0;       // rows of A that may be READ in every group (0: M).  Operand buffers that are padded to whole
                         // tiles let a ragged M take the copies without per-lane clamping; rows >= M are never stored
 };
+
+// Narrow a group's operands (one weight block) and its K to the group's own part of the reduction; false: nothing to do.
+template <typename T>
+__device__ __forceinline__ bool restrict_k(GemmGroup& g, GemmShape& s) {
+  if (!g.krange) return true;
+  const int first = __builtin_amdgcn_readfirstlane(g.krange[0]), count = __builtin_amdgcn_readfirstlane(g.krange[1]);
+  const size_t skip = (size_t)first * s.k_slot * 64 * sizeof(T);
+  s.K = count * s.k_slot * 64;
+  g.A = (const char*)g.A + skip;
+  g.B0 = (const char*)g.B0 + skip;
+  return s.K > 0;
+}
 
 }  // namespace armt

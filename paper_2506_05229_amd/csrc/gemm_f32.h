@@ -25,7 +25,8 @@ template <int TM, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s) {
   constexpr int TN = 2, NB = SWIGLU ? 2 : 1, BM = 16 * TM, BN = 16 * TN, LD = BN + 4;
   __shared__ __align__(16) float part[NB][4][BM][LD];
-  const GemmGroup g = table[first + blockIdx.z];
+  GemmGroup g = table[first + blockIdx.z];
+  if (!restrict_k<float>(g, s)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, q = lane >> 4;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;

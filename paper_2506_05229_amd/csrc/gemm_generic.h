@@ -21,7 +21,8 @@ __device__ __forceinline__ const T* weight_row(const GemmGroup& g, const GemmSha
 template <typename T>
 __global__ __launch_bounds__(256) void gemm_generic_kernel(const GemmGroup* __restrict__ table, int first,
                                                            GemmShape s) {
-  const GemmGroup g = table[first + blockIdx.z];
+  GemmGroup g = table[first + blockIdx.z];
+  if (!restrict_k<T>(g, s)) return;
   const bool swiglu = (s.epi == EPI_SWIGLU);
   __shared__ float As[GG_BK][GG_BM + 4];
   __shared__ float Bs[GG_BK][GG_BN + 4];

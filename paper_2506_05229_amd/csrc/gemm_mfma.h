@@ -123,7 +123,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   const int mg = rem / (m_group * tiles_n), rem_mg = rem - mg * (m_group * tiles_n);
   const int mg_tiles = min(m_group, tiles_m - mg * m_group);
   const int tn = rem_mg / mg_tiles, tm = mg * m_group + rem_mg - tn * mg_tiles;
-  const GemmGroup g = table[first + grp];
+  GemmGroup g = table[first + grp];
+  if (!restrict_k<bf16>(g, s)) return;
   const int m0 = tm * BM, n0 = tn * BN_OUT;
   const int m0_strip = tiles_m * BM;                        // first row of the strip (TAIL)
   // Who computes the strip of 16 rows behind the last M-tile: the last M-tile, or, pipelined, the last M-tiles of the last
