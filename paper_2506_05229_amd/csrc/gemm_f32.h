@@ -3,7 +3,7 @@
 // These problems are small (a cell of the fp32 configuration is 72 x 128 ... 512 with K = 128 ... 512) and what bounds a launch is one
 // chain of memory latencies, not arithmetic: with 64 x 64 tiles staged through LDS in k-steps of 16 the down projection (K = 512)
 // went through 32 of them.  Here a workgroup owns a 32 x 32 tile (16 x 32 for at most 16 rows), its four waves a quarter of K each,
-// and a wave loads its operands straight into registers, F32_CH chunks of 16 k ahead: a lane holds four consecutive k of one row, and
+// and a wave loads its operands straight into registers, CH chunks of 16 k ahead: a lane holds four consecutive k of one row, and
 // the i-th of four MFMAs takes element i of either operand (the products of a chunk are summed in that order on both sides).  The four
 // partial tiles are added in wave order through LDS, so a result depends on K alone.
 //
@@ -18,10 +18,9 @@
 
 namespace armt {
 
-constexpr int F32_CH = 4;      // chunks of 16 k per batch of loads
-
 // grid: (ceil(N / 32), ceil(M / (16 TM)), g); block: 256.
-template <int TM, bool SWIGLU>
+// CH: chunks of 16 k per batch of loads; a wave's share should be a batch (K <= 128: 2) or several (4).
+template <int TM, bool SWIGLU, int CH>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s) {
   constexpr int TN = 2, NB = SWIGLU ? 2 : 1, BM = 16 * TM, BN = 16 * TN, LD = BN + 4;
   __shared__ __align__(16) float part[NB][4][BM][LD];
@@ -47,17 +46,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
       b[0][j] = weight_row<float>(g, s, n);
     }
   }
-  auto load = [&](const float* row, int k) __attribute__((always_inline)) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (wide) {
-      if (k < s.K) v = *(const f32x4*)(row + k);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (k + e < s.K) v[e] = row[k + e];
-    }
-    return v;
-  };
   // this thread's four results, and what their epilogue reads: requested together with the operands
   const int row = tid >> 3, col = (tid & 7) * 4, m = m0 + row, n = n0 + col;
   const bool mine = row < BM && m < s.M && n < s.N;
@@ -87,40 +75,64 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
       for (int j = 0; j < TN; ++j) acc[u][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int chunks = (s.K + 15) >> 4, per = (chunks + 3) >> 2;
   const int c0 = min(wave * per, chunks), c1 = min(c0 + per, chunks);
-  struct Batch { f32x4 a[F32_CH][TM], b[F32_CH][NB][TN]; };
-  auto fetch = [&](Batch& t, int c) __attribute__((always_inline)) {
+  struct Batch { f32x4 a[CH][TM], b[CH][NB][TN]; };
+  auto multiply = [&](const Batch& t, int h) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < F32_CH; ++h) {
-      const int k = c + h < c1 ? 16 * (c + h) + 4 * q : s.K;      // past this wave's share: zeros
-#pragma unroll
-      for (int i = 0; i < TM; ++i) t.a[h][i] = load(a[i], k);
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int u = 0; u < NB; ++u)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) t.b[h][u][j] = load(b[u][j], k);
-    }
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[u][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.a[h][i][e], t.b[h][u][j][e], acc[u][i][j], 0, 0, 0);
   };
-  auto multiply = [&](const Batch& t) __attribute__((always_inline)) {
+  if (wide) {
+    // branch-free: past this wave's share the last 16 bytes of the row are read and replaced by zeros
+    auto fetch = [&](Batch& t, int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < F32_CH; ++h)
+      for (int h = 0; h < CH; ++h) {
+        const int k = 16 * (c + h) + 4 * q;
+        const bool in = c + h < c1 && k < s.K;
+        const int at = min(k, s.K - 4);
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int i = 0; i < TM; ++i) { const f32x4 v = *(const f32x4*)(a[i] + at); t.a[h][i] = in ? v : zero; }
 #pragma unroll
         for (int u = 0; u < NB; ++u)
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+          for (int j = 0; j < TN; ++j) t.b[h][u][j] = *(const f32x4*)(b[u][j] + at);
+      }
+    };
+    Batch t, next;
+    fetch(t, c0);
+#pragma unroll 1
+    for (int c = c0; c < c1; c += CH) {
+      const bool more = c + CH < c1;
+      if (more) fetch(next, c + CH);
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[u][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.a[h][i][e], t.b[h][u][j][e], acc[u][i][j], 0, 0, 0);
-  };
-  Batch t0, t1;
-  if (c0 < c1) fetch(t0, c0);
-  for (int c = c0; c < c1; c += 2 * F32_CH) {
-    const bool two = c + F32_CH < c1;
-    if (two) fetch(t1, c + F32_CH);
-    multiply(t0);
-    if (c + 2 * F32_CH < c1) fetch(t0, c + 2 * F32_CH);
-    if (two) multiply(t1);
+      for (int h = 0; h < CH; ++h) multiply(t, h);
+      if (more) t = next;
+    }
+  } else {
+#pragma unroll 1
+    for (int c = c0; c < c1; ++c) {
+      Batch t;
+      auto load = [&](const float* row) __attribute__((always_inline)) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (16 * c + 4 * q + e < s.K) v[e] = row[16 * c + 4 * q + e];
+        return v;
+      };
+#pragma unroll
+      for (int i = 0; i < TM; ++i) t.a[0][i] = load(a[i]);
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) t.b[0][u][j] = load(b[u][j]);
+      multiply(t, 0);
+    }
   }
   // a 16 x 16 result block has lane = column lane % 16 and registers = rows 4 * (lane / 16) + r
 #pragma unroll
@@ -175,16 +187,13 @@ inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, cons
   if (g <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
   if (((s.K | s.lda | s.ldb) & 3) && (int64_t)g * ((s.M + 63) / 64) * ((s.N + 63) / 64) >= 512)
     return launch_gemm_generic<float>(table, first, g, s, st);
-  const bool swiglu = s.epi == EPI_SWIGLU;
-  const int bm = s.M <= 16 ? 16 : 32;
-  const dim3 grid((s.N + 31) / 32, (s.M + bm - 1) / bm, g);
-  if (bm == 16) {
-    if (swiglu) gemm_f32_kernel<1, true><<<grid, 256, 0, st>>>(table, first, s);
-    else gemm_f32_kernel<1, false><<<grid, 256, 0, st>>>(table, first, s);
-  } else {
-    if (swiglu) gemm_f32_kernel<2, true><<<grid, 256, 0, st>>>(table, first, s);
-    else gemm_f32_kernel<2, false><<<grid, 256, 0, st>>>(table, first, s);
-  }
+  const bool swiglu = s.epi == EPI_SWIGLU, narrow = s.M <= 16, brief = s.K <= 128;
+  const dim3 grid((s.N + 31) / 32, (s.M + (narrow ? 15 : 31)) / (narrow ? 16 : 32), g);
+  auto kern = swiglu ? (narrow ? (brief ? gemm_f32_kernel<1, true, 2> : gemm_f32_kernel<1, true, 4>)
+                               : (brief ? gemm_f32_kernel<2, true, 2> : gemm_f32_kernel<2, true, 4>))
+                     : (narrow ? (brief ? gemm_f32_kernel<1, false, 2> : gemm_f32_kernel<1, false, 4>)
+                               : (brief ? gemm_f32_kernel<2, false, 2> : gemm_f32_kernel<2, false, 4>));
+  kern<<<grid, 256, 0, st>>>(table, first, s);
   return hipGetLastError();
 }
 
