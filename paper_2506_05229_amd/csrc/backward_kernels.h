@@ -66,6 +66,16 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16* __restr
   }
 }
 
+// u[i] += u[n + i] + u[2 n + i] + ...: partial results of a product, added in order.
+__global__ void sum_parts_kernel(float* __restrict__ u, size_t n, int parts) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    float s = u[i];
+#pragma unroll 4
+    for (int p = 1; p < parts; ++p) s += u[p * n + i];
+    u[i] = s;
+  }
+}
+
 template <typename Tin, typename Tout>
 __global__ void convert_kernel(const Tin* __restrict__ src, Tout* __restrict__ dst, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
