@@ -201,7 +201,10 @@ void fill_train_shapes(BCtx& c) {
   set(TK_WMQ, D.dm, D.d, Kw, Kw, D.d, EPI_RESID_F32, -1, 0, Kw);
   set(TK_WMK, D.dm, D.d, Km, Km, D.d, EPI_RESID_F32, -1, 0, Km);
   set(TK_WMV, D.d, D.d, Km, Km, D.d, EPI_RESID_F32, -1, 0, Km);
-  for (int k : kWindowGrads) c.shape[k].k_slot = D.B * ((k == TK_WMK || k == TK_WMV) ? o.mp : o.Tp) / 64;
+  for (int k : kWindowGrads) {
+    c.shape[k].k_slot = D.B * ((k == TK_WMK || k == TK_WMV) ? o.mp : o.Tp) / 64;
+    c.shape[k].spread = 1;
+  }
 }
 
 armt_status upload_train_tables(BCtx& c, const armt_layer_weights* W, const armt_layer_grads* G) {

@@ -95,6 +95,7 @@ struct GemmShape {
   int ldb;              // row stride of the weight blocks in elements (>= K); the weights of the model are dense: ldb = K
   float fparam = 0.f;   // EPI_DPFP_READ: assoc_eps
   int k_slot = 0;       // steps of 64 per unit of GemmGroup::krange
+  int spread = 0;       // 1: the groups differ in length, every one is spread over all XCDs
   int a_rows = 0;       // rows of A that may be READ in every group (0: M).  Operand buffers that are padded to whole
                         // tiles let a ragged M take the copies without per-lane clamping; rows >= M are never stored
 };

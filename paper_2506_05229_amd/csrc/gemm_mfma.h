@@ -116,8 +116,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   const int per_xcd = (total_tiles + 7) >> 3;
   const int lid0 = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (lid0 >= total_tiles) return;
-  const int lid = tile_begin + lid0;
   const int per_group = tiles_m * tiles_n;
+  int lid = tile_begin + lid0;
+  if (s.spread) {                          // (whole launches, groups of a multiple of 8 tiles)
+    const int share = per_group >> 3, i = blockIdx.x >> 3;
+    lid = i / share * per_group + (blockIdx.x & 7) * share + i % share;
+  }
   const int grp = lid / per_group, rem = lid - grp * per_group;
   // M-tiles of one weight panel are adjacent; tall problems are cut into M-groups of m_group tiles (mfma_m_group)
   const int mg = rem / (m_group * tiles_n), rem_mg = rem - mg * (m_group * tiles_n);
@@ -923,7 +927,7 @@ inline int mfma_unit_tile(int u, int tiles_m, int m_group, int tiles_n, int cols
 }
 
 template <int BM, int BN, int WGM, int WGN, bool REG, int EPI, bool TAIL, int NS>
-inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, const GemmShape& s, hipStream_t st,
+inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, GemmShape s, hipStream_t st,
                                    const TileRange& rng) {
   constexpr int BN_OUT = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   constexpr int LDS = mfma_tile_lds_bytes<BM, BN, WGM, WGN, EPI, TAIL, NS>() + (BM + 16) * 4;
@@ -936,6 +940,9 @@ inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, con
     total = mfma_unit_tile(rng.end, tiles_m, m_group, tiles_n, rng.unit_cols / BN_OUT) - begin;
   }
   if (total <= 0) return hipSuccess;
+  // Groups of unequal length (ranges of a reduction): a contiguous run of tiles per XCD would give some of them the long groups
+  // only, so every XCD takes an eighth of each group.  (Groups of equal length keep an XCD's weights to themselves.)
+  s.spread = s.spread && rng.unit_cols == 0 && tiles_m * tiles_n % 8 == 0;
   const int grid = ((total + 7) / 8) * 8;
   auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, REG, EPI, TAIL, NS>;
   // raising the dynamic-LDS limit is a per-function, per-device, idempotent setting: done once per device (a second
@@ -1048,7 +1055,7 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
           const int tiles = g * tm * panels, rem = tiles % MF_CUS, units = g * ((tm + mg - 1) / mg) * panels;
           int cut = units;                 // the last units that hold at least the tiles of the partial round
           while (cut > 0 && tiles - mfma_unit_tile(cut, tm, mg, panels, 1) < rem) --cut;
-          if (force_cfg < 0 && tiles > MF_CUS && rem != 0 && rem <= MF_CUS / 2 && cut > 0 && mfma_regular_shape<128, 128, EPI>(s)) {
+          if (force_cfg < 0 && !s.spread && tiles > MF_CUS && rem != 0 && rem <= MF_CUS / 2 && cut > 0 && mfma_regular_shape<128, 128, EPI>(s)) {
             TileRange big, rest;
             big.unit_cols = rest.unit_cols = 256;
             big.begin = 0; big.end = rest.begin = cut; rest.end = units;
