@@ -311,6 +311,32 @@ armt_status transpose(hipStream_t st, const Tin* src, size_t src_cell, int lds, 
   return ARMT_OK;
 }
 
+// Transposes whose results nobody needs before the end of a step: fp32 ones are collected and run in one launch (bf16 ones, of
+// wide models, run at once with 16-byte accesses).  The sources must stay as they are until run().
+template <typename T>
+struct TransposeQueue {
+  hipStream_t st;
+  TransposeJobs q;
+  int cells = 0;
+  explicit TransposeQueue(hipStream_t s) : st(s) { q.n = 0; }
+  armt_status add(const T* src, size_t src_cell, int lds, T* dst, size_t dst_cell, int ldd, int R, int C, int g) {
+    if (!std::is_same<T, float>::value) return transpose<T, T>(st, src, src_cell, lds, dst, dst_cell, ldd, R, C, g);
+    if (g <= 0 || R <= 0 || C <= 0) return ARMT_OK;
+    if (q.n == TRANSPOSE_JOBS) ARMT_TRY(run());
+    const int tc = (C + 31) / 32, before = q.n ? q.job[q.n - 1].end : 0;
+    q.job[q.n++] = TransposeJob{src, dst, src_cell, dst_cell, lds, ldd, R, C, g, tc, before + tc * ((R + 31) / 32), 0};
+    cells = std::max(cells, g);
+    return ARMT_OK;
+  }
+  armt_status run() {
+    if (q.n == 0) return ARMT_OK;
+    transpose_many_kernel<T><<<dim3(q.job[q.n - 1].end, 1, cells), dim3(32, 8), 0, st>>>(q);
+    q.n = cells = 0;
+    HIP_TRY(hipGetLastError());
+    return ARMT_OK;
+  }
+};
+
 inline unsigned ew_blocks(size_t n) { return (unsigned)std::max<size_t>(1, std::min<size_t>((n + 255) / 256, 65535)); }
 
 // Transposed copies of the weights, once per call: they are the B operands of the activation-gradient GEMMs.
@@ -323,6 +349,7 @@ armt_status transpose_weights(BCtx& c, const armt_layer_weights* W) {
   fill_f32_kernel<<<ew_blocks(nq), 256, 0, c.st>>>(c.at<float>(o.WmqT), nq * D.esz / 4, 0.f);   // K padding must read as zero
   fill_f32_kernel<<<ew_blocks(nk), 256, 0, c.st>>>(c.at<float>(o.WmkvT), nk * D.esz / 4, 0.f);
   HIP_TRY(hipGetLastError());
+  TransposeQueue<T> queue(c.st);
   for (int l = 0; l < D.Lr; ++l) {
     const armt_layer_weights& w = W[l];
     T* WdT = c.at<T>(o.WdT) + l * F * d;
@@ -331,18 +358,18 @@ armt_status transpose_weights(BCtx& c, const armt_layer_weights* W) {
     T* WqkvT = c.at<T>(o.WqkvT) + l * d * D.Nqkv;
     T* WmqT = c.at<T>(o.WmqT) + l * d * o.dmP;
     T* WmkvT = c.at<T>(o.WmkvT) + l * d * o.Kmkv;
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wdown, 0, D.F, WdT, 0, D.d, D.d, D.F, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wgate, 0, D.d, WguT, 0, 2 * D.F, D.F, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wup, 0, D.d, WguT + F, 0, 2 * D.F, D.F, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wo, 0, (int)Hd, WoT, 0, D.d, D.d, (int)Hd, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wq, 0, D.d, WqkvT, 0, D.Nqkv, (int)Hd, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wk, 0, D.d, WqkvT + Hd, 0, D.Nqkv, (int)Hkd, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wv, 0, D.d, WqkvT + Hd + Hkd, 0, D.Nqkv, (int)Hkd, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wm_q, 0, D.d, WmqT, 0, o.dmP, D.dm, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wm_k, 0, D.d, WmkvT, 0, o.Kmkv, D.dm, D.d, 1)));
-    ARMT_TRY((transpose<T, T>(c.st, (const T*)w.wm_v, 0, D.d, WmkvT + D.dm, 0, o.Kmkv, D.d, D.d, 1)));
+    ARMT_TRY(queue.add((const T*)w.wdown, 0, D.F, WdT, 0, D.d, D.d, D.F, 1));
+    ARMT_TRY(queue.add((const T*)w.wgate, 0, D.d, WguT, 0, 2 * D.F, D.F, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wup, 0, D.d, WguT + F, 0, 2 * D.F, D.F, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wo, 0, (int)Hd, WoT, 0, D.d, D.d, (int)Hd, 1));
+    ARMT_TRY(queue.add((const T*)w.wq, 0, D.d, WqkvT, 0, D.Nqkv, (int)Hd, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wk, 0, D.d, WqkvT + Hd, 0, D.Nqkv, (int)Hkd, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wv, 0, D.d, WqkvT + Hd + Hkd, 0, D.Nqkv, (int)Hkd, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wm_q, 0, D.d, WmqT, 0, o.dmP, D.dm, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wm_k, 0, D.d, WmkvT, 0, o.Kmkv, D.dm, D.d, 1));
+    ARMT_TRY(queue.add((const T*)w.wm_v, 0, D.d, WmkvT + D.dm, 0, o.Kmkv, D.d, D.d, 1));
   }
-  return ARMT_OK;
+  return queue.run();
 }
 
 // bf16 with head_dim 64 or 128 (what check_config admits for bf16): attention forward and backward on the matrix cores
@@ -448,11 +475,11 @@ armt_status backward_group(const BCtx& c, int lo, int g, int gr, int slot) {
   T* WB = c.at<T>(o.WinB) + lo_r * wb_cell + (size_t)slot * B * Tp;
   auto arow = [&](size_t r) { return WA + r * Kw; };
   auto brow = [&](size_t r) { return WB + r * Kw; };
+  TransposeQueue<T> queue(st);
   // transposes of n cells (from cell `lo` on) into window rows: sequence b of every layer goes to columns b * colstep
   auto wtr = [&](const T* src, size_t src_cell, int lds, T* dst, size_t dst_cell, int colstep, int ldd, int R, int C, int n) -> armt_status {
     for (int b = 0; b < B; ++b)
-      ARMT_TRY((transpose<T, T>(st, src + (size_t)b * src_cell, (size_t)B * src_cell, lds, dst + (size_t)b * colstep, dst_cell, ldd, R, C,
-                                n / B)));
+      ARMT_TRY(queue.add(src + (size_t)b * src_cell, (size_t)B * src_cell, lds, dst + (size_t)b * colstep, dst_cell, ldd, R, C, n / B));
     return ARMT_OK;
   };
   float* DX = c.at<float>(o.DX);
@@ -563,7 +590,7 @@ armt_status backward_group(const BCtx& c, int lo, int g, int gr, int slot) {
     ARMT_TRY(wtr(c.at<T>(o.DQr) + (size_t)lo * D.T * o.dmP, (size_t)D.T * o.dmP, o.dmP, arow(o.aDQR), wa_cell, Tp, Kw, D.T, D.dm, gr));
     ARMT_TRY(wtr(Xop + lo * cell, cell, D.d, brow(o.bX), wb_cell, Tp, Kw, D.T, D.d, gr));
   }
-  return ARMT_OK;
+  return queue.run();
 }
 
 template <typename T>

@@ -32,6 +32,34 @@ __global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ 
   }
 }
 
+// Up to TRANSPOSE_JOBS transposes of that kind in one launch, each with its own number of cells.  A step of the fp32 configuration has a
+// dozen of them of a few microseconds each, which were launches and little else.
+// grid: (tiles of all jobs, 1, largest number of cells), block: (32, 8).
+constexpr int TRANSPOSE_JOBS = 32;
+struct TransposeJob { const void* src; void* dst; size_t src_cell, dst_cell; int lds, ldd, R, C, cells, tiles_c, end, pad_; };
+struct TransposeJobs { TransposeJob job[TRANSPOSE_JOBS]; int n; };       // end: tiles of this job and those before it
+static_assert(sizeof(TransposeJobs) <= 3600, "kernel arguments are limited to 4 KB");
+template <typename T>
+__global__ __launch_bounds__(256) void transpose_many_kernel(TransposeJobs jobs) {
+  __shared__ float tile[32][33];
+  int w = 0;
+  while (w < jobs.n - 1 && (int)blockIdx.x >= jobs.job[w].end) ++w;
+  const TransposeJob j = jobs.job[w];
+  if ((int)blockIdx.z >= j.cells) return;
+  const int t = blockIdx.x - (w ? jobs.job[w - 1].end : 0), c0 = t % j.tiles_c * 32, r0 = t / j.tiles_c * 32;
+  const T* s = (const T*)j.src + (size_t)blockIdx.z * j.src_cell;
+  T* o = (T*)j.dst + (size_t)blockIdx.z * j.dst_cell;
+  for (int y = threadIdx.y; y < 32; y += 8) {
+    const int r = r0 + y, c = c0 + threadIdx.x;
+    tile[y][threadIdx.x] = (r < j.R && c < j.C) ? to_f32(s[(size_t)r * j.lds + c]) : 0.f;
+  }
+  __syncthreads();
+  for (int y = threadIdx.y; y < 32; y += 8) {
+    const int c = c0 + y, r = r0 + threadIdx.x;
+    if (c < j.C && r < j.R) o[(size_t)c * j.ldd + r] = from_f32<T>(tile[threadIdx.x][y]);
+  }
+}
+
 // The same for bf16 -> bf16 with 16-byte accesses on both sides: 64 x 64 tiles through LDS (row stride 66 keeps the
 // column reads of the second phase on distinct banks).  Needs C, lds, ldd multiples of 8 and 16-byte aligned bases;
 // rows [R, ldd) of a tile are written as zeros, which is what the padding columns of dst must hold anyway.
