@@ -88,28 +88,42 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
             acc[u][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.a[h][i][e], t.b[h][u][j][e], acc[u][i][j], 0, 0, 0);
   };
   if (wide) {
-    // branch-free: past this wave's share the last 16 bytes of the row are read and replaced by zeros
+    // branch-free: past the row's end its last 16 bytes are read again
     auto fetch = [&](Batch& t, int c) __attribute__((always_inline)) {
 #pragma unroll
       for (int h = 0; h < CH; ++h) {
-        const int k = 16 * (c + h) + 4 * q;
-        const bool in = c + h < c1 && k < s.K;
-        const int at = min(k, s.K - 4);
-        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        const int at = min(16 * (c + h) + 4 * q, s.K - 4);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) { const f32x4 v = *(const f32x4*)(a[i] + at); t.a[h][i] = in ? v : zero; }
+        for (int i = 0; i < TM; ++i) t.a[h][i] = *(const f32x4*)(a[i] + at);
 #pragma unroll
         for (int u = 0; u < NB; ++u)
 #pragma unroll
           for (int j = 0; j < TN; ++j) t.b[h][u][j] = *(const f32x4*)(b[u][j] + at);
       }
     };
+    // a batch that reaches past this wave's share of K: what lies there becomes zero in both operands (an infinity or NaN there
+    // times a zero would be a NaN in the sum).  Done in front of the products, where the batch has landed anyway.
+    auto trim = [&](Batch& t, int c) __attribute__((always_inline)) {
+#pragma unroll
+      for (int h = 0; h < CH; ++h) {
+        const bool in = c + h < c1 && 16 * (c + h) + 4 * q < s.K;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < TM; ++i) t.a[h][i] = in ? t.a[h][i] : zero;
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) t.b[h][u][j] = in ? t.b[h][u][j] : zero;
+      }
+    };
+    const int whole = min(16 * c1, s.K);
     Batch t, next;
     fetch(t, c0);
 #pragma unroll 1
     for (int c = c0; c < c1; c += CH) {
       const bool more = c + CH < c1;
       if (more) fetch(next, c + CH);
+      if (16 * (c + CH) > whole) trim(t, c);
 #pragma unroll
       for (int h = 0; h < CH; ++h) multiply(t, h);
       if (more) t = next;

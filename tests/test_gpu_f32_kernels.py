@@ -36,6 +36,22 @@ def test_f32_gemm(g, M, N, K, shift):
         assert ((out[i].double() - want).abs() <= bound + 1e-30).all(), i
 
 
+@pytest.mark.parametrize("operand", ["a", "b"])
+@pytest.mark.parametrize("K", [60, 192, 320, 2116])     # shares of K that end inside a batch of loads, or K inside a chunk
+def test_f32_gemm_infinities(K, operand):
+    """One infinity in every row of an operand, at positions spread over all of K: results are +-infinity, and never the NaN of
+    an infinity that was read past the end of a share of K and multiplied by zero."""
+    M, N = 33, 64
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    a, b = (torch.randn(r, K, device="cuda", generator=gen) for r in (M, N))
+    t = b if operand == "b" else a
+    rows = torch.arange(t.shape[0], device="cuda")
+    t[rows, rows * (K - 1) // (t.shape[0] - 1)] = float("inf")
+    out, = P.grouped_gemm([a], [b])
+    want = a.double() @ b.double().T
+    assert torch.isinf(want).all() and torch.equal(out.double(), want)
+
+
 @pytest.mark.parametrize("n_mem, d_mem", [(1, 32), (5, 32), (15, 64), (16, 32)])
 @pytest.mark.parametrize("d_model", [128, 200])
 def test_delta_rule_few_tokens(n_mem, d_mem, d_model):
