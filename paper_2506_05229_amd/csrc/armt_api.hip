@@ -303,10 +303,10 @@ template <typename T>
 armt_status gemm(hipStream_t st, const GemmGroup* table, int first, int g, const GemmShape& s) {
   if (g <= 0) return ARMT_OK;
   const bool timed = prof_start(s.tag, st);
-  if (std::is_same<T, bf16>::value && !debug_generic()) {
-    HIP_TRY(launch_gemm_mfma(table, first, g, s, st, g_gemm_tile_config));
-  } else if (std::is_same<T, float>::value) {
+  if constexpr (std::is_same<T, float>::value) {
     HIP_TRY(launch_gemm_f32(table, first, g, s, st));
+  } else if (!debug_generic()) {
+    HIP_TRY(launch_gemm_mfma(table, first, g, s, st, g_gemm_tile_config));
   } else {
     HIP_TRY(launch_gemm_generic<T>(table, first, g, s, st));
   }

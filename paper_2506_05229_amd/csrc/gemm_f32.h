@@ -9,8 +9,10 @@
 //
 // Against the plain FMA kernel, us per launch: 4 x (72 x 256, K 128) 19.9 -> 13.9, 4 x (72 x 128, K 512) 61.3 -> 14.4, 4 x (512 x 128,
 // K 2560) 313 -> 51, 1040 x 2048 x 2048 561 -> 226, 4096 x 4096 x 1024 1350 -> 824; error against 64 bits half as large (sums of
-// a quarter of the length).  Only many tiles whose rows cannot be read 16 bytes at a time stay with the other kernel
-// (launch_gemm_f32): 4 x (1000 x 1000, K 333) 127 us there, 144 here.
+// a quarter of the length).  Rows that cannot be read 16 bytes at a time are read element by element, in the same order: 4 x (1000 x
+// 1000, K 333) 127 -> 108 us, 4 x (4096 x 4096, K 1023) 6.56 -> 4.80 ms, 1 x (1032 x 512, K 1002) 139 -> 60.  One kernel for
+// all launches: which kernel runs may not depend on the number of groups, or a cell would have other bits alone, on a diagonal and
+// in a batch.
 #pragma once
 
 #include "common.h"
@@ -199,8 +201,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
 
 inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, const GemmShape& s, hipStream_t st) {
   if (g <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
-  if (((s.K | s.lda | s.ldb) & 3) && (int64_t)g * ((s.M + 63) / 64) * ((s.N + 63) / 64) >= 512)
-    return launch_gemm_generic<float>(table, first, g, s, st);
   const bool swiglu = s.epi == EPI_SWIGLU, narrow = s.M <= 16, brief = s.K <= 128;
   const dim3 grid((s.N + 31) / 32, (s.M + (narrow ? 15 : 31)) / (narrow ? 16 : 32), g);
   auto kern = swiglu ? (narrow ? (brief ? gemm_f32_kernel<1, true, 2> : gemm_f32_kernel<1, true, 4>)

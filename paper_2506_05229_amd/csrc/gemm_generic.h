@@ -1,6 +1,5 @@
 // Grouped GEMM, plain fp32 FMA version: any M, N, K, any activation type.
-// The shape-agnostic reference the matrix-core kernels are checked against, and the fp32 path of large problems whose
-// rows are not aligned to 16 bytes.
+// What the bf16 matrix-core kernels can be replaced by for debugging (ARMT_DEBUG_GENERIC=1).
 #pragma once
 
 #include "common.h"

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (2, 72, 128, 512, 0),
     (2, 72, 128, 512, 1),       # rows that start 4 bytes past a 16-byte boundary
     (1, 33, 40, 2116, 0),       # shares of 33 chunks: several batches and a partial one
-    (4, 700, 1000, 333, 0),     # many tiles of rows that cannot be read 16 bytes at a time
+    (4, 700, 1000, 333, 0),     # many tiles of rows that are not multiples of 16 bytes
 ])
 def test_f32_gemm(g, M, N, K, shift):
     gen = torch.Generator(device="cuda").manual_seed(M * N + K)
@@ -50,6 +50,28 @@ def test_f32_gemm_infinities(K, operand):
     out, = P.grouped_gemm([a], [b])
     want = a.double() @ b.double().T
     assert torch.isinf(want).all() and torch.equal(out.double(), want)
+
+
+@pytest.mark.parametrize("g, M, N, K", [(4, 700, 1000, 333), (9, 520, 512, 130)])
+def test_f32_gemm_bits_do_not_depend_on_the_group(g, M, N, K):
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    a, b = ([torch.randn(r, K, device="cuda", generator=gen) for _ in range(g)] for r in (M, N))
+    for i, t in enumerate(P.grouped_gemm(a, b)):
+        assert torch.equal(t, P.grouped_gemm([a[i]], [b[i]])[0]), i
+
+
+def test_f32_orders_same_bits_with_unaligned_rows():
+    """Diagonal, sequential and batched execution are the same recurrence bit for bit, also where the rows of a weight (d_ff = 1002)
+    are not multiples of 16 bytes and a diagonal holds many more tiles than a cell."""
+    shape = S.get_shape("tiny").replace(n_layers=4, d_model=512, n_heads=8, n_kv_heads=4, head_dim=64, d_ff=1002, seg_len=1032,
+                                        n_mem=8, d_mem=32, n_tokens=1032 * 4)
+    layers, mem_emb = S.make_weights(shape, seed=1)
+    model = P.Armt(shape, layers, mem_emb)
+    x = model.embed(np.stack([S.make_embeddings(shape, seed=2 + b) for b in range(2)]))
+    diagonal = [t.clone() for t in model.forward(x[0].contiguous(), diagonal=True)]
+    for other in (model.forward(x[0].contiguous(), diagonal=False), [t[0] for t in model.forward_batched(x, diagonal=True)]):
+        for u, v in zip(diagonal, other):
+            assert torch.equal(u, v)
 
 
 @pytest.mark.parametrize("n_mem, d_mem", [(1, 32), (5, 32), (15, 64), (16, 32)])
