@@ -349,7 +349,8 @@ armt_status step_attention(hipStream_t st, T* QKV, T* Att, bf16* Vt, const float
     return ARMT_OK;
   }
   attention_generic_kernel<T><<<dim3(Trows, H, g), 64, (dh + Trows) * 4, st>>>(QKV, Att, first, Trows, H, Hkv, dh,
-                                                                              1.0f / sqrtf((float)dh));
+                                                                              1.0f / sqrtf((float)dh),
+                                                                              (((uintptr_t)QKV | (uintptr_t)Att) & 15) == 0);
   HIP_TRY(hipGetLastError());
   return ARMT_OK;
 }

@@ -8,7 +8,8 @@ namespace armt {
 
 // The fp32 kernels (this one and the backward in backward_kernels.h) run one wave per row and head, so what bounds them is the chain of
 // memory latencies of that wave.  Where a head is 4, 8, ... 256 columns, rows are read 16 bytes at a time: a lane takes whole rows for the dot
-// products and, for weighted sums of rows, four columns of every (64 / (dh / 4))-th row.
+// products and, for weighted sums of rows, four columns of every (64 / (dh / 4))-th row.  The rows must then start on 16 bytes: the buffers of
+// the workspace do, a caller's need not.
 template <typename T>
 __device__ __forceinline__ bool quads_of_columns(int dh) {
   return sizeof(T) == 4 && (dh & 3) == 0 && dh <= 256 && 64 % (dh >> 2) == 0;
@@ -52,11 +53,11 @@ __device__ __forceinline__ void add_rows(f32x4& a, const float* w, const float* 
 }
 
 // QKV: [L][T][(H + 2 Hkv) dh], rows laid out [q heads | k heads | v heads], q and k already rotated.
-// Out: [L][T][H dh].  grid: (T, H, g), block: 64 (one wave per query row and head).
+// Out: [L][T][H dh].  aligned: both start on 16 bytes.  grid: (T, H, g), block: 64 (one wave per query row and head).
 template <typename T>
 __global__ __launch_bounds__(64) void attention_generic_kernel(const T* __restrict__ QKV, T* __restrict__ Out,
                                                                int first, int Trows, int H, int Hkv, int dh,
-                                                               float scale) {
+                                                               float scale, bool aligned) {
   extern __shared__ __align__(16) float sm[];      // q: dh floats, p: Trows floats
   float* q = sm;
   float* p = sm + dh;
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(64) void attention_generic_kernel(const T* __restri
   const T* vbase = base + (H + Hkv) * dh + kvh * dh;
   for (int c = lane; c < dh; c += 64) q[c] = to_f32(base[(size_t)i * ldq + h * dh + c]);
   __syncthreads();
-  const bool quads = quads_of_columns<T>(dh);
+  const bool quads = aligned && quads_of_columns<T>(dh);
   float mx = -INFINITY;
   for (int j = lane; j <= i; j += 64) {
     const float s = row_dot(q, kbase + (size_t)j * ldq, dh, quads) * scale;

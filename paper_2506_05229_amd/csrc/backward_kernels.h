@@ -318,7 +318,7 @@ __global__ __launch_bounds__(64) void attention_bwd_q_kernel(const T* __restrict
                                                              const T* __restrict__ dO, T* __restrict__ dQKV,
                                                              float* __restrict__ LSE, float* __restrict__ Dv, int first,
                                                              int Trows, int H, int Hkv, int dh, float scale) {
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* q = sm;
   float* go = sm + dh;
   float* p = sm + 2 * dh;
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(64) void attention_bwd_kv_kernel(const T* __restric
                                                               T* __restrict__ dQKV, const float* __restrict__ LSE,
                                                               const float* __restrict__ Dv, int first, int Trows, int H,
                                                               int Hkv, int dh, float scale) {
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* kj = sm;
   float* vj = sm + dh;
   float* pp = sm + 2 * dh;       // p_ij of the current 64 query rows

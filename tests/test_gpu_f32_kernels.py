@@ -1,5 +1,7 @@
 """The fp32 grouped GEMM and the delta rule with fewer than 16 memory tokens at the sizes where their tiles, K shares and
 vector loads end."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -72,6 +74,30 @@ def test_f32_orders_same_bits_with_unaligned_rows():
     for other in (model.forward(x[0].contiguous(), diagonal=False), [t[0] for t in model.forward_batched(x, diagonal=True)]):
         for u, v in zip(diagonal, other):
             assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("shift_in, shift_out", [(0, 0), (1, 0), (0, 3), (2, 1)])
+@pytest.mark.parametrize("dh", [4, 32, 20])
+def test_f32_attention_on_buffers_of_any_alignment(dh, shift_in, shift_out):
+    """The entry point asks for no alignment of its fp32 buffers: floats in front of them shift them off 16 bytes."""
+    H, Hkv, g = 4, 2, 2
+    shape = S.get_shape("tiny").replace(n_layers=g, d_model=H * dh, n_heads=H, n_kv_heads=Hkv, head_dim=dh, seg_len=70, n_mem=5)
+    T, steps = shape.T, P.ArmtSteps(shape)
+    qkv = np.random.default_rng(dh).standard_normal((g, T, (H + 2 * Hkv) * dh)).astype(np.float32)
+    src = torch.zeros(shift_in + qkv.size, device="cuda")[shift_in:].view(qkv.shape)
+    src.copy_(torch.from_numpy(qkv))
+    room = torch.full((shift_out + g * T * H * dh + 1,), 7.0, device="cuda")
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    code = steps.lib.armt_segment_attention(C.byref(steps.cfg), g, ptr(src), ptr(room[shift_out:]), ptr(steps.ws), steps.ws.numel(),
+                                            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert code == 0
+    got = room[shift_out:-1].view(g, T, H * dh).cpu().numpy()
+    assert (room[:shift_out] == 7.0).all() and room[-1] == 7.0
+    for i in range(g):
+        q, k, v = (t.reshape(T, -1, dh).astype(np.float64) for t in np.split(qkv[i], [H * dh, (H + Hkv) * dh], axis=1))
+        want = O.causal_gqa_attention(O.rope(q, shape.rope_theta), O.rope(k, shape.rope_theta), v).reshape(T, H * dh)
+        # averages of up to 75 values of order 1 with weights of sums of dh fp32 products
+        assert np.abs(got[i] - want).max() <= 2e-5
 
 
 @pytest.mark.parametrize("n_mem, d_mem", [(1, 32), (5, 32), (15, 64), (16, 32)])
