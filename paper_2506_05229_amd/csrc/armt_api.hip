@@ -370,11 +370,16 @@ armt_status step_assoc_update(hipStream_t st, const GemmGroup* t_mkv, const Gemm
   HIP_TRY(hipGetLastError());
   timed = prof_start(PK_DELTA_RULE, st);
   if (m <= 16 && Phi % 64 == 0 && Phi <= 512) {
-    // A block needs the 4 m Phi bytes of phi(k) once; fewer rows per block while the launch has less than two blocks per CU
-    const int rows_per_block = (int64_t)g * ((d + 31) / 32) >= 2 * MF_CUS ? 32 : 8;
+    // A block needs the 4 m Phi bytes of phi(k) once, so it takes as few rows as leave all blocks on the chip at the same time (three per
+    // CU: 133 registers at Phi = 384), and 32 in larger launches.  us for 8 / 16 / 32 rows, Phi = 384:
+    // d 2048: 1 cell 5.4 / 6.8 / 9.9, 3 cells 9.3 / 10.6 / 12.7, 4 cells 12.2 / 11.2 / 13.5, 6 cells 16.1 / 14.3 / 17.1, 8 cells 20.5 / 18.6 / 18.1,
+    // 12 cells 29.4 / 25.1 / 23.0; d 768: 8 cells 9.4 / 10.6 / 12.4, 12 cells 13.7 / 13.6 / 16.6, 16 cells 16.7 / 14.6 / 17.4
+    int rows_per_block = 8;
+    while (rows_per_block < 32 && (int64_t)g * ((d + rows_per_block - 1) / rows_per_block) > 3 * MF_CUS) rows_per_block *= 2;
     const dim3 grid((d + rows_per_block - 1) / rows_per_block, g);
 #define ARMT_DELTA16(NPL) \
-  case NPL: delta_rule16_kernel<NPL><<<grid, 256, 0, st>>>(KVm, Fm, Coef, aux, first, m, d, dm, rows_per_block); break;
+  case NPL: (m == 16 ? delta_rule16_kernel<NPL, true> : delta_rule16_kernel<NPL, false>)<<<grid, 256, 0, st>>>( \
+      KVm, Fm, Coef, aux, first, m, d, dm, rows_per_block); break;
     switch (Phi / 64) {
       ARMT_DELTA16(1) ARMT_DELTA16(2) ARMT_DELTA16(3) ARMT_DELTA16(4) ARMT_DELTA16(5) ARMT_DELTA16(6) ARMT_DELTA16(7)
       ARMT_DELTA16(8)

@@ -122,3 +122,20 @@ def test_delta_rule_few_tokens(n_mem, d_mem, d_model):
         # sums of d_model and Phi fp32 products, squared once by the feature map
         for got, want in ((Ad[i], wA), (zd[i], wz)):
             assert np.linalg.norm(got.cpu().numpy() - want) <= 1e-5 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n_mem", [5, 16])
+@pytest.mark.parametrize("d_model", [1000, 2048])       # 8 cells: 16 and 32 rows per block; one cell: 8
+def test_delta_rule_bits_do_not_depend_on_the_group(n_mem, d_model):
+    g = 8
+    shape = S.get_shape("tiny").replace(n_layers=g, d_model=d_model, n_heads=4, n_kv_heads=2, head_dim=d_model // 4, n_mem=n_mem,
+                                        d_mem=64, seg_len=16)
+    gen = torch.Generator(device="cuda").manual_seed(n_mem)
+    normal = lambda *dims: torch.randn(*dims, device="cuda", generator=gen)
+    w = [[0.05 * normal(r, d_model) for _ in range(g)] for r in (64, d_model, 1)]
+    ym, A, z = normal(g, n_mem, d_model), 0.1 * normal(g, d_model, shape.phi), normal(g, shape.phi).abs() + 0.1
+    steps = P.ArmtSteps(shape)
+    together = steps.assoc_update(ym, *w, A.clone(), z.clone())
+    for i in range(g):
+        alone = steps.assoc_update(ym[i:i + 1].contiguous(), *[t[i:i + 1] for t in w], A[i:i + 1].clone(), z[i:i + 1].clone())
+        assert torch.equal(alone[0][0], together[0][i]) and torch.equal(alone[1][0], together[1][i]), i
