@@ -1029,19 +1029,14 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
     case 1: return launch_mfma_cfg<128, 128, 2, 2, EPI>(table, first, g, s, st);
     case 3:   // 64 x 64: only instantiated for the plain fp32 store
       // four k-tiles in LDS: the loop of these small tiles is bound by the latency of a copy, not by its arithmetic
-      // (eight while there is at most one workgroup per CU)
-      if constexpr (EPI == EPI_STORE_F32) {
-        if ((long)g * ((s.N + 63) / 64) <= MF_CUS) return launch_mfma_cfg<64, 64, 2, 2, EPI, false, 8>(table, first, g, s, st);
-        return launch_mfma_cfg<64, 64, 2, 2, EPI, false, 4>(table, first, g, s, st);
-      }
+      // (eight do not pay, also not for at most one workgroup per CU: 12.0 us against 12.4 for one cell of d 2048, 20.6 / 19.4 for four of
+      // 3072, 7.9 / 8.9 for twelve of 768)
+      if constexpr (EPI == EPI_STORE_F32) return launch_mfma_cfg<64, 64, 2, 2, EPI, false, 4>(table, first, g, s, st);
       break;
     case 4:   // 32 x 128, waves side by side: only instantiated for the feature-map epilogue of the W_Q projection
       // three k-tiles in LDS (two workgroups still fit on a CU)
-      // (six while there is at most one workgroup per CU)
-      if constexpr (EPI == EPI_DPFP_READ) {
-        if ((long)g * ((s.M + 31) / 32) <= MF_CUS) return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 6>(table, first, g, s, st);
-        return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 3>(table, first, g, s, st);
-      }
+      // (six do not pay, also not for at most one workgroup per CU: 25.7 us with either for one cell of d 2048)
+      if constexpr (EPI == EPI_DPFP_READ) return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 3>(table, first, g, s, st);
       break;
     case 5:   // 256 x 256: pipelined loop of eight waves where the shape allows its copies to be addressed by scalar base + lane
               // offset, else 16 waves
