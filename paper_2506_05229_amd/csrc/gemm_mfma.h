@@ -123,10 +123,17 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     lid = i / share * per_group + (blockIdx.x & 7) * share + i % share;
   }
   const int grp = lid / per_group, rem = lid - grp * per_group;
-  // M-tiles of one weight panel are adjacent; tall problems are cut into M-groups of m_group tiles (mfma_m_group)
-  const int mg = rem / (m_group * tiles_n), rem_mg = rem - mg * (m_group * tiles_n);
-  const int mg_tiles = min(m_group, tiles_m - mg * m_group);
-  const int tn = rem_mg / mg_tiles, tm = mg * m_group + rem_mg - tn * mg_tiles;
+  // M-tiles of one weight panel are adjacent; tall problems are cut into M-groups of m_group tiles (mfma_m_group).  (A division is a
+  // few hundred cycles in front of the first copy of every tile: none for groups that a problem does not have.)
+  int mg0 = 0, rem_mg = rem, mg_tiles = tiles_m, last_tiles = tiles_m;      // first M-tile and M-tiles of the group, of the last one
+  if (m_group < tiles_m) {
+    const int mg = rem / (m_group * tiles_n);
+    mg0 = mg * m_group;
+    rem_mg = rem - mg0 * tiles_n;
+    mg_tiles = min(m_group, tiles_m - mg0);
+    last_tiles = tiles_m - (tiles_m - 1) / m_group * m_group;
+  }
+  const int tn = rem_mg / mg_tiles, tm = mg0 + rem_mg - tn * mg_tiles;
   GemmGroup g = table[first + grp];
   if (!restrict_k<bf16>(g, s)) return;
   const int m0 = tm * BM, n0 = tn * BN_OUT;
@@ -136,9 +143,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // halves of 128 columns (what a partial sum of squares and a head need), four interleaved ones for SwiGLU.  Tiles of unequal duration drift apart and then no longer find each
   // other's operands in the L2: with the whole strip on one of four M-tiles the gate/up launch of 16 cells took 1.04 ms
   // for 1040 rows and 0.914 ms for 1024.
-  const int strip_tiles = PIPE ? min(tiles_m - (tiles_m - 1) / m_group * m_group, EPI == EPI_SWIGLU ? 4 : 2) : 1;
-  const bool tail_blk = TAIL && tiles_m - 1 - tm < strip_tiles;        // block-uniform
-  auto my_unit = [&](int u) { return u % strip_tiles == tiles_m - 1 - tm; };
+  const int strip_tiles = PIPE ? min(last_tiles, EPI == EPI_SWIGLU ? 4 : 2) : 1, from_end = tiles_m - 1 - tm;
+  const bool tail_blk = TAIL && from_end < strip_tiles;        // block-uniform
+  // u mod strip_tiles == from_end, for u < 4
+  auto my_unit = [&](int u) { return strip_tiles == 1 || u == from_end || u == from_end + strip_tiles; };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -167,7 +175,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   int strip_sel = -1;
   if (PIPE && tail_blk) {
     if (EPI == EPI_SWIGLU) strip_sel = my_unit((wn + 2 * wm) & 3) ? wm : -1;
-    else strip_sel = strip_tiles == 1 ? wm : wm == 0 ? tiles_m - 1 - tm : -1;
+    else strip_sel = strip_tiles == 1 ? wm : wm == 0 ? from_end : -1;
   }
   auto blk_col = [&](int j) { return PIPE ? (j >> 1) * 128 + wn * 32 + (j & 1) * 16 : wn * WCOLS + j * 16; };
 
@@ -527,7 +535,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   const bool vec_ok = ((s.N | s.ldc | s.ldr | s.ldc2) & 3) == 0;
   // silu(gate) * up; the reciprocal is the hardware's (1 ulp), the result is rounded to bf16 afterwards
   auto silu_mul = [](float gt, float up) { return gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * up; };
-  auto row_scale = [&](int m) { return rs_lds[TAIL && m >= m0_strip ? BM + m - m0_strip : m - m0]; };
+  // scale of output row m; rs0: the row that entry 0 belongs to (strip_rs0 for rows of the strip).  (A test per element whether
+  // its row lies in the strip is a quarter of the vector instructions of the SwiGLU epilogue: 1.5 us per round of K = 768 tiles.)
+  auto row_scale = [&](int m, int rs0) { return rs_lds[m - rs0]; };
+  const int strip_rs0 = PIPE ? m0_strip - BM : m0;
   // EPI_DPFP_READ: feature idx = lane + 64 k of phi(q) = r[i] r[(i - j) mod 2 d_mem], r = [relu(q), relu(-q)], j = 1..nu
   // (the untrained feature map of Section 2.1) is max(sa q[ia], 0) max(sb q[ib], 0); which columns and signs, and the
   // lane's entries of z, are the same for every row: set up once per thread
@@ -594,7 +605,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   };
   // walk NROWS staged rows of staging tile stg; staged row sr is output row m_of(sr)
   // (`mine`, here and above: this thread's columns belong to this workgroup; always, except in a strip that several M-tiles share)
-  auto drain = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre, bool mine = true) __attribute__((always_inline)) {
+  auto drain = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre, int rs0, bool mine = true) __attribute__((always_inline)) {
     constexpr int NROWS = decltype(nrows_c)::value, ITER = (NROWS * C4 + NT - 1) / NT;
     if constexpr (EPI == EPI_DPFP_READ) {
       // One wave per staged row: the row's d_mem values q sit in the staging tile; lane L computes the features
@@ -658,13 +669,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       f32x4 o = {0.f, 0.f, 0.f, 0.f};
       if (valid) {
         o = *(const f32x4*)(stg + sr * SLD + c4 * 4);
-        if (EPI != EPI_SWIGLU) o *= row_scale(m);        // SwiGLU applied it before the nonlinearity
+        if (EPI != EPI_SWIGLU) o *= row_scale(m, rs0);        // SwiGLU applied it before the nonlinearity
         if constexpr (EPI == EPI_QKV_ROPE) {
           if (n < s.n0 + s.n1) {
             // rotary embedding (rotate-half): column j of a head pairs with j +- dh/2, which lies in the same
             // staged row; out_j = x_j cos_j' - x_{j+h} sin_j' (j < h), x_j cos_j' + x_{j-h} sin_j' (j >= h), j' = j mod h
             const int dh = s.ldr, hd = dh >> 1, j = n % dh, lo = j < hd;
-            const f32x4 p = *(const f32x4*)(stg + sr * SLD + c4 * 4 + (lo ? hd : -hd)) * row_scale(m);
+            const f32x4 p = *(const f32x4*)(stg + sr * SLD + c4 * 4 + (lo ? hd : -hd)) * row_scale(m, rs0);
             const f32x4 cs0 = rc0[it], cs1 = rc1[it];
             const float sg = lo ? -1.f : 1.f;
             o[0] = o[0] * cs0[0] + sg * p[0] * cs0[1];
@@ -734,7 +745,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       pre.r[it] = g.R ? *(const f32x4*)(g.R + (size_t)m * s.ldr + n) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
-  auto drain_whole = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre, bool mine = true) __attribute__((always_inline)) {
+  auto drain_whole = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre) __attribute__((always_inline)) {
     constexpr int ITER = decltype(nrows_c)::value * C4 / NT;
     f32x4 o[ITER];
     float rs[ITER];
@@ -742,12 +753,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     for (int it = 0; it < ITER; ++it) {
       const int sr = sr_first + it * (NT / C4);
       o[it] = *(const f32x4*)(stg + sr * SLD + c4 * 4);
-      rs[it] = EPI == EPI_SWIGLU ? 1.f : row_scale(m_of(sr));
+      rs[it] = EPI == EPI_SWIGLU ? 1.f : row_scale(m_of(sr), m0);
     }
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
       const int m = m_of(sr_first + it * (NT / C4));
-      const bool valid = m < s.M && mine;
+      const bool valid = m < s.M;
       f32x4 v = o[it];
       if (EPI != EPI_SWIGLU) v *= rs[it];
       if (EPI == EPI_RESID_F32) v += pre.r[it];
@@ -787,7 +798,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       pre.r[RIT + it] = *(const f32x4*)(cs + 4);
     }
   };
-  auto drain_rope = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre, bool strip = false) __attribute__((always_inline)) {
+  auto drain_rope = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre) __attribute__((always_inline)) {
     constexpr int ROWS = decltype(nrows_c)::value, ITER = (ROWS * R2 + NT - 1) / NT;
     f32x4 lo[ITER], hi[ITER];
     float rs[ITER];
@@ -796,7 +807,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       const int sr = rrow + it * (NT / R2);
       lo[it] = *(const f32x4*)(stg + sr * SLD + rlo);
       hi[it] = *(const f32x4*)(stg + sr * SLD + rlo + rhd);
-      rs[it] = row_scale(m_of(sr));
+      rs[it] = row_scale(m_of(sr), m0);
     }
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
@@ -808,7 +819,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       oa[1] = (bf16)(a[1] * c0[2] + -1.f * b[1] * c0[3]);  ob[1] = (bf16)(b[1] * c0[2] + 1.f * a[1] * c0[3]);
       oa[2] = (bf16)(a[2] * c1[0] + -1.f * b[2] * c1[1]);  ob[2] = (bf16)(b[2] * c1[0] + 1.f * a[2] * c1[1]);
       oa[3] = (bf16)(a[3] * c1[2] + -1.f * b[3] * c1[3]);  ob[3] = (bf16)(b[3] * c1[2] + 1.f * a[3] * c1[3]);
-      if (m >= s.M || (strip && !strip_mine(rlo))) continue;
+      if (m >= s.M) continue;
       bf16* out = (bf16*)g.C + (size_t)m * s.ldc + n0 + rlo;
       *(bf16x4*)out = oa;
       *(bf16x4*)(out + rhd) = ob;
@@ -817,7 +828,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // EPI_QKV_ROPE, tiles of the v columns: the attention kernel wants V transposed ([column][row], row stride ldc2),
   // so these tiles are drained column-wise: a thread takes 8 consecutive rows of one column, 16 bytes per store.
   const bool vt_tile = EPI == EPI_QKV_ROPE && s.ldc2 > 0 && n0 >= s.n0 + s.n1;      // block-uniform
-  auto drain_vt = [&](const float* stg, int nrows, auto m_of, bool strip = false) __attribute__((always_inline)) {
+  auto drain_vt = [&](const float* stg, int nrows, auto m_of, int rs0, bool strip = false) __attribute__((always_inline)) {
     bf16* vt = (bf16*)g.C2 + (size_t)(n0 - (s.n0 + s.n1)) * s.ldc2;
     for (int u = tid; u < (nrows >> 3) * BN_OUT; u += NT) {
       const int rg = u / BN_OUT, col = u - rg * BN_OUT;
@@ -826,7 +837,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       bf16x8 v;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        v[i] = (m + i < s.M) ? (bf16)(stg[(rg * 8 + i) * SLD + col] * row_scale(m + i)) : (bf16)0.f;
+        v[i] = (m + i < s.M) ? (bf16)(stg[(rg * 8 + i) * SLD + col] * row_scale(m + i, rs0)) : (bf16)0.f;
       *(bf16x8*)(vt + (size_t)col * s.ldc2 + m) = v;
     }
   };
@@ -861,7 +872,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
           // the wave's weight rows come in 32-row blocks, gate / up alternating: tiles 4q + h (gate) and 4q + 2 + h
           // (up), h = 0, 1, give output columns (wn * WCOLS / 64 + q) * 32 + h * 16 + lane % 16; the same for the pipelined
           // tile (q = 0), whose gate and up blocks are its lower and upper half
-          const float rs = row_scale(m0 + blk_row(i) + row16);
+          const float rs = rs_lds[blk_row(i) + row16];
 #pragma unroll
           for (int j = 0; j < TN; ++j)
             if ((j & 2) == 0)
@@ -873,10 +884,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       }
     if (whole && AHEAD && pass + 1 < PASSES) request(AllRows{}, row_of_pass(pass + 1), pre[(pass + 1) & 1]);
     __syncthreads();         // pass p is staged; everybody has left the walk of pass p - 1, whose tile pass p + 1 reuses
-    if (vt_tile) drain_vt(stg, SR, pass_row);
+    if (vt_tile) drain_vt(stg, SR, pass_row, m0);
     else if (EPI == EPI_QKV_ROPE && whole && rotated) drain_rope(stg, AllRows{}, pass_row, now);
     else if (whole) drain_whole(stg, AllRows{}, pass_row, now);
-    else drain(stg, AllRows{}, pass_row, now);
+    else drain(stg, AllRows{}, pass_row, now, m0);
   }
   if (TAIL && tail_blk) {     // 16x16 result tile: lane holds column lane % 16, rows 4*(lane/16) + r
     float* stg = (float*)smem + (PASSES & 1) * STG_FLOATS;
@@ -887,7 +898,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       for (int r = 0; r < 4; ++r) {
         float* dst = stg + (4 * t_q + r) * SLD;
         if (EPI == EPI_SWIGLU) {
-          const float rs = row_scale(m0_strip + 4 * t_q + r);
+          const float rs = rs_lds[BM + 4 * t_q + r];
           dst[PIPE ? t_brow : (wave >> 1) * 32 + (wave & 1) * 16 + (lane & 15)] = silu_mul(rs * tacc[0][r], rs * tacc[1][r]);
         } else {
           dst[t_brow] = tacc[0][r];
@@ -896,8 +907,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       }
     }
     __syncthreads();
-    if (vt_tile) drain_vt(stg, 16, tail_row, true);
-    else drain(stg, std::integral_constant<int, 16>{}, tail_row, pre[0], strip_mine(c4 * 4));
+    if (vt_tile) drain_vt(stg, 16, tail_row, strip_rs0, true);
+    else drain(stg, std::integral_constant<int, 16>{}, tail_row, pre[0], strip_rs0, strip_mine(c4 * 4));
   }
 #ifdef ARMT_GEMM_TIMELINE
   if (tl_on && threadIdx.x == 0) { tl[5] = __builtin_readcyclecounter(); tl[6] = __builtin_amdgcn_s_memrealtime(); }
