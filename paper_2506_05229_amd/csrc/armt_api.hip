@@ -961,7 +961,7 @@ int32_t armt_set_gemm_tile_config(int32_t config) {
   const int32_t old = g_gemm_tile_config;
   g_gemm_dbg = config >= 100 ? config / 100 : 0;
   if (config >= 100) config %= 100;
-  g_gemm_tile_config = (config >= 1 && config <= 6) ? config : -1;
+  g_gemm_tile_config = (config >= 1 && config < MF_NUM_CONFIGS) ? config : -1;
   return old;
 }
 
