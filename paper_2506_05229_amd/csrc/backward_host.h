@@ -203,6 +203,8 @@ void fill_train_shapes(BCtx& c) {
   set(TK_WMV, D.d, D.d, Km, Km, D.d, EPI_RESID_F32, -1, 0, Km);
   for (int k : kWindowGrads) {
     c.shape[k].k_slot = D.B * ((k == TK_WMK || k == TK_WMV) ? o.mp : o.Tp) / 64;
+    // also where all layers are live in the whole window: 1B, backward over 49152 tokens 392.0 ms, 393.6 with an XCD's layers to itself,
+    // over 98304 tokens 767.4 and 770.5
     c.shape[k].spread = 1;
   }
 }
@@ -293,6 +295,10 @@ armt_status upload_train_tables(BCtx& c, const armt_layer_weights* W, const armt
   return ARMT_OK;
 }
 
+// Only the 16-byte bf16 kernel writes the zeros behind the R columns that a reduction needs (up to the next multiple of 64); the
+// other one leaves them as they are.  The bf16 operands of the weight gradients rely on it and are never cleared: their widths are
+// multiples of 8, their strides of 64 (check_config), their sources and destinations in the workspace.  A caller's weight may
+// be anywhere; where its transpose has padding that is cleared first (W_Q^mem, [W_K | W_V]^mem, a head that starts off 16 bytes).
 template <typename Tin, typename Tout>
 armt_status transpose(hipStream_t st, const Tin* src, size_t src_cell, int lds, Tout* dst, size_t dst_cell, int ldd, int R, int C,
                       int g) {
@@ -320,7 +326,7 @@ struct TransposeQueue {
   int cells = 0;
   explicit TransposeQueue(hipStream_t s) : st(s) { q.n = 0; }
   armt_status add(const T* src, size_t src_cell, int lds, T* dst, size_t dst_cell, int ldd, int R, int C, int g) {
-    if (!std::is_same<T, float>::value) return transpose<T, T>(st, src, src_cell, lds, dst, dst_cell, ldd, R, C, g);
+    if constexpr (!std::is_same<T, float>::value) return transpose<T, T>(st, src, src_cell, lds, dst, dst_cell, ldd, R, C, g);
     if (g <= 0 || R <= 0 || C <= 0) return ARMT_OK;
     if (q.n == TRANSPOSE_JOBS) ARMT_TRY(run());
     const int tc = (C + 31) / 32, before = q.n ? q.job[q.n - 1].end : 0;
@@ -329,10 +335,12 @@ struct TransposeQueue {
     return ARMT_OK;
   }
   armt_status run() {
-    if (q.n == 0) return ARMT_OK;
-    transpose_many_kernel<T><<<dim3(q.job[q.n - 1].end, 1, cells), dim3(32, 8), 0, st>>>(q);
-    q.n = cells = 0;
-    HIP_TRY(hipGetLastError());
+    if constexpr (std::is_same<T, float>::value) {
+      if (q.n == 0) return ARMT_OK;
+      transpose_many_kernel<<<dim3(q.job[q.n - 1].end, 1, cells), dim3(32, 8), 0, st>>>(q);
+      q.n = cells = 0;
+      HIP_TRY(hipGetLastError());
+    }
     return ARMT_OK;
   }
 };

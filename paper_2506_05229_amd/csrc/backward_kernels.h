@@ -39,7 +39,6 @@ constexpr int TRANSPOSE_JOBS = 32;
 struct TransposeJob { const void* src; void* dst; size_t src_cell, dst_cell; int lds, ldd, R, C, cells, tiles_c, end, pad_; };
 struct TransposeJobs { TransposeJob job[TRANSPOSE_JOBS]; int n; };       // end: tiles of this job and those before it
 static_assert(sizeof(TransposeJobs) <= 3600, "kernel arguments are limited to 4 KB");
-template <typename T>
 __global__ __launch_bounds__(256) void transpose_many_kernel(TransposeJobs jobs) {
   __shared__ float tile[32][33];
   int w = 0;
@@ -47,16 +46,16 @@ __global__ __launch_bounds__(256) void transpose_many_kernel(TransposeJobs jobs)
   const TransposeJob j = jobs.job[w];
   if ((int)blockIdx.z >= j.cells) return;
   const int t = blockIdx.x - (w ? jobs.job[w - 1].end : 0), c0 = t % j.tiles_c * 32, r0 = t / j.tiles_c * 32;
-  const T* s = (const T*)j.src + (size_t)blockIdx.z * j.src_cell;
-  T* o = (T*)j.dst + (size_t)blockIdx.z * j.dst_cell;
+  const float* s = (const float*)j.src + (size_t)blockIdx.z * j.src_cell;
+  float* o = (float*)j.dst + (size_t)blockIdx.z * j.dst_cell;
   for (int y = threadIdx.y; y < 32; y += 8) {
     const int r = r0 + y, c = c0 + threadIdx.x;
-    tile[y][threadIdx.x] = (r < j.R && c < j.C) ? to_f32(s[(size_t)r * j.lds + c]) : 0.f;
+    tile[y][threadIdx.x] = (r < j.R && c < j.C) ? s[(size_t)r * j.lds + c] : 0.f;
   }
   __syncthreads();
   for (int y = threadIdx.y; y < 32; y += 8) {
     const int c = c0 + y, r = r0 + threadIdx.x;
-    if (c < j.C && r < j.R) o[(size_t)c * j.ldd + r] = from_f32<T>(tile[threadIdx.x][y]);
+    if (c < j.C && r < j.R) o[(size_t)c * j.ldd + r] = tile[threadIdx.x][y];
   }
 }
 
@@ -536,7 +535,10 @@ __global__ __launch_bounds__(128) void read_bwd_dpfp_kernel(const float* __restr
 // of the outer products are broadcast through scalar registers; the next row is requested before the current one is worked on.
 // grid: (ceil(d / rows_per_block), g), block: 256; Phi <= 64 * NPL; LDS: UB_M * (64 NPL + Phi + 2) floats.
 constexpr int UB_M = 16;
-// rows per block: a wave takes a quarter of them one after another, so narrow models, whose launches are few blocks, take fewer
+// rows per block: a wave takes a quarter of them one after another, so narrow models, whose launches are few blocks, take fewer.  A CU holds
+// one block (256 registers and more at Phi = 384), so more than 256 blocks are a second round.  us for 8 / 32 rows, this kernel and
+// update_bwd_tokens_kernel, which adds the blocks' parts: d 128: 42 / 54 (44 / 55 for 16 cells); d 256: 44 / 57, 76 / 58 from 12 cells
+// on; d 512: 47 / 54 for one cell, 80 / 55 for 8; d 2048: 68 / 61 and 283 / 105
 inline int update_bwd_rows_per_block(int d) { return d >= 512 ? 32 : 8; }
 template <int NPL>
 __global__ __launch_bounds__(256) void update_bwd_rows_kernel(const float* __restrict__ KV, const float* __restrict__ Fm,
