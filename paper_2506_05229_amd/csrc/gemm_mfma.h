@@ -140,9 +140,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   const int m0_strip = tiles_m * BM;                        // first row of the strip (TAIL)
   // Who computes the strip of 16 rows behind the last M-tile: the last M-tile, or, pipelined, the last M-tiles of the last
   // M-group, each on a share of the columns: unit u belongs to the M-tile u % strip_tiles from the end.  The units are the two
-  // halves of 128 columns (what a partial sum of squares and a head need), four interleaved ones for SwiGLU.  Tiles of unequal duration drift apart and then no longer find each
-  // other's operands in the L2: with the whole strip on one of four M-tiles the gate/up launch of 16 cells took 1.04 ms
-  // for 1040 rows and 0.914 ms for 1024.
+  // halves of 128 columns (what a partial sum of squares and a head need), four interleaved ones for SwiGLU.  The strip still costs more
+  // than its 1.6 % of the products: 16 x (1040 x 16384, K 2048) takes 0.960 ms, 1024 rows 0.892 (tiles of unequal duration drift
+  // apart and then no longer find each other's operands in the L2).
   const int strip_tiles = PIPE ? min(last_tiles, EPI == EPI_SWIGLU ? 4 : 2) : 1, from_end = tiles_m - 1 - tm;
   const bool tail_blk = TAIL && from_end < strip_tiles;        // block-uniform
   // u mod strip_tiles == from_end, for u < 4
@@ -1050,7 +1050,8 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
       if constexpr (EPI == EPI_DPFP_READ) return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 3>(table, first, g, s, st);
       break;
     case 5:   // 256 x 256: pipelined loop of eight waves where the shape allows its copies to be addressed by scalar base + lane
-              // offset, else 16 waves
+              // offset, else 16 waves.  Also for short loops and the SwiGLU strip, where it gains least; us per launch of gate/up with
+              // 16 waves / pipelined: twelve cells of 1040 x 6144, K 768: 105.4 / 103.4; sixteen of 528 x 16384, K 2048: 409 / 403
       if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) {
         if constexpr (EPI != EPI_SWIGLU) {
           // Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs
