@@ -338,7 +338,7 @@ armt_status armt_lm_head_static(const armt_config *cfg, const void *hidden, int6
  * epilogue of the W_Q projection only (other epilogues run 2 instead);
  * 5: 256x256, 8 waves with a pipelined main loop where the shape lets its copies be addressed by scalar base + lane offset, else 16
  * waves; 6: as 1 with copies addressed that way where the shape allows; 7: 64x128, 4 waves, and 8: 128x128, 8 waves, four k-tiles in LDS,
- * for launches of at most one workgroup per CU; anything else below 100: choose by shape and tile count, the default). config = 100 *
+ * for launches of at most one workgroup per CU; anything else below 100: choose by shape and tile count, the default).  config = 100 *
  * switches + tile configuration (or + 99 for the default choice) additionally turns fusions off, for A/B timing:
  * switch 16 the feature map of the read in the epilogue of the W_Q projection, 32 the strip of memory rows in the last
  * M-tile, 64 the transposed V written by the QKV epilogue, 128 the rotary embedding in the QKV epilogue (plain kernels
