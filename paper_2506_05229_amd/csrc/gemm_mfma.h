@@ -42,6 +42,15 @@ template <int N>
 __device__ __forceinline__ void mf_wait_vmcnt() {      // s_waitcnt vmcnt(N) only (N <= 63)
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
 }
+// vmcnt(N) if left >= 0, else vmcnt(0); left is wave-uniform.  The branch is inside the asm: one that the compiler sees ends its block, and
+// then the barrier behind the wait is not moved in front of a k-tile's last MFMAs, which need nothing but registers.  64 x 128 tiles with
+// four stages, us, branch in the source / here: 16 x 2048, K 5632 36.1 / 32.9 (operands from the L2; two stages: 32.9)
+template <int N>
+__device__ __forceinline__ void mf_wait_vmcnt_if(int left) {
+  static_assert(N <= 63, "vmcnt has six bits");
+  asm volatile("s_cmp_ge_i32 %0, 0\n\ts_cbranch_scc1 .Lmf_wait_%=\n\ts_waitcnt vmcnt(0)\n.Lmf_wait_%=:\n\ts_waitcnt vmcnt(%1)"
+               : : "s"(__builtin_amdgcn_readfirstlane(left)), "n"(N) : "memory", "scc");
+}
 
 #ifdef ARMT_GEMM_TIMELINE
 // Probe build (paper_2506_05229_amd.build.build_timeline, never the product library): one armed launch records, per
@@ -479,6 +488,19 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       if (kt + NS - 1 < nk) issue_tile(kt + NS - 1, nxt);
       const unsigned char* As = smem + cur * A_BYTES;
       const unsigned char* Bs = smem + NS * A_BYTES + cur * B_BYTES;
+      // (the strip first: behind the others, its branch would stand between the last products and the barrier; 80 x 64, K 5632: 51.1 -> 47.9 us)
+      if (TAIL && tail) {
+#pragma unroll
+        for (int ks2 = 0; ks2 < KS2; ++ks2) {
+          const int ko = koff[ks2];
+          const bf16x8 ta = *(const bf16x8*)(As + t_a + ko);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const bf16x8 tb = *(const bf16x8*)(Bs + t_b + t * 32 * ROWB + ko);
+            tacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta, tb, tacc[t], 0, 0, 0);
+          }
+        }
+      }
 #pragma unroll
       for (int ks2 = 0; ks2 < KS2; ++ks2) {
         bf16x8 af[TM], bfr[TN];
@@ -492,24 +514,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
           for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
       }
-      if (TAIL && tail) {
-#pragma unroll
-        for (int ks2 = 0; ks2 < KS2; ++ks2) {
-          const int ko = koff[ks2];
-          const bf16x8 ta = *(const bf16x8*)(As + t_a + ko);
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            const bf16x8 tb = *(const bf16x8*)(Bs + t_b + t * 32 * ROWB + ko);
-            tacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta, tb, tacc[t], 0, 0, 0);
-          }
-        }
-      }
-      // tile kt+1 must have landed; tiles kt+2 .. kt+NS-1 (if they were issued) may stay in flight
-      if (NS > 2 && kt + NS - 1 < nk) {
-        if (extra) mf_wait_vmcnt<(NS - 2) * (CNT + 1)>(); else mf_wait_vmcnt<(NS - 2) * CNT>();
-      } else {
-        mf_wait_vmcnt<0>();
-      }
+      // tile kt+1 must have landed; tiles kt+2 .. kt+NS-1 (if they were issued) may stay in flight (waves that also copy the strip
+      // wait for a little more than they need)
+      if constexpr (NS > 2) mf_wait_vmcnt_if<(NS - 2) * CNT>(nk - kt - NS);
+      else mf_wait_vmcnt<0>();
       __syncthreads();
       cur = (cur + 1 == NS) ? 0 : cur + 1;
       nxt = (nxt + 1 == NS) ? 0 : nxt + 1;
@@ -1019,7 +1027,8 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
     const long tm = (s.M > bm && s.M % bm == 16) ? s.M / bm : (s.M + bm - 1) / bm, cols = s.epi == EPI_SWIGLU ? 64 : 128;
     return g * tm * ((s.N + cols - 1) / cols);
   };
-  if (s.epi != EPI_DPFP_READ && tiles_of(64) <= MF_CUS) return 7;
+  // (one or two k-tiles do not fill a ring: 64 x 1536, K 128 6.3 us with two stages, 6.7 with four, K 192 7.1 and 7.0, K 1024 14.6 and 11.7)
+  if (s.epi != EPI_DPFP_READ && tiles_of(64) <= MF_CUS) return s.K > 2 * MF_BK ? 7 : 2;
   if (s.M < 96 || s.N < 96) return 2;
   if (s.epi != EPI_DPFP_READ && tiles_of(128) <= MF_CUS) return 8;
   const int tm = (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256;
