@@ -405,18 +405,27 @@ armt_status step_assoc_update(hipStream_t st, const GemmGroup* t_mkv, const Gemm
   return ARMT_OK;
 }
 
-// One step: the cells of layers [lo, hi] (each on its own segment), as one group.
-//   read_hi: highest layer whose memory is non-empty (the associative read applies to [lo, read_hi]);
-//   empty_layer: the layer whose memory is still empty (v_bar = 0), or -1.
+// Memory update of the cells of layers [lo, hi], whose block has run, from the output rows in their slots;
+//   [empty_lo, empty_hi): the layers whose memory is still empty (v_bar = 0).
 template <typename T>
-armt_status run_group(const Ctx& c, int lo, int hi, int read_hi, int empty_layer) {
+armt_status update_group(const Ctx& c, int lo, int hi, int empty_lo, int empty_hi) {
+  const Dims& D = c.D;
+  const T* Xop = D.bf16 ? c.at<T>(c.o.Xb) : (const T*)c.at<float>(c.o.X);
+  const T* Y0 = Xop + ((size_t)D.B * D.T + D.S) * D.d;  // memory row 0 of slot B = output of cell 0
+  return step_assoc_update<T>(c.st, c.table(K_MKV), c.shape[K_MKV], c.aux, lo * D.B, (hi - lo + 1) * D.B, empty_lo * D.B,
+                              empty_hi * D.B, Y0, (size_t)D.T * D.d, D.m, D.d, D.dm, D.nu, D.assoc_eps, c.at<float>(c.o.KVm),
+                              c.at<float>(c.o.Fm), c.at<float>(c.o.Coef));
+}
+
+// One step without its memory update: the cells of layers [lo, hi] (each on its own segment), as one group.
+//   read_hi: highest layer whose memory is non-empty (the associative read applies to [lo, read_hi]).
+template <typename T>
+armt_status run_group(const Ctx& c, int lo, int hi, int read_hi) {
   const Dims& D = c.D;
   // real layers -> cells: layer l of the B sequences = cells l * B .. l * B + B - 1
   const int g = (hi - lo + 1) * D.B, gr = (read_hi - lo + 1) * D.B;
-  const int e0 = empty_layer < 0 ? -1 : empty_layer * D.B, e1 = empty_layer < 0 ? -1 : e0 + D.B;
   lo *= D.B;
   float* X = c.at<float>(c.o.X);
-  T* Xop = D.bf16 ? c.at<T>(c.o.Xb) : (T*)X;
   // (1) associative read
   ARMT_TRY(step_assoc_read<T>(c.st, c.table(K_MQ), c.shape[K_MQ], c.table(K_READ), c.shape[K_READ], c.aux, lo,
                               gr, D.T, D.dm, D.nu, D.assoc_eps, c.at<float>(c.o.Qm), c.at<T>(c.o.Fphi),
@@ -450,12 +459,7 @@ armt_status run_group(const Ctx& c, int lo, int hi, int read_hi, int empty_layer
   }
   HIP_TRY(hipGetLastError());
   ARMT_TRY(gemm<T>(c.st, c.table(K_GU), lo, g, c.shape[K_GU]));
-  ARMT_TRY(gemm<T>(c.st, c.table(K_DOWN), lo, g, c.shape[K_DOWN]));
-  // (3) memory update from the block's output at the memory rows
-  const T* Y0 = Xop + ((size_t)D.B * D.T + D.S) * D.d;  // memory row 0 of slot B = output of cell 0
-  return step_assoc_update<T>(c.st, c.table(K_MKV), c.shape[K_MKV], c.aux, lo, g, e0, e1, Y0, (size_t)D.T * D.d,
-                              D.m, D.d, D.dm, D.nu, D.assoc_eps, c.at<float>(c.o.KVm), c.at<float>(c.o.Fm),
-                              c.at<float>(c.o.Coef));
+  return gemm<T>(c.st, c.table(K_DOWN), lo, g, c.shape[K_DOWN]);
 }
 
 // Training forward: record the inputs of the cells of layers [lo, hi] (cell l belongs to segment t - l).
@@ -509,8 +513,11 @@ armt_status forward_typed(Ctx& c, const void* mem_emb, const void* x, int64_t N,
       const bool empty = (s == 0 && !carry_in);
       for (int l = 0; l < L; ++l) {
         ARMT_TRY(save_tape(c, l, l, (int)s + l));
-        ARMT_TRY(run_group<T>(c, l, l, empty ? l - 1 : l, empty ? l : -1));
+        ARMT_TRY(run_group<T>(c, l, l, empty ? l - 1 : l));
       }
+      // Nothing of this segment reads an updated memory and every layer's output stays in its slot until the next one, so the
+      // updates of all layers go out together: a cell's three launches are 23 us of latencies, 16 cells' are 70.
+      ARMT_TRY(update_group<T>(c, 0, L - 1, 0, empty ? L : 0));
       ARMT_TRY(emit(s));
     }
   } else {
@@ -525,12 +532,12 @@ armt_status forward_typed(Ctx& c, const void* mem_emb, const void* x, int64_t N,
       if (hi - lo + 1 <= split_upto) {
         // the cells of a small group one at a time, highest layer first: cell l writes slot l + 1, the input of cell l + 1
         for (int l = hi; l >= lo; --l) {
-          const bool e = top_empty && l == hi;
-          ARMT_TRY(run_group<T>(c, l, l, e ? l - 1 : l, e ? l : -1));
+          ARMT_TRY(run_group<T>(c, l, l, top_empty && l == hi ? l - 1 : l));
         }
       } else {
-        ARMT_TRY(run_group<T>(c, lo, hi, top_empty ? hi - 1 : hi, top_empty ? hi : -1));
+        ARMT_TRY(run_group<T>(c, lo, hi, top_empty ? hi - 1 : hi));
       }
+      ARMT_TRY(update_group<T>(c, lo, hi, top_empty ? hi : 0, top_empty ? hi + 1 : 0));
       if (hi == L - 1) ARMT_TRY(emit(t - (L - 1)));
     }
   }
