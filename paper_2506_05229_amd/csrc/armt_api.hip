@@ -514,10 +514,12 @@ armt_status forward_typed(Ctx& c, const void* mem_emb, const void* x, int64_t N,
       for (int l = 0; l < L; ++l) {
         ARMT_TRY(save_tape(c, l, l, (int)s + l));
         ARMT_TRY(run_group<T>(c, l, l, empty ? l - 1 : l));
+        if (!D.bf16) ARMT_TRY(update_group<T>(c, l, l, empty ? l : 0, empty ? l + 1 : 0));
       }
-      // Nothing of this segment reads an updated memory and every layer's output stays in its slot until the next one, so the
-      // updates of all layers go out together: a cell's three launches are 23 us of latencies, 16 cells' are 70.
-      ARMT_TRY(update_group<T>(c, 0, L - 1, 0, empty ? L : 0));
+      // Nothing of this segment reads an updated memory, and the bf16 copy of every layer's output stays in its slot until the next one
+      // (the next layer's read adds to the fp32 slot in place, which is the only copy of the fp32 configurations): the updates of all
+      // layers go out together.  A cell's three launches are 23 us of latencies, 16 cells' are 70.
+      if (D.bf16) ARMT_TRY(update_group<T>(c, 0, L - 1, 0, empty ? L : 0));
       ARMT_TRY(emit(s));
     }
   } else {
