@@ -1,7 +1,7 @@
 // Backward of the segment attention on the CDNA4 matrix cores (bf16, head_dim 64 or 128).
 //
 // With P = softmax(scale Q K^T) (causal), O = P V and upstream gradient dO:
-//   D_i = dO_i . O_i,   dP = dO V^T,   dS = P (dP - D) scale,   dQ = dS K,   dK = dS^T Q,   dV = P^T dO.
+//   D_i = dO_i . O_i,   dP = dO V^T,   dS = P (dP - D),   dQ = scale dS K,   dK = scale dS^T Q,   dV = P^T dO.
 // P is recomputed from the log-sum-exp the forward kernel leaves behind (log2 domain), so no T x T matrix is stored.
 // Two kernels, both built like the forward one (v_mfma_f32_32x32x16_bf16, a lane owns ONE column of every 32 x 32
 // result, so the result of one product is directly the B operand of the next):
@@ -18,43 +18,76 @@
 
 namespace armt {
 
-// Xt[l][h][c][j] = X[l][j][col0 + h * dh + c], j padded with zeros to Tp.  X: [cells][T][ldx].
-// grid: (Tp / 64, heads, g), block: 256; LDS: 64 * (dh + 2) bf16.
-__global__ __launch_bounds__(256) void head_transpose_kernel(const bf16* __restrict__ X, int ldx, int col0, bf16* __restrict__ Xt,
-                                                             int first, int Trows, int Tp, int heads, int dh) {
-  extern __shared__ __align__(16) unsigned char smraw[];
-  bf16* tile = (bf16*)smraw;                   // [64][dh + 2]
-  const int l = first + blockIdx.z, h = blockIdx.y, j0 = blockIdx.x * 64;
-  const int ldt = dh + 2;
-  const bf16* src = X + (size_t)l * Trows * ldx + col0 + h * dh;
-  for (int idx = threadIdx.x; idx < 64 * dh; idx += blockDim.x) {
-    const int jr = idx / dh, c = idx - jr * dh;
-    tile[jr * ldt + c] = (j0 + jr < Trows) ? src[(size_t)(j0 + jr) * ldx + c] : (bf16)0.f;
+// The three transposed operands of a cell in one launch: Xt[l][h][c][j] = X[l][j][h * dh + c], j padded with zeros to Tp, for the heads of Q and K
+// (columns of QKV) and of dO.  64 x 64 tiles through LDS with 16-byte accesses on both sides, as in transpose_bf16_kernel: the pass is bound by
+// memory, and 2-byte accesses in three launches took three times as long (1B shape, mean of 5.6 cells: 63 -> 19 us).
+// grid: (Tp / 64, (2 H + Hkv) dh / 64, g), block: 256.
+__global__ __launch_bounds__(256) void head_transpose_kernel(const bf16* __restrict__ QKV, const bf16* __restrict__ dO, bf16* __restrict__ Kt,
+                                                             bf16* __restrict__ Qt, bf16* __restrict__ Gt, int first, int Trows, int Tp,
+                                                             int H, int Hkv, int dh) {
+  __shared__ unsigned int tile[64 * 33];
+  const int l = first + blockIdx.z, j0 = blockIdx.x * 64;
+  const int q_tiles = H * dh / 64, qk_tiles = q_tiles + Hkv * dh / 64;      // tiles of 64 columns: Q, K, then dO
+  const int ct = blockIdx.y;
+  const bool grad = ct >= qk_tiles;
+  const int ldx = grad ? H * dh : (H + 2 * Hkv) * dh, c0 = (grad ? ct - qk_tiles : ct) * 64;
+  const bf16* src = (grad ? dO : QKV) + (size_t)l * Trows * ldx + c0;
+  // row c of a cell's Xt is its column c: heads are dh rows each
+  bf16* dst = grad ? Gt + ((size_t)l * H * dh + c0) * Tp
+                   : ct < q_tiles ? Qt + ((size_t)l * H * dh + c0) * Tp : Kt + ((size_t)l * Hkv * dh + c0 - H * dh) * Tp;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int idx = threadIdx.x + 256 * k, r = idx >> 3, ch = idx & 7;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (j0 + r < Trows) v = *(const uint4*)(src + (size_t)(j0 + r) * ldx + 8 * ch);
+    unsigned int* t = tile + r * 33 + 4 * ch;
+    t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
   }
   __syncthreads();
-  bf16* dst = Xt + ((size_t)(l * heads + h) * dh) * Tp + j0;
-  for (int idx = threadIdx.x; idx < 64 * dh; idx += blockDim.x) {
-    const int c = idx >> 6, jr = idx & 63;
-    dst[(size_t)c * Tp + jr] = tile[jr * ldt + c];
+  const unsigned short* th = (const unsigned short*)tile;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int idx = threadIdx.x + 256 * k, c = idx >> 3, rch = idx & 7;
+    unsigned int w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned int lo = th[(8 * rch + 2 * e) * 66 + c], hi = th[(8 * rch + 2 * e + 1) * 66 + c];
+      w[e] = lo | (hi << 16);
+    }
+    *(uint4*)(dst + (size_t)c * Tp + j0 + 8 * rch) = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
-// D[l][h][i] = dO[l][i][h*dh : (h+1)*dh] . O[same].  grid: (ceil(T / 4), g), block: 256 (a wave per row, all heads).
+// D[l][h][i] = dO[l][i][h*dh : (h+1)*dh] . O[same]: 16 bytes of either per lane, DH / 8 lanes a head (1B shape, mean of 5.6 cells:
+// 28.8 -> 9.8 us; one head at a time, two bytes per lane, was a chain of H reductions).
+// grid: (ceil(T / 4), g), block: 256 (a wave per row, all heads).
+template <int DH>
 __global__ __launch_bounds__(256) void attention_dvec_kernel(const bf16* __restrict__ O, const bf16* __restrict__ dO,
-                                                             float* __restrict__ Dv, int first, int Trows, int H, int dh) {
+                                                             float* __restrict__ Dv, int first, int Trows, int H) {
   const int l = first + blockIdx.y, i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= Trows) return;
-  const size_t row = ((size_t)l * Trows + i) * (H * dh);
-  for (int h = 0; h < H; ++h) {
+  const size_t row = ((size_t)l * Trows + i) * (H * DH);
+#pragma unroll 4
+  for (int c0 = 0; c0 < H * DH; c0 += 512) {
+    const int c = c0 + 8 * lane, at = min(c, H * DH - 8);
+    const bf16x8 a = *(const bf16x8*)(dO + row + at), b = *(const bf16x8*)(O + row + at);
     float s = 0.f;
-    for (int c = lane; c < dh; c += 64) s = fmaf((float)dO[row + h * dh + c], (float)O[row + h * dh + c], s);
-    s = wave_sum(s);
-    if (lane == 0) Dv[((size_t)l * H + h) * Trows + i] = s;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s = fmaf((float)a[e], (float)b[e], s);
+#pragma unroll
+    for (int o = 1; o < DH / 8; o <<= 1) s += __shfl_xor(s, o, kWave);
+    if (c < H * DH && c % DH == 0) Dv[((size_t)l * H + c / DH) * Trows + i] = s;
   }
+}
+
+// One KB of a tile into LDS: 16 bytes from base + voff for every lane, in lane order from LDS address `lds` on.
+__device__ __forceinline__ void bwd_copy_slab(const char* base, unsigned voff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
 }
 
 // dQ.  QKV: [cells][T][(H + 2 Hkv) dh] (q, k rotated); Kt: [cells][Hkv][dh][Tp]; dO: [cells][T][H dh];
 // LSE2 (log2 domain), Dv: [cells][H][T]; dQKV: gradient rows, q columns written here.
+// (68 us per launch with 8-byte reads of K^T and a copy addressed per lane, 60 as it is; 1B shape, mean of 5.6 cells.)
 // As in the forward kernel a workgroup takes NQ consecutive 32-row tiles (NQ > 1 when a KV head has fewer than four
 // query heads): wave w handles query head kv * GROUP + w % GROUP and row tile w / GROUP.
 // grid: 1-D, 8 * ceil(Hkv g / 8) * ceil(T / (32 NQ)) workgroups, block: NQ * GROUP * 64; LDS: 2 stages of K, V, K^T tiles.
@@ -106,24 +139,35 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
   const float lse = LSE2[((size_t)l * H + head) * Trows + qrow];
   const float dvec = Dv[((size_t)l * H + head) * Trows + qrow];
 
+  // tile copies as in the forward kernel: scalar base + one lane offset per operand, the K and V rows permuted (at_key_of_row)
   const int R = lane >> 3, pc = lane & 7;
+  const unsigned chunk0 = (unsigned)((pc ^ mf_swz(R)) << 4);
+  const unsigned voffK = (unsigned)((R & 3) + ((R >> 2) << 3)) * (unsigned)ldq * 2u + chunk0;
+  const unsigned voffT = (unsigned)R * (unsigned)Tp * 2u + chunk0;
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
   auto issue_tile = [&](int kt, int buf) {
     typedef const __attribute__((address_space(1))) void* gptr_t;
     typedef __attribute__((address_space(3))) void* lptr_t;
     unsigned char* Ks = smem + buf * STAGE;
+    const unsigned lds = lds0 + buf * STAGE;
     const int k0 = kt * AT_KT;
+    const bool whole = k0 + AT_KT <= Trows;            // wave-uniform: every key of the tile exists
     for (int sl = wave; sl < 2 * K_SLABS + T_SLABS; sl += nw) {
       if (sl < 2 * K_SLABS) {
         const bool isv = sl >= K_SLABS;
-        const int s2 = isv ? sl - K_SLABS : sl;
-        const int sub = s2 >> 3, row = (s2 & 7) * 8 + R;
-        const int key = min(k0 + row, Trows - 1);
-        const char* src = (isv ? vbase : kbase) + ((size_t)key * ldq + sub * 64 + ((pc ^ mf_swz(row)) << 3)) * 2;
-        __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(Ks + sl * 1024), 16, 0, 0);
+        const int s2 = isv ? sl - K_SLABS : sl, sub = s2 >> 3, a = s2 & 7;
+        const char* base = isv ? vbase : kbase;
+        if (whole) {
+          const int keyS = k0 + ((a & 1) << 2) + ((a >> 1) << 4);
+          bwd_copy_slab(base + ((size_t)keyS * ldq + sub * 64) * 2, voffK ^ ((unsigned)(a & 1) << 6), lds + sl * 1024);
+        } else {
+          const int row = a * 8 + R, key = min(k0 + at_key_of_row(row), Trows - 1);
+          const char* src = base + ((size_t)key * ldq + sub * 64 + ((pc ^ mf_swz(row)) << 3)) * 2;
+          __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(Ks + sl * 1024), 16, 0, 0);
+        }
       } else {
-        const int ts = sl - 2 * K_SLABS, row = ts * 8 + R;
-        const char* src = tbase + ((size_t)row * Tp + k0 + ((pc ^ mf_swz(row)) << 3)) * 2;
-        __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(Ks + 2 * K_BYTES + ts * 1024), 16, 0, 0);
+        const int ts = sl - 2 * K_SLABS;
+        bwd_copy_slab(tbase + ((size_t)ts * 8 * Tp + k0) * 2, voffT ^ ((unsigned)(ts & 1) << 6), lds + sl * 1024);
       }
     }
   };
@@ -164,32 +208,27 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
       if (k0 + jj * 32 + 31 > q0) {              // this half crosses the diagonal: keys after the query contribute nothing
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = k0 + jj * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+          const int key = k0 + jj * 32 + 16 * (r >> 3) + 8 * half + (r & 7);   // see at_key_of_row
           const float p = key > qi ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2e, -lse));
-          dsf[jj][r >> 3][r & 7] = (bf16)(p * (dp[r] - dvec) * scale);
+          dsf[jj][r >> 3][r & 7] = (bf16)(p * (dp[r] - dvec));
         }
       } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float p = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2e, -lse));
-          dsf[jj][r >> 3][r & 7] = (bf16)(p * (dp[r] - dvec) * scale);
+          dsf[jj][r >> 3][r & 7] = (bf16)(p * (dp[r] - dvec));
         }
       }
     }
     // dQ^T[dim][query] += K^T[dim][key] dS^T[key][query]
 #pragma unroll
     for (int t = 0; t < OT; ++t) {
-      const unsigned char* trow = Ts + (t * 32 + (lane & 31)) * MF_ROW_BYTES + 8 * half;
+      const unsigned char* trow = Ts + (t * 32 + (lane & 31)) * MF_ROW_BYTES;
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
         for (int ss = 0; ss < 2; ++ss) {
-          const int ch = jj * 4 + 2 * ss;
-          const bf16x4 lo = *(const bf16x4*)(trow + ((ch ^ fl) << 4));
-          const bf16x4 hi = *(const bf16x4*)(trow + (((ch + 1) ^ fl) << 4));
-          bf16x8 tf;
-          tf[0] = lo[0]; tf[1] = lo[1]; tf[2] = lo[2]; tf[3] = lo[3];
-          tf[4] = hi[0]; tf[5] = hi[1]; tf[6] = hi[2]; tf[7] = hi[3];
+          const bf16x8 tf = *(const bf16x8*)(trow + (((jj * 4 + 2 * ss + half) ^ fl) << 4));
           o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf, dsf[jj][ss], o[t], 0, 0, 0);
         }
     }
@@ -206,7 +245,7 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
       for (int rg = 0; rg < 4; ++rg) {
         bf16x4 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16)o[t][4 * rg + e];
+        for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[t][4 * rg + e] * scale);
         *(bf16x4*)(dst + t * 32 + 8 * rg + 4 * half) = v;
       }
   }
@@ -217,10 +256,15 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
 // as B operands) for the whole kernel and adds the contributions of all query heads of the KV group, one after the
 // other, in its registers: no reduction between waves or workgroups.  The eight waves share the tiles of the current
 // (query head, 64 query rows): Q and dO rows, Q^T and dO^T columns, the rows' log-sum-exp and D, double buffered in LDS.
+// What bounds it: the longest workgroup (key block 0 meets every query of every head) and, inside an iteration, two waves per SIMD that take
+// turns with products and exponentials.  1B shape, us per launch (mean of 5.6 cells): 237 with
+// the transposed operands read 8 bytes at a time (bank conflicts) and a branch around every exponential, 206 with permuted rows
+// (at_key_of_row: a fragment is one 16-byte read), 165 with the mask in a loop of its own.  Four or two waves (128 or 64 keys) per workgroup
+// copy more and gain no balance: 193, 261.
 // grid: 1-D, 8 * ceil(Hkv g / 8) * ceil(T / 256) workgroups, block: 512; LDS: 2 stages of 4 tiles + 512 bytes.
 constexpr int DKV_WAVES = 8;
 template <int DH>
-__global__ __launch_bounds__(512) void attention_bwd_dkv_kernel(const bf16* __restrict__ QKV, const bf16* __restrict__ Qt,
+__global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const bf16* __restrict__ QKV, const bf16* __restrict__ Qt,
                                                                 const bf16* __restrict__ dO, const bf16* __restrict__ dOt,
                                                                 const float* __restrict__ LSE2, const float* __restrict__ Dv,
                                                                 bf16* __restrict__ dQKV, int first, int Trows, int Tp, int H,
@@ -263,28 +307,40 @@ __global__ __launch_bounds__(512) void attention_bwd_dkv_kernel(const bf16* __re
   const int qt_first = kb * (DKV_WAVES / 2);       // first 64-row query tile that can see these keys
   const int nq = Tp / 64 - qt_first;               // query tiles per head
   const int iters = group * nq;
+  // tile copies as in the forward kernel: scalar base + one lane offset per operand, the Q and dO rows permuted (at_key_of_row)
   const int R = lane >> 3, pc = lane & 7;
-  auto issue_tile = [&](int it, int buf) {
+  const unsigned chunk0 = (unsigned)((pc ^ mf_swz(R)) << 4);
+  const unsigned rowR = (unsigned)((R & 3) + ((R >> 2) << 3));
+  const unsigned voffQ = rowR * (unsigned)ldq * 2u + chunk0, voffG = rowR * (unsigned)ldo * 2u + chunk0;
+  const unsigned voffT = (unsigned)R * (unsigned)Tp * 2u + chunk0;
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
+  auto issue_tile = [&](int head, int q0, int buf) {
     typedef const __attribute__((address_space(1))) void* gptr_t;
     typedef __attribute__((address_space(3))) void* lptr_t;
-    const int head = kvh * group + it / nq, q0 = (qt_first + it % nq) * 64;
     unsigned char* base = smem + buf * STAGE;
+    const unsigned lds = lds0 + buf * STAGE;
     const char* qrows = (const char*)(cell + head * DH);
     const char* grows = (const char*)(gcell + head * DH);
-    const char* qcols = (const char*)(Qt + (size_t)(l * H + head) * DH * Tp);
-    const char* gcols = (const char*)(dOt + (size_t)(l * H + head) * DH * Tp);
+    const char* qcols = (const char*)(Qt + (size_t)(l * H + head) * DH * Tp + q0);
+    const char* gcols = (const char*)(dOt + (size_t)(l * H + head) * DH * Tp + q0);
+    const bool whole = q0 + 64 <= Trows;             // wave-uniform: every query of the tile exists
     for (int sl = wave; sl < 4 * Q_SLABS; sl += DKV_WAVES) {
       const int which = sl / Q_SLABS, s2 = sl - which * Q_SLABS;
-      const char* src;
       if (which < 2) {           // rows of Q / dO: DH / 64 sub-tiles [64 rows][64 dims]
-        const int sub = s2 >> 3, row = (s2 & 7) * 8 + R;
-        const int q = min(q0 + row, Trows - 1);
-        src = (which == 0 ? qrows + (size_t)q * ldq * 2 : grows + (size_t)q * ldo * 2) + (sub * 64 + ((pc ^ mf_swz(row)) << 3)) * 2;
+        const int sub = s2 >> 3, a = s2 & 7;
+        const char* rows = which == 0 ? qrows : grows;
+        const size_t ld = which == 0 ? ldq : ldo;
+        if (whole) {
+          const int qS = q0 + ((a & 1) << 2) + ((a >> 1) << 4);
+          bwd_copy_slab(rows + (qS * ld + sub * 64) * 2, (which == 0 ? voffQ : voffG) ^ ((unsigned)(a & 1) << 6), lds + sl * 1024);
+        } else {
+          const int row = a * 8 + R, q = min(q0 + at_key_of_row(row), Trows - 1);
+          const char* src = rows + (q * ld + sub * 64 + ((pc ^ mf_swz(row)) << 3)) * 2;
+          __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(base + sl * 1024), 16, 0, 0);
+        }
       } else {                   // columns: [DH dims][64 rows of the sequence]
-        const int row = s2 * 8 + R;
-        src = (which == 2 ? qcols : gcols) + ((size_t)row * Tp + q0 + ((pc ^ mf_swz(row)) << 3)) * 2;
+        bwd_copy_slab((which == 2 ? qcols : gcols) + (size_t)s2 * 8 * Tp * 2, voffT ^ ((unsigned)(s2 & 1) << 6), lds + sl * 1024);
       }
-      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(base + sl * 1024), 16, 0, 0);
     }
     if (wave < 2) {              // lse (wave 0) and D (wave 1) of the 64 rows, also as direct loads: a load through
       const float* srcf = (wave == 0 ? LSE2 : Dv) + ((size_t)l * H + head) * Trows + min(q0 + lane, Trows - 1);   // registers
@@ -299,13 +355,16 @@ __global__ __launch_bounds__(512) void attention_bwd_dkv_kernel(const bf16* __re
 #pragma unroll
     for (int r = 0; r < 16; ++r) dk[t][r] = dv[t][r] = 0.f;
 
-  issue_tile(0, 0);
+  int head = kvh * group, q0 = qt_first * 64;        // of the current tile
+  issue_tile(head, q0, 0);
   __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();
 
   for (int it = 0; it < iters; ++it) {
-    const int cur = it & 1, q0 = (qt_first + it % nq) * 64;
-    if (it + 1 < iters) issue_tile(it + 1, cur ^ 1);
+    const int cur = it & 1;
+    const bool wrap = q0 + 64 >= Tp;                 // last tile of the head
+    const int next_head = wrap ? head + 1 : head, next_q0 = wrap ? qt_first * 64 : q0 + 64;
+    if (it + 1 < iters) issue_tile(next_head, next_q0, cur ^ 1);
     const unsigned char* Qs = smem + cur * STAGE;
     const unsigned char* Gs = Qs + Q_BYTES;
     const unsigned char* QTs = Qs + 2 * Q_BYTES;
@@ -329,38 +388,45 @@ __global__ __launch_bounds__(512) void attention_bwd_dkv_kernel(const bf16* __re
         bf16x8 pf[2], dsf[2];
         // all 32 queries of this half exist and lie at or after all 32 keys of the wave: nothing to mask
         const bool interior = q0 + jj * 32 >= k0 + 31 && q0 + jj * 32 + 31 < Trows;
+        // (the mask is a loop of its own: with its condition inside the common one the compiler branched around every exponential)
+        f32x4 l4[4], d4[4];
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {         // registers 4 rg .. 4 rg + 3 hold four consecutive query rows
-          const int j4 = jj * 32 + 8 * rg + 4 * half;
-          const f32x4 l4 = *(const f32x4*)(sL + j4), d4 = *(const f32x4*)(sD + j4);
+        for (int rg = 0; rg < 4; ++rg) {         // registers 4 rg .. 4 rg + 3 hold four consecutive query rows (at_key_of_row)
+          const int j4 = jj * 32 + 16 * (rg >> 1) + 8 * half + 4 * (rg & 1);
+          l4[rg] = *(const f32x4*)(sL + j4);
+          d4[rg] = *(const f32x4*)(sD + j4);
+        }
+        float p[16];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int r = 4 * rg + e, q = q0 + j4 + e;
-            const bool live = interior || (q < Trows && ki <= q);
-            const float p = live ? __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2e, -l4[e])) : 0.f;
-            pf[r >> 3][r & 7] = (bf16)p;
-            dsf[r >> 3][r & 7] = (bf16)(p * (dp[r] - d4[e]) * scale);
+        for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2e, -l4[r >> 2][r & 3]));
+        if (!interior) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int q = q0 + jj * 32 + 16 * (r >> 3) + 8 * half + (r & 7);
+            p[r] = q < Trows && ki <= q ? p[r] : 0.f;
           }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          pf[r >> 3][r & 7] = (bf16)p[r];
+          dsf[r >> 3][r & 7] = (bf16)(p[r] * (dp[r] - d4[r >> 2][r & 3]));
         }
         // dV^T[dim][key] += dO^T[dim][query] P[query][key],  dK^T[dim][key] += Q^T[dim][query] dS[query][key]
 #pragma unroll
         for (int t = 0; t < OT; ++t) {
-          const int toff = (t * 32 + (lane & 31)) * MF_ROW_BYTES + 8 * half;
+          const int toff = (t * 32 + (lane & 31)) * MF_ROW_BYTES;
 #pragma unroll
           for (int ss = 0; ss < 2; ++ss) {
-            const int ch = jj * 4 + 2 * ss;
-            const int o0 = toff + ((ch ^ fl) << 4), o1 = toff + (((ch + 1) ^ fl) << 4);
-            const bf16x4 glo = *(const bf16x4*)(GTs + o0), ghi = *(const bf16x4*)(GTs + o1);
-            const bf16x4 qlo = *(const bf16x4*)(QTs + o0), qhi = *(const bf16x4*)(QTs + o1);
-            bf16x8 ga, qa;
-            ga[0] = glo[0]; ga[1] = glo[1]; ga[2] = glo[2]; ga[3] = glo[3]; ga[4] = ghi[0]; ga[5] = ghi[1]; ga[6] = ghi[2]; ga[7] = ghi[3];
-            qa[0] = qlo[0]; qa[1] = qlo[1]; qa[2] = qlo[2]; qa[3] = qlo[3]; qa[4] = qhi[0]; qa[5] = qhi[1]; qa[6] = qhi[2]; qa[7] = qhi[3];
+            const int at = toff + (((jj * 4 + 2 * ss + half) ^ fl) << 4);
+            const bf16x8 ga = *(const bf16x8*)(GTs + at), qa = *(const bf16x8*)(QTs + at);
             dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, pf[ss], dv[t], 0, 0, 0);
             dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, dsf[ss], dk[t], 0, 0, 0);
           }
         }
       }
     }
+    head = next_head;
+    q0 = next_q0;
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
   }
@@ -375,7 +441,7 @@ __global__ __launch_bounds__(512) void attention_bwd_dkv_kernel(const bf16* __re
         bf16x4 a, b;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          a[e] = (bf16)dk[t][4 * rg + e];
+          a[e] = (bf16)(dk[t][4 * rg + e] * scale);
           b[e] = (bf16)dv[t][4 * rg + e];
         }
         *(bf16x4*)(dkp + t * 32 + 8 * rg + 4 * half) = a;
@@ -397,34 +463,23 @@ inline hipError_t launch_attention_bwd_mfma(const bf16* QKV, const bf16* O, cons
   bf16* Kt = scratch;
   bf16* Qt = Kt + (size_t)Lcells * Hkv * dh * Tp;
   bf16* Gt = Qt + (size_t)Lcells * H * dh * Tp;
-  const size_t lds_t = 64 * (dh + 2) * 2;
-  head_transpose_kernel<<<dim3(Tp / 64, Hkv, g), 256, lds_t, st>>>(QKV, ldq, H * dh, Kt, first, Trows, Tp, Hkv, dh);
-  head_transpose_kernel<<<dim3(Tp / 64, H, g), 256, lds_t, st>>>(QKV, ldq, 0, Qt, first, Trows, Tp, H, dh);
-  head_transpose_kernel<<<dim3(Tp / 64, H, g), 256, lds_t, st>>>(dO, H * dh, 0, Gt, first, Trows, Tp, H, dh);
-  attention_dvec_kernel<<<dim3((Trows + 3) / 4, g), 256, 0, st>>>(O, dO, Dv, first, Trows, H, dh);
+  head_transpose_kernel<<<dim3(Tp / 64, (2 * H + Hkv) * dh / 64, g), 256, 0, st>>>(QKV, dO, Kt, Qt, Gt, first, Trows, Tp, H, Hkv, dh);
+  (dh == 64 ? attention_dvec_kernel<64> : attention_dvec_kernel<128>)<<<dim3((Trows + 3) / 4, g), 256, 0, st>>>(O, dO, Dv, first, Trows, H);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const float scale = 1.0f / sqrtf((float)dh);
   const int nq = group == 1 ? 4 : (group == 2 ? 2 : 1);       // row tiles per dQ workgroup, as in the forward kernel
-  const int nqt = (Trows + 32 * nq - 1) / (32 * nq), nkb = (Trows + 32 * DKV_WAVES - 1) / (32 * DKV_WAVES), npairs = Hkv * g;
+  const int nqt = (Trows + 32 * nq - 1) / (32 * nq), npairs = Hkv * g;
+  const int nkb = (Trows + 32 * DKV_WAVES - 1) / (32 * DKV_WAVES);
   const dim3 grid(8 * ((npairs + 7) / 8) * nqt), gkv(8 * ((npairs + 7) / 8) * nkb);
-  if (dh == 64) {
-    attention_bwd_dq_kernel<64><<<grid, nq * group * 64, 2 * 3 * (64 * 64 * 2), st>>>(QKV, Kt, dO, LSE2, Dv, dQKV, first, Trows, Tp, H, Hkv,
-                                                                                   nq, scale, nqt, npairs);
-    attention_bwd_dkv_kernel<64><<<gkv, 64 * DKV_WAVES, 2 * (4 * 64 * 64 * 2 + 512), st>>>(QKV, Qt, dO, Gt, LSE2, Dv, dQKV, first, Trows, Tp, H, Hkv,
-                                                                              scale, npairs);
-  } else {
-    hipError_t a = hipFuncSetAttribute((const void*)attention_bwd_dq_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       2 * 3 * (64 * 128 * 2));
-    if (a != hipSuccess) return a;
-    attention_bwd_dq_kernel<128><<<grid, nq * group * 64, 2 * 3 * (64 * 128 * 2), st>>>(QKV, Kt, dO, LSE2, Dv, dQKV, first, Trows, Tp, H,
-                                                                                     Hkv, nq, scale, nqt, npairs);
-    a = hipFuncSetAttribute((const void*)attention_bwd_dkv_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            2 * (4 * 64 * 128 * 2 + 512));
-    if (a != hipSuccess) return a;
-    attention_bwd_dkv_kernel<128><<<gkv, 64 * DKV_WAVES, 2 * (4 * 64 * 128 * 2 + 512), st>>>(QKV, Qt, dO, Gt, LSE2, Dv, dQKV, first, Trows, Tp, H,
-                                                                                Hkv, scale, npairs);
-  }
+  const int lds_q = 2 * 3 * (64 * dh * 2), lds_kv = 2 * (4 * 64 * dh * 2 + 512);
+  auto dq = dh == 64 ? attention_bwd_dq_kernel<64> : attention_bwd_dq_kernel<128>;
+  auto dkv = dh == 64 ? attention_bwd_dkv_kernel<64> : attention_bwd_dkv_kernel<128>;
+  e = hipFuncSetAttribute((const void*)dq, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dkv, hipFuncAttributeMaxDynamicSharedMemorySize, lds_kv);
+  if (e != hipSuccess) return e;
+  dq<<<grid, nq * group * 64, lds_q, st>>>(QKV, Kt, dO, LSE2, Dv, dQKV, first, Trows, Tp, H, Hkv, nq, scale, nqt, npairs);
+  dkv<<<gkv, 64 * DKV_WAVES, lds_kv, st>>>(QKV, Qt, dO, Gt, LSE2, Dv, dQKV, first, Trows, Tp, H, Hkv, scale, npairs);
   return hipGetLastError();
 }
 
