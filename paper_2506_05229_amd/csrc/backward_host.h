@@ -241,7 +241,7 @@ armt_status upload_train_tables(BCtx& c, const armt_layer_weights* W, const armt
     g = E(TK_MQ); g->A = Xop; g->B0 = w.wm_q; g->C = ws + o.Qm + l * T * D.dm * 4;
     g = E(TK_READ); g->A = ws + o.Fphi + l * T * D.Phi * e;
     g->B0 = D.bf16 ? ws + o.A16w + l * d * D.Phi * 2 : ws + o.Aw + l * d * D.Phi * 4;
-    g->C = X1; g->R = (const float*)X1; g->rowscale = (const float*)(ws + o.RDen + l * T * 4);
+    g->C = X1; g->R = (const float*)Xin; g->rowscale = (const float*)(ws + o.RDen + l * T * 4);
     g = E(TK_QKV); g->A = ws + o.N1 + l * T * d * e; g->B0 = w.wq; g->B1 = w.wk; g->B2 = w.wv;
     g->C = ws + o.QKV + l * T * D.Nqkv * e;
     g = E(TK_O); g->A = ws + o.Att + l * T * Hd * e; g->B0 = w.wo; g->C = ws + o.Hres + l * T * d * 4; g->R = (const float*)X1;
@@ -413,13 +413,6 @@ armt_status recompute_group(const BCtx& c, int lo, int g, int gr, int e0, int e1
   const TrainLayout& o = c.o;
   const size_t cell = (size_t)D.T * D.d;
   float* X1 = c.at<float>(o.X1);
-  copy_f32_kernel<<<ew_blocks(g * cell), 256, 0, c.st>>>(X1 + lo * cell, c.at<float>(o.Xin) + lo * cell, g * cell);
-  if (D.bf16) {
-    f32_to_bf16_kernel<<<ew_blocks(g * cell), 256, 0, c.st>>>(c.at<bf16>(o.Xb) + lo * cell, c.at<float>(o.Xin) + lo * cell, g * cell);
-    const size_t nA = (size_t)D.d * D.Phi;
-    f32_to_bf16_kernel<<<ew_blocks(g * nA), 256, 0, c.st>>>(c.at<bf16>(o.A16w) + lo * nA, c.at<float>(o.Aw) + lo * nA, g * nA);
-  }
-  HIP_TRY(hipGetLastError());
   ARMT_TRY(step_assoc_read<T>(c.st, c.table(TK_MQ), c.shape[TK_MQ], c.table(TK_READ), c.shape[TK_READ], c.aux, lo, gr, D.T,
                               D.dm, D.nu, D.assoc_eps, c.at<float>(o.Qm), c.at<T>(o.Fphi), c.at<float>(o.RDen)));
   rmsnorm_train_kernel<T><<<dim3(D.T, g), 256, 0, c.st>>>(X1, cell, c.aux, lo, 0, D.T, D.d, D.rms_eps, c.at<T>(o.N1),
@@ -669,8 +662,9 @@ armt_status backward_typed(BCtx& c, const armt_layer_weights* W, int64_t N, floa
     // the cells of segment 0 met an empty memory unless a state was carried in
     const bool top_empty = !carry_in && (t - hi) == 0;
     const int grc = top_empty ? gc - B : gc;
-    tape_kernel<<<dim3(128, gc), 256, 0, c.st>>>(tape, rec_floats, c.at<float>(o.Xin), cell, c.aux, c.at<float>(o.Aw),
-                                                c.at<float>(o.zw), loc, t, L, B, cell, nA, (size_t)D.Phi, 0);
+    tape_restore_kernel<T><<<dim3(256, gc), 256, 0, c.st>>>(
+        tape, rec_floats, c.at<float>(o.Xin), c.at<T>(o.Xb), c.at<float>(o.X1), c.at<float>(o.Aw), c.at<T>(o.A16w), c.at<float>(o.zw),
+        loc, t, L, B, loc + grc, cell, nA, (size_t)D.Phi);
     if (hi == Lr - 1) {
       const int64_t s = t - (Lr - 1);
       for (int b = 0; b < B; ++b)

@@ -759,22 +759,75 @@ __global__ __launch_bounds__(256) void beta_bwd_kernel(const float* __restrict__
 // ------------------------------------------------------------------------------------------------
 // Tape of the training forward: inputs of a cell that the backward pass cannot recompute from its neighbours.
 // Per cell (segment s, layer l, sequence b), record index s * n_cells + l * batch + b: the cell input [T][d] fp32, the layer's A [d][Phi] and
-// z [Phi] from BEFORE the cell's update.  save = 1 copies slots / state into the tape, save = 0 copies back.
-// Cell l of a launch belongs to layer l / batch and to segment t - l / batch.  grid: (blocks, g), block: 256.
-__global__ __launch_bounds__(256) void tape_kernel(float* __restrict__ tape, size_t rec_floats, float* __restrict__ X,
-                                                   size_t x_cell, const LayerAux* __restrict__ aux, float* __restrict__ Aw,
-                                                   float* __restrict__ zw, int first, int t, int n_cells, int batch, size_t nx,
-                                                   size_t nA, size_t nz, int save) {
-  const int l = first + blockIdx.y;            // cell = layer * batch + sequence
-  float* rec = tape + ((size_t)(t - l / batch) * n_cells + l) * rec_floats;
-  float* x = X + (size_t)l * x_cell;
-  float* A = save ? aux[l].A : Aw + (size_t)l * nA;
-  float* z = save ? aux[l].z : zw + (size_t)l * nz;
-  const size_t total = nx + nA + nz;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    float* p = i < nx ? x + i : (i < nx + nA ? A + (i - nx) : z + (i - nx - nA));
-    if (save) rec[i] = *p; else *p = rec[i];
+// z [Phi] from BEFORE the cell's update.  Cell l of a launch belongs to layer l / batch and to segment t - l / batch.
+// Saving and restoring are copies and nothing else, bound by memory if enough of it is asked for: 16 bytes at a time, four of them in flight
+// per thread (1B shape, mean of 5.6 cells: save 57 -> 24 us).
+__device__ __forceinline__ float* tape_record(float* tape, size_t rec_floats, int t, int l, int n_cells, int batch) {
+  return tape + ((size_t)(t - l / batch) * n_cells + l) * rec_floats;
+}
+// put(i, v, n): v holds n = 4 or 1 floats from src + i on.
+template <typename Put>
+__device__ __forceinline__ void tape_span(const float* __restrict__ src, size_t n, bool quads, Put put) {
+  const size_t step = (size_t)gridDim.x * blockDim.x, at = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (quads) {
+    const size_t nq = n >> 2;
+    size_t i = at;
+    for (; i + 3 * step < nq; i += 4 * step) {
+      f32x4 v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = *(const f32x4*)(src + 4 * (i + k * step));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) put(4 * (i + k * step), v[k], 4);
+    }
+    for (; i < nq; i += step) put(4 * i, *(const f32x4*)(src + 4 * i), 4);
+  } else {
+    for (size_t i = at; i < n; i += step) put(i, f32x4{src[i], 0.f, 0.f, 0.f}, 1);
   }
+}
+__device__ __forceinline__ void tape_put(float* dst, size_t i, f32x4 v, int n) {
+  if (n == 4) *(f32x4*)(dst + i) = v; else dst[i] = v[0];
+}
+__device__ __forceinline__ void tape_put(bf16* dst, size_t i, f32x4 v, int n) {
+  if (n == 4) *(bf16x4*)(dst + i) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]}; else dst[i] = (bf16)v[0];
+}
+
+// Slots and memory state -> tape.  The state is the caller's and may start anywhere.  grid: (blocks, g), block: 256.
+__global__ __launch_bounds__(256) void tape_save_kernel(float* __restrict__ tape, size_t rec_floats, const float* __restrict__ X,
+                                                        const LayerAux* __restrict__ aux, int first, int t, int n_cells, int batch,
+                                                        size_t nx, size_t nA, size_t nz) {
+  const int l = first + blockIdx.y;
+  float* rec = tape_record(tape, rec_floats, t, l, n_cells, batch);
+  const float *A = aux[l].A, *z = aux[l].z;
+  const bool x4 = (nx & 3) == 0;           // slots and records then start on 16 bytes
+  tape_span(X + (size_t)l * nx, nx, x4, [&](size_t i, f32x4 v, int n) { tape_put(rec, i, v, n); });
+  tape_span(A, nA, x4 && (nA & 3) == 0 && ((uintptr_t)A & 15) == 0, [&](size_t i, f32x4 v, int n) { tape_put(rec + nx, i, v, n); });
+  tape_span(z, nz, false, [&](size_t i, f32x4 v, int n) { tape_put(rec + nx + nA, i, v, n); });
+}
+
+// Tape -> what the recomputation of a cell starts from, in one pass: the input in fp32 (Xin) and as the GEMM operand (Xop; T = float: Xin
+// itself), A likewise, z; for the cells from `no_read` on, which have no read in front of the block, also X1 (elsewhere the read writes it).
+// 1B shape, mean of 5.6 cells: 31 us; a restoring copy, a copy and two conversions took 57 + 21 + 28.
+// grid: (blocks, g), block: 256.
+template <typename T>
+__global__ __launch_bounds__(256) void tape_restore_kernel(float* __restrict__ tape, size_t rec_floats, float* __restrict__ Xin,
+                                                           T* __restrict__ Xop, float* __restrict__ X1, float* __restrict__ Aw,
+                                                           T* __restrict__ Aop, float* __restrict__ zw, int first, int t, int n_cells,
+                                                           int batch, int no_read, size_t nx, size_t nA, size_t nz) {
+  constexpr bool OPERANDS = sizeof(T) != 4;      // T = float: the fp32 copies are the operands
+  const int l = first + blockIdx.y;
+  const float* rec = tape_record(tape, rec_floats, t, l, n_cells, batch);
+  const size_t x = (size_t)l * nx, a = (size_t)l * nA;
+  const bool x4 = (nx & 3) == 0, has_x1 = l >= no_read;
+  tape_span(rec, nx, x4, [&](size_t i, f32x4 v, int n) {
+    tape_put(Xin + x, i, v, n);
+    if (OPERANDS) tape_put(Xop + x, i, v, n);
+    if (has_x1) tape_put(X1 + x, i, v, n);
+  });
+  tape_span(rec + nx, nA, x4 && (nA & 3) == 0, [&](size_t i, f32x4 v, int n) {
+    tape_put(Aw + a, i, v, n);
+    if (OPERANDS) tape_put(Aop + a, i, v, n);
+  });
+  tape_span(rec + nx + nA, nz, false, [&](size_t i, f32x4 v, int n) { tape_put(zw + (size_t)l * nz, i, v, n); });
 }
 
 // Memory-state gradients between the caller's order [batch][layers][n] and the cell order [layers][batch][n] of a step.
