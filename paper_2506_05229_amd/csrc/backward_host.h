@@ -120,7 +120,7 @@ TrainLayout carve_train(const Dims& D) {
   o.wb_rows = o.bX + d;
   o.WinA = take(Lr * o.wa_rows * o.Kw * e);
   o.WinB = take(Lr * o.wb_rows * o.Kw * e);
-  o.CPart = take(L * CS_CHUNKS * std::max(d, (size_t)D.Phi) * 4);
+  o.CPart = take(L * std::max(NORM_CHUNKS * d, CS_CHUNKS * (size_t)D.Phi) * 4);
   o.WdT = take(Lr * F * d * e);
   o.WguT = take(Lr * d * 2 * F * e);
   o.WoT = take(Lr * Hd * d * e);
@@ -405,6 +405,30 @@ armt_status colsum(const BCtx& c, const T* a, const float* b, size_t b_cell, con
   return ARMT_OK;
 }
 
+// Backward of norm `which` (n = x rstd gain) of the cells [lo, lo + g): dout (and doutb) = din + the gradient through the norm, and the
+// gradient of the gain into dg.  One pass where a lane can hold its columns of a row (d a multiple of 4, at most 4096), else two.
+template <typename T>
+armt_status norm_backward(const BCtx& c, int lo, int g, int which, const float* x, const float* rstd, const float* din, float* dout,
+                          T* doutb, float* const* dg) {
+  const Dims& D = c.D;
+  const size_t cell = (size_t)D.T * D.d;
+  const T* dn = c.at<T>(c.o.DN);
+  if (D.d % 4 || D.d > 4096) {
+    ARMT_TRY(colsum<T>(c, dn, x, cell, rstd, dg, nullptr, lo, g, D.d));
+    rmsnorm_bwd_kernel<T><<<dim3(D.T, g), 256, 0, c.st>>>(dn, x, cell, c.aux, lo, which, rstd, din, cell, dout, cell, doutb, D.T, D.d);
+    HIP_TRY(hipGetLastError());
+    return ARMT_OK;
+  }
+  float* part = c.at<float>(c.o.CPart);
+  const int nc = (D.d + 255) / 256;
+  auto kern = nc <= 1 ? rmsnorm_bwd_cols_kernel<T, 1> : nc <= 2 ? rmsnorm_bwd_cols_kernel<T, 2> : nc <= 4 ? rmsnorm_bwd_cols_kernel<T, 4>
+            : nc <= 8 ? rmsnorm_bwd_cols_kernel<T, 8> : nc <= 12 ? rmsnorm_bwd_cols_kernel<T, 12> : rmsnorm_bwd_cols_kernel<T, 16>;
+  kern<<<dim3(NORM_CHUNKS, g), 256, 0, c.st>>>(dn, x, cell, c.aux, lo, which, rstd, din, cell, dout, cell, doutb, part, D.T, D.d);
+  colsum_finish_kernel<<<dim3((D.d + 255) / 256, g / D.B), 256, 0, c.st>>>(part, NORM_CHUNKS, dg, nullptr, lo, D.d, D.B);
+  HIP_TRY(hipGetLastError());
+  return ARMT_OK;
+}
+
 // Forward of the cells [lo, lo + g) from their restored inputs, every intermediate kept.  The first gr cells read
 // their memory; cells [e0, e1) meet an empty one.
 template <typename T>
@@ -542,10 +566,7 @@ armt_status backward_group(const BCtx& c, int lo, int g, int gr, int slot) {
   ARMT_TRY(bgemm<T>(c, TK_DN2, lo, g));
   if (!std::is_same<T, bf16>::value) ARMT_TRY(wtr(GU, (size_t)D.T * 2 * D.F, 2 * D.F, arow(o.aDGU), wa_cell, Tp, Kw, D.T, 2 * D.F, g));
   ARMT_TRY(wtr(c.at<T>(o.N2) + lo * cell, cell, D.d, brow(o.bN2), wb_cell, Tp, Kw, D.T, D.d, g));
-  ARMT_TRY(colsum<T>(c, c.at<T>(o.DN), c.at<float>(o.Hres), cell, c.at<float>(o.RStd2), c.dg2, nullptr, lo, g, D.d));   // d gain 2
-  rmsnorm_bwd_kernel<T><<<dim3(D.T, g), 256, 0, st>>>(c.at<T>(o.DN), c.at<float>(o.Hres), cell, c.aux, lo, 1, c.at<float>(o.RStd2),
-                                                     DX + B * cell, cell, c.at<float>(o.DH), cell, c.at<T>(o.DHb), D.T, D.d);
-  HIP_TRY(hipGetLastError());
+  ARMT_TRY(norm_backward<T>(c, lo, g, 1, c.at<float>(o.Hres), c.at<float>(o.RStd2), DX + B * cell, c.at<float>(o.DH), c.at<T>(o.DHb), c.dg2));
   // ---- attention half
   ARMT_TRY(bgemm<T>(c, TK_DATT, lo, g));
   ARMT_TRY(wtr(c.at<T>(o.DHb) + lo * cell, cell, D.d, arow(o.aDH), wa_cell, Tp, Kw, D.T, D.d, g));
@@ -567,10 +588,7 @@ armt_status backward_group(const BCtx& c, int lo, int g, int gr, int slot) {
   ARMT_TRY(bgemm<T>(c, TK_DN1, lo, g));
   ARMT_TRY(wtr(c.at<T>(o.DQKV) + (size_t)lo * D.T * D.Nqkv, (size_t)D.T * D.Nqkv, D.Nqkv, arow(o.aDQKV), wa_cell, Tp, Kw, D.T, D.Nqkv, g));
   ARMT_TRY(wtr(c.at<T>(o.N1) + lo * cell, cell, D.d, brow(o.bN1), wb_cell, Tp, Kw, D.T, D.d, g));
-  ARMT_TRY(colsum<T>(c, c.at<T>(o.DN), c.at<float>(o.X1), cell, c.at<float>(o.RStd1), c.dg1, nullptr, lo, g, D.d));     // d gain 1
-  rmsnorm_bwd_kernel<T><<<dim3(D.T, g), 256, 0, st>>>(c.at<T>(o.DN), c.at<float>(o.X1), cell, c.aux, lo, 0, c.at<float>(o.RStd1),
-                                                     c.at<float>(o.DH), cell, DX, cell, (T*)nullptr, D.T, D.d);
-  HIP_TRY(hipGetLastError());
+  ARMT_TRY(norm_backward<T>(c, lo, g, 0, c.at<float>(o.X1), c.at<float>(o.RStd1), c.at<float>(o.DH), DX, (T*)nullptr, c.dg1));
   // ---- associative read (Eq. 6)
   if (gr > 0) {
     read_bwd_rows_kernel<T><<<dim3(D.T, gr), 256, 0, st>>>(DX, cell, c.at<float>(o.X1), cell, c.at<float>(o.Xin), cell,
