@@ -547,10 +547,15 @@ armt_status backward_group(const BCtx& c, int lo, int g, int gr, int slot) {
   }
   // ---- feed-forward half of the block
   T* DYb = c.at<T>(o.DYb) + lo * cell;
-  convert_kernel<float, T><<<ew_blocks(g * cell), 256, 0, st>>>(DX + (lo + B) * cell, DYb, g * cell);
+  if constexpr (std::is_same<T, bf16>::value) {      // d_model is a multiple of 64
+    convert_transpose_kernel<<<dim3(D.d / 64, (D.T + 63) / 64, g), 256, 0, st>>>(DX + (lo + B) * cell, cell, D.d, true, DYb, cell, D.d,
+                                                                               arow(o.aDY), wa_cell, Kw, B, D.T, D.d, Tp);
+  } else {
+    convert_kernel<float, T><<<ew_blocks(g * cell), 256, 0, st>>>(DX + (lo + B) * cell, DYb, g * cell);
+    ARMT_TRY(wtr(DYb, cell, D.d, arow(o.aDY), wa_cell, Tp, Kw, D.T, D.d, g));
+  }
   HIP_TRY(hipGetLastError());
   ARMT_TRY(bgemm<T>(c, TK_DU, lo, g));
-  ARMT_TRY(wtr(DYb, cell, D.d, arow(o.aDY), wa_cell, Tp, Kw, D.T, D.d, g));
   if (!std::is_same<T, bf16>::value)      // bf16: the recomputation wrote U^T already
     ARMT_TRY(wtr(c.at<T>(o.Uff) + (size_t)lo * D.T * D.F, (size_t)D.T * D.F, D.F, brow(o.bU), wb_cell, Tp, Kw, D.T, D.F, g));
   T* GU = c.at<T>(o.GU) + (size_t)lo * D.T * 2 * D.F;
@@ -919,7 +924,12 @@ armt_status lm_head_backward_typed(const Dims& D, const HeadBwdLayout& h, const 
     }
     const int parts = head_parts(r, D.d, h.Vp);
     final_norm_train_kernel<T><<<r, 256, 0, st>>>(hs, (const T*)gain, D.d, D.rms_eps, Nn, rstd);
-    pad_convert_rows_kernel<T><<<r, 256, 0, st>>>(d_logits + (size_t)r0 * vocab, vocab, DLb, h.Vp);
+    const float* dl = d_logits + (size_t)r0 * vocab;
+    if constexpr (std::is_same<T, bf16>::value)
+      convert_transpose_kernel<<<dim3(h.Vp / 64, (r + 63) / 64), 256, 0, st>>>(dl, 0, vocab, vocab % 4 == 0 && (uintptr_t)dl % 16 == 0, DLb, 0,
+                                                                            h.Vp, DLT, 0, h.Rp, 1, r, vocab, h.Rp);
+    else
+      pad_convert_rows_kernel<T><<<r, 256, 0, st>>>(dl, vocab, DLb, h.Vp);
     HIP_TRY(hipGetLastError());
     su.M = r;
     su.a_rows = (int)round256(r);
@@ -934,7 +944,7 @@ armt_status lm_head_backward_typed(const Dims& D, const HeadBwdLayout& h, const 
     colsum_partial_kernel<T><<<dim3((D.d + 255) / 256, 1, CS_CHUNKS), 256, 0, st>>>(hs, U, 0, rstd, part, 0, r, D.d);
     colsum_finish_kernel<<<dim3((D.d + 255) / 256, 1), 256, 0, st>>>(part, CS_CHUNKS, nullptr, d_gain, 0, D.d, 1);
     HIP_TRY(hipGetLastError());
-    ARMT_TRY((transpose<T, T>(st, DLb, 0, h.Vp, DLT, 0, h.Rp, r, h.Vp, 1)));
+    if (!std::is_same<T, bf16>::value) ARMT_TRY((transpose<T, T>(st, DLb, 0, h.Vp, DLT, 0, h.Rp, r, h.Vp, 1)));
     ARMT_TRY((transpose<T, T>(st, Nn, 0, D.d, NT, 0, h.Rp, r, D.d, 1)));
     sw.K = round64(r);
     ARMT_TRY(gemm<T>(st, table, kHeadParts, 1, sw));

@@ -93,6 +93,68 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16* __restr
   }
 }
 
+// An fp32 gradient as the operands of the two products it enters, in one pass over it: dst [R][ldd] in bf16, columns [C, Cp) zero, and its
+// transpose dst_t[c][r] (c < Cp, row stride ldt, rows [R, Rp) zero).  Cell z of the launch writes its transpose at layer z / batch and column
+// offset (z % batch) * Rp, as the windows of the weight gradients want it.  Bound by memory; reading the bf16 copy back for a transpose of its
+// own cost a third more traffic: 4096 x 128256 835 + 470 us -> 920, 1B shape (mean of 5.6 cells) 25 + 9 -> 19.
+// wide: src and its rows start on 16 bytes; else it is read in 4-byte accesses, a row of the tile per wave.
+// Cp, Rp, ldd, ldt multiples of 8 (Cp and Rp of 64); bases of the destinations on 16 bytes.
+// grid: (Cp / 64, ceil(R / 64), cells), block: 256.
+__global__ __launch_bounds__(256) void convert_transpose_kernel(const float* __restrict__ src, size_t src_cell, int lds, bool wide,
+                                                                bf16* __restrict__ dst, size_t dst_cell, int ldd, bf16* __restrict__ dst_t,
+                                                                size_t dst_t_layer, int ldt, int batch, int R, int C, int Rp) {
+  __shared__ unsigned int tile[64 * 33];
+  const float* s = src + (size_t)blockIdx.z * src_cell;
+  bf16* o = dst + (size_t)blockIdx.z * dst_cell;
+  bf16* ot = dst_t + (size_t)(blockIdx.z / batch) * dst_t_layer + (size_t)(blockIdx.z % batch) * Rp;
+  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+  unsigned short* th = (unsigned short*)tile;
+  if (wide && c0 + 64 <= C) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int idx = threadIdx.x + 256 * k, r = idx >> 3, ch = idx & 7;
+      bf16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (r0 + r < R) {
+        const float* p = s + (size_t)(r0 + r) * lds + c0 + 8 * ch;
+        const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[e] = (bf16)a[e]; v[4 + e] = (bf16)b[e]; }
+      }
+      const uint4 u = __builtin_bit_cast(uint4, v);
+      unsigned int* t = tile + r * 33 + 4 * ch;
+      t[0] = u.x; t[1] = u.y; t[2] = u.z; t[3] = u.w;
+    }
+  } else {
+    const int c = c0 + (threadIdx.x & 63), rw = threadIdx.x >> 6;
+    float v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int r = r0 + rw + 4 * k;
+      v[k] = r < R && c < C ? s[(size_t)r * lds + c] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) th[(rw + 4 * k) * 66 + (threadIdx.x & 63)] = __builtin_bit_cast(unsigned short, (bf16)v[k]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int idx = threadIdx.x + 256 * k, r = idx >> 3, ch = idx & 7;
+    if (r0 + r < R) {
+      const unsigned int* t = tile + r * 33 + 4 * ch;
+      *(uint4*)(o + (size_t)(r0 + r) * ldd + c0 + 8 * ch) = make_uint4(t[0], t[1], t[2], t[3]);
+    }
+    if (r0 + 8 * ch + 7 < Rp) {                 // r counts columns here, ch eighths of the tile's rows
+      unsigned int w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned int lo = th[(8 * ch + 2 * e) * 66 + r], hi = th[(8 * ch + 2 * e + 1) * 66 + r];
+        w[e] = lo | (hi << 16);
+      }
+      *(uint4*)(ot + (size_t)(c0 + r) * ldt + r0 + 8 * ch) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+  }
+}
+
 // u[i] += u[n + i] + u[2 n + i] + ...: partial results of a product, added in order.
 __global__ void sum_parts_kernel(float* __restrict__ u, size_t n, int parts) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
