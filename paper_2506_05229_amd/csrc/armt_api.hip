@@ -148,6 +148,7 @@ struct Ctx {
   bool fused_rope;           // bf16 MFMA path: rotary embedding applied by the QKV GEMM epilogue
   bool fused_vt;             // ... which also writes V transposed
   bool fused_dpfp;           // bf16 MFMA path: feature map and denominator of the read in the epilogue of the W_Q projection
+  bool fused_prep;           // fp32: EPI_UPDATE_F32 where a whole step is run
   int ssq_parts;             // partial sums of squares per row written by the GEMMs that produce a normalised row
   float* tape = nullptr;     // training forward: per-cell records of what the backward pass cannot recompute
   size_t rec_floats = 0;     // floats per record
@@ -176,18 +177,23 @@ void fill_shapes(Ctx& c) {
     for (int k : {K_MQ, K_READ, K_QKV, K_O, K_GU, K_DOWN}) c.shape[k].a_rows = (int)padded_rows(D.T);
   c.fused_norm = D.bf16 && !debug_generic();
   // rotary embedding as the epilogue of the QKV GEMM: heads must not straddle its output tiles
-  c.fused_rope = D.bf16 && !debug_generic() && 128 % D.dh == 0 && !(g_gemm_dbg & 128);
+  // (fp32 tiles are 32 columns wide)
+  c.fused_rope = D.bf16 ? !debug_generic() && 128 % D.dh == 0 && !(g_gemm_dbg & 128) : D.dh == 8 || D.dh == 16 || D.dh == 32;
   if (c.fused_rope) { c.shape[K_QKV].epi = EPI_QKV_ROPE; c.shape[K_QKV].ldr = D.dh; }
   // ... and V written transposed for the attention kernel, if the v columns start on a tile boundary
-  c.fused_vt = c.fused_rope && ((D.H + D.Hkv) * D.dh) % 256 == 0 && D.T % 8 == 0 && !(g_gemm_dbg & 64);
+  c.fused_vt = D.bf16 && c.fused_rope && ((D.H + D.Hkv) * D.dh) % 256 == 0 && D.T % 8 == 0 && !(g_gemm_dbg & 64);
   if (c.fused_vt) c.shape[K_QKV].ldc2 = attention_tp(D.T);
   if (c.fused_norm) c.shape[K_READ].ldc2 = c.shape[K_O].ldc2 = D.d;
   // feature map + denominator of the read (Eq. 6) as the epilogue of the W_Q projection: q never goes to memory
-  c.fused_dpfp = D.bf16 && !debug_generic() && D.dm <= 128 && !(g_gemm_dbg & 16);
+  c.fused_dpfp = D.bf16 ? !debug_generic() && D.dm <= 128 && !(g_gemm_dbg & 16) : D.dm <= 32;
   if (c.fused_dpfp) {
     GemmShape& q = c.shape[K_MQ];
     q.epi = EPI_DPFP_READ; q.ldc = D.Phi; q.ldr = D.nu; q.fparam = D.assoc_eps;
   }
+  // fp32: both norms inside the products behind them; features and coefficients of the update behind the projection of its rows
+  if (!D.bf16)
+    for (int k : {K_QKV, K_GU}) { c.shape[k].norm = 1; c.shape[k].fparam = D.rms_eps; }
+  c.fused_prep = !D.bf16 && D.dm <= 32 && D.m <= 16;
   c.ssq_parts = (D.d + 127) / 128;   // the GEMM epilogue writes one partial sum of squares per 128 columns
 }
 
@@ -249,6 +255,7 @@ armt_status upload_tables(Ctx& c, const armt_layer_weights* W, float* A, float* 
     if (c.fused_norm) { g->C2 = nrm; g->gain = w.rms1; g->ssq_out = ssq; }   // input of the first norm
     g = &tab[K_QKV * L + l];
     g->A = nrm; g->B0 = w.wq; g->B1 = w.wk; g->B2 = w.wv;
+    if (c.shape[K_QKV].norm) { g->A = X + l * slotX; g->gain = w.rms1; }
     if (c.fused_rope) g->R = (const float*)(c.ws + c.o.Rope);
     if (c.fused_vt) g->C2 = c.ws + c.o.Vt + l * (size_t)D.Hkv * D.dh * attention_tp(D.T) * 2;
     g->C = c.ws + c.o.QKV + l * T * D.Nqkv * D.esz;
@@ -259,6 +266,7 @@ armt_status upload_tables(Ctx& c, const armt_layer_weights* W, float* A, float* 
     if (c.fused_norm) { g->C2 = nrm; g->gain = w.rms2; g->ssq_out = ssq; }   // input of the second norm
     g = &tab[K_GU * L + l];
     g->A = nrm; g->B0 = w.wgate; g->B1 = w.wup;
+    if (c.shape[K_GU].norm) { g->A = c.ws + c.o.Hres + l * T * D.d * 4; g->gain = w.rms2; }
     g->C = c.ws + c.o.Uff + l * T * D.F * D.esz;
     if (c.fused_norm) g->rowscale = rstd;
     g = &tab[K_DOWN * L + l];
@@ -268,6 +276,10 @@ armt_status upload_tables(Ctx& c, const armt_layer_weights* W, float* A, float* 
     g = &tab[K_MKV * L + l];
     g->A = Xop + (l + B) * slotXop + (size_t)D.S * D.d * D.esz; g->B0 = w.wm_k; g->B1 = w.wm_v;
     g->C = c.ws + c.o.KVm + l * D.m * (size_t)(D.dm + D.d) * 4;
+    if (c.fused_prep) {
+      g->gain = w.wm_b; g->R = z + state * (size_t)D.Phi;
+      g->C2 = c.ws + c.o.Fm + l * D.m * (size_t)D.Phi * 4; g->ssq_out = (float*)(c.ws + c.o.Coef) + l * D.m * 4;
+    }
     LayerAux& a = aux[l];
     a.rms1 = w.rms1; a.rms2 = w.rms2; a.wm_b = w.wm_b;
     a.A = Al; a.z = z + state * (size_t)D.Phi; a.A16 = A16l;
@@ -363,11 +375,14 @@ armt_status step_assoc_update(hipStream_t st, const GemmGroup* t_mkv, const Gemm
   if (g <= 0) return ARMT_OK;
   const int Phi = 2 * nu * dm;
   ARMT_TRY(gemm<T>(st, t_mkv, first, g, s_mkv));
-  bool timed = prof_start(PK_UPD_PREP, st);
-  memupd_prep_kernel<T><<<dim3(m, g), 128, (dm + 17) * 4, st>>>(KVm, Y0, y_stride, aux, first, empty_lo, empty_hi, m, d, dm, nu,
-                                                               eps, Fm, Coef);
-  prof_stop(timed, st, g);
-  HIP_TRY(hipGetLastError());
+  bool timed = false;
+  if (s_mkv.epi != EPI_UPDATE_F32) {     // features and coefficients not yet produced by the projection's epilogue
+    timed = prof_start(PK_UPD_PREP, st);
+    memupd_prep_kernel<T><<<dim3(m, g), 128, (dm + 17) * 4, st>>>(KVm, Y0, y_stride, aux, first, empty_lo, empty_hi, m, d, dm, nu,
+                                                                 eps, Fm, Coef);
+    prof_stop(timed, st, g);
+    HIP_TRY(hipGetLastError());
+  }
   timed = prof_start(PK_DELTA_RULE, st);
   if (m <= 16 && Phi % 64 == 0 && Phi <= 512) {
     // A block needs the 4 m Phi bytes of phi(k) once, so it takes as few rows as leave all blocks on the chip at the same time (three per
@@ -412,7 +427,11 @@ armt_status update_group(const Ctx& c, int lo, int hi, int empty_lo, int empty_h
   const Dims& D = c.D;
   const T* Xop = D.bf16 ? c.at<T>(c.o.Xb) : (const T*)c.at<float>(c.o.X);
   const T* Y0 = Xop + ((size_t)D.B * D.T + D.S) * D.d;  // memory row 0 of slot B = output of cell 0
-  return step_assoc_update<T>(c.st, c.table(K_MKV), c.shape[K_MKV], c.aux, lo * D.B, (hi - lo + 1) * D.B, empty_lo * D.B,
+  GemmShape mkv = c.shape[K_MKV];
+  if (c.fused_prep) {
+    mkv.epi = EPI_UPDATE_F32; mkv.nu = D.nu; mkv.fparam = D.assoc_eps; mkv.empty_lo = empty_lo * D.B; mkv.empty_hi = empty_hi * D.B;
+  }
+  return step_assoc_update<T>(c.st, c.table(K_MKV), mkv, c.aux, lo * D.B, (hi - lo + 1) * D.B, empty_lo * D.B,
                               empty_hi * D.B, Y0, (size_t)D.T * D.d, D.m, D.d, D.dm, D.nu, D.assoc_eps, c.at<float>(c.o.KVm),
                               c.at<float>(c.o.Fm), c.at<float>(c.o.Coef));
 }
@@ -443,7 +462,7 @@ armt_status run_group(const Ctx& c, int lo, int hi, int read_hi) {
       rmsnorm_kernel<T><<<dim3(D.T, g - gr), 256, 0, c.st>>>(X, c.aux, lo + gr, 0, D.T, D.d, D.rms_eps, c.at<T>(c.o.Nrm), rstd);
       HIP_TRY(hipGetLastError());
     }
-  } else {
+  } else if (!c.shape[K_QKV].norm) {
     rmsnorm_kernel<T><<<dim3(D.T, g), 256, 0, c.st>>>(X, c.aux, lo, 0, D.T, D.d, D.rms_eps, c.at<T>(c.o.Nrm), nullptr);
     HIP_TRY(hipGetLastError());
   }
@@ -453,7 +472,7 @@ armt_status run_group(const Ctx& c, int lo, int hi, int read_hi) {
   ARMT_TRY(gemm<T>(c.st, c.table(K_O), lo, g, c.shape[K_O]));
   if (c.fused_norm) {
     rstd_kernel<<<dim3((D.T + 255) / 256, g), 256, 0, c.st>>>(c.at<float>(c.o.Ssq), lo, D.T, c.ssq_parts, D.d, D.rms_eps, rstd);
-  } else {
+  } else if (!c.shape[K_GU].norm) {
     rmsnorm_kernel<T><<<dim3(D.T, g), 256, 0, c.st>>>(c.at<float>(c.o.Hres), c.aux, lo, 1, D.T, D.d, D.rms_eps,
                                                       c.at<T>(c.o.Nrm), nullptr);
   }

@@ -77,6 +77,9 @@ enum GemmEpilogue : int {
                        // columns q of a row never leave the workgroup; written are phi(q) (DPFP-nu, nu = ldr; activation
                        // type, C [M][ldc], ldc >= 2 nu d_mem) and 1 / (z . phi(q) + fparam) (fp32, C2 [M]); z = R [2 nu d_mem].
                        // All N columns must lie in one output tile.
+  EPI_UPDATE_F32 = 6,  // fp32 only: EPI_STORE_F32 of the k | v projections of the memory rows, and from the k columns (n0 = d_mem <= 32,
+                       // M <= 16 rows) what the delta rule needs: phi(k) (DPFP-nu) -> C2 [M][2 nu d_mem] and {beta, gamma, 1 / den, z . phi}
+                       // -> ssq_out [M][4] (see memupd_prep_kernel); gain = W_beta, R = z, fparam = eps, [empty_lo, empty_hi) groups without v_bar
   EPI_QKV_ROPE = 4     // EPI_STORE_ACT of the fused q | k | v projection with the rotary embedding applied to the q and k
                        // columns [0, n0 + n1): heads of ldr columns, rotate-half pairing, position = row; R = cos/sin table
                        // [M][ldr / 2][2].  Heads must not straddle output tiles (tile width a multiple of ldr).
@@ -95,6 +98,10 @@ struct GemmShape {
   int ldb;              // row stride of the weight blocks in elements (>= K); the weights of the model are dense: ldb = K
   float fparam = 0.f;   // EPI_DPFP_READ: assoc_eps
   int k_slot = 0;       // steps of 64 per unit of GemmGroup::krange
+  int norm = 0;         // fp32 only (EPI_STORE_ACT, EPI_QKV_ROPE, EPI_SWIGLU): A is multiplied by `gain` column by column and the result rows
+                        // by 1 / sqrt(mean of the row's squares + fparam): RMSNorm of A inside the product
+  int nu = 0;           // EPI_UPDATE_F32: order of the feature map
+  int empty_lo = 0, empty_hi = 0;
   int spread = 0;       // 1: the groups differ in length, every one is spread over all XCDs
   int a_rows = 0;       // rows of A that may be READ in every group (0: M).  Operand buffers that are padded to whole
                         // tiles let a ragged M take the copies without per-lane clamping; rows >= M are never stored

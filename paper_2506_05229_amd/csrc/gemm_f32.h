@@ -13,26 +13,41 @@
 // 1000, K 333) 127 -> 108 us, 4 x (4096 x 4096, K 1023) 6.56 -> 4.80 ms, 1 x (1032 x 512, K 1002) 139 -> 60.  One kernel for
 // all launches: which kernel runs may not depend on the number of groups, or a cell would have other bits alone, on a diagonal and
 // in a batch.
+//
+// What is left of a step is its chain of launches of 2 to 8 us, so the small kernels around the products are part of them (F32With):
+// the norm in front of QKV and gate/up, the rotation of q and k, the feature map and denominator of the read behind W_Q, features and
+// coefficients of the update behind W_K | W_V.  A step of the 4-layer configuration is 9 launches instead of 14: 8 segments of 64 in 587 us, 683 before.
 #pragma once
 
 #include "common.h"
 #include "gemm_generic.h"
+#include "rowwise_kernels.h"
 
 namespace armt {
 
+enum F32With {
+  F32_PLAIN,
+  F32_NORM,       // GemmShape::norm; with EPI_QKV_ROPE also the rotation of heads of 8, 16 or 32 columns, which lie inside a tile
+  F32_DPFP,       // EPI_DPFP_READ, N <= 32: one tile column
+  F32_UPDATE      // EPI_UPDATE_F32
+};
+
 // grid: (ceil(N / 32), ceil(M / (16 TM)), g); block: 256.
 // CH: chunks of 16 k per batch of loads; a wave's share should be a batch (K <= 128: 2) or several (4).
-template <int TM, bool SWIGLU, int CH>
+template <int TM, bool SWIGLU, int CH, F32With WITH>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s) {
   constexpr int TN = 2, NB = SWIGLU ? 2 : 1, BM = 16 * TM, BN = 16 * TN, LD = BN + 4;
+  constexpr bool ROWSUM = WITH == F32_NORM || WITH == F32_UPDATE;      // a sum over each row of A: squares, or products with W_beta
   __shared__ __align__(16) float part[NB][4][BM][LD];
+  __shared__ float rowsum[4][BM];
   GemmGroup g = table[first + blockIdx.z];
   if (!restrict_k<float>(g, s)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, q = lane >> 4;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
   // 16-byte loads need 16-byte aligned rows and a K that ends with one; anything else is read element by element
-  const bool wide = (((uintptr_t)g.A | (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)g.B2) & 15) == 0 &&
+  const float* along = (const float*)g.gain;               // ROWSUM: gain or W_beta
+  const bool wide = (((uintptr_t)g.A | (uintptr_t)g.B0 | (uintptr_t)g.B1 | (uintptr_t)g.B2 | (ROWSUM ? (uintptr_t)along : 0)) & 15) == 0 &&
                     ((s.K | s.lda | s.ldb) & 3) == 0;
   const float* a[TM];
   const float* b[NB][TN];
@@ -55,6 +70,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
                         (((uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.R) & 15) == 0;
   f32x4 res = {0.f, 0.f, 0.f, 0.f};
   float rs = 1.f;
+  const bool rotate = WITH == F32_NORM && !SWIGLU && s.epi == EPI_QKV_ROPE && n < s.n0 + s.n1;
+  const int half = s.ldr >> 1, in_head = rotate ? n & (s.ldr - 1) : 0;      // (rotate: ldr = 8, 16 or 32)
+  f32x4 cs0 = {0.f, 0.f, 0.f, 0.f}, cs1 = cs0;                               // cos and sin of this thread's four columns
+  if (rotate && mine) {
+    const float* cs = g.R + ((size_t)m * half + (in_head & (half - 1))) * 2;
+    cs0 = *(const f32x4*)cs;
+    cs1 = *(const f32x4*)(cs + 4);
+  }
   if (mine) {
     if (g.rowscale) rs = g.rowscale[m];
     if (s.epi == EPI_RESID_F32 && g.R) {
@@ -68,6 +91,22 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
       }
     }
   }
+  // features lane, lane + 64, ...: z there, and the two factors of feature c as columns of the row and their signs (see dpfp_at)
+  const int Phi = 2 * (WITH == F32_DPFP ? s.ldr : s.nu) * s.n0;
+  float zv[8], sign_a[8], sign_b[8];
+  int col_a[8], col_b[8];
+  if (WITH == F32_DPFP || WITH == F32_UPDATE) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (64 * k >= Phi) break;
+      const int c = lane + 64 * k, dm = s.n0, j = c / (2 * dm) + 1, i = c % (2 * dm), i2 = i >= j ? i - j : i - j + 2 * dm;
+      zv[k] = c < Phi ? g.R[c] : 0.f;
+      sign_a[k] = i < dm ? 1.f : -1.f;
+      sign_b[k] = i2 < dm ? 1.f : -1.f;
+      col_a[k] = c < Phi ? (i < dm ? i : i - dm) : 0;
+      col_b[k] = c < Phi ? (i2 < dm ? i2 : i2 - dm) : 0;
+    }
+  }
   f32x4 acc[NB][TM][TN];
 #pragma unroll
   for (int u = 0; u < NB; ++u)
@@ -77,8 +116,22 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
       for (int j = 0; j < TN; ++j) acc[u][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int chunks = (s.K + 15) >> 4, per = (chunks + 3) >> 2;
   const int c0 = min(wave * per, chunks), c1 = min(c0 + per, chunks);
-  struct Batch { f32x4 a[CH][TM], b[CH][NB][TN]; };
-  auto multiply = [&](const Batch& t, int h) __attribute__((always_inline)) {
+  struct Batch { f32x4 a[CH][TM], b[CH][NB][TN], along[ROWSUM ? CH : 1]; };
+  float sum[TM] = {};
+  auto multiply = [&](Batch& t, int h) __attribute__((always_inline)) {
+    if (ROWSUM) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (WITH == F32_NORM) {
+            sum[i] = fmaf(t.a[h][i][e], t.a[h][i][e], sum[i]);
+            t.a[h][i][e] *= t.along[h][e];
+          } else {
+            sum[i] = fmaf(t.a[h][i][e], t.along[h][e], sum[i]);
+          }
+        }
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -97,6 +150,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
         const int at = min(16 * (c + h) + 4 * q, s.K - 4);
 #pragma unroll
         for (int i = 0; i < TM; ++i) t.a[h][i] = *(const f32x4*)(a[i] + at);
+        if (ROWSUM) t.along[h] = *(const f32x4*)(along + at);
 #pragma unroll
         for (int u = 0; u < NB; ++u)
 #pragma unroll
@@ -112,6 +166,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < TM; ++i) t.a[h][i] = in ? t.a[h][i] : zero;
+        if (ROWSUM) t.along[h] = in ? t.along[h] : zero;
 #pragma unroll
         for (int u = 0; u < NB; ++u)
 #pragma unroll
@@ -143,6 +198,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
       };
 #pragma unroll
       for (int i = 0; i < TM; ++i) t.a[0][i] = load(a[i]);
+      if (ROWSUM) t.along[0] = load(along);
 #pragma unroll
       for (int u = 0; u < NB; ++u)
 #pragma unroll
@@ -159,8 +215,76 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) part[u][wave][16 * i + 4 * q + r][16 * j + r16] = acc[u][i][j][r];
+  if (ROWSUM) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      sum[i] += __shfl_xor(sum[i], 16, kWave);
+      sum[i] += __shfl_xor(sum[i], 32, kWave);
+      if (q == 0) rowsum[wave][16 * i + r16] = sum[i];
+    }
+  }
   __syncthreads();
+  auto row_total = [&](int r) { return (rowsum[0][r] + rowsum[1][r]) + (rowsum[2][r] + rowsum[3][r]); };
+  if (WITH == F32_DPFP || (WITH == F32_UPDATE && blockIdx.x == 0)) {
+    // The N = d_mem (F32_UPDATE: n0) columns of a row lie in this tile: they go back to LDS, and a wave expands whole rows.
+    float(&x)[BM][LD] = part[0][0];
+    if (row < BM) {
+      f32x4 v = *(const f32x4*)&x[row][col];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += *(const f32x4*)&part[0][w][row][col];
+      *(f32x4*)&x[row][col] = v;           // read and written by this thread only
+      if (WITH == F32_UPDATE && mine) {
+        float* out = (float*)g.C + (size_t)m * s.ldc + n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < s.N) out[e] = v[e];
+      }
+    }
+    __syncthreads();
+    constexpr int ROWS = BM / 4;           // of this wave: their reductions go side by side
+    float zf[ROWS], ff[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const int r = wave + 4 * i;
+      zf[i] = ff[i] = 0.f;
+      float* out = (float*)(WITH == F32_DPFP ? g.C : g.C2) + (size_t)(m0 + r) * (WITH == F32_DPFP ? s.ldc : Phi);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (64 * k >= Phi) break;
+        const float f = fmaxf(sign_a[k] * x[r][col_a[k]], 0.f) * fmaxf(sign_b[k] * x[r][col_b[k]], 0.f);
+        if (lane + 64 * k < Phi) {
+          zf[i] = fmaf(f, zv[k], zf[i]);
+          ff[i] = fmaf(f, f, ff[i]);
+          if (m0 + r < s.M) out[lane + 64 * k] = f;
+        }
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        zf[i] += __shfl_xor(zf[i], o, kWave);
+        if (WITH == F32_UPDATE) ff[i] += __shfl_xor(ff[i], o, kWave);
+      }
+    const int l = first + blockIdx.z;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const int r = wave + 4 * i;
+      if (lane != i || m0 + r >= s.M) continue;
+      if (WITH == F32_DPFP) {
+        ((float*)g.C2)[m0 + r] = 1.0f / (zf[i] + s.fparam);
+      } else {
+        float* cf = g.ssq_out + 4 * (m0 + r);
+        cf[0] = 1.0f / (1.0f + expf(-row_total(r)));
+        cf[1] = 1.0f - zf[i] / (ff[i] + s.fparam);
+        cf[2] = l >= s.empty_lo && l < s.empty_hi ? 0.f : 1.0f / (zf[i] + s.fparam);
+        cf[3] = zf[i];
+      }
+    }
+    return;
+  }
   if (!mine) return;
+  if (WITH == F32_NORM) rs = 1.0f / sqrtf(row_total(row) / (float)s.K + s.fparam);
   auto total = [&](int u) {
     f32x4 v = *(const f32x4*)&part[u][0][row][col];
 #pragma unroll
@@ -174,6 +298,16 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
     for (int e = 0; e < 4; ++e) {
       const float gv = v[e] * rs;
       v[e] = gv / (1.f + expf(-gv)) * (up[e] * rs);
+    }
+  } else if (rotate) {      // rotate-half pairing: column j of a head with j + half
+    const bool low = in_head < half;
+    f32x4 w = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w += *(const f32x4*)&part[0][i][row][low ? col + half : col - half];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float c = e < 2 ? cs0[2 * e] : cs1[2 * e - 4], sn = e < 2 ? cs0[2 * e + 1] : cs1[2 * e - 3];
+      v[e] = v[e] * rs * c + (low ? -w[e] : w[e]) * rs * sn;
     }
   } else {
 #pragma unroll
@@ -201,12 +335,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
 
 inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, const GemmShape& s, hipStream_t st) {
   if (g <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
-  const bool swiglu = s.epi == EPI_SWIGLU, narrow = s.M <= 16, brief = s.K <= 128;
+  // the feature map is a chain of its own behind the product: the fewer rows per wave the better (32-row tiles 13.5 us per launch of 4 cells of 72 rows, 16-row tiles with the reductions of a wave's rows side by side 6.4)
+  const bool narrow = s.M <= 16 || s.epi == EPI_DPFP_READ, brief = s.K <= 128;
   const dim3 grid((s.N + 31) / 32, (s.M + (narrow ? 15 : 31)) / (narrow ? 16 : 32), g);
-  auto kern = swiglu ? (narrow ? (brief ? gemm_f32_kernel<1, true, 2> : gemm_f32_kernel<1, true, 4>)
-                               : (brief ? gemm_f32_kernel<2, true, 2> : gemm_f32_kernel<2, true, 4>))
-                     : (narrow ? (brief ? gemm_f32_kernel<1, false, 2> : gemm_f32_kernel<1, false, 4>)
-                               : (brief ? gemm_f32_kernel<2, false, 2> : gemm_f32_kernel<2, false, 4>));
+#define ARMT_F32(SW, WITH)                                                                                            \
+  (narrow ? (brief ? gemm_f32_kernel<1, SW, 2, WITH> : gemm_f32_kernel<1, SW, 4, WITH>)                                \
+          : (brief ? gemm_f32_kernel<2, SW, 2, WITH> : gemm_f32_kernel<2, SW, 4, WITH>))
+  auto kern = ARMT_F32(false, F32_PLAIN);
+  if (s.epi == EPI_DPFP_READ) {
+    if (s.N != s.n0 || s.N > 32 || s.ldr < 1 || 2 * s.ldr * s.n0 > 512 || s.ldc < 2 * s.ldr * s.n0) return hipErrorInvalidValue;
+    kern = brief ? gemm_f32_kernel<1, false, 2, F32_DPFP> : gemm_f32_kernel<1, false, 4, F32_DPFP>;
+  } else if (s.epi == EPI_UPDATE_F32) {
+    if (!narrow || s.n0 > 32 || s.nu < 1 || 2 * s.nu * s.n0 > 512) return hipErrorInvalidValue;
+    kern = brief ? gemm_f32_kernel<1, false, 2, F32_UPDATE> : gemm_f32_kernel<1, false, 4, F32_UPDATE>;
+  } else if (s.norm) {
+    if (s.epi == EPI_QKV_ROPE && s.ldr != 8 && s.ldr != 16 && s.ldr != 32) return hipErrorInvalidValue;
+    kern = s.epi == EPI_SWIGLU ? ARMT_F32(true, F32_NORM) : ARMT_F32(false, F32_NORM);
+  } else if (s.epi == EPI_SWIGLU) {
+    kern = ARMT_F32(true, F32_PLAIN);
+  }
+#undef ARMT_F32
   kern<<<grid, 256, 0, st>>>(table, first, s);
   return hipGetLastError();
 }
