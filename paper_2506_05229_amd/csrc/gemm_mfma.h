@@ -1087,9 +1087,13 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
       if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 2, 2, EPI, true>(table, first, g, s, st);
       return launch_mfma_cfg<128, 128, 2, 2, EPI>(table, first, g, s, st);
     case 7:   // at most one workgroup per CU: nobody else fills the waits for a copy, so four k-tiles in LDS
+      // Nor for a fragment: eight waves of 32 x 32, two per SIMD, instead of four of 32 x 64 (SwiGLU needs these: whole gate/up pairs of
+      // blocks).  One cell of 1040 rows, us per launch (read, attention output and down together): 39.2 -> 31.1; six k-tiles
+      // 40.5 and 31.4, so it was the SIMD's one wave that waited and not the copies.
       if constexpr (EPI != EPI_DPFP_READ) {
-        if (mfma_regular_shape<64, 128, EPI>(s)) return launch_mfma_cfg<64, 128, 2, 2, EPI, true, 4>(table, first, g, s, st);
-        return launch_mfma_cfg<64, 128, 2, 2, EPI, false, 4>(table, first, g, s, st);
+        constexpr int WGN = EPI == EPI_SWIGLU ? 2 : 4;
+        if (mfma_regular_shape<64, 128, EPI>(s)) return launch_mfma_cfg<64, 128, 2, WGN, EPI, true, 4>(table, first, g, s, st);
+        return launch_mfma_cfg<64, 128, 2, WGN, EPI, false, 4>(table, first, g, s, st);
       }
       break;
     case 8:   // the same for 128 x 128 tiles, eight waves
