@@ -1077,14 +1077,17 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
             big.begin = 0; big.end = rest.begin = cut; rest.end = units;
             hipError_t e = launch_mfma_cfg<256, 256, 2, 4, EPI, true>(table, first, g, s, st, big);
             if (e != hipSuccess) return e;
-            return launch_mfma_cfg<128, 128, 2, 2, EPI, true>(table, first, g, s, st, rest);
+            return launch_mfma_cfg<128, 128, 4, 2, EPI, true>(table, first, g, s, st, rest);
           }
         }
         return launch_mfma_cfg<256, 256, 2, 4, EPI, true>(table, first, g, s, st);
       }
       return launch_mfma_cfg<256, 256, 4, 4, EPI>(table, first, g, s, st);
     case 6:   // as 1, copies addressed by scalar base + lane offset where the shape allows
-      if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 2, 2, EPI, true>(table, first, g, s, st);
+      // Eight waves of 32 x 64 instead of four of 64 x 64: two workgroups of four waves leave a SIMD two waves, which wait for their
+      // fragments together.  us per launch, four / eight: attention output and down of the 768-wide model (mean of its launches)
+      // 49.5 / 44.3, QKV 25.0 / 21.6, gate/up of one cell 20.3 / 18.7; down of two and three cells of d 2048 109.6 / 104.0
+      if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 4, 2, EPI, true>(table, first, g, s, st);
       return launch_mfma_cfg<128, 128, 2, 2, EPI>(table, first, g, s, st);
     case 7:   // at most one workgroup per CU: nobody else fills the waits for a copy, so four k-tiles in LDS
       // Nor for a fragment: eight waves of 32 x 32, two per SIMD, instead of four of 32 x 64 (SwiGLU needs these: whole gate/up pairs of
@@ -1096,9 +1099,11 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
         return launch_mfma_cfg<64, 128, 2, WGN, EPI, false, 4>(table, first, g, s, st);
       }
       break;
-    case 8:   // the same for 128 x 128 tiles, eight waves
+    case 8:   // the same for 128 x 128 tiles: sixteen waves of 32 x 32 (SwiGLU eight of 32 x 64); sixteen against eight: QKV of one cell of d 2048
+              // 27.2 -> 26.1 us, attention output of two 27.3 -> 25.9, of the 768-wide model 23.4 -> 22.2
       if constexpr (EPI != EPI_DPFP_READ) {
-        if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 4, 2, EPI, true, 4>(table, first, g, s, st);
+        constexpr int WGN = EPI == EPI_SWIGLU ? 2 : 4;
+        if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 4, WGN, EPI, true, 4>(table, first, g, s, st);
         return launch_mfma_cfg<128, 128, 4, 2, EPI, false, 4>(table, first, g, s, st);
       }
       break;
