@@ -80,11 +80,6 @@ __global__ __launch_bounds__(256) void attention_dvec_kernel(const bf16* __restr
   }
 }
 
-// One KB of a tile into LDS: 16 bytes from base + voff for every lane, in lane order from LDS address `lds` on.
-__device__ __forceinline__ void bwd_copy_slab(const char* base, unsigned voff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
-}
-
 // dQ.  QKV: [cells][T][(H + 2 Hkv) dh] (q, k rotated); Kt: [cells][Hkv][dh][Tp]; dO: [cells][T][H dh];
 // LSE2 (log2 domain), Dv: [cells][H][T]; dQKV: gradient rows, q columns written here.
 // (68 us per launch with 8-byte reads of K^T and a copy addressed per lane, 60 as it is; 1B shape, mean of 5.6 cells.)
@@ -159,7 +154,7 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
         const char* base = isv ? vbase : kbase;
         if (whole) {
           const int keyS = k0 + ((a & 1) << 2) + ((a >> 1) << 4);
-          bwd_copy_slab(base + ((size_t)keyS * ldq + sub * 64) * 2, voffK ^ ((unsigned)(a & 1) << 6), lds + sl * 1024);
+          lds_copy16(base + ((size_t)keyS * ldq + sub * 64) * 2, voffK ^ ((unsigned)(a & 1) << 6), lds + sl * 1024);
         } else {
           const int row = a * 8 + R, key = min(k0 + at_key_of_row(row), Trows - 1);
           const char* src = base + ((size_t)key * ldq + sub * 64 + ((pc ^ mf_swz(row)) << 3)) * 2;
@@ -167,7 +162,7 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
         }
       } else {
         const int ts = sl - 2 * K_SLABS;
-        bwd_copy_slab(tbase + ((size_t)ts * 8 * Tp + k0) * 2, voffT ^ ((unsigned)(ts & 1) << 6), lds + sl * 1024);
+        lds_copy16(tbase + ((size_t)ts * 8 * Tp + k0) * 2, voffT ^ ((unsigned)(ts & 1) << 6), lds + sl * 1024);
       }
     }
   };
@@ -332,14 +327,14 @@ __global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const
         const size_t ld = which == 0 ? ldq : ldo;
         if (whole) {
           const int qS = q0 + ((a & 1) << 2) + ((a >> 1) << 4);
-          bwd_copy_slab(rows + (qS * ld + sub * 64) * 2, (which == 0 ? voffQ : voffG) ^ ((unsigned)(a & 1) << 6), lds + sl * 1024);
+          lds_copy16(rows + (qS * ld + sub * 64) * 2, (which == 0 ? voffQ : voffG) ^ ((unsigned)(a & 1) << 6), lds + sl * 1024);
         } else {
           const int row = a * 8 + R, q = min(q0 + at_key_of_row(row), Trows - 1);
           const char* src = rows + (q * ld + sub * 64 + ((pc ^ mf_swz(row)) << 3)) * 2;
           __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(base + sl * 1024), 16, 0, 0);
         }
       } else {                   // columns: [DH dims][64 rows of the sequence]
-        bwd_copy_slab((which == 2 ? qcols : gcols) + (size_t)s2 * 8 * Tp * 2, voffT ^ ((unsigned)(s2 & 1) << 6), lds + sl * 1024);
+        lds_copy16((which == 2 ? qcols : gcols) + (size_t)s2 * 8 * Tp * 2, voffT ^ ((unsigned)(s2 & 1) << 6), lds + sl * 1024);
       }
     }
     if (wave < 2) {              // lse (wave 0) and D (wave 1) of the 64 rows, also as direct loads: a load through

@@ -121,9 +121,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
   const unsigned voffK = (unsigned)((R & 3) + ((R >> 2) << 3)) * (unsigned)ldq * 2u + chunk0;
   const unsigned voffV = (unsigned)R * (unsigned)Tp * 2u + chunk0;
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
-  auto dma = [&](const char* base, unsigned voff, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
-  };
   auto issue_tile = [&](int kt, int buf) {
     typedef const __attribute__((address_space(1))) void* gptr_t;
     typedef __attribute__((address_space(3))) void* lptr_t;
@@ -136,7 +133,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
         const int sub = sl >> 3, a = sl & 7;
         if (whole) {
           const int keyS = k0 + ((a & 1) << 2) + ((a >> 1) << 4);
-          dma(kbase + ((size_t)keyS * ldq + sub * 64) * 2, voffK ^ ((unsigned)(a & 1) << 6), ldsK + sl * 1024);
+          lds_copy16(kbase + ((size_t)keyS * ldq + sub * 64) * 2, voffK ^ ((unsigned)(a & 1) << 6), ldsK + sl * 1024);
         } else {
           const int row = a * 8 + R;                                     // row of the tile in LDS
           const int key = min(k0 + at_key_of_row(row), Trows - 1);       // keys past T are masked by causality
@@ -145,7 +142,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
         }
       } else {
         const int vs = sl - K_SLABS;                                     // dim rows 8 vs .. 8 vs + 7 of V^T
-        dma(vbase + ((size_t)vs * 8 * Tp + k0) * 2, voffV ^ ((unsigned)(vs & 1) << 6), ldsV + vs * 1024);
+        lds_copy16(vbase + ((size_t)vs * 8 * Tp + k0) * 2, voffV ^ ((unsigned)(vs & 1) << 6), ldsV + vs * 1024);
       }
     }
   };

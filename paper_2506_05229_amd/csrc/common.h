@@ -31,6 +31,17 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Copies into LDS written as instructions: 16 bytes per lane, in lane order from LDS address `lds` (wave-uniform, M0) on.  The compiler does not
+// count them among the outstanding memory operations, so whoever issues them waits for them (vmcnt) and fences.  It does not look into
+// the text for hazards either: a copy needs one wait state behind the scalar write of M0, or it may go to the address M0 held before.
+// (The s_nop is one issue cycle of a copy.)
+__device__ __forceinline__ void lds_copy16(const char* base, unsigned voff, unsigned lds) {      // from base (wave-uniform) + voff
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_copy16(const char* src, unsigned lds) {                     // from one 64-bit pointer per lane
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds) : "memory", "m0");
+}
+
 // Sum over the threads of a block (blockDim.x a multiple of 64, at most 1024); every thread gets it.
 __device__ __forceinline__ float block_sum(float v, float* red /* >= 17 floats of LDS */) {
   v = wave_sum(v);

@@ -269,35 +269,28 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     return (const char*)w_row(n0 + RPS * slab);
   };
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
-  // one copy: 64 lanes x 16 bytes from base + lane offset to LDS address `lds` (M0) onwards; scalar operands only
-  auto dma = [&](const char* base, unsigned voff, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
-  };
-  // the same copy from one 64-bit pointer per lane.  Written as an instruction like the one above: the compiler then
-  // does not count it among the outstanding memory operations, so the fence of a barrier does not wait for the
-  // copies of the younger k-tiles that are meant to stay in flight (the waits for the copies are explicit, below)
-  auto dma_ptr = [&](const char* src, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds) : "memory", "m0");
-  };
+  // A copy from one 64-bit pointer per lane is an instruction like the ones with a scalar base (lds_copy16) and no builtin, too: the fence
+  // of a barrier then does not wait for the copies of the younger k-tiles that are meant to stay in flight (the waits for the copies are
+  // explicit, below).
   auto issue_tile = [&](int kt, int buf) {
     const size_t ka = (size_t)kt * ROWB, kb = ka;
     if (KEEP_PTRS) {
       const unsigned ldsA = lds0 + buf * A_BYTES, ldsB = lds0 + NS * A_BYTES + buf * B_BYTES;
 #pragma unroll
       for (int j = 0; j < A_DMA; ++j)
-        dma_ptr(ap[KEEP_PTRS ? j : 0] + ka, ldsA + (wave + j * NW) * 1024);
+        lds_copy16(ap[KEEP_PTRS ? j : 0] + ka, ldsA + (wave + j * NW) * 1024);
       if (TAIL && tail_blk && wave < 2)
-        dma_ptr(tp + ka, ldsA + BM * MF_ROW_BYTES + wave * 1024);
+        lds_copy16(tp + ka, ldsA + BM * MF_ROW_BYTES + wave * 1024);
 #pragma unroll
       for (int j = 0; j < B_DMA; ++j)
-        dma_ptr(bp[KEEP_PTRS ? j : 0] + kb, ldsB + (wave + j * NW) * 1024);
+        lds_copy16(bp[KEEP_PTRS ? j : 0] + kb, ldsB + (wave + j * NW) * 1024);
     } else {
       const unsigned As = lds0 + buf * A_BYTES, Bs = lds0 + NS * A_BYTES + buf * B_BYTES;
 #pragma unroll
-      for (int j = 0; j < A_DMA; ++j) dma(a_base(wave + j * NW) + ka, a_off0, As + (wave + j * NW) * 1024);
-      if (TAIL && tail_blk && wave < TAIL_SLABS) dma(a_base(BM / RPS + wave) + ka, a_off0, As + BM * ROWB + wave * 1024);
+      for (int j = 0; j < A_DMA; ++j) lds_copy16(a_base(wave + j * NW) + ka, a_off0, As + (wave + j * NW) * 1024);
+      if (TAIL && tail_blk && wave < TAIL_SLABS) lds_copy16(a_base(BM / RPS + wave) + ka, a_off0, As + BM * ROWB + wave * 1024);
 #pragma unroll
-      for (int j = 0; j < B_DMA; ++j) dma(b_base(wave + j * NW) + kb, b_off0, Bs + (wave + j * NW) * 1024);
+      for (int j = 0; j < B_DMA; ++j) lds_copy16(b_base(wave + j * NW) + kb, b_off0, Bs + (wave + j * NW) * 1024);
     }
   };
 
@@ -355,15 +348,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     auto copy_a = [&](int kt, int h) __attribute__((always_inline)) {
       const unsigned at = lds0 + (kt & 1) * A_BYTES + wave * 1024;
 #pragma unroll
-      for (int j = 2 * h; j < 2 * h + 2; ++j) dma(sA[j] + (size_t)kt * ROWB, a_off0, at + j * NW * 1024);
+      for (int j = 2 * h; j < 2 * h + 2; ++j) lds_copy16(sA[j] + (size_t)kt * ROWB, a_off0, at + j * NW * 1024);
     };
     auto copy_b = [&](int kt, int h) __attribute__((always_inline)) {
       const unsigned at = lds0 + NS * A_BYTES + (kt & 1) * B_BYTES + wave * 1024;
 #pragma unroll
-      for (int j = 2 * h; j < 2 * h + 2; ++j) dma(sB[j] + (size_t)kt * ROWB, b_off0, at + j * NW * 1024);
+      for (int j = 2 * h; j < 2 * h + 2; ++j) lds_copy16(sB[j] + (size_t)kt * ROWB, b_off0, at + j * NW * 1024);
     };
     auto copy_t = [&](int kt) __attribute__((always_inline)) {
-      if (TAIL && extra) dma(sT + (size_t)kt * ROWB, a_off0, lds0 + (kt & 1) * A_BYTES + BM * ROWB + wave * 1024);
+      if (TAIL && extra) lds_copy16(sT + (size_t)kt * ROWB, a_off0, lds0 + (kt & 1) * A_BYTES + BM * ROWB + wave * 1024);
     };
     bf16x8 a0[KS2][4], a1[KS2][4], b0[KS2][2], b1[KS2][2];
     // fragment q of a half-tile: k-step q / 4 (A) or q / 2 (B)

@@ -1,0 +1,47 @@
+"""Rules for the gfx950 machine code of the built library that neither the compiler nor a run checks: the instructions of an inline-asm block
+get no wait states from the compiler, and results can be right by luck."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+LLVM = next((d for d in ("/opt/rocm/llvm/bin", "/opt/rocm/lib/llvm/bin") if os.path.exists(os.path.join(d, "llvm-objdump"))), None)
+pytestmark = pytest.mark.skipif(LLVM is None, reason="needs the ROCm LLVM tools")
+
+
+@pytest.fixture(scope="module")
+def code_object(tmp_path_factory):
+    """The gfx950 code object of the library, unpacked."""
+    import paper_2506_05229_amd as P
+    if not os.path.exists(P.library_path()):
+        from paper_2506_05229_amd.build import build
+        build()
+    where = tmp_path_factory.mktemp("device_code")
+    lib = shutil.copy(P.library_path(), where / "lib.so")
+    subprocess.run([f"{LLVM}/llvm-objdump", "--offloading", lib], check=True, capture_output=True, cwd=where)
+    found = [f for f in os.listdir(where) if "gfx950" in f]
+    assert len(found) == 1, found
+    return str(where / found[0])
+
+
+def test_lds_copies_wait_for_m0(code_object):
+    """A scalar write of M0 needs one wait state in front of a global load to LDS."""
+    text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", code_object], check=True, capture_output=True, text=True).stdout
+    copies, bad, kernel, before = 0, {}, None, ""
+    for line in text.splitlines():
+        label = re.match(r"[0-9a-f]+ <(.*)>:", line)
+        if label:
+            kernel, before = label.group(1), ""
+            continue
+        instruction = line.split("//")[0].strip()
+        if not instruction:
+            continue
+        if "load_lds" in instruction or (instruction.startswith("buffer_load") and re.search(r"\blds\b", instruction)):
+            copies += 1
+            if re.match(r"s_\w+ m0,", before):
+                bad[kernel] = bad.get(kernel, 0) + 1
+        before = instruction
+    assert copies > 1000          # the pattern still finds the copies
+    assert not bad
