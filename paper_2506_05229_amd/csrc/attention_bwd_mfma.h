@@ -252,10 +252,14 @@ __global__ __launch_bounds__(512) void attention_bwd_dq_kernel(const bf16* __res
 // other, in its registers: no reduction between waves or workgroups.  The eight waves share the tiles of the current
 // (query head, 64 query rows): Q and dO rows, Q^T and dO^T columns, the rows' log-sum-exp and D, double buffered in LDS.
 // What bounds it: the longest workgroup (key block 0 meets every query of every head) and, inside an iteration, two waves per SIMD that take
-// turns with products and exponentials.  1B shape, us per launch (mean of 5.6 cells): 237 with
+// turns with products and exponentials.  head_dim 64, 1B shape, us per launch (mean of 5.6 cells): 237 with
 // the transposed operands read 8 bytes at a time (bank conflicts) and a branch around every exponential, 206 with permuted rows
-// (at_key_of_row: a fragment is one 16-byte read), 165 with the mask in a loop of its own.  Four or two waves (128 or 64 keys) per workgroup
-// copy more and gain no balance: 193, 261.
+// (at_key_of_row: a fragment is one 16-byte read), 153 with the mask in a loop of its own.  Four or two waves (128 or 64 keys) per workgroup
+// copy more and gain no balance: 193, 261 (205 with eight).
+// head_dim 128: K, V, dK and dV of a wave are 192 of its 256 registers, and what does not fit is loaded again behind the prefetch of the next
+// tile.  So it takes the products one by one (P, dV, dP, dK: one 32 x 32 result and P at a time), half a tile at a time, which spills nothing:
+// 3B shape (mean of 2.8 cells) 348 us with 8-byte reads, 375 with the steps of head_dim 64 (49 registers spilled), 230 as it is; d 4096 498 -> 304.
+// In that order head_dim 64 takes 174.
 // grid: 1-D, 8 * ceil(Hkv g / 8) * ceil(T / 256) workgroups, block: 512; LDS: 2 stages of 4 tiles + 512 bytes.
 constexpr int DKV_WAVES = 8;
 template <int DH>
@@ -268,6 +272,8 @@ __global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const
   constexpr int STAGE = 4 * Q_BYTES + 512;         // Q, dO, Q^T, dO^T, then lse[64], D[64]
   constexpr int Q_SLABS = Q_BYTES / 1024;
   constexpr int KS = DH / 16, OT = DH / 32;
+  constexpr bool ONE_BY_ONE = DH == 128;           // one product at a time (see above)
+  constexpr int HALVES = ONE_BY_ONE ? 1 : 2;       // of a tile, unrolled
   extern __shared__ __align__(16) unsigned char smem[];   // [2][STAGE]
 
   // key block 0 meets every query row, the last one a few: longest first over all (cell, KV head) pairs, a pair on one XCD
@@ -303,13 +309,15 @@ __global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const
   const int nq = Tp / 64 - qt_first;               // query tiles per head
   const int iters = group * nq;
   // tile copies as in the forward kernel: scalar base + one lane offset per operand, the Q and dO rows permuted (at_key_of_row)
-  const int R = lane >> 3, pc = lane & 7;
-  const unsigned chunk0 = (unsigned)((pc ^ mf_swz(R)) << 4);
-  const unsigned rowR = (unsigned)((R & 3) + ((R >> 2) << 3));
+  const unsigned chunk0 = (unsigned)(((lane & 7) ^ mf_swz(lane >> 3)) << 4);
+  const unsigned rowR = (unsigned)(((lane >> 3) & 3) + ((lane >> 5) << 3));
   const unsigned voffQ = rowR * (unsigned)ldq * 2u + chunk0, voffG = rowR * (unsigned)ldo * 2u + chunk0;
-  const unsigned voffT = (unsigned)R * (unsigned)Tp * 2u + chunk0;
+  const unsigned voffT = (unsigned)(lane >> 3) * (unsigned)Tp * 2u + chunk0;
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
   auto issue_tile = [&](int head, int q0, int buf) {
+    int at = lane;               // (DH 128: no register is left to keep the lane in)
+    if constexpr (ONE_BY_ONE) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(at));
+    const int R = at >> 3, pc = at & 7;
     typedef const __attribute__((address_space(1))) void* gptr_t;
     typedef __attribute__((address_space(3))) void* lptr_t;
     unsigned char* base = smem + buf * STAGE;
@@ -338,7 +346,7 @@ __global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const
       }
     }
     if (wave < 2) {              // lse (wave 0) and D (wave 1) of the 64 rows, also as direct loads: a load through
-      const float* srcf = (wave == 0 ? LSE2 : Dv) + ((size_t)l * H + head) * Trows + min(q0 + lane, Trows - 1);   // registers
+      const float* srcf = (wave == 0 ? LSE2 : Dv) + ((size_t)l * H + head) * Trows + min(q0 + at, Trows - 1);     // registers
       __builtin_amdgcn_global_load_lds((gptr_t)srcf, (lptr_t)(base + 4 * Q_BYTES + wave * 256), 4, 0, 0);         // would make the
     }                            // wave wait for the whole prefetch before it starts on the current tile
   };
@@ -367,33 +375,39 @@ __global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const
     const float* sL = (const float*)(Qs + 4 * Q_BYTES);
     const float* sD = sL + 64;
     if (k0 <= q0 + 63 && k0 < Trows) {             // wave-uniform: some query of the tile can see some key of this wave
-#pragma unroll
+#pragma unroll HALVES
       for (int jj = 0; jj < 2; ++jj) {
         if (q0 + jj * 32 + 31 < k0) continue;      // this half of the tile lies before the keys
+        const int roff = (jj * 32 + (lane & 31)) * MF_ROW_BYTES;
+        auto row_at = [&](int ks) { return roff + (ks >> 2) * (64 * MF_ROW_BYTES) + (((2 * (ks & 3) + half) ^ fl) << 4); };
+        auto col_at = [&](int t, int ss) { return (t * 32 + (lane & 31)) * MF_ROW_BYTES + (((jj * 4 + 2 * ss + half) ^ fl) << 4); };
+        auto row_of = [&](int rg) { return jj * 32 + 16 * (rg >> 1) + 8 * half + 4 * (rg & 1); };   // rows of registers 4 rg .. 4 rg + 3
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
-        const int roff = (jj * 32 + (lane & 31)) * MF_ROW_BYTES;
+        auto add_dp = [&](int ks) { dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(Gs + row_at(ks)), vf[ks], dp, 0, 0, 0); };
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          const int off = roff + (ks >> 2) * (64 * MF_ROW_BYTES) + (((2 * (ks & 3) + half) ^ fl) << 4);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(Qs + off), kf[ks], s, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(Gs + off), vf[ks], dp, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(Qs + row_at(ks)), kf[ks], s, 0, 0, 0);
+          if constexpr (!ONE_BY_ONE) add_dp(ks);
         }
-        bf16x8 pf[2], dsf[2];
         // all 32 queries of this half exist and lie at or after all 32 keys of the wave: nothing to mask
         const bool interior = q0 + jj * 32 >= k0 + 31 && q0 + jj * 32 + 31 < Trows;
-        // (the mask is a loop of its own: with its condition inside the common one the compiler branched around every exponential)
         f32x4 l4[4], d4[4];
+        auto lse_of = [&](int rg) { l4[rg] = *(const f32x4*)(sL + row_of(rg)); };
+        auto d_of = [&](int rg) { d4[rg] = *(const f32x4*)(sD + row_of(rg)); };
+        if constexpr (!ONE_BY_ONE) {
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {         // registers 4 rg .. 4 rg + 3 hold four consecutive query rows (at_key_of_row)
-          const int j4 = jj * 32 + 16 * (rg >> 1) + 8 * half + 4 * (rg & 1);
-          l4[rg] = *(const f32x4*)(sL + j4);
-          d4[rg] = *(const f32x4*)(sD + j4);
+          for (int rg = 0; rg < 4; ++rg) { lse_of(rg); d_of(rg); }
         }
         float p[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2e, -l4[r >> 2][r & 3]));
+        for (int rg = 0; rg < 4; ++rg) {
+          if constexpr (ONE_BY_ONE) lse_of(rg);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[4 * rg + e] = __builtin_amdgcn_exp2f(fmaf(s[4 * rg + e], scale_log2e, -l4[rg][e]));
+        }
+        // (the mask is a loop of its own: with its condition inside the common one the compiler branched around every exponential)
         if (!interior) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
@@ -401,23 +415,34 @@ __global__ __launch_bounds__(64 * DKV_WAVES) void attention_bwd_dkv_kernel(const
             p[r] = q < Trows && ki <= q ? p[r] : 0.f;
           }
         }
+        bf16x8 pf[2], dsf[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          pf[r >> 3][r & 7] = (bf16)p[r];
-          dsf[r >> 3][r & 7] = (bf16)(p[r] * (dp[r] - d4[r >> 2][r & 3]));
-        }
+        for (int r = 0; r < 16; ++r) pf[r >> 3][r & 7] = (bf16)p[r];
         // dV^T[dim][key] += dO^T[dim][query] P[query][key],  dK^T[dim][key] += Q^T[dim][query] dS[query][key]
+        auto add_dv = [&](int t, int ss) {
+          dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(GTs + col_at(t, ss)), pf[ss], dv[t], 0, 0, 0);
+        };
+        if constexpr (ONE_BY_ONE) {
 #pragma unroll
-        for (int t = 0; t < OT; ++t) {
-          const int toff = (t * 32 + (lane & 31)) * MF_ROW_BYTES;
+          for (int t = 0; t < OT; ++t)
+#pragma unroll
+            for (int ss = 0; ss < 2; ++ss) add_dv(t, ss);
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) add_dp(ks);
+        }
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          if constexpr (ONE_BY_ONE) d_of(rg);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dsf[rg >> 1][4 * (rg & 1) + e] = (bf16)(p[4 * rg + e] * (dp[4 * rg + e] - d4[rg][e]));
+        }
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
 #pragma unroll
           for (int ss = 0; ss < 2; ++ss) {
-            const int at = toff + (((jj * 4 + 2 * ss + half) ^ fl) << 4);
-            const bf16x8 ga = *(const bf16x8*)(GTs + at), qa = *(const bf16x8*)(QTs + at);
-            dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, pf[ss], dv[t], 0, 0, 0);
-            dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, dsf[ss], dk[t], 0, 0, 0);
+            if constexpr (!ONE_BY_ONE) add_dv(t, ss);
+            dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(QTs + col_at(t, ss)), dsf[ss], dk[t], 0, 0, 0);
           }
-        }
       }
     }
     head = next_head;

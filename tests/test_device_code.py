@@ -45,3 +45,30 @@ def test_lds_copies_wait_for_m0(code_object):
         before = instruction
     assert copies > 1000          # the pattern still finds the copies
     assert not bad
+
+
+# Vector registers a kernel may keep in scratch memory (a reload waits behind every copy in flight): the feature-map epilogue of the
+# W_Q projection, in the tiles that wide d_mem and large or irregular launches take.
+SPILLS = {
+    r"gemm_mfma_kernelILi128ELi128ELi4ELi2ELb1ELi5E": 31,      # faster than without: see the tile's comment
+    r"gemm_mfma_kernelILi256ELi256ELi4ELi4ELb0ELi5E": 141,
+}
+
+
+def kernel_resources(code_object):
+    """[(mangled name, vector registers, spilled vector registers)]"""
+    notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", code_object], check=True, capture_output=True, text=True).stdout
+    found = []
+    for kernel in notes.split("\n  - .a")[1:]:
+        name, spilled, registers = (re.search(rf"\.{key}:\s+(\S+)", kernel) for key in (r"symbol", "vgpr_spill_count", "vgpr_count"))
+        found.append((name.group(1), int(registers.group(1)), int(spilled.group(1))))
+    assert len(found) > 100
+    return found
+
+
+def test_register_spills(code_object):
+    over = {}
+    for name, _, spilled in kernel_resources(code_object):
+        if spilled > max((most for pattern, most in SPILLS.items() if re.search(pattern, name)), default=0):
+            over[name] = spilled
+    assert not over
