@@ -33,7 +33,7 @@ enum F32With {
 };
 
 // grid: (ceil(N / 32), ceil(M / (16 TM)), g); block: 256.
-// CH: chunks of 16 k per batch of loads; a wave's share should be a batch (K <= 128: 2) or several (4).
+// CH: chunks of 16 k per batch of loads; a wave's share should be a batch (K <= 128: 2) or several (4; 32-row tiles with the norm: 2).
 template <int TM, bool SWIGLU, int CH, F32With WITH>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s) {
   constexpr int TN = 2, NB = SWIGLU ? 2 : 1, BM = 16 * TM, BN = 16 * TN, LD = BN + 4;
@@ -338,10 +338,10 @@ inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, cons
   // the feature map is a chain of its own behind the product: the fewer rows per wave the better (32-row tiles 13.5 us per launch of 4 cells of 72 rows, 16-row tiles with the reductions of a wave's rows side by side 6.4)
   const bool narrow = s.M <= 16 || s.epi == EPI_DPFP_READ, brief = s.K <= 128;
   const dim3 grid((s.N + 31) / 32, (s.M + (narrow ? 15 : 31)) / (narrow ? 16 : 32), g);
-#define ARMT_F32(SW, WITH)                                                                                            \
-  (narrow ? (brief ? gemm_f32_kernel<1, SW, 2, WITH> : gemm_f32_kernel<1, SW, 4, WITH>)                                \
-          : (brief ? gemm_f32_kernel<2, SW, 2, WITH> : gemm_f32_kernel<2, SW, 4, WITH>))
-  auto kern = ARMT_F32(false, F32_PLAIN);
+#define ARMT_F32(SW)                                                                                                  \
+  (narrow ? (brief ? gemm_f32_kernel<1, SW, 2, F32_PLAIN> : gemm_f32_kernel<1, SW, 4, F32_PLAIN>)                      \
+          : (brief ? gemm_f32_kernel<2, SW, 2, F32_PLAIN> : gemm_f32_kernel<2, SW, 4, F32_PLAIN>))
+  auto kern = ARMT_F32(false);
   if (s.epi == EPI_DPFP_READ) {
     if (s.N != s.n0 || s.N > 32 || s.ldr < 1 || 2 * s.ldr * s.n0 > 512 || s.ldc < 2 * s.ldr * s.n0) return hipErrorInvalidValue;
     kern = brief ? gemm_f32_kernel<1, false, 2, F32_DPFP> : gemm_f32_kernel<1, false, 4, F32_DPFP>;
@@ -350,9 +350,16 @@ inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, cons
     kern = brief ? gemm_f32_kernel<1, false, 2, F32_UPDATE> : gemm_f32_kernel<1, false, 4, F32_UPDATE>;
   } else if (s.norm) {
     if (s.epi == EPI_QKV_ROPE && s.ldr != 8 && s.ldr != 16 && s.ldr != 32) return hipErrorInvalidValue;
-    kern = s.epi == EPI_SWIGLU ? ARMT_F32(true, F32_NORM) : ARMT_F32(false, F32_NORM);
+    // Batches of two chunks also for a long K in 32-row tiles: with four, the gain's registers leave gate/up one wave per SIMD (280 registers; 167
+    // here) and QKV two (240; 144 and three).  Same order of every sum.  us per launch, d_ff 4 d, four / two (norm in a launch of its own):
+    // gate/up 4 x (1040 x 512) 359 / 211 (304), 1 x (272 x 512) 33.7 / 24.7 (31.0), 4 x (72 x 1024) 118 / 78 (128), 4 x (1040 x 2048) 4327 / 3082 (4746);
+    // QKV 4 x (1040 x 512) 93.8 / 78.6 (99.7), 4 x (1040 x 2048) 1285 / 1198 (1497)
+    if (s.epi == EPI_SWIGLU)
+      kern = !narrow ? gemm_f32_kernel<2, true, 2, F32_NORM> : brief ? gemm_f32_kernel<1, true, 2, F32_NORM> : gemm_f32_kernel<1, true, 4, F32_NORM>;
+    else
+      kern = !narrow ? gemm_f32_kernel<2, false, 2, F32_NORM> : brief ? gemm_f32_kernel<1, false, 2, F32_NORM> : gemm_f32_kernel<1, false, 4, F32_NORM>;
   } else if (s.epi == EPI_SWIGLU) {
-    kern = ARMT_F32(true, F32_PLAIN);
+    kern = ARMT_F32(true);
   }
 #undef ARMT_F32
   kern<<<grid, 256, 0, st>>>(table, first, s);

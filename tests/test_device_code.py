@@ -72,3 +72,13 @@ def test_register_spills(code_object):
         if spilled > max((most for pattern, most in SPILLS.items() if re.search(pattern, name)), default=0):
             over[name] = spilled
     assert not over
+
+
+# 256 threads without an LDS use that would limit them: a second wave on every SIMD is what hides the first one's loads.
+TWO_WAVES = r"gemm_f32_kernel"
+
+
+def test_registers_leave_two_waves(code_object):
+    found = {name: registers for name, registers, _ in kernel_resources(code_object) if re.search(TWO_WAVES, name)}
+    assert len(found) > 10
+    assert not {name: registers for name, registers in found.items() if registers > 256}
