@@ -335,8 +335,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroup* __restri
 
 inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, const GemmShape& s, hipStream_t st) {
   if (g <= 0 || s.M <= 0 || s.N <= 0) return hipSuccess;
-  // the feature map is a chain of its own behind the product: the fewer rows per wave the better (32-row tiles 13.5 us per launch of 4 cells of 72 rows, 16-row tiles with the reductions of a wave's rows side by side 6.4)
-  const bool narrow = s.M <= 16 || s.epi == EPI_DPFP_READ, brief = s.K <= 128;
+  // The feature map is a chain of its own behind the product: the fewer rows per wave the better (4 cells of 72 rows, K 128: 32-row tiles 7.6 us
+  // per launch, 16-row tiles with the reductions of a wave's rows side by side 4.9), until a long product on more 16-row tiles than CUs costs more.
+  // us per launch of 4 cells, 16 / 32 rows: 1040 rows, K 512 11.3 / 13.1, 1024 18.0 / 18.6, 2048 29.9 / 25.7, 3072 41.8 / 32.7;
+  // 4112 rows, K 2048 68.5 / 65.7; one cell of 1040 rows, K 2048 (65 tiles) 16.6 / 24.6.  Either tile gives the same bits.
+  const bool read16 = s.epi == EPI_DPFP_READ && !(s.K > 1024 && (int64_t)g * ((s.M + 15) / 16) > 256);
+  const bool narrow = s.M <= 16 || read16, brief = s.K <= 128;
   const dim3 grid((s.N + 31) / 32, (s.M + (narrow ? 15 : 31)) / (narrow ? 16 : 32), g);
 #define ARMT_F32(SW)                                                                                                  \
   (narrow ? (brief ? gemm_f32_kernel<1, SW, 2, F32_PLAIN> : gemm_f32_kernel<1, SW, 4, F32_PLAIN>)                      \
@@ -344,7 +348,7 @@ inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, cons
   auto kern = ARMT_F32(false);
   if (s.epi == EPI_DPFP_READ) {
     if (s.N != s.n0 || s.N > 32 || s.ldr < 1 || 2 * s.ldr * s.n0 > 512 || s.ldc < 2 * s.ldr * s.n0) return hipErrorInvalidValue;
-    kern = brief ? gemm_f32_kernel<1, false, 2, F32_DPFP> : gemm_f32_kernel<1, false, 4, F32_DPFP>;
+    kern = !narrow ? gemm_f32_kernel<2, false, 4, F32_DPFP> : brief ? gemm_f32_kernel<1, false, 2, F32_DPFP> : gemm_f32_kernel<1, false, 4, F32_DPFP>;
   } else if (s.epi == EPI_UPDATE_F32) {
     if (!narrow || s.n0 > 32 || s.nu < 1 || 2 * s.nu * s.n0 > 512) return hipErrorInvalidValue;
     kern = brief ? gemm_f32_kernel<1, false, 2, F32_UPDATE> : gemm_f32_kernel<1, false, 4, F32_UPDATE>;
