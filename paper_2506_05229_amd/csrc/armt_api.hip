@@ -145,9 +145,9 @@ struct Ctx {
   const LayerAux* aux;       // device: [L]
   GemmShape shape[K_COUNT];
   bool fused_norm;           // bf16 MFMA path: RMSNorm folded into the GEMM epilogues around it
-  bool fused_rope;           // bf16 MFMA path: rotary embedding applied by the QKV GEMM epilogue
+  bool fused_rope;           // rotary embedding applied by the QKV GEMM epilogue (fp32: together with the norm)
   bool fused_vt;             // ... which also writes V transposed
-  bool fused_dpfp;           // bf16 MFMA path: feature map and denominator of the read in the epilogue of the W_Q projection
+  bool fused_dpfp;           // feature map and denominator of the read in the epilogue of the W_Q projection
   bool fused_prep;           // fp32: EPI_UPDATE_F32 where a whole step is run
   int ssq_parts;             // partial sums of squares per row written by the GEMMs that produce a normalised row
   float* tape = nullptr;     // training forward: per-cell records of what the backward pass cannot recompute

@@ -364,6 +364,8 @@ inline hipError_t launch_gemm_f32(const GemmGroup* table, int first, int g, cons
       kern = !narrow ? gemm_f32_kernel<2, false, 2, F32_NORM> : brief ? gemm_f32_kernel<1, false, 2, F32_NORM> : gemm_f32_kernel<1, false, 4, F32_NORM>;
   } else if (s.epi == EPI_SWIGLU) {
     kern = ARMT_F32(true);
+  } else if (s.epi == EPI_QKV_ROPE) {
+    return hipErrorInvalidValue;         // only the kernel with the norm rotates
   }
 #undef ARMT_F32
   kern<<<grid, 256, 0, st>>>(table, first, s);

@@ -82,3 +82,26 @@ def test_registers_leave_two_waves(code_object):
     found = {name: registers for name, registers, _ in kernel_resources(code_object) if re.search(TWO_WAVES, name)}
     assert len(found) > 10
     assert not {name: registers for name, registers in found.items() if registers > 256}
+
+
+REFUSALS = r"""
+#include <cstdio>
+#include "gemm_f32.h"
+using namespace armt;
+int main() {
+  GemmShape s{};
+  s.M = 72; s.N = 256; s.K = s.lda = s.ldb = 128; s.ldc = 256; s.n0 = 128; s.n1 = 64; s.ldr = 32; s.epi = EPI_QKV_ROPE;
+  std::printf("%d", launch_gemm_f32(nullptr, 0, 0, s, nullptr) == hipSuccess);      // no groups: nothing to do, nothing to refuse
+  return launch_gemm_f32(nullptr, 0, 1, s, nullptr) == hipErrorInvalidValue ? 0 : 1;
+}
+"""
+
+
+def test_f32_rotation_needs_the_norm(tmp_path):
+    """The plain fp32 product does not rotate: a shape that asks for it is refused on the host.  (Run without a GPU: nothing can be launched.)"""
+    from paper_2506_05229_amd.build import CSRC
+    (tmp_path / "refusals.hip").write_text(REFUSALS)
+    flags = ["-O1", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", f"-I{CSRC}"]
+    subprocess.run(["/opt/rocm/bin/hipcc", *flags, "-o", tmp_path / "refusals", tmp_path / "refusals.hip"], check=True, capture_output=True)
+    ran = subprocess.run([tmp_path / "refusals"], env={**os.environ, "HIP_VISIBLE_DEVICES": "-1"}, capture_output=True, text=True)
+    assert ran.returncode == 0 and ran.stdout == "1"
