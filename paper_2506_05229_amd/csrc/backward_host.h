@@ -406,7 +406,7 @@ armt_status colsum(const BCtx& c, const T* a, const float* b, size_t b_cell, con
 }
 
 // Backward of norm `which` (n = x rstd gain) of the cells [lo, lo + g): dout (and doutb) = din + the gradient through the norm, and the
-// gradient of the gain into dg.  One pass where a lane can hold its columns of a row (d a multiple of 4, at most 4096), else two.
+// gradient of the gain into dg.  One pass where a thread can hold its columns of a few rows (d a multiple of 4, at most 4096), else two.
 template <typename T>
 armt_status norm_backward(const BCtx& c, int lo, int g, int which, const float* x, const float* rstd, const float* din, float* dout,
                           T* doutb, float* const* dg) {
@@ -420,11 +420,11 @@ armt_status norm_backward(const BCtx& c, int lo, int g, int which, const float* 
     return ARMT_OK;
   }
   float* part = c.at<float>(c.o.CPart);
-  const int nc = (D.d + 255) / 256;
-  auto kern = nc <= 1 ? rmsnorm_bwd_cols_kernel<T, 1> : nc <= 2 ? rmsnorm_bwd_cols_kernel<T, 2> : nc <= 4 ? rmsnorm_bwd_cols_kernel<T, 4>
-            : nc <= 8 ? rmsnorm_bwd_cols_kernel<T, 8> : nc <= 12 ? rmsnorm_bwd_cols_kernel<T, 12> : rmsnorm_bwd_cols_kernel<T, 16>;
-  kern<<<dim3(NORM_CHUNKS, g), 256, 0, c.st>>>(dn, x, cell, c.aux, lo, which, rstd, din, cell, dout, cell, doutb, part, D.T, D.d);
-  colsum_finish_kernel<<<dim3((D.d + 255) / 256, g / D.B), 256, 0, c.st>>>(part, NORM_CHUNKS, dg, nullptr, lo, D.d, D.B);
+  const int chunks = norm_chunks(D.T), threads = D.d < 1024 ? round64((D.d + 3) / 4) : 256;
+  auto kern = D.d <= 1024 ? rmsnorm_bwd_cols_kernel<T, 1, 4> : D.d <= 2048 ? rmsnorm_bwd_cols_kernel<T, 2, 2>
+            : D.d <= 3072 ? rmsnorm_bwd_cols_kernel<T, 3, 2> : rmsnorm_bwd_cols_kernel<T, 4, 2>;
+  kern<<<dim3(chunks, g), threads, 0, c.st>>>(dn, x, cell, c.aux, lo, which, rstd, din, cell, dout, cell, doutb, part, D.T, D.d);
+  colsum_finish_kernel<<<dim3((D.d + 255) / 256, g / D.B), 256, 0, c.st>>>(part, chunks, dg, nullptr, lo, D.d, D.B);
   HIP_TRY(hipGetLastError());
   return ARMT_OK;
 }

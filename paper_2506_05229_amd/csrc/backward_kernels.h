@@ -220,86 +220,104 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
 }
 
 // rmsnorm_bwd_kernel and the gradient of the gain in one pass over dN and X (the pass is bound by memory, and the column sums over the rows
-// read both of them again): part[cell][chunk][c] = sum_{i in chunk} rstd[i] dN[i, c] X[i, c], for colsum_finish_kernel.  A wave takes
-// whole rows, NC times four columns per lane, so that a row needs no barrier and a column's sum stays in a register; the four waves' sums are
-// added in wave order at the end.  NORM_CHUNKS blocks per cell: 4 to 5 rows of 1040 per wave, enough waves for the memory from one cell on.
-// 1B shape, mean of 5.6 cells: 43 (rmsnorm_bwd_kernel) + 34 (colsum_partial_kernel) -> 48 us.
-// d a multiple of 4, at most 256 NC.  grid: (NORM_CHUNKS, g), block: 256.
-constexpr int NORM_CHUNKS = 64;
-template <typename T, int NC>
+// read both of them again): part[cell][chunk][c] = sum_{i in chunk} rstd[i] dN[i, c] X[i, c], for colsum_finish_kernel.  A chunk is a block,
+// whose threads share a row, R rows at a time: a thread holds the gain, the sums and R rows of its 4 NB columns only, so that 3 to 7 waves fit on a
+// SIMD, and one barrier serves R rows.  (A wave per row held 4 d / 64 registers of each: one wave per SIMD from d 2048 on, and slower than two
+// passes for few rows and at d 4096.)  us with the finish, 1040 rows, two passes / wave per row / here: d 768 1 cell 16.2 / 12.2 / 12.3,
+// 5 cells 37.3 / 19.5 / 19.3; d 2048 1 cell 32.1 / 22.6 / 17.9, 5 cells 59.1 / 47.5 / 33.8, 16 cells 171 / 133 / 122; d 3072 1 cell 37.1 / 34.2 / 22.3,
+// 5 cells 81.2 / 76.8 / 54.9; d 4096 1 cell 42.6 / 53.7 / 25.2, 5 cells 116 / 150 / 79; one cell of 272 rows, d 3072 13.3 / 18.4 / 12.4.
+// d a multiple of 4, at most 1024 NB.  grid: (chunks, g), block: 256, or with d < 1024 the multiple of 64 that holds d / 4.
+// 128 chunks of a cell's rows (9 rows of 1040), fewer below 512 and 128 rows, where empty chunks and the finish cost more than the blocks bring
+// (us with 32 / 64 / 128: 1 cell of 1040 rows, d 2048 35.9 / 23.3 / 17.9; 8 cells of 272 rows, d 2048 18.8 / 17.9 / 20.1; 4 cells of 72 rows, d 128, fp32
+// 5.7 / 6.3 / 7.3).  By the rows alone: a cell's sums may not depend on the cells beside it.
+constexpr int NORM_CHUNKS = 128;
+inline int norm_chunks(int Trows) { return Trows >= 512 ? NORM_CHUNKS : Trows >= 128 ? 64 : 32; }
+template <typename T, int NB, int R>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_cols_kernel(const T* __restrict__ dN, const float* __restrict__ X, size_t x_cell,
                                                                const LayerAux* __restrict__ aux, int first, int which,
                                                                const float* __restrict__ rstd_all, const float* __restrict__ din,
                                                                size_t din_cell, float* __restrict__ dout, size_t dout_cell,
                                                                T* __restrict__ doutb, float* __restrict__ part, int Trows, int d) {
   typedef T T4 __attribute__((ext_vector_type(4)));
-  __shared__ __align__(16) float acc[256 * NC];
-  const int l = first + blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __shared__ float red[2][R][4];             // the waves' sums of R rows; the other half while a wave may still read this one
+  const int l = first + blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int c0 = 4 * threadIdx.x, step = 4 * blockDim.x;
   const T* gain = (const T*)(which == 0 ? aux[l].rms1 : aux[l].rms2);
-  const int per = (Trows + NORM_CHUNKS - 1) / NORM_CHUNKS;
+  const int per = (Trows + gridDim.x - 1) / gridDim.x;
   const int i0 = blockIdx.x * per, i1 = min(Trows, i0 + per);
-  f32x4 gn[NC], cs[NC];
+  f32x4 gn[NB], cs[NB];
 #pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = 4 * (lane + 64 * k);
+  for (int k = 0; k < NB; ++k)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      gn[k][e] = c < d ? to_f32(gain[c + e]) : 0.f;     // (a caller's weight: may start anywhere)
+      gn[k][e] = c0 + k * step < d ? to_f32(gain[c0 + k * step + e]) : 0.f;     // (a caller's weight: may start anywhere)
       cs[k][e] = 0.f;
     }
-  }
-  for (int i = i0 + w; i < i1; i += 4) {
-    const T* dn = dN + ((size_t)l * Trows + i) * d;
-    const float* x = X + (size_t)l * x_cell + (size_t)i * d;
-    const float* di = din + (size_t)l * din_cell + (size_t)i * d;
-    float* dout_r = dout + (size_t)l * dout_cell + (size_t)i * d;
-    const float rstd = rstd_all[(size_t)l * Trows + i];
-    f32x4 xv[NC], dv[NC], iv[NC];
+  int half = 0;
+  for (int i = i0; i < i1; i += R, half ^= 1) {
+    f32x4 xv[R][NB], iv[R][NB];
+    T4 t[R][NB];
+    float rstd[R], s[R] = {};
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int c = 4 * (lane + 64 * k), at = min(c, d - 4);
-      const T4 t = *(const T4*)(dn + at);
-      xv[k] = *(const f32x4*)(x + at);
-      iv[k] = *(const f32x4*)(di + at);
+    for (int r = 0; r < R; ++r) {
+      const int row = min(i + r, i1 - 1);
+      const size_t at_row = (size_t)row * d;
+      rstd[r] = rstd_all[(size_t)l * Trows + row];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) dv[k][e] = c < d ? to_f32(t[e]) : 0.f;
-    }
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < NC; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        cs[k][e] = fmaf(dv[k][e] * xv[k][e], rstd, cs[k][e]);
-        dv[k][e] *= gn[k][e];
-        s = fmaf(dv[k][e], xv[k][e], s);
-      }
-    const float f = rstd * rstd * (wave_sum(s) / (float)d);
-#pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int c = 4 * (lane + 64 * k);
-      if (c >= d) continue;
-      f32x4 v;
-      T4 b;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = iv[k][e] + rstd * (dv[k][e] - xv[k][e] * f);
-        b[e] = from_f32<T>(v[e]);
-      }
-      *(f32x4*)(dout_r + c) = v;
-      if (doutb) *(T4*)(doutb + ((size_t)l * Trows + i) * d + c) = b;
-    }
-  }
-  for (int ww = 0; ww < 4; ++ww) {
-    if (w == ww) {
-#pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        f32x4* a = (f32x4*)(acc + 4 * (lane + 64 * k));
-        *a = ww ? *a + cs[k] : cs[k];
+      for (int k = 0; k < NB; ++k) {
+        const int at = min(c0 + k * step, d - 4);
+        t[r][k] = *(const T4*)(dN + (size_t)l * Trows * d + at_row + at);
+        xv[r][k] = *(const f32x4*)(X + (size_t)l * x_cell + at_row + at);
+        iv[r][k] = *(const f32x4*)(din + (size_t)l * din_cell + at_row + at);
       }
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (i + r >= i1) break;                // the last rows of a chunk: block-uniform
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float dn = c0 + k * step < d ? to_f32(t[r][k][e]) : 0.f;
+          cs[k][e] = fmaf(dn * xv[r][k][e], rstd[r], cs[k][e]);
+          s[r] = fmaf(dn * gn[k][e], xv[r][k][e], s[r]);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int r = 0; r < R; ++r) s[r] += __shfl_xor(s[r], o, kWave);
+    if (lane == 0)
+#pragma unroll
+      for (int r = 0; r < R; ++r) red[half][r][w] = s[r];
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (i + r >= i1) break;
+      float sum = red[half][r][0];
+      for (int v = 1; v < nw; ++v) sum += red[half][r][v];
+      const float f = rstd[r] * rstd[r] * (sum / (float)d);
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        const int c = c0 + k * step;
+        if (c >= d) continue;
+        f32x4 v;
+        T4 b;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = iv[r][k][e] + rstd[r] * (to_f32(t[r][k][e]) * gn[k][e] - xv[r][k][e] * f);
+          b[e] = from_f32<T>(v[e]);
+        }
+        *(f32x4*)(dout + (size_t)l * dout_cell + (size_t)(i + r) * d + c) = v;
+        if (doutb) *(T4*)(doutb + ((size_t)l * Trows + i + r) * d + c) = b;
+      }
+    }
   }
-  for (int c = threadIdx.x; c < d; c += 256) part[((size_t)l * NORM_CHUNKS + blockIdx.x) * d + c] = acc[c];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    const int c = c0 + k * step;
+    if (c < d) *(f32x4*)(part + ((size_t)l * gridDim.x + blockIdx.x) * d + c) = cs[k];
+  }
 }
 
 // Column sums over the T rows of a cell, in two deterministic stages.  Stage 1: the rows are cut into gridDim.z

@@ -75,7 +75,7 @@ def test_register_spills(code_object):
 
 
 # 256 threads without an LDS use that would limit them: a second wave on every SIMD is what hides the first one's loads.
-TWO_WAVES = r"gemm_f32_kernel"
+TWO_WAVES = r"gemm_f32_kernel|rmsnorm_bwd_cols_kernel"
 
 
 def test_registers_leave_two_waves(code_object):

@@ -7,7 +7,7 @@ import torch
 import armt_synth as S
 from gpu_util import make_problem, rel_fro
 from oracle import armt_oracle_grad as G
-from test_gpu_backward import F32_REL, compare, run_hip_grad, upstream
+from test_gpu_backward import BF16_REL, BF16_REL_MEM, F32_REL, compare, run_hip_grad, upstream
 from test_gpu_token_ends import _ends
 
 pytestmark = pytest.mark.gpu
@@ -21,6 +21,19 @@ def test_norm_backward_widths(heads, dh):
     layers, mem_emb, x = make_problem(shape, seed=5, std=0.02, gain_std=0.1, v_scale=64.0)
     Gs = upstream(shape, 5, with_state=False)
     compare(run_hip_grad(shape, layers, mem_emb, x, Gs, None, True), G.armt_grad(shape, layers, mem_emb, x, *Gs), F32_REL, f"width {d}")
+
+
+@pytest.mark.parametrize("heads,dh,seg_len", [(12, 64, 520), (24, 128, 128), (32, 128, 112)])
+def test_norm_backward_widths_bf16(heads, dh, seg_len):
+    """d 768, 3072 and 4096; rows of a chunk that fill and miss the rows a block takes at once (5 of 4, 3 and 2 of 2).  One segment and no gradient into
+    the state: random keys of these widths drive gamma of the update through zero, where bf16 sets no bound to the gradient of W_K (1.6e-1 at
+    d 768; see test_gpu_backward.py), and the norms are what is compared here."""
+    shape = S.get_shape("tiny").replace(dtype="bf16", n_layers=2, d_model=heads * dh, n_heads=heads, n_kv_heads=heads // 4, head_dim=dh, d_ff=64,
+                                        seg_len=seg_len, n_mem=16, d_mem=32, n_tokens=seg_len)
+    layers, mem_emb, x = make_problem(shape, seed=6, std=0.02, gain_std=0.1)
+    Gs = upstream(shape, 6, with_state=False)
+    compare(run_hip_grad(shape, layers, mem_emb, x, Gs, None, True), G.armt_grad(shape, layers, mem_emb, x, *Gs), BF16_REL,
+            f"bf16 width {heads * dh}", tol_mem=BF16_REL_MEM)
 
 
 @pytest.mark.parametrize("rows", [1, 63, 65])
