@@ -495,8 +495,9 @@ inline hipError_t launch_attention_bwd_mfma(const bf16* QKV, const bf16* O, cons
   const int lds_q = 2 * 3 * (64 * dh * 2), lds_kv = 2 * (4 * 64 * dh * 2 + 512);
   auto dq = dh == 64 ? attention_bwd_dq_kernel<64> : attention_bwd_dq_kernel<128>;
   auto dkv = dh == 64 ? attention_bwd_dkv_kernel<64> : attention_bwd_dkv_kernel<128>;
-  e = hipFuncSetAttribute((const void*)dq, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dkv, hipFuncAttributeMaxDynamicSharedMemorySize, lds_kv);
+  static std::atomic<uint64_t> dq_raised[2], dkv_raised[2];      // head_dim 64, 128
+  e = raise_lds_limit((const void*)dq, lds_q, dq_raised[dh != 64]);
+  if (e == hipSuccess) e = raise_lds_limit((const void*)dkv, lds_kv, dkv_raised[dh != 64]);
   if (e != hipSuccess) return e;
   dq<<<grid, nq * group * 64, lds_q, st>>>(QKV, Kt, dO, LSE2, Dv, dQKV, first, Trows, Tp, H, Hkv, nq, scale, nqt, npairs);
   dkv<<<gkv, 64 * DKV_WAVES, lds_kv, st>>>(QKV, Qt, dO, Gt, LSE2, Dv, dQKV, first, Trows, Tp, H, Hkv, scale, npairs);

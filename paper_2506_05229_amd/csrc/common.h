@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace armt {
 
 typedef __bf16 bf16;
@@ -40,6 +42,19 @@ __device__ __forceinline__ void lds_copy16(const char* base, unsigned voff, unsi
 }
 __device__ __forceinline__ void lds_copy16(const char* src, unsigned lds) {                     // from one 64-bit pointer per lane
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds) : "memory", "m0");
+}
+
+// Raises the dynamic-LDS limit of a kernel, a per-function, per-device, idempotent setting: done once per device (a second thread that gets
+// here first merely repeats it).  done: one word per kernel and limit.
+inline hipError_t raise_lds_limit(const void* kern, int bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
 }
 
 // Sum over the threads of a block (blockDim.x a multiple of 64, at most 1024); every thread gets it.

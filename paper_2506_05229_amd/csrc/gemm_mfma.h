@@ -957,18 +957,9 @@ inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, Gem
   s.spread = s.spread && rng.unit_cols == 0 && tiles_m * tiles_n % 8 == 0;
   const int grid = ((total + 7) / 8) * 8;
   auto kern = gemm_mfma_kernel<BM, BN, WGM, WGN, REG, EPI, TAIL, NS>;
-  // raising the dynamic-LDS limit is a per-function, per-device, idempotent setting: done once per device (a second
-  // thread that gets here first merely repeats it)
-  static std::atomic<uint64_t> attr_set{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  static std::atomic<uint64_t> lds_raised{0};
+  const hipError_t e = raise_lds_limit((const void*)kern, LDS, lds_raised);
   if (e != hipSuccess) return e;
-  const uint64_t bit = 1ull << (dev & 63);
-  if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return e;
-    attr_set.fetch_or(bit, std::memory_order_release);
-  }
 #ifdef ARMT_GEMM_TIMELINE
   if (s.tag == g_tl_kind && g_tl_countdown >= 0 && g_tl_countdown-- == 0) {
     GemmShape s_tl = s;
