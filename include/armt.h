@@ -337,7 +337,8 @@ armt_status armt_lm_head_static(const armt_config *cfg, const void *hidden, int6
  * 2: 64x128, 4 waves; 3: 64x64, 4 waves, for the plain fp32 store only, and 4: 32x128, 4 waves, for the feature-map
  * epilogue of the W_Q projection only (other epilogues run 2 instead);
  * 5: 256x256, 8 waves with a pipelined main loop where the shape lets its copies be addressed by scalar base + lane offset, else 16
- * waves; 6: as 1 with copies addressed that way where the shape allows; 7: 64x128, 4 waves, and 8: 128x128, 8 waves, four k-tiles in LDS,
+ * waves; 6: 128x128, 8 waves with copies addressed that way where the shape allows, else as 1; 7: 64x128, 8 waves (SwiGLU 4), and
+ * 8: 128x128, 16 waves (SwiGLU and irregular shapes 8), four k-tiles in LDS,
  * for launches of at most one workgroup per CU; anything else below 100: choose by shape and tile count, the default).  config = 100 *
  * switches + tile configuration (or + 99 for the default choice) additionally turns fusions off, for A/B timing:
  * switch 16 the feature map of the read in the epilogue of the W_Q projection, 32 the strip of memory rows in the last
@@ -350,7 +351,8 @@ int32_t armt_set_gemm_tile_config(int32_t config);
  * kernel kind of the step (up to max_launches of them) made by this process is bracketed by a pair of
  * HIP events on the launch stream.  gemm_kind: 0 W_Q projection of the read, 1 read A phi, 2 QKV,
  * 3 attention output, 4 gate/up with SwiGLU, 5 down, 6 W_K / W_V projections of the update (the grouped GEMMs);
- * 7 feature map + denominator of the read, 8 feature map + coefficients of the update, 9 the delta rule's pass over A,
+ * 7 feature map + denominator of the read, 8 feature map + coefficients of the update (both only where they are launches of
+ * their own and not the epilogue of their projection), 9 the delta rule's pass over A,
  * 10 segment attention.
  * armt_profile_end waits for the recorded events and returns the summed kernel time in milliseconds,
  * the number of launches timed and the number of groups (cells) they covered; any pointer may be NULL.

@@ -1070,7 +1070,10 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
     case 6:   // as 1, copies addressed by scalar base + lane offset where the shape allows
       // Eight waves of 32 x 64 instead of four of 64 x 64: two workgroups of four waves leave a SIMD two waves, which wait for their
       // fragments together.  us per launch, four / eight: attention output and down of the 768-wide model (mean of its launches)
-      // 49.5 / 44.3, QKV 25.0 / 21.6, gate/up of one cell 20.3 / 18.7; down of two and three cells of d 2048 109.6 / 104.0
+      // 49.5 / 44.3, QKV 25.0 / 21.6, gate/up of one cell 20.3 / 18.7; down of two and three cells of d 2048 109.6 / 104.0.
+      // The feature map of d_mem 128 too, though eight waves keep 31 registers of it in scratch memory (3 without the strip): 64 cells of 1040 rows,
+      // K 2048 130.3 / 117.0, 84 of K 3072 222.8 / 205.7, 16 of 4224 rows 157.1 / 143.2, 96 of K 768 106.5 / 104.3.
+      // Irregular shapes keep four waves: only few launches of a model come here (timed: feature map of d_mem 96, 64 cells, K 2048 125.5 / 114.4).
       if (mfma_regular_shape<128, 128, EPI>(s)) return launch_mfma_cfg<128, 128, 4, 2, EPI, true>(table, first, g, s, st);
       return launch_mfma_cfg<128, 128, 2, 2, EPI>(table, first, g, s, st);
     case 7:   // at most one workgroup per CU: nobody else fills the waits for a copy, so four k-tiles in LDS
