@@ -923,6 +923,7 @@ armt_status lm_head_backward_typed(const Dims& D, const HeadBwdLayout& h, const 
       last_r = r;
     }
     const int parts = head_parts(r, D.d, h.Vp);
+    su.k_min = h.Vp / 64 / parts;
     final_norm_train_kernel<T><<<r, 256, 0, st>>>(hs, (const T*)gain, D.d, D.rms_eps, Nn, rstd);
     const float* dl = d_logits + (size_t)r0 * vocab;
     if constexpr (std::is_same<T, bf16>::value)

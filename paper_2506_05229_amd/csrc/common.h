@@ -124,6 +124,7 @@ struct GemmShape {
   int ldb;              // row stride of the weight blocks in elements (>= K); the weights of the model are dense: ldb = K
   float fparam = 0.f;   // EPI_DPFP_READ: assoc_eps
   int k_slot = 0;       // steps of 64 per unit of GemmGroup::krange
+  int k_min = 0;        // fewest steps of 64 of a group with a range that has any (0: k_slot)
   int norm = 0;         // fp32 only (EPI_STORE_ACT, EPI_QKV_ROPE, EPI_SWIGLU): A is multiplied by `gain` column by column and the result rows
                         // by 1 / sqrt(mean of the row's squares + fparam): RMSNorm of A inside the product
   int nu = 0;           // EPI_UPDATE_F32: order of the feature map

@@ -13,7 +13,7 @@
 // global-to-LDS loads (no staging registers): the copies of k-tile i+1 are in flight while k-tile i
 // is multiplied.  For regular shapes (template flag REG) the copies are addressed by a scalar base
 // and one lane offset per operand, so that issuing them needs no vector-ALU instruction.
-// The 256 x 256 tile of regular shapes (eight waves) has a main loop of its own that never drains the copies; see there.
+// The 256 x 256 tile of regular shapes is a kernel of its own (gemm_tile256.h).
 // The 1-D grid is laid out so that each XCD (workgroup id mod 8) owns a contiguous run of the
 // group-major tile sequence: with 16 groups every XCD streams the weights of 2 layers through its
 // own L2, and the M-tiles sharing a weight panel run back to back.
@@ -66,19 +66,18 @@ inline int g_tl_kind = -2, g_tl_countdown = -1;      // host: the n-th next laun
 #define TL_STAMP(i) do {} while (0)
 #endif
 
-// The 256 x 256 tile with eight waves (2 x 4) runs the pipelined main loop: see the comment there.
-template <int BM, int WGM, int WGN>
-constexpr bool mfma_pipelined() { return BM == 256 && WGM == 2 && WGN == 4; }
-// rows of a staging tile of the epilogue: one 16-row block of every wave row, two of the pipelined tile's
-template <int BM, int WGM, int WGN>
-constexpr int mfma_stage_rows() { return mfma_pipelined<BM, WGM, WGN>() ? 64 : WGM * 16; }
+}  // namespace armt
+
+#include "gemm_tile256.h"
+
+namespace armt {
 
 // LDS bytes of the tile buffers of a configuration: NS buffers of a k-tile (A rows, B rows), and at least the two fp32
 // staging tiles [staged rows][tile columns + 4] of the epilogue, which reuse them.
 template <int BM, int BN, int WGM, int WGN, int EPI, bool TAIL, int NS>
 constexpr int mfma_tile_lds_bytes() {
   const int tiles = NS * ((TAIL ? BM + 16 : BM) + BN) * MF_ROW_BYTES;
-  const int stg = 2 * mfma_stage_rows<BM, WGM, WGN>() * (((EPI == EPI_SWIGLU) ? BN / 2 : BN) + 4) * 4;
+  const int stg = 2 * WGM * 16 * (((EPI == EPI_SWIGLU) ? BN / 2 : BN) + 4) * 4;
   return ((tiles > stg ? tiles : stg) + 255) / 256 * 256;
 }
 
@@ -90,8 +89,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
                                                                   GemmShape s, int tiles_m, int tiles_n, int m_group,
                                                                   int total_tiles, int tile_begin) {
   constexpr int NW = WGM * WGN, BK = MF_BK;
-  constexpr bool PIPE = mfma_pipelined<BM, WGM, WGN>();
-  static_assert(!PIPE || (REG && BN == 256 && NS == 2), "the pipelined loop is written for regular 256 x 256 tiles");
   constexpr int WROWS = BM / WGM, WCOLS = BN / WGN;       // wave tile
   constexpr int TM = WROWS / 16, TN = WCOLS / 16;         // 16x16 MFMA tiles per wave
   constexpr int ROWB = BK * 2;                            // bytes of a tile row
@@ -134,28 +131,19 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   const int grp = lid / per_group, rem = lid - grp * per_group;
   // M-tiles of one weight panel are adjacent; tall problems are cut into M-groups of m_group tiles (mfma_m_group).  (A division is a
   // few hundred cycles in front of the first copy of every tile: none for groups that a problem does not have.)
-  int mg0 = 0, rem_mg = rem, mg_tiles = tiles_m, last_tiles = tiles_m;      // first M-tile and M-tiles of the group, of the last one
+  int mg0 = 0, rem_mg = rem, mg_tiles = tiles_m;      // first M-tile and M-tiles of the group
   if (m_group < tiles_m) {
     const int mg = rem / (m_group * tiles_n);
     mg0 = mg * m_group;
     rem_mg = rem - mg0 * tiles_n;
     mg_tiles = min(m_group, tiles_m - mg0);
-    last_tiles = tiles_m - (tiles_m - 1) / m_group * m_group;
   }
   const int tn = rem_mg / mg_tiles, tm = mg0 + rem_mg - tn * mg_tiles;
   GemmGroup g = table[first + grp];
   if (!restrict_k<bf16>(g, s)) return;
   const int m0 = tm * BM, n0 = tn * BN_OUT;
   const int m0_strip = tiles_m * BM;                        // first row of the strip (TAIL)
-  // Who computes the strip of 16 rows behind the last M-tile: the last M-tile, or, pipelined, the last M-tiles of the last
-  // M-group, each on a share of the columns: unit u belongs to the M-tile u % strip_tiles from the end.  The units are the two
-  // halves of 128 columns (what a partial sum of squares and a head need), four interleaved ones for SwiGLU.  The strip still costs more
-  // than its 1.6 % of the products: 16 x (1040 x 16384, K 2048) takes 0.960 ms, 1024 rows 0.892 (tiles of unequal duration drift
-  // apart and then no longer find each other's operands in the L2).
-  const int strip_tiles = PIPE ? min(last_tiles, EPI == EPI_SWIGLU ? 4 : 2) : 1, from_end = tiles_m - 1 - tm;
-  const bool tail_blk = TAIL && from_end < strip_tiles;        // block-uniform
-  // u mod strip_tiles == from_end, for u < 4
-  auto my_unit = [&](int u) { return strip_tiles == 1 || u == from_end || u == from_end + strip_tiles; };
+  const bool tail_blk = TAIL && tm == tiles_m - 1;             // block-uniform: the last M-tile computes the strip behind it
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -166,27 +154,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     const int m = r < BM ? m0 + r : m0_strip + r - BM;
     return (g.rowscale && m < s.M) ? g.rowscale[m] : 1.f;
   };
-  // (pipelined: one row per thread, kept in a register until the last k-tile, so that the first copies do not wait for it)
-  float rs_mine = 1.f;
-  if (PIPE) {
-    if (tid < A_ROWS) rs_mine = row_scale_of(tid);
-  } else {
-    for (int r = tid; r < A_ROWS; r += NW * 64) rs_lds[r] = row_scale_of(r);
-  }
+  for (int r = tid; r < A_ROWS; r += NW * 64) rs_lds[r] = row_scale_of(r);
   const int wm = wave / WGN, wn = wave % WGN;
   const bool tail = tail_blk && wave < (TAIL ? BN / 32 : 0);   // wave-uniform: this wave computes part of the strip
-  // Which rows / columns of the tile a wave's 16 x 16 result blocks cover.  Pipelined tile: the tile is four quadrants of
-  // 128 x 128, a wave owns 64 x 32 of each (blocks i >> 2, j >> 1 select the quadrant); otherwise one WROWS x WCOLS patch.
-  auto blk_row = [&](int i) { return PIPE ? (i >> 2) * 128 + wm * 64 + (i & 3) * 16 : wm * WROWS + i * 16; };
-  // pipelined: which pair of its fragments of B a wave multiplies with the strip, -1 none.  Both fragments of the quadrant
-  // column 0 or 1 (one of the two waves of a SIMD is enough for a share; both if this M-tile has both halves), SwiGLU: the gate
-  // and the up fragment 0 or 1.  Chosen so that every product names its registers: no selects in front of the MFMAs.
-  int strip_sel = -1;
-  if (PIPE && tail_blk) {
-    if (EPI == EPI_SWIGLU) strip_sel = my_unit((wn + 2 * wm) & 3) ? wm : -1;
-    else strip_sel = strip_tiles == 1 ? wm : wm == 0 ? from_end : -1;
-  }
-  auto blk_col = [&](int j) { return PIPE ? (j >> 1) * 128 + wn * 32 + (j & 1) * 16 : wn * WCOLS + j * 16; };
+  // first row / column of the 16 x 16 result blocks of a wave
+  auto blk_row = [&](int i) { return wm * WROWS + i * 16; };
+  auto blk_col = [&](int j) { return wn * WCOLS + j * 16; };
 
   // ---- global -> LDS copies go straight to LDS (global_load_lds_dwordx4): one instruction moves 64 x 16
   // bytes into 1 KB of consecutive LDS = 8 tile rows.  Lane i fills row i / 8, physical chunk i % 8 of the
@@ -257,10 +230,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // scalar source of the first row of slab `slab` (REG only)
   auto a_base = [&](int slab) -> const char* { return (const char*)g.A + (size_t)(m0 + RPS * slab) * s.lda * 2; };
   auto b_base = [&](int slab) -> const char* {
-    if (EPI == EPI_SWIGLU && PIPE) {   // lower half of the tile rows from the gate, upper half from the up weight, same columns
-      const int row = slab * RPS;
-      return (const char*)(row >= 128 ? g.B1 : g.B0) + (size_t)(n0 + (row & 127)) * s.ldb * 2;
-    }
     if (EPI == EPI_SWIGLU) {   // tile rows 32 * blk ..: blk even from the gate, odd from the up weight, columns n0 + 32 * (blk / 2) ..
       const int row = slab * RPS, blk = row >> 5;
       const int n = n0 + (blk >> 1) * 32 + (row & 31);
@@ -309,9 +278,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // tiles whose B rows lie 32 apart, so that for SwiGLU tile 0 is the gate and tile 1 the up projection of the
   // same 16 output columns: B tile rows ((w / 2) * 2 + t) * 32 + (w % 2) * 16 + lane % 16.
   const int t_a = (BM + (lane & 15)) * ROWB;
-  const int t_brow = (PIPE ? wn * 32 + (EPI == EPI_SWIGLU ? wm * 16 : strip_sel * 128) : ((wave >> 1) * 2) * 32 + (wave & 1) * 16) +
-                     (lane & 15);                          // pipelined: column in the staging tile
-  constexpr int T_STEP = PIPE ? 16 : 32;                   // columns between the wave's two blocks of the strip
+  const int t_brow = ((wave >> 1) * 2) * 32 + (wave & 1) * 16 + (lane & 15);
+  constexpr int T_STEP = 32;                               // columns between the wave's two blocks of the strip
   const int t_b = t_brow * ROWB;
 
   f32x4 acc[TM][TN];
@@ -321,144 +289,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   f32x4 tacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 
-  if constexpr (PIPE) {
-    // Main loop of the 256 x 256 tile.  A k-tile of 64 is four half-tiles of 128 rows (A0, A1, B0, B1) and its products are
-    // four phases (A0 B0), (A0 B1), (A1 B1), (A1 B0) of 16 MFMAs per wave; while the MFMAs of a phase run, the wave reads the
-    // fragments of the next ones into registers.  A half-tile of the LDS is free again one phase after it was read, and the copy of
-    // the same half-tile two k-tiles on is issued right then, so five or six half-tiles (80 - 96 KB) are in flight at every
-    // barrier and the copy queue never drains, in the two buffers that a loop with one barrier per k-tile empties once
-    // per k-tile.  Eight waves of 128 x 64 also read a quarter less from LDS than sixteen of 64 x 64 (192 KB per k-tile
-    // instead of 256 KB).  Against sixteen waves and one barrier per k-tile: loop of 128 k-tiles (down projection) 404 -> 365 kcycles,
-    // of 32 (gate/up) 96.4 -> 91.4; one product of 8192^3 1.07 -> 1.24 PFLOP/s (1.38 with the M-groups of the tile order).  What is left:
-    // the same loop takes 0.74 of its time without the copies and 0.77 without the MFMAs (1024 x 16384 x 2048, 16 groups), and the
-    // clock is 1.96 GHz under both.
-    //   phase      reads                             copies (k-tile kt + 2)   landed by its end (read in the next phase)
-    //   1: A0 B0   B1(kt)                            A0, B0                   A1(kt)
-    //   2: A0 B1   A1(kt)                            B1                       A0(kt + 1), strip(kt)
-    //   3: A1 B1   half of A0(kt + 1), strip(kt)     A1                       B0(kt + 1)
-    //   4: A1 B0   rest of A0(kt + 1), B0(kt + 1)    strip                    B1(kt + 1)
-    // Copies complete in issue order, two per wave and half-tile, so "landed" is a count of younger copies outstanding (the
-    // waves that also copy the strip wait for a little more than they need).
-    const int nk = s.K / BK;
-    const char *sA[4], *sB[4];                         // sources of this wave's slabs wave + 8 j
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { sA[j] = a_base(wave + j * NW); sB[j] = b_base(wave + j * NW); }
-    const char* sT = (const char*)g.A + (size_t)(m0_strip + RPS * (wave & 1)) * s.lda * 2;
-    const bool extra = TAIL && tail_blk && wave < TAIL_SLABS;
-    auto copy_a = [&](int kt, int h) __attribute__((always_inline)) {
-      const unsigned at = lds0 + (kt & 1) * A_BYTES + wave * 1024;
-#pragma unroll
-      for (int j = 2 * h; j < 2 * h + 2; ++j) lds_copy16(sA[j] + (size_t)kt * ROWB, a_off0, at + j * NW * 1024);
-    };
-    auto copy_b = [&](int kt, int h) __attribute__((always_inline)) {
-      const unsigned at = lds0 + NS * A_BYTES + (kt & 1) * B_BYTES + wave * 1024;
-#pragma unroll
-      for (int j = 2 * h; j < 2 * h + 2; ++j) lds_copy16(sB[j] + (size_t)kt * ROWB, b_off0, at + j * NW * 1024);
-    };
-    auto copy_t = [&](int kt) __attribute__((always_inline)) {
-      if (TAIL && extra) lds_copy16(sT + (size_t)kt * ROWB, a_off0, lds0 + (kt & 1) * A_BYTES + BM * ROWB + wave * 1024);
-    };
-    bf16x8 a0[KS2][4], a1[KS2][4], b0[KS2][2], b1[KS2][2];
-    // fragment q of a half-tile: k-step q / 4 (A) or q / 2 (B)
-    auto read_a = [&](bf16x8 (&f)[KS2][4], int kt, int h, int q) __attribute__((always_inline)) {
-      const unsigned char* p = smem + (kt & 1) * A_BYTES + h * 128 * ROWB + a_frag;
-      f[q >> 2][q & 3] = *(const bf16x8*)(p + (q & 3) * 16 * ROWB + koff[q >> 2]);
-    };
-    auto read_b = [&](bf16x8 (&f)[KS2][2], int kt, int h, int q) __attribute__((always_inline)) {
-      const unsigned char* p = smem + NS * A_BYTES + (kt & 1) * B_BYTES + h * 128 * ROWB + b_frag;
-      f[q >> 1][q & 1] = *(const bf16x8*)(p + (q & 1) * 16 * ROWB + koff[q >> 1]);
-    };
-    // The 16 MFMAs of a phase with the copies behind the first and one of the next phase's `reads` fragment reads behind each of
-    // the following.  The order is pinned: left to itself the compiler moves the reads to the end of the phase, where
-    // everybody waits for them.
-    auto phase = [&](const bf16x8 (&a)[KS2][4], const bf16x8 (&b)[KS2][2], auto ha, auto hb, auto reads, auto read, auto copy)
-        __attribute__((always_inline)) {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        f32x4& c = acc[decltype(ha)::value * 4 + ((q >> 1) & 3)][decltype(hb)::value * 2 + (q & 1)];
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q >> 3][(q >> 1) & 3], b[q >> 3][q & 1], c, 0, 0, 0);
-        if (q == 0) copy();
-        else if (q <= decltype(reads)::value) read(q - 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    // end of a phase: this wave's fragment reads are complete (their half-tile may be overwritten after the barrier) and
-    // all but the N youngest copies have landed
-    auto phase_end = [&](auto n) __attribute__((always_inline)) {
-      constexpr int N = decltype(n)::value;
-      __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);      // vmcnt(N) lgkmcnt(0)
-      asm volatile("s_barrier" : : : "memory");
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    using H0 = std::integral_constant<int, 0>;
-    using H1 = std::integral_constant<int, 1>;
-    // k-tile kt with LEFT (at most 2) k-tiles behind it
-    auto k_tile = [&](int kt, auto left) __attribute__((always_inline)) {
-      constexpr int LEFT = decltype(left)::value;
-      // copies that may be outstanding at the ends of the phases
-      constexpr int W1 = LEFT == 2 ? 12 : LEFT == 1 ? 8 : 0, W2 = LEFT == 2 ? 12 : LEFT == 1 ? 6 : 0;
-      constexpr int W3 = LEFT == 2 ? 12 : LEFT == 1 ? 4 : 0, W4 = LEFT == 2 ? 10 : LEFT == 1 ? 2 : 0;
-      constexpr int RA = LEFT ? 4 : 0, RT = TAIL ? KS2 : 0;      // fragments of half of A0(kt + 1), of the strip
-      using std::integral_constant;
-      phase(a0, b0, H0{}, H0{}, integral_constant<int, 4>{}, [&](int q) { read_b(b1, kt, 1, q); },
-            [&] { if (LEFT == 2) { copy_a(kt + 2, 0); copy_b(kt + 2, 0); } });
-      phase_end(integral_constant<int, W1>{});
-      if (LEFT == 0 && tid < A_ROWS) rs_lds[tid] = rs_mine;
-      phase(a0, b1, H0{}, H1{}, integral_constant<int, 8>{}, [&](int q) { read_a(a1, kt, 1, q); },
-            [&] { if (LEFT == 2) copy_b(kt + 2, 1); });
-      phase_end(integral_constant<int, W2>{});
-      bf16x8 ta[KS2];                                  // rows of the strip (read in every tile of the variant: no branch here)
-      phase(a1, b1, H1{}, H1{}, integral_constant<int, RA + RT>{}, [&](int q) {
-        if (q < RT) ta[q] = *(const bf16x8*)(smem + (kt & 1) * A_BYTES + t_a + koff[q]);
-        else read_a(a0, kt + 1, 0, q - RT);
-      }, [&] { if (LEFT == 2) copy_a(kt + 2, 1); });
-      phase_end(integral_constant<int, W3>{});
-      if (TAIL) {
-        auto strip = [&](const bf16x8& p0, const bf16x8& p1, const bf16x8& q0, const bf16x8& q1) __attribute__((always_inline)) {
-          tacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta[0], p0, tacc[0], 0, 0, 0);
-          tacc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta[0], q0, tacc[1], 0, 0, 0);
-          tacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta[1], p1, tacc[0], 0, 0, 0);
-          tacc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta[1], q1, tacc[1], 0, 0, 0);
-        };
-        if (EPI == EPI_SWIGLU) {
-          if (strip_sel == 0) strip(b0[0][0], b0[1][0], b1[0][0], b1[1][0]);
-          else if (strip_sel == 1) strip(b0[0][1], b0[1][1], b1[0][1], b1[1][1]);
-        } else {
-          if (strip_sel == 0) strip(b0[0][0], b0[1][0], b0[0][1], b0[1][1]);
-          else if (strip_sel == 1) strip(b1[0][0], b1[1][0], b1[0][1], b1[1][1]);
-        }
-      }
-      phase(a1, b0, H1{}, H0{}, integral_constant<int, 2 * RA>{}, [&](int q) {
-        if (q < RA) read_a(a0, kt + 1, 0, 4 + q);
-        else read_b(b1, kt + 1, 0, q - RA);
-      }, [&] { if (LEFT == 2) copy_t(kt + 2); });
-      if (LEFT) {
-        phase_end(integral_constant<int, W4>{});
-#pragma unroll
-        for (int ks2 = 0; ks2 < KS2; ++ks2)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) b0[ks2][j] = b1[ks2][j];      // B0 of the next k-tile
-      }
-    };
-    copy_a(0, 0); copy_b(0, 0); copy_b(0, 1); copy_a(0, 1); copy_t(0);
-    if (nk > 1) {
-      copy_a(1, 0); copy_b(1, 0); copy_b(1, 1); copy_a(1, 1); copy_t(1);
-      phase_end(std::integral_constant<int, 12>{});    // A0, B0 of k-tile 0 have landed
-    } else {
-      phase_end(std::integral_constant<int, 4>{});
-    }
-    TL_STAMP(3);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) read_a(a0, 0, 0, q);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) read_b(b0, 0, 0, q);
-    if (nk > 1) phase_end(std::integral_constant<int, 10>{});   // B1
-    else phase_end(std::integral_constant<int, 2>{});
-    int kt = 0;
-    for (; kt < nk - 2; ++kt) k_tile(kt, std::integral_constant<int, 2>{});
-    if (nk > 1) k_tile(kt++, std::integral_constant<int, 1>{});
-    k_tile(kt, std::integral_constant<int, 0>{});
-  } else {
+  {
     // main loop: NS tile buffers; the copies of k-tiles kt+1 .. kt+NS-1 are in flight while k-tile kt is
     // multiplied (copies complete in issue order, so waiting for tile kt+1 leaves the younger ones outstanding);
     // one barrier per k-tile
@@ -528,7 +359,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // while pass p is still being drained, so a pass costs one barrier, and nothing of it waits for global memory
   // between the barriers: what a pass reads from global memory (residual rows, rotary table) is requested before its
   // staging writes, and the barriers wait for LDS traffic only.
-  constexpr int SLD = BN_OUT + 4, SR = mfma_stage_rows<BM, WGM, WGN>(), C4 = BN_OUT / 4, NT = NW * 64;
+  constexpr int SLD = BN_OUT + 4, SR = WGM * 16, C4 = BN_OUT / 4, NT = NW * 64;
   constexpr int STG_FLOATS = SR * SLD;
   static_assert(2 * STG_FLOATS * 4 <= mfma_tile_lds_bytes<BM, BN, WGM, WGN, EPI, TAIL, NS>(), "two staging tiles must fit in the tile buffers");
   static_assert(C4 == 16 || C4 == 32 || C4 == 64, "a staged row is handled by 16, 32 or 64 consecutive lanes");
@@ -536,10 +367,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   const bool vec_ok = ((s.N | s.ldc | s.ldr | s.ldc2) & 3) == 0;
   // silu(gate) * up; the reciprocal is the hardware's (1 ulp), the result is rounded to bf16 afterwards
   auto silu_mul = [](float gt, float up) { return gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * up; };
-  // scale of output row m; rs0: the row that entry 0 belongs to (strip_rs0 for rows of the strip).  (A test per element whether
-  // its row lies in the strip is a quarter of the vector instructions of the SwiGLU epilogue: 1.5 us per round of K = 768 tiles.)
-  auto row_scale = [&](int m, int rs0) { return rs_lds[m - rs0]; };
-  const int strip_rs0 = PIPE ? m0_strip - BM : m0;
+  auto row_scale = [&](int m) { return rs_lds[m - m0]; };      // scale of output row m
   // EPI_DPFP_READ: feature idx = lane + 64 k of phi(q) = r[i] r[(i - j) mod 2 d_mem], r = [relu(q), relu(-q)], j = 1..nu
   // (the untrained feature map of Section 2.1) is max(sa q[ia], 0) max(sb q[ib], 0); which columns and signs, and the
   // lane's entries of z, are the same for every row: set up once per thread
@@ -585,13 +413,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   // What one pass of the walk reads from global memory, requested ahead of the pass.
   constexpr int MAX_ITER = (SR * C4 + NT - 1) / NT;
   struct Pre { f32x4 r[MAX_ITER]; };
-  auto prefetch = [&](auto nrows_c, auto m_of, Pre& pre, bool mine = true) __attribute__((always_inline)) {
+  auto prefetch = [&](auto nrows_c, auto m_of, Pre& pre) __attribute__((always_inline)) {
     constexpr int NROWS = decltype(nrows_c)::value, ITER = (NROWS * C4 + NT - 1) / NT;
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
       const int sr = sr_first + it * (NT / C4);
       const int m = m_of(min(sr, NROWS - 1));
-      const bool valid = sr < NROWS && m < s.M && n < s.N && mine;
+      const bool valid = sr < NROWS && m < s.M && n < s.N;
       pre.r[it] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (EPI == EPI_RESID_F32 && g.R && valid) {
         if (vec_ok) {
@@ -605,8 +433,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     }
   };
   // walk NROWS staged rows of staging tile stg; staged row sr is output row m_of(sr)
-  // (`mine`, here and above: this thread's columns belong to this workgroup; always, except in a strip that several M-tiles share)
-  auto drain = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre, int rs0, bool mine = true) __attribute__((always_inline)) {
+  auto drain = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre) __attribute__((always_inline)) {
     constexpr int NROWS = decltype(nrows_c)::value, ITER = (NROWS * C4 + NT - 1) / NT;
     if constexpr (EPI == EPI_DPFP_READ) {
       // One wave per staged row: the row's d_mem values q sit in the staging tile; lane L computes the features
@@ -666,17 +493,17 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
     for (int it = 0; it < ITER; ++it) {
       const int sr = sr_first + it * (NT / C4);
       const int m = m_of(min(sr, NROWS - 1));
-      const bool valid = sr < NROWS && m < s.M && n < s.N && mine;
+      const bool valid = sr < NROWS && m < s.M && n < s.N;
       f32x4 o = {0.f, 0.f, 0.f, 0.f};
       if (valid) {
         o = *(const f32x4*)(stg + sr * SLD + c4 * 4);
-        if (EPI != EPI_SWIGLU) o *= row_scale(m, rs0);        // SwiGLU applied it before the nonlinearity
+        if (EPI != EPI_SWIGLU) o *= row_scale(m);        // SwiGLU applied it before the nonlinearity
         if constexpr (EPI == EPI_QKV_ROPE) {
           if (n < s.n0 + s.n1) {
             // rotary embedding (rotate-half): column j of a head pairs with j +- dh/2, which lies in the same
             // staged row; out_j = x_j cos_j' - x_{j+h} sin_j' (j < h), x_j cos_j' + x_{j-h} sin_j' (j >= h), j' = j mod h
             const int dh = s.ldr, hd = dh >> 1, j = n % dh, lo = j < hd;
-            const f32x4 p = *(const f32x4*)(stg + sr * SLD + c4 * 4 + (lo ? hd : -hd)) * row_scale(m, rs0);
+            const f32x4 p = *(const f32x4*)(stg + sr * SLD + c4 * 4 + (lo ? hd : -hd)) * row_scale(m);
             const f32x4 cs0 = rc0[it], cs1 = rc1[it];
             const float sg = lo ? -1.f : 1.f;
             o[0] = o[0] * cs0[0] + sg * p[0] * cs0[1];
@@ -725,182 +552,68 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
         // are fixed, not tied to the tile width, so that every tile configuration produces the same partials bit for bit.
         static_assert(EPI != EPI_RESID_F32 || BN_OUT % 128 == 0, "partials cover 128 columns = 32 lanes");
         const float part = sum32(o[0] * o[0] + o[1] * o[1] + o[2] * o[2] + o[3] * o[3]);
-        if ((c4 & 31) == 0 && sr < NROWS && m < s.M && mine)
+        if ((c4 & 31) == 0 && sr < NROWS && m < s.M)
           g.ssq_out[(size_t)m * ((s.N + 127) >> 7) + tn * (BN_OUT / 128) + (c4 >> 5)] = part;
       }
-    }
-  };
-  auto strip_mine = [&](int col) {         // output column of the tile -> its strip unit
-    if (!PIPE) return true;
-    return my_unit(EPI == EPI_SWIGLU ? ((col >> 5) + 2 * ((col >> 4) & 1)) & 3 : col >> 7);
-  };
-  // The same for the pipelined tile, whose rows are whole (N a multiple of the tile) and whose eight waves hide less for one
-  // another than sixteen: what a pass reads from global memory is requested a pass ahead, its LDS reads go out together,
-  // and only the stores are predicated (rows past M of a ragged last tile).  Against the walk above, cycles per tile: residual 84.5 k ->
-  // 48 k (sixteen waves: 60 k; 655 KB of traffic), SwiGLU 15.4 -> 12.8 k (9.9 k), rotary 38 -> 30 k (25 k).
-  auto prefetch_whole = [&](auto nrows_c, auto m_of, Pre& pre) __attribute__((always_inline)) {
-    constexpr int ITER = decltype(nrows_c)::value * C4 / NT;
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int m = min(m_of(sr_first + it * (NT / C4)), s.M - 1);
-      pre.r[it] = g.R ? *(const f32x4*)(g.R + (size_t)m * s.ldr + n) : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  auto drain_whole = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre) __attribute__((always_inline)) {
-    constexpr int ITER = decltype(nrows_c)::value * C4 / NT;
-    f32x4 o[ITER];
-    float rs[ITER];
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int sr = sr_first + it * (NT / C4);
-      o[it] = *(const f32x4*)(stg + sr * SLD + c4 * 4);
-      rs[it] = EPI == EPI_SWIGLU ? 1.f : row_scale(m_of(sr), m0);
-    }
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int m = m_of(sr_first + it * (NT / C4));
-      const bool valid = m < s.M;
-      f32x4 v = o[it];
-      if (EPI != EPI_SWIGLU) v *= rs[it];
-      if (EPI == EPI_RESID_F32) v += pre.r[it];
-      bf16x4 ob, og;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ob[e] = (bf16)v[e];
-      if (EPI == EPI_RESID_F32 && g.C2) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) og[e] = g.gain ? (bf16)(v[e] * gq[e]) : ob[e];
-      }
-      if (valid) {
-        if (EPI == EPI_STORE_ACT || EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE) {
-          *(bf16x4*)((bf16*)g.C + (size_t)m * s.ldc + n) = ob;
-        } else {
-          *(f32x4*)((float*)g.C + (size_t)m * s.ldc + n) = v;
-          if (EPI == EPI_RESID_F32 && g.C2) *(bf16x4*)((bf16*)g.C2 + (size_t)m * s.ldc2 + n) = og;
-        }
-      }
-      if (EPI == EPI_RESID_F32 && g.ssq_out) {
-        const float part = sum32(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
-        if ((c4 & 31) == 0 && valid)
-          g.ssq_out[(size_t)m * ((s.N + 127) >> 7) + tn * (BN_OUT / 128) + (c4 >> 5)] = part;
-      }
-    }
-  };
-  // ... and for the q and k columns of EPI_QKV_ROPE: a thread takes four columns of a head's lower half and their four partners,
-  // so that a row's entries of the table and its staged values are read once and not twice (32 threads a row).
-  constexpr int R2 = BN_OUT / 8, RIT = SR * R2 / NT > 0 ? SR * R2 / NT : 1;
-  const int rq = tid % R2, rrow = tid / R2, rhd = max(s.ldr >> 1, 1);
-  const int rlo = 4 * rq / rhd * s.ldr + 4 * rq % rhd;                    // lower column inside the tile; partner rhd further on
-  auto prefetch_rope = [&](auto nrows_c, auto m_of, Pre& pre) __attribute__((always_inline)) {
-    constexpr int ROWS = decltype(nrows_c)::value, ITER = (ROWS * R2 + NT - 1) / NT;
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const float* cs = g.R + 2 * ((size_t)min(m_of(rrow + it * (NT / R2)), s.M - 1) * rhd + 4 * rq % rhd);
-      pre.r[it] = *(const f32x4*)cs;                     // c0 s0 c1 s1 | c2 s2 c3 s3
-      pre.r[RIT + it] = *(const f32x4*)(cs + 4);
-    }
-  };
-  auto drain_rope = [&](const float* stg, auto nrows_c, auto m_of, const Pre& pre) __attribute__((always_inline)) {
-    constexpr int ROWS = decltype(nrows_c)::value, ITER = (ROWS * R2 + NT - 1) / NT;
-    f32x4 lo[ITER], hi[ITER];
-    float rs[ITER];
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int sr = rrow + it * (NT / R2);
-      lo[it] = *(const f32x4*)(stg + sr * SLD + rlo);
-      hi[it] = *(const f32x4*)(stg + sr * SLD + rlo + rhd);
-      rs[it] = row_scale(m_of(sr), m0);
-    }
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int m = m_of(rrow + it * (NT / R2));
-      const f32x4 a = lo[it] * rs[it], b = hi[it] * rs[it], c0 = pre.r[it], c1 = pre.r[RIT + it];
-      bf16x4 oa, ob;
-      // out_j = x_j cos - x_{j+h} sin, out_{j+h} = x_{j+h} cos + x_j sin (written as in the walk above: same bits)
-      oa[0] = (bf16)(a[0] * c0[0] + -1.f * b[0] * c0[1]);  ob[0] = (bf16)(b[0] * c0[0] + 1.f * a[0] * c0[1]);
-      oa[1] = (bf16)(a[1] * c0[2] + -1.f * b[1] * c0[3]);  ob[1] = (bf16)(b[1] * c0[2] + 1.f * a[1] * c0[3]);
-      oa[2] = (bf16)(a[2] * c1[0] + -1.f * b[2] * c1[1]);  ob[2] = (bf16)(b[2] * c1[0] + 1.f * a[2] * c1[1]);
-      oa[3] = (bf16)(a[3] * c1[2] + -1.f * b[3] * c1[3]);  ob[3] = (bf16)(b[3] * c1[2] + 1.f * a[3] * c1[3]);
-      if (m >= s.M) continue;
-      bf16* out = (bf16*)g.C + (size_t)m * s.ldc + n0 + rlo;
-      *(bf16x4*)out = oa;
-      *(bf16x4*)(out + rhd) = ob;
     }
   };
   // EPI_QKV_ROPE, tiles of the v columns: the attention kernel wants V transposed ([column][row], row stride ldc2),
   // so these tiles are drained column-wise: a thread takes 8 consecutive rows of one column, 16 bytes per store.
   const bool vt_tile = EPI == EPI_QKV_ROPE && s.ldc2 > 0 && n0 >= s.n0 + s.n1;      // block-uniform
-  auto drain_vt = [&](const float* stg, int nrows, auto m_of, int rs0, bool strip = false) __attribute__((always_inline)) {
+  auto drain_vt = [&](const float* stg, int nrows, auto m_of) __attribute__((always_inline)) {
     bf16* vt = (bf16*)g.C2 + (size_t)(n0 - (s.n0 + s.n1)) * s.ldc2;
     for (int u = tid; u < (nrows >> 3) * BN_OUT; u += NT) {
       const int rg = u / BN_OUT, col = u - rg * BN_OUT;
       const int m = m_of(rg * 8);          // rows rg * 8 .. + 7 of the staging tile are consecutive output rows
-      if (m >= s.M || n0 + col >= s.N || (strip && !strip_mine(col))) continue;
+      if (m >= s.M || n0 + col >= s.N) continue;
       bf16x8 v;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        v[i] = (m + i < s.M) ? (bf16)(stg[(rg * 8 + i) * SLD + col] * row_scale(m + i, rs0)) : (bf16)0.f;
+        v[i] = (m + i < s.M) ? (bf16)(stg[(rg * 8 + i) * SLD + col] * row_scale(m + i)) : (bf16)0.f;
       *(bf16x8*)(vt + (size_t)col * s.ldc2 + m) = v;
     }
   };
   const int col_in = lane & 15;
-  // a pass stages one 16-row block of every wave row, the pipelined tile's one of either half (HB of them)
-  constexpr int HB = PIPE ? 2 : 1, PASSES = TM / HB;
-  auto row_of_pass = [&](int pass) { return [=](int sr) { return m0 + (sr >> 4) * (BM / (SR / 16)) + pass * 16 + (sr & 15); }; };
+  auto row_of_pass = [&](int pass) { return [=](int sr) { return m0 + (sr >> 4) * WROWS + pass * 16 + (sr & 15); }; };
   using AllRows = std::integral_constant<int, SR>;
-  const bool whole = PIPE && vec_ok && (EPI != EPI_QKV_ROPE || s.ldr >= 8);
-  constexpr bool AHEAD = EPI == EPI_RESID_F32;      // the rotary table comes from the L2: requested in front of the staging of its pass
-  const bool rotated = EPI == EPI_QKV_ROPE && n0 < s.n0 + s.n1;      // block-uniform: weight blocks end on tiles
-  auto request = [&](auto nrows_c, auto m_of, Pre& pre) __attribute__((always_inline)) {
-    if constexpr (EPI == EPI_QKV_ROPE) { if (rotated) prefetch_rope(nrows_c, m_of, pre); }
-    else if constexpr (EPI == EPI_RESID_F32) prefetch_whole(nrows_c, m_of, pre);
-  };
-  Pre pre[2];
-  if (whole && AHEAD) request(AllRows{}, row_of_pass(0), pre[0]);
+  Pre pre;
 #pragma unroll
-  for (int pass = 0; pass < PASSES; ++pass) {
+  for (int pass = 0; pass < TM; ++pass) {        // a pass stages one 16-row block of every wave row
     float* stg = (float*)smem + (pass & 1) * STG_FLOATS;
     const auto pass_row = row_of_pass(pass);
-    Pre& now = pre[AHEAD ? pass & 1 : 0];
-    if (whole && !AHEAD) request(AllRows{}, pass_row, now);
-    if (!whole && EPI == EPI_RESID_F32) prefetch(AllRows{}, pass_row, now);
+    if (EPI == EPI_RESID_F32) prefetch(AllRows{}, pass_row, pre);
 #pragma unroll
-    for (int hb = 0; hb < HB; ++hb)
+    for (int r = 0; r < 4; ++r) {
+      const int row16 = 4 * t_q + r;
+      float* dst = stg + (wm * 16 + row16) * SLD + col_in;
+      if (EPI == EPI_SWIGLU) {
+        // the wave's weight rows come in 32-row blocks, gate / up alternating: tiles 4q + h (gate) and 4q + 2 + h
+        // (up), h = 0, 1, give output columns (wn * WCOLS / 64 + q) * 32 + h * 16 + lane % 16
+        const float rs = rs_lds[blk_row(pass) + row16];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = hb * PASSES + pass, row16 = 4 * t_q + r;
-        float* dst = stg + ((hb * WGM + wm) * 16 + row16) * SLD + col_in;
-        if (EPI == EPI_SWIGLU) {
-          // the wave's weight rows come in 32-row blocks, gate / up alternating: tiles 4q + h (gate) and 4q + 2 + h
-          // (up), h = 0, 1, give output columns (wn * WCOLS / 64 + q) * 32 + h * 16 + lane % 16; the same for the pipelined
-          // tile (q = 0), whose gate and up blocks are its lower and upper half
-          const float rs = rs_lds[blk_row(i) + row16];
+        for (int j = 0; j < TN; ++j)
+          if ((j & 2) == 0)
+            dst[(wn * (WCOLS / 64) + (j >> 2)) * 32 + (j & 1) * 16] = silu_mul(rs * acc[pass][j][r], rs * acc[pass][j + 2][r]);
+      } else {
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            if ((j & 2) == 0)
-              dst[(wn * (WCOLS / 64) + (j >> 2)) * 32 + (j & 1) * 16] = silu_mul(rs * acc[i][j][r], rs * acc[i][j + 2][r]);
-        } else {
-#pragma unroll
-          for (int j = 0; j < TN; ++j) dst[blk_col(j)] = acc[i][j][r];
-        }
+        for (int j = 0; j < TN; ++j) dst[blk_col(j)] = acc[pass][j][r];
       }
-    if (whole && AHEAD && pass + 1 < PASSES) request(AllRows{}, row_of_pass(pass + 1), pre[(pass + 1) & 1]);
+    }
     __syncthreads();         // pass p is staged; everybody has left the walk of pass p - 1, whose tile pass p + 1 reuses
-    if (vt_tile) drain_vt(stg, SR, pass_row, m0);
-    else if (EPI == EPI_QKV_ROPE && whole && rotated) drain_rope(stg, AllRows{}, pass_row, now);
-    else if (whole) drain_whole(stg, AllRows{}, pass_row, now);
-    else drain(stg, AllRows{}, pass_row, now, m0);
+    if (vt_tile) drain_vt(stg, SR, pass_row);
+    else drain(stg, AllRows{}, pass_row, pre);
   }
   if (TAIL && tail_blk) {     // 16x16 result tile: lane holds column lane % 16, rows 4*(lane/16) + r
-    float* stg = (float*)smem + (PASSES & 1) * STG_FLOATS;
+    float* stg = (float*)smem + (TM & 1) * STG_FLOATS;
     auto tail_row = [&](int sr) { return m0_strip + sr; };
-    if (EPI == EPI_RESID_F32) prefetch(std::integral_constant<int, 16>{}, tail_row, pre[0], strip_mine(c4 * 4));
-    if (PIPE ? strip_sel >= 0 : tail) {
+    if (EPI == EPI_RESID_F32) prefetch(std::integral_constant<int, 16>{}, tail_row, pre);
+    if (tail) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float* dst = stg + (4 * t_q + r) * SLD;
         if (EPI == EPI_SWIGLU) {
           const float rs = rs_lds[BM + 4 * t_q + r];
-          dst[PIPE ? t_brow : (wave >> 1) * 32 + (wave & 1) * 16 + (lane & 15)] = silu_mul(rs * tacc[0][r], rs * tacc[1][r]);
+          dst[(wave >> 1) * 32 + (wave & 1) * 16 + (lane & 15)] = silu_mul(rs * tacc[0][r], rs * tacc[1][r]);
         } else {
           dst[t_brow] = tacc[0][r];
           dst[t_brow + T_STEP] = tacc[1][r];
@@ -908,8 +621,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
       }
     }
     __syncthreads();
-    if (vt_tile) drain_vt(stg, 16, tail_row, strip_rs0, true);
-    else drain(stg, std::integral_constant<int, 16>{}, tail_row, pre[0], strip_rs0, strip_mine(c4 * 4));
+    if (vt_tile) drain_vt(stg, 16, tail_row);
+    else drain(stg, std::integral_constant<int, 16>{}, tail_row, pre);
   }
 #ifdef ARMT_GEMM_TIMELINE
   if (tl_on && threadIdx.x == 0) { tl[5] = __builtin_readcyclecounter(); tl[6] = __builtin_amdgcn_s_memrealtime(); }
@@ -969,6 +682,57 @@ inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, Gem
   }
 #endif
   kern<<<grid, WGM * WGN * 64, LDS, st>>>(table, first, s, tiles_m, tiles_n, m_group, total, begin);
+  return hipGetLastError();
+}
+
+// Shapes that the persistent 256 x 256 tile takes, of the regular ones: at least three k-tiles, rows that can be stored in 16-byte pieces and reached by
+// 32-bit offsets from a tile's first row, heads of 64 or 128 columns (a wave's columns hold whole ones).
+template <int EPI>
+inline bool tile256_shape(const GemmShape& s) {
+  constexpr int LD = 1 << 21;
+  // its copies are two k-tiles ahead, but never more than one tile
+  if (s.K < 3 * MF_BK || (s.k_slot > 0 && (s.k_min > 0 ? s.k_min : s.k_slot) < 3)) return false;
+  if (((s.N | s.ldc | s.ldr | s.ldc2) & 3) != 0 || s.lda > LD || s.ldb > LD || s.ldc > LD || s.ldr > LD || s.ldc2 > LD) return false;
+  if (s.M > 256 && s.M % 256 == 16 && !(s.dbg & 32)) {      // two M-tiles of the last M-group share the strip
+    const int tm = s.M / 256, mg = mfma_m_group(s);
+    if (tm - (tm - 1) / mg * mg < 2) return false;
+  }
+  return EPI != EPI_QKV_ROPE || s.ldr == 64 || s.ldr == 128;
+}
+
+template <int EPI>
+inline hipError_t launch_tile256(const GemmGroup* table, int first, int g, GemmShape s, hipStream_t st, const TileRange& rng = TileRange()) {
+  constexpr int BN_OUT = EPI == EPI_SWIGLU ? 128 : 256;
+  const bool tail = s.M > 256 && s.M % 256 == 16 && !(s.dbg & 32);
+  TileWalk w;
+  w.tiles_m = tail ? s.M / 256 : (s.M + 255) / 256;
+  w.tiles_n = s.N / BN_OUT;
+  w.m_group = mfma_m_group(s);
+  w.begin = 0;
+  w.total = g * w.tiles_m * w.tiles_n;
+  if (rng.unit_cols > 0) {
+    w.begin = mfma_unit_tile(rng.begin, w.tiles_m, w.m_group, w.tiles_n, rng.unit_cols / BN_OUT);
+    w.total = mfma_unit_tile(rng.end, w.tiles_m, w.m_group, w.tiles_n, rng.unit_cols / BN_OUT) - w.begin;
+  }
+  if (w.total <= 0) return hipSuccess;
+  s.spread = s.spread && rng.unit_cols == 0 && w.tiles_m * w.tiles_n % 8 == 0;
+  w.r_group = t256_recip(w.tiles_m * w.tiles_n);
+  w.r_mgroup = t256_recip(w.m_group * w.tiles_n);
+  w.r_full = t256_recip(w.m_group < w.tiles_m ? w.m_group : w.tiles_m);
+  w.r_last = t256_recip(w.tiles_m - (w.tiles_m - 1) / w.m_group * w.m_group);
+  w.r_share = t256_recip(w.tiles_m * w.tiles_n / 8);
+  const int grid = w.total < MF_CUS ? (w.total + 7) / 8 * 8 : MF_CUS;
+  constexpr int HB = EPI == EPI_QKV_ROPE ? 2 : 0;
+  const bool wide = HB > 0 && s.ldr == 128;
+  auto kern = wide ? (tail ? gemm_tile256_kernel<EPI, true, 2 * HB> : gemm_tile256_kernel<EPI, false, 2 * HB>)
+                   : (tail ? gemm_tile256_kernel<EPI, true, HB> : gemm_tile256_kernel<EPI, false, HB>);
+  static std::atomic<uint64_t> lds_raised[4];
+  const hipError_t e = raise_lds_limit((const void*)kern, T256_LDS, lds_raised[2 * wide + tail]);
+  if (e != hipSuccess) return e;
+#ifdef ARMT_GEMM_TIMELINE
+  if (s.tag == g_tl_kind && g_tl_countdown >= 0 && g_tl_countdown-- == 0) s.dbg |= 1 << 20;
+#endif
+  kern<<<grid, 256, T256_LDS, st>>>(table, first, s, w);
   return hipGetLastError();
 }
 
@@ -1042,10 +806,11 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
       // (six do not pay, also not for at most one workgroup per CU: 25.7 us with either for one cell of d 2048)
       if constexpr (EPI == EPI_DPFP_READ) return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 3>(table, first, g, s, st);
       break;
-    case 5:   // 256 x 256: pipelined loop of eight waves where the shape allows its copies to be addressed by scalar base + lane
-              // offset, else 16 waves.  Also for short loops and the SwiGLU strip, where it gains least; us per launch of gate/up with
-              // 16 waves / pipelined: twelve cells of 1040 x 6144, K 768: 105.4 / 103.4; sixteen of 528 x 16384, K 2048: 409 / 403
-      if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) {
+    case 5:   // 256 x 256: the persistent tile of four waves (gemm_tile256.h), for other shapes 16 waves and one barrier per k-tile.  us per
+              // launch, eight waves in four phases per k-tile (what was here) / four: gate/up of twelve cells of 1040 x 6144, K 768 107.0 / 94.3, of
+              // the 3B model (mean of its launches) 907 / 824, of the 1B model 346 / 315; QKV 56.7 / 50.1, 325 / 310, 70.5 / 66.5; attention
+              // output, down and read of K 3072 and 8192 275 / 272, of the 768-wide model, whose launches are at most one tile per CU, 57.6 / 60.9
+      if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s) && tile256_shape<EPI>(s)) {
         if constexpr (EPI != EPI_SWIGLU) {
           // Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs
           // as 128 x 128 tiles (four times as many, two workgroups per CU: one short round instead of a long one
@@ -1059,12 +824,12 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
             TileRange big, rest;
             big.unit_cols = rest.unit_cols = 256;
             big.begin = 0; big.end = rest.begin = cut; rest.end = units;
-            hipError_t e = launch_mfma_cfg<256, 256, 2, 4, EPI, true>(table, first, g, s, st, big);
+            hipError_t e = launch_tile256<EPI>(table, first, g, s, st, big);
             if (e != hipSuccess) return e;
             return launch_mfma_cfg<128, 128, 4, 2, EPI, true>(table, first, g, s, st, rest);
           }
         }
-        return launch_mfma_cfg<256, 256, 2, 4, EPI, true>(table, first, g, s, st);
+        return launch_tile256<EPI>(table, first, g, s, st);
       }
       return launch_mfma_cfg<256, 256, 4, 4, EPI>(table, first, g, s, st);
     case 6:   // as 1, copies addressed by scalar base + lane offset where the shape allows
