@@ -8,8 +8,8 @@
 // every sixth.)  Four waves read 128 KB of LDS per k-tile where eight of 128 x 64 read 192.
 // Tiles.  The copies run two k-tiles ahead through ALL tiles of the workgroup: the last two k-tiles of a tile fetch the first two of the next, whose
 // start costs no latency, and the epilogue, which uses registers and global memory only, runs while they land.
-// Epilogue.  A 16 x 16 block is multiplied with the weights as first operand: a lane then holds four consecutive columns of one
-// row (fp32: 16 bytes, four lanes 64 consecutive ones; bf16: two blocks are exchanged between lane rows first).  Buffer stores drop what lies past M.
+// Epilogue.  A 16 x 16 block is multiplied with the weights as first operand: a lane then holds four consecutive columns of one row.  Whole rows of
+// 64 columns leave through LDS of the wave's own.  Buffer stores drop what lies past M.
 #pragma once
 
 #include "common.h"
@@ -58,7 +58,8 @@ constexpr int T256_KEEP = 2;
 constexpr int T256_STAGE = 65536;                             // a k-tile: 256 rows of A, 256 of B
 constexpr int T256_STRIP = 2 * T256_STAGE;                    // two buffers of the 16 strip rows
 constexpr int T256_SSQ = T256_STRIP + 2 * 2048;               // sums of squares: [half][wave column][256], strip [wave][16]
-constexpr int T256_LDS = T256_SSQ + 4 * 256 * 4 + 4 * 16 * 4;
+constexpr int T256_OUT = T256_SSQ + 4 * 256 * 4 + 4 * 16 * 4;      // results on their way out: 4 KB per wave
+constexpr int T256_LDS = T256_OUT + 4 * 4096;
 
 // HB: EPI_QKV_ROPE, blocks of 16 columns in half a head (2 or 4), otherwise 0
 template <int EPI, bool TAIL, int HB>
@@ -319,24 +320,64 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       const bf16x2 v = {(bf16)a, (bf16)b};
       return __builtin_bit_cast(unsigned, v);
     };
-    // 16 bytes per lane out of two neighbouring blocks of four columns each: lane row t_q holds columns 8 (t_q >> 1) .. + 7 of block t_q & 1
-    auto join = [&](f32x4t a, f32x4t b) __attribute__((always_inline)) {
-      const u32x2t lo = __builtin_amdgcn_permlane16_swap(pack(a[0], a[1]), pack(b[0], b[1]), false, false);
-      const u32x2t hi = __builtin_amdgcn_permlane16_swap(pack(a[2], a[3]), pack(b[2], b[3]), false, false);
-      return u32x4t{lo[0], hi[0], lo[1], hi[1]};
-    };
-    const int jcol = (t_q & 1) * 16 + (t_q >> 1) * 8;          // first column of a joined store, from its first block
-    // Two stores of 16 rows x 64 bytes, v2 64 bytes further on in the rows of v1, as two of eight rows x 128 bytes (whole lines): lanes l16 >= 8
-    // of the first take v2 of row l16 - 8, lanes l16 < 8 of the second v1 of row l16 + 8.
-    auto lines = [&](u32x4t& v1, u32x4t& v2) __attribute__((always_inline)) {
-      const u32x4t a = v1, b = v2;
+    // Results leave through 4 KB of LDS per wave (no barrier: a wave's LDS accesses run in order).  A result block has neighbouring lanes in different
+    // rows, and the memory pipe takes four neighbouring lanes at a time, at a quarter of its rate if their 16 bytes are not neighbours.  us per launch, straight
+    // from the registers / this way: attention output, down and read 275 / 267 (3B model), 60.8 / 57.0 (768-wide), QKV 50.0 / 48.5,
+    // the head on 4096 rows 1817 / 1751, its weight gradient 1955 / 1890; gate/up 0.5 % slower.  The 16-byte chunks of a row are exchanged (XOR) so that neither side meets a bank twice.
+    unsigned char* out_lds = smem + T256_OUT + wave * 4096;
+    const int r8 = lane_e >> 3, c8 = lane_e & 7, r4 = t_q, c4 = l16;       // row and 16-byte column of a lane in rows of 128, of 256 bytes
+    // 16 rows x 64 columns in bf16; back: rows 8 k + r8, columns 8 c8 .. + 7
+    auto put16 = [&](int half, const f32x4t (&v)[4]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v1[e] = __builtin_amdgcn_update_dpp(a[e], b[e], 0x128, 0xF, 0xC, false);       // row_ror:8
-        v2[e] = __builtin_amdgcn_update_dpp(b[e], a[e], 0x128, 0xF, 0x3, false);
+      for (int x = 0; x < 4; ++x)
+        *(u32x2t*)(out_lds + half * 2048 + l16 * 128 + (((2 * x + (t_q >> 1)) ^ (l16 >> 1)) << 4) + (t_q & 1) * 8) = u32x2t{pack(v[x][0], v[x][1]), pack(v[x][2], v[x][3])};
+    };
+    auto get16 = [&](int half, u32x4t (&r)[2]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) r[k] = *(const u32x4t*)(out_lds + half * 2048 + (8 * k + r8) * 128 + ((c8 ^ (((8 * k + r8) >> 1) & 7)) << 4));
+    };
+    // 16 rows x 64 columns in fp32; back: rows 4 k + r4, columns 4 c4 .. + 3
+    auto put32 = [&](const f32x4t (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) *(f32x4t*)(out_lds + l16 * 256 + (((4 * x + t_q) ^ l16) << 4)) = v[x];
+    };
+    auto get32 = [&](f32x4t (&r)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) r[k] = *(const f32x4t*)(out_lds + (4 * k + r4) * 256 + ((c4 ^ (4 * k + r4)) << 4));
+    };
+    // N pieces of 16 x 64: piece i + 1 is made while piece i comes back from LDS
+    auto out16 = [&](auto n_c, auto make, auto store) __attribute__((always_inline)) {
+      constexpr int N = decltype(n_c)::value;
+      u32x4t r[2][2];
+#pragma unroll
+      for (int i = 0; i <= N; ++i) {
+        if (i < N) {
+          f32x4t v[4];
+          make(i, v);
+          put16(i & 1, v);
+        }
+        if (i > 0) store(i - 1, r[(i - 1) & 1]);
+        if (i < N) get16(i & 1, r[i & 1]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
-    const int l8 = l16 & 7, h8 = l16 >> 3;                     // row of a whole-line store, half of the line
+    auto out32 = [&](auto n_c, auto make, auto store) __attribute__((always_inline)) {
+      constexpr int N = decltype(n_c)::value;
+      f32x4t r[2][4];
+#pragma unroll
+      for (int i = 0; i <= N; ++i) {
+        if (i < N) {
+          f32x4t v[4];
+          make(i, v);
+          put32(v);
+        }
+        if (i > 0) store(i - 1, r[(i - 1) & 1]);
+        if (i < N) get32(r[i & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    using N8 = std::integral_constant<int, 8>;
+    using N16 = std::integral_constant<int, 16>;
     auto take = [&](int y, int x) __attribute__((always_inline)) {       // a result block; its accumulators start the next tile at zero
       f32x4t v;
       // (where it is needed: the compiler would copy them all out at the end of the loop)
@@ -356,7 +397,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
     auto silu_mul = [](float gt, float up) { return gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * up; };
 
     if (vt) {
-      // columns n0 + .. of the V block transposed: C2[column][row]; a joined store is eight rows of a column (M is a multiple of 8 here)
+      // columns n0 + .. of the V block transposed: C2[column][row], eight rows of a column per lane (M is a multiple of 8 here)
       bf16* out = (bf16*)g.C2 + (size_t)(tile.n0 - (s.n0 + s.n1)) * ldc2 + tile.m0;
       auto o = rsrc(out, (size_t)256 * ldc2 * 2);
       f32x4t rs[8];
@@ -364,15 +405,17 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       for (int x = 0; x < 8; ++x) {
         rs[x] = __builtin_bit_cast(f32x4t, __builtin_amdgcn_raw_buffer_load_b128(scale_rsrc, (at16(wx, x) + 4 * t_q) * 4, 0, 0));
       }
+      out16(N16{}, [&](int i, f32x4t (&v)[4]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int y = 0; y < 8; ++y)
+        for (int x = 0; x < 4; ++x) v[x] = take(i >> 1, 4 * (i & 1) + x) * rs[4 * (i & 1) + x];
+      }, [&](int i, const u32x4t (&r)[2]) __attribute__((always_inline)) {
+        const int m = at16(wx, 4 * (i & 1)) + 8 * c8;
 #pragma unroll
-        for (int x = 0; x < 8; x += 2) {
-          const u32x4t v = join(take(y, x) * rs[x], take(y, x + 1) * rs[x + 1]);
-          const int m = at16(wx, x) + jcol;
-          const unsigned off = ((unsigned)(at16(wy, y) + l16) * (unsigned)ldc2 + m) * 2u;
-          __builtin_amdgcn_raw_buffer_store_b128(v, o, m < rows ? off : 0xfffffff0u, 0, 0);
+        for (int k = 0; k < 2; ++k) {
+          const unsigned off = ((unsigned)(at16(wy, i >> 1) + 8 * k + r8) * (unsigned)ldc2 + m) * 2u;
+          __builtin_amdgcn_raw_buffer_store_b128(r[k], o, m < rows ? off : 0xfffffff0u, 0, T256_KEEP);
         }
+      });
       if (TAIL && tile.half >= 0) {
         bf16* ts = (bf16*)g.C2 + (size_t)(tile.n0 - (s.n0 + s.n1) + r0 + l16) * ldc2 + m0_strip + 4 * t_q;
         f32x4t r = {1.f, 1.f, 1.f, 1.f};
@@ -387,28 +430,19 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       auto o = rsrc((bf16*)g.C + (size_t)tile.m0 * ldc, (size_t)rows * ldc * 2);
       float rs[8];
       rs[0] = scale_of(0);
-#pragma unroll
-      for (int y = 0; y < 8; ++y) {
+      out16(N8{}, [&](int y, f32x4t (&v)[4]) __attribute__((always_inline)) {
         if (y < 7) rs[y + 1] = scale_of(y + 1);
-        const unsigned row = (unsigned)(at16(wy, y) + l8) * (unsigned)ldc + tile.n0 + wx * 64 + h8 * 32 + jcol;
-        u32x4t joined[2];
 #pragma unroll
-        for (int x = 0; x < 4; x += 2) {
-          f32x4t v[2];
+        for (int x = 0; x < 4; ++x) {
+          const f32x4t gt = take(y, x), up = take(y, x + 4);
 #pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            const f32x4t gt = take(y, x + b), up = take(y, x + b + 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[b][e] = silu_mul(rs[y] * gt[e], rs[y] * up[e]);
-          }
-          joined[x >> 1] = join(v[0], v[1]);
-          __builtin_amdgcn_sched_barrier(0);                   // (more of them side by side would not fit the registers)
+          for (int e = 0; e < 4; ++e) v[x][e] = silu_mul(rs[y] * gt[e], rs[y] * up[e]);
         }
-        lines(joined[0], joined[1]);
-        __builtin_amdgcn_raw_buffer_store_b128(joined[0], o, row * 2u, 0, T256_KEEP);
-        __builtin_amdgcn_raw_buffer_store_b128(joined[1], o, (row + 8 * ldc) * 2u, 0, T256_KEEP);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      }, [&](int y, const u32x4t (&r)[2]) __attribute__((always_inline)) {
+        const unsigned at = (unsigned)(at16(wy, y) + r8) * (unsigned)ldc + tile.n0 + wx * 64 + 8 * c8;
+        __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_KEEP);
+        __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
+      });
       if (TAIL && tile.half >= 0) {
         const float r = strip_scale();
         f32x4t v;
@@ -418,23 +452,20 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       }
     } else {
       float rs[8];
-      if constexpr (!ROPE) rs[0] = scale_of(0);
+      if constexpr (!ROPE && !RESID) rs[0] = scale_of(0);
+      auto scaled = [&](int i, f32x4t (&v)[4]) __attribute__((always_inline)) {       // half h = i & 1 of row block y = i >> 1
+        const int y = i >> 1, h = i & 1;
+        if (h == 0 && y < 7) rs[y + 1] = scale_of(y + 1);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v[x] = take(y, 4 * h + x) * rs[y];
+      };
       if constexpr (EPI == EPI_STORE_ACT) {
         auto o = rsrc((bf16*)g.C + (size_t)tile.m0 * ldc, (size_t)rows * ldc * 2);
-#pragma unroll
-        for (int y = 0; y < 8; ++y) {
-        if (y < 7) rs[y + 1] = scale_of(y + 1);
-          const unsigned row = (unsigned)(at16(wy, y) + l8) * (unsigned)ldc;
-#pragma unroll
-          for (int x = 0; x < 8; x += 4) {
-            u32x4t v1 = join(take(y, x) * rs[y], take(y, x + 1) * rs[y]), v2 = join(take(y, x + 2) * rs[y], take(y, x + 3) * rs[y]);
-            lines(v1, v2);
-            const unsigned at = row + tile.n0 + at16(wx, x) + h8 * 32 + jcol;
-            __builtin_amdgcn_raw_buffer_store_b128(v1, o, at * 2u, 0, T256_KEEP);
-            __builtin_amdgcn_raw_buffer_store_b128(v2, o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        out16(N16{}, scaled, [&](int i, const u32x4t (&r)[2]) __attribute__((always_inline)) {
+          const unsigned at = (unsigned)(at16(wy, i >> 1) + r8) * (unsigned)ldc + tile.n0 + at16(wx, 4 * (i & 1)) + 8 * c8;
+          __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_KEEP);
+          __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
+        });
         if (TAIL && tile.half >= 0) {
           const float r = strip_scale();
           bf16* out = (bf16*)g.C + (size_t)(m0_strip + l16) * ldc + tile.n0 + r0 + 4 * t_q;
@@ -446,20 +477,11 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
         }
       } else if constexpr (EPI == EPI_STORE_F32) {
         auto o = rsrc((float*)g.C + (size_t)tile.m0 * ldc, (size_t)rows * ldc * 4);
+        out32(N16{}, scaled, [&](int i, const f32x4t (&r)[4]) __attribute__((always_inline)) {
+          const unsigned at = (unsigned)(at16(wy, i >> 1) + r4) * (unsigned)ldc + tile.n0 + at16(wx, 4 * (i & 1)) + 4 * c4;
 #pragma unroll
-        for (int y = 0; y < 8; ++y) {
-        if (y < 7) rs[y + 1] = scale_of(y + 1);
-          const unsigned row = (unsigned)(at16(wy, y) + l8) * (unsigned)ldc;
-#pragma unroll
-          for (int x = 0; x < 8; x += 2) {
-            u32x4t v1 = __builtin_bit_cast(u32x4t, take(y, x) * rs[y]), v2 = __builtin_bit_cast(u32x4t, take(y, x + 1) * rs[y]);
-            lines(v1, v2);
-            const unsigned at = row + tile.n0 + at16(wx, x) + h8 * 16 + 4 * t_q;
-            __builtin_amdgcn_raw_buffer_store_b128(v1, o, at * 4u, 0, T256_KEEP);
-            __builtin_amdgcn_raw_buffer_store_b128(v2, o, (at + 8 * ldc) * 4u, 0, T256_KEEP);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
+          for (int k = 0; k < 4; ++k) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4t, r[k]), o, (at + 4 * k * ldc) * 4u, 0, T256_KEEP);
+        });
         if (TAIL && tile.half >= 0) {
           const float r = strip_scale();
           float* out = (float*)g.C + (size_t)(m0_strip + l16) * ldc + tile.n0 + r0 + 4 * t_q;
@@ -475,22 +497,33 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
         const bool copied = g.C2 != nullptr, summed = g.ssq_out != nullptr;
         const bf16* gains = copied && g.gain ? (const bf16*)g.gain + tile.n0 : t256_ones.h;
         auto gain_rsrc = rsrc(gains, 512);
-        u32x2t gq[8];                                          // gains of the copy
+        bf16x4 gq[2];                                          // gains of the copy, columns of half h
 #pragma unroll
-        for (int x = 0; x < 8; ++x) gq[x] = __builtin_amdgcn_raw_buffer_load_b64(gain_rsrc, (at16(wx, x) + 4 * t_q) * 2, 0, 0);
-        auto gained = [&](f32x4t v, int x) __attribute__((always_inline)) {
-          const bf16x4 b = __builtin_bit_cast(bf16x4, gq[x]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] *= (float)b[e];
-          return v;
-        };
-        // residual rows, requested AHEAD half rows of blocks (64 columns) ahead
-        constexpr int AHEAD = 4;
-        f32x4t pre[AHEAD + 1][4];
+        for (int h = 0; h < 2; ++h) gq[h] = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(gain_rsrc, (at16(wx, 4 * h) + 4 * c4) * 2, 0, 0));
+        // residual rows, requested AHEAD pieces in front of the one that is made, which is one in front of the one that uses them, and their scales
+        constexpr int AHEAD = 2, RING = AHEAD + 2;
+        f32x4t pre[RING][4];
+        float rr[3][4];
         auto request = [&](int i) __attribute__((always_inline)) {
-          const unsigned at = (unsigned)(at16(wy, i >> 1) + l16) * (unsigned)ldr + nc + at16(wx, 4 * (i & 1));
+          const unsigned at = (unsigned)(at16(wy, i >> 1) + r4) * (unsigned)ldr + tile.n0 + at16(wx, 4 * (i & 1)) + 4 * c4;
 #pragma unroll
-          for (int x = 0; x < 4; ++x) pre[i % (AHEAD + 1)][x] = __builtin_bit_cast(f32x4t, __builtin_amdgcn_raw_buffer_load_b128(res, (at + 16 * x) * 4u, 0, 0));
+          for (int k = 0; k < 4; ++k) pre[i % RING][k] = __builtin_bit_cast(f32x4t, __builtin_amdgcn_raw_buffer_load_b128(res, (at + 4 * k * ldr) * 4u, 0, 0));
+        };
+        auto row_scales = [&](int y) __attribute__((always_inline)) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            rr[y % 3][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(scale_rsrc, (at16(wy, y) + 4 * k + r4) * 4, 0, 0));
+        };
+        // sum over the 16 lanes of a row: the columns of its half in the order of the tiles' other sums (gemm_mfma.h)
+        auto sum16 = [](float v) __attribute__((always_inline)) {
+          auto dpp = [](float x, auto ctrl) {
+            return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
+          };
+          v += dpp(v, std::integral_constant<int, 0xB1>{});
+          v += dpp(v, std::integral_constant<int, 0x4E>{});
+          v += dpp(v, std::integral_constant<int, 0x141>{});
+          v += dpp(v, std::integral_constant<int, 0x140>{});
+          return v;
         };
         // sums over the four lane rows of 16 columns, over the blocks in column order: lane row t_q first holds the sum of block t_q
         auto sum64 = [&](const float (&p)[4]) __attribute__((always_inline)) {
@@ -507,43 +540,41 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
           return fold32(h, h);
         };
         auto ssq4 = [](f32x4t v) { return v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]; };
+        row_scales(0);
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) request(i);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int y = i >> 1, h = i & 1;
-          if (h == 0 && y < 7) rs[y + 1] = scale_of(y + 1);
+        out32(N16{}, [&](int i, f32x4t (&v)[4]) __attribute__((always_inline)) {
+          if ((i & 1) == 0 && i < 14) row_scales((i >> 1) + 1);
           if (i + AHEAD < 16) request(i + AHEAD);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) v[x] = take(i >> 1, 4 * (i & 1) + x);
+        }, [&](int i, const f32x4t (&r)[4]) __attribute__((always_inline)) {
+          const int y = i >> 1, h = i & 1;
+          const unsigned row = (unsigned)(at16(wy, y) + r4), col = tile.n0 + at16(wx, 4 * h) + 4 * c4;
           f32x4t v[4];
 #pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            v[x] = take(y, 4 * h + x);
+          for (int k = 0; k < 4; ++k) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[x][e] = fmaf(v[x][e], rs[y], pre[i % (AHEAD + 1)][x][e]);
-          }
-          const unsigned col = tile.n0 + at16(wx, 4 * h), row8 = (unsigned)(at16(wy, y) + l8);
-#pragma unroll
-          for (int x = 0; x < 4; x += 2) {
-            u32x4t v1 = __builtin_bit_cast(u32x4t, v[x]), v2 = __builtin_bit_cast(u32x4t, v[x + 1]);
-            lines(v1, v2);
-            const unsigned at = row8 * (unsigned)ldc + col + 16 * x + h8 * 16 + 4 * t_q;
-            __builtin_amdgcn_raw_buffer_store_b128(v1, o, at * 4u, 0, T256_KEEP);
-            __builtin_amdgcn_raw_buffer_store_b128(v2, o, (at + 8 * ldc) * 4u, 0, T256_KEEP);
+            for (int e = 0; e < 4; ++e) v[k][e] = fmaf(r[k][e], rr[y % 3][k], pre[i % RING][k][e]);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4t, v[k]), o, ((row + 4 * k) * (unsigned)ldc + col) * 4u, 0, T256_KEEP);
           }
           if (copied) {
-            u32x4t v1 = join(gained(v[0], 4 * h), gained(v[1], 4 * h + 1)), v2 = join(gained(v[2], 4 * h + 2), gained(v[3], 4 * h + 3));
-            lines(v1, v2);
-            const unsigned at = row8 * (unsigned)ldc2 + col + h8 * 32 + jcol;
-            __builtin_amdgcn_raw_buffer_store_b128(v1, o2, at * 2u, 0, T256_KEEP);
-            __builtin_amdgcn_raw_buffer_store_b128(v2, o2, (at + 8 * ldc2) * 2u, 0, T256_KEEP);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              f32x4t c = v[k];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) c[e] *= (float)gq[h][e];
+              __builtin_amdgcn_raw_buffer_store_b64(u32x2t{pack(c[0], c[1]), pack(c[2], c[3])}, o2, ((row + 4 * k) * (unsigned)ldc2 + col) * 2u, 0, T256_KEEP);
+            }
           }
           if (summed) {
-            const float p[4] = {ssq4(v[0]), ssq4(v[1]), ssq4(v[2]), ssq4(v[3])};
-            const float sum = sum64(p);
-            if (t_q == 0) part[(h * 2 + wx) * 256 + at16(wy, y) + l16] = sum;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const float sum = sum16(ssq4(v[k]));
+              if (c4 == 0) part[(h * 2 + wx) * 256 + row + 4 * k] = sum;
+            }
           }
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        });
         float* tpart = part + 4 * 256;
         if (TAIL && tile.half >= 0) {
           const float r = strip_scale();
@@ -612,29 +643,27 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
               for (int e = 0; e < 2; ++e) c[y & 1][k][e] = __builtin_bit_cast(f32x4t, __builtin_amdgcn_raw_buffer_load_b128(cs, at + 128 * k + 16 * e, 0, 0));
           };
           entries(0);
+          f32x4t v[8];
+          out16(N16{}, [&](int i, f32x4t (&out)[4]) __attribute__((always_inline)) {
+            const int y = i >> 1, h = i & 1;
+            if (h == 0) {
+              if (y < 7) { rs[y + 1] = scale_of(y + 1); entries(y + 1); }
 #pragma unroll
-          for (int y = 0; y < 8; ++y) {
-        if (y < 7) { rs[y + 1] = scale_of(y + 1); entries(y + 1); }
-            const unsigned row = (unsigned)(at16(wy, y) + l16);
-            f32x4t v[8];
+              for (int x = 0; x < 8; ++x) v[x] = take(y, x) * rs[y];
+              if (turn) {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) v[x] = take(y, x) * rs[y];
-            if (turn) {
+                for (int k = 0; k < HB; ++k)
 #pragma unroll
-              for (int k = 0; k < HB; ++k)
-#pragma unroll
-                for (int x = k; x < 8; x += 2 * HB) rotate(v[x], v[x + HB], c[y & 1][k][0], c[y & 1][k][1]);
+                  for (int x = k; x < 8; x += 2 * HB) rotate(v[x], v[x + HB], c[y & 1][k][0], c[y & 1][k][1]);
+              }
             }
 #pragma unroll
-            for (int x = 0; x < 8; x += 4) {
-              u32x4t v1 = join(v[x], v[x + 1]), v2 = join(v[x + 2], v[x + 3]);
-              lines(v1, v2);
-              const unsigned at = (row - l16 + l8) * (unsigned)ldc + col + x * 16 + h8 * 32 + jcol;
-              __builtin_amdgcn_raw_buffer_store_b128(v1, o, at * 2u, 0, T256_KEEP);
-              __builtin_amdgcn_raw_buffer_store_b128(v2, o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
+            for (int x = 0; x < 4; ++x) out[x] = v[4 * h + x];
+          }, [&](int i, const u32x4t (&r)[2]) __attribute__((always_inline)) {
+            const unsigned at = (unsigned)(at16(wy, i >> 1) + r8) * (unsigned)ldc + col + 64 * (i & 1) + 8 * c8;
+            __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_KEEP);
+            __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
+          });
           if (TAIL && tile.half >= 0) {
             const float r = strip_scale();
             const size_t m = m0_strip + l16;
