@@ -98,7 +98,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
   constexpr int A_ROWS = TAIL ? BM + 16 : BM;
   constexpr int A_BYTES = A_ROWS * ROWB, B_BYTES = BN * ROWB;
   constexpr int BN_OUT = (EPI == EPI_SWIGLU) ? BN / 2 : BN;   // output columns per tile
-  static_assert(BM % (WGM * 32) == 0 && BN % (WGN * 32) == 0, "wave tile must be a multiple of 32x32");
+  static_assert(BM % (WGM * 16) == 0 && BN % (WGN * 16) == 0, "wave tile must be a multiple of 16x16");
   static_assert(EPI != EPI_SWIGLU || WCOLS % 64 == 0, "SwiGLU: a wave owns whole gate/up pairs of 32-row weight blocks");
   static_assert(BM % (RPS * NW) == 0 && BN % (RPS * NW) == 0, "tile rows must divide into slabs per wave");
   static_assert(!TAIL || (BN <= NW * 32 && NW >= 2), "the tail strip gives each of the first BN / 32 waves two 16-column tiles");
@@ -801,10 +801,17 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
       // 3072, 7.9 / 8.9 for twelve of 768)
       if constexpr (EPI == EPI_STORE_F32) return launch_mfma_cfg<64, 64, 2, 2, EPI, false, 4>(table, first, g, s, st);
       break;
-    case 4:   // 32 x 128, waves side by side: only instantiated for the feature-map epilogue of the W_Q projection
-      // three k-tiles in LDS (two workgroups still fit on a CU)
-      // (six do not pay, also not for at most one workgroup per CU: 25.7 us with either for one cell of d 2048)
-      if constexpr (EPI == EPI_DPFP_READ) return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 3>(table, first, g, s, st);
+    case 4:   // only instantiated for the feature-map epilogue of the W_Q projection
+      // 32 x 64 where that holds all columns (d_mem 64): half of a 128-wide tile's copies and products would be of columns past d_mem.  Four waves of
+      // 16 x 32, four k-tiles in LDS (two workgroups still fit on a CU; three lose what the tile gains, six 0 - 25 %); two waves of 32 x 32
+      // and 64 x 64 tiles wait longer in the epilogue.  us per launch, 32 x 128 / 32 x 64 (means of a pass): 1B model, one cell 23.5 / 21.3,
+      // 1 - 8 cells 29.7 / 23.5, 16 cells of 528 rows 31.7 / 25.4, twelve of width 768 18.6 / 17.4
+      if constexpr (EPI == EPI_DPFP_READ) {
+        if (mfma_regular_shape<32, 64, EPI>(s) && s.N == 64) return launch_mfma_cfg<32, 64, 2, 2, EPI, true, 4>(table, first, g, s, st);
+        // else 32 x 128, waves side by side, three k-tiles in LDS (two workgroups still fit on a CU)
+        // (six do not pay, also not for at most one workgroup per CU: 25.7 us with either for one cell of d 2048)
+        return launch_mfma_cfg<32, 128, 1, 4, EPI, false, 3>(table, first, g, s, st);
+      }
       break;
     case 5:   // 256 x 256: the persistent tile of four waves (gemm_tile256.h), for other shapes 16 waves and one barrier per k-tile.  us per
               // launch, eight waves in four phases per k-tile (what was here) / four: gate/up of twelve cells of 1040 x 6144, K 768 107.0 / 94.3, of
