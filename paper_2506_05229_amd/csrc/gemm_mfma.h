@@ -782,9 +782,10 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
   const int tm = (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256;
   const int bn_out = (s.epi == EPI_SWIGLU) ? 128 : 256;
   const long tiles = (long)g * tm * ((s.N + bn_out - 1) / bn_out);
-  // measured crossover (1040-row cells, N = 768 ... 3072, K = 768 ... 8192): 128x128 tiles win up to 128 tiles of
-  // 256x256 (they still fit the chip in one round of two workgroups per CU), 256x256 tiles from 144 on
-  return (s.M >= 192 && s.N >= 192 && tiles >= 136) ? 5 : 6;
+  // measured crossover (1040- and 528-row cells, N = 768 ... 3072, K = 768 ... 8192): 128x128 tiles win up to 128 tiles of
+  // 256x256 (they still fit the chip in one round of two workgroups per CU; 2048 x 2048 at 128 tiles 39.4 us against 48.3), 256x256 tiles
+  // beyond (132 tiles: 768 x 768 29.0 us against 24.4, K 3072 81.1 against 66.8)
+  return (s.M >= 192 && s.N >= 192 && tiles > MF_CUS / 2) ? 5 : 6;
 }
 
 // Tile configuration by problem shape: big square tiles for the block's linears, small tiles for
