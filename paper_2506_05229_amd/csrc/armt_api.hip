@@ -510,25 +510,23 @@ armt_status forward_typed(Ctx& c, const void* mem_emb, const void* x, int64_t N,
       HIP_TRY(hipGetLastError());
     }
   }
-  auto ingest = [&](int64_t s) -> armt_status {       // Algorithm 1: ingest a new segment at layer 0
-    for (int b = 0; b < D.B; ++b) {                  // sequence b enters at cell b (layer 0)
-      const size_t slot = (size_t)b * D.T * D.d;
-      pack_segment_kernel<T><<<D.T, 256, 0, c.st>>>((const T*)x + b * seq + (size_t)s * D.S * D.d, (const T*)mem_emb, D.S, D.d,
-                                                    X + slot, Xb ? Xb + slot : nullptr);
-    }
+  // Between two steps: segment `out` went through all layers, segment `in` enters at layer 0 (Algorithm 1); -1: none.  Sequence b enters at cell b
+  // (layer 0) and leaves in slot L * B + b.
+  const bool vec = D.d % 4 == 0 && (((uintptr_t)x | (uintptr_t)mem_emb | (uintptr_t)hidden_out) % (4 * sizeof(T))) == 0;
+  auto edge = [&](int64_t out, int64_t in) -> armt_status {
+    const int out_rows = out >= 0 ? D.S : 0, in_rows = in >= 0 ? D.T : 0;
+    if (out_rows + in_rows == 0) return ARMT_OK;
+    const size_t slot = (size_t)D.T * D.d, segment = (size_t)D.S * D.d;
+    auto kern = vec ? segment_edge_kernel<T, true> : segment_edge_kernel<T, false>;
+    kern<<<dim3(out_rows + in_rows, D.B), 256, 0, c.st>>>((const T*)x + (in >= 0 ? in : 0) * segment, (const T*)mem_emb,
+                                                          (T*)hidden_out + (out >= 0 ? out : 0) * segment, seq, out_rows, D.S, D.d, slot, X, Xb,
+                                                          X + (size_t)D.L * slot);
     HIP_TRY(hipGetLastError());
     return ARMT_OK;
   };
-  auto emit = [&](int64_t s) -> armt_status {         // segment s went through all layers
-    for (int b = 0; b < D.B; ++b)                    // output of the last layer's cell of sequence b: slot L * B + b
-      store_hidden_kernel<T><<<D.S, 256, 0, c.st>>>(X + (size_t)(D.L + b) * D.T * D.d, D.d,
-                                                    (T*)hidden_out + b * seq + (size_t)s * D.S * D.d);
-    HIP_TRY(hipGetLastError());
-    return ARMT_OK;
-  };
+  ARMT_TRY(edge(-1, 0));
   if (!diagonal) {
     for (int64_t s = 0; s < N; ++s) {
-      ARMT_TRY(ingest(s));
       const bool empty = (s == 0 && !carry_in);
       for (int l = 0; l < L; ++l) {
         ARMT_TRY(save_tape(c, l, l, (int)s + l));
@@ -539,14 +537,13 @@ armt_status forward_typed(Ctx& c, const void* mem_emb, const void* x, int64_t N,
       // (the next layer's read adds to the fp32 slot in place, which is the only copy of the fp32 configurations): the updates of all
       // layers go out together.  A cell's three launches are 23 us of latencies, 16 cells' are 70.
       if (D.bf16) ARMT_TRY(update_group<T>(c, 0, L - 1, 0, empty ? L : 0));
-      ARMT_TRY(emit(s));
+      ARMT_TRY(edge(s, s + 1 < N ? s + 1 : -1));
     }
   } else {
     const int64_t steps = L + N - 1;
     for (int64_t t = 0; t < steps; ++t) {
       int32_t lo, hi;
       armt_diagonal_group(L, (int32_t)N, (int32_t)t, &lo, &hi);
-      if (t < N) ARMT_TRY(ingest(t));
       // only the cell of segment 0 (layer t, while t < L) can meet an empty memory
       const bool top_empty = (!carry_in && t < L);
       ARMT_TRY(save_tape(c, lo, hi, (int)t));
@@ -559,7 +556,7 @@ armt_status forward_typed(Ctx& c, const void* mem_emb, const void* x, int64_t N,
         ARMT_TRY(run_group<T>(c, lo, hi, top_empty ? hi - 1 : hi));
       }
       ARMT_TRY(update_group<T>(c, lo, hi, top_empty ? hi : 0, top_empty ? hi + 1 : 0));
-      if (hi == L - 1) ARMT_TRY(emit(t - (L - 1)));
+      ARMT_TRY(edge(hi == L - 1 ? t - (L - 1) : -1, t + 1 < N ? t + 1 : -1));
     }
   }
   return ARMT_OK;

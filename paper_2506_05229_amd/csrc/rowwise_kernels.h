@@ -18,27 +18,44 @@ struct LayerAux {
 };
 
 // ------------------------------------------------------------------------------------------------
-// Cell input of a new segment at layer 0: seg_len embedding rows followed by the n_mem memory-token
-// embeddings (Eq. 2, "[H, M]"; Algorithm 1, Segment).  grid: (T), block: 256.
-template <typename T>
-__global__ __launch_bounds__(256) void pack_segment_kernel(const T* __restrict__ x_seg,
-                                                           const T* __restrict__ mem_emb, int S, int d,
-                                                           float* __restrict__ X0, T* __restrict__ Xb0) {
-  const int r = blockIdx.x;
-  const T* src = (r < S) ? x_seg + (size_t)r * d : mem_emb + (size_t)(r - S) * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) {
-    const T v = src[c];
-    X0[(size_t)r * d + c] = to_f32(v);
-    if (Xb0) Xb0[(size_t)r * d + c] = v;
+// What goes in and out between two steps, in one launch: the hidden states of a segment that has passed all layers (rows [0, out_rows) of the grid: the
+// last layer's output at the token rows), and behind them the cell input of the next one at layer 0, its seg_len embedding rows followed by the
+// memory-token embeddings (Eq. 2, "[H, M]"; Algorithm 1, Segment).  Either may be missing.  grid: (out_rows + in_rows, sequences), block: 256.
+// Bound by its launch: as two launches per step and sequence 3.6 + 2.6 us (fp32, d 128), 4.8 + 5.0 (bf16, d 768); three sequences of the 1B model
+// 24.9 -> 24.7 ms a pass, the fp32 configuration 588 -> 584 us.
+// VEC: four elements per access, for buffers and rows that allow it.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void segment_edge_kernel(const T* __restrict__ x_in, const T* __restrict__ mem_emb, T* __restrict__ hidden_out,
+                                                           size_t seq, int out_rows, int S, int d, size_t slot, float* __restrict__ X0,
+                                                           T* __restrict__ Xb0, const float* __restrict__ XL) {
+  constexpr int E = VEC ? 4 : 1;
+  typedef T TE __attribute__((ext_vector_type(E)));
+  typedef float FE __attribute__((ext_vector_type(E)));
+  const size_t b = blockIdx.y;
+  int r = blockIdx.x;
+  if (r < out_rows) {
+    const float* from = XL + b * slot + (size_t)r * d;
+    T* to = hidden_out + b * seq + (size_t)r * d;
+    for (int c = threadIdx.x * E; c < d; c += 256 * E) {
+      const FE v = *(const FE*)(from + c);
+      TE o;
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[e] = from_f32<T>(v[e]);
+      *(TE*)(to + c) = o;
+    }
+    return;
   }
-}
-
-// Output of the last layer at the token rows of a segment -> hidden_out.  grid: (S), block: 256.
-template <typename T>
-__global__ __launch_bounds__(256) void store_hidden_kernel(const float* __restrict__ XL, int d,
-                                                           T* __restrict__ out) {
-  const size_t r = blockIdx.x;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) out[r * d + c] = from_f32<T>(XL[r * d + c]);
+  r -= out_rows;
+  const T* from = r < S ? x_in + b * seq + (size_t)r * d : mem_emb + (size_t)(r - S) * d;
+  const size_t to = b * slot + (size_t)r * d;
+  for (int c = threadIdx.x * E; c < d; c += 256 * E) {
+    const TE v = *(const TE*)(from + c);
+    FE o;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = to_f32(v[e]);
+    *(FE*)(X0 + to + c) = o;
+    if (Xb0) *(TE*)(Xb0 + to + c) = v;
+  }
 }
 
 __global__ void fill_f32_kernel(float* __restrict__ p, size_t n, float v) {
