@@ -839,6 +839,10 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
         }
         return launch_tile256<EPI>(table, first, g, s, st);
       }
+      // Regular shapes that the persistent tile leaves (one M-tile and a strip of 16 rows, two k-tiles): the same 16 waves without the address
+      // arithmetic of ragged ones.  us per launch, general / regular: 32 x (272 x 768, K 3072) 60.0 / 52.5, 32 x (272 x 3072, K 2048)
+      // 148.0 / 147.7, 16 x (272 x 8192, K 2048) 157.1 / 156.8; eight waves of it 55.1 / 149.7 / 160.3
+      if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) return launch_mfma_cfg<256, 256, 4, 4, EPI, true>(table, first, g, s, st);
       return launch_mfma_cfg<256, 256, 4, 4, EPI>(table, first, g, s, st);
     case 6:   // as 1, copies addressed by scalar base + lane offset where the shape allows
       // Eight waves of 32 x 64 instead of four of 64 x 64: two workgroups of four waves leave a SIMD two waves, which wait for their

@@ -20,6 +20,8 @@ def tile_config():
     (3, 2064, 4096, 192),       # 384 tiles on 256 workgroups, strip on two M-tiles of each group
     (2, 768, 97 * 256, 448),    # 582 tiles, seven k-tiles
     (1, 33 * 256, 8 * 256, 256),        # 33 M-tiles in five M-groups, the last of five
+    (20, 272, 7 * 256, 320),    # 16 waves: a strip behind a single M-tile
+    (3, 2064, 4096, 128),       # 16 waves: two k-tiles
 ])
 def test_store(tile_config, g, M, N, K):
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
