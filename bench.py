@@ -221,7 +221,7 @@ def main():
         flops_per_cell = 2.0 * shape.T * shape.d_model * 2 * shape.d_ff
         per_launch = flops_per_cell * k_groups / k_launches
         achieved = per_launch / (k_ms / k_launches / 1e3) / 1e12
-        res["roofline"] = {"kernel": "gemm_mfma_kernel<..., EPI_SWIGLU> (gate/up grouped GEMM + SiLU*up)",
+        res["roofline"] = {"kernel": "gemm_tile256_kernel<EPI_SWIGLU, ...> (gate/up grouped GEMM + SiLU*up)",
                            "bound": "mfma", "achieved": achieved, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                            "frac": achieved / MFMA_PEAK_TFLOPS,
                            "traffic": (traffic_cell * k_groups / k_launches
