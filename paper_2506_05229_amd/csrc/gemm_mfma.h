@@ -629,22 +629,26 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
 #endif
 }
 
+// M-tiles of 256 rows, of which the last takes a strip of 16 rows behind it along
+constexpr int mfma_m_tiles(const GemmShape& s) { return (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256; }
+
 // M-tiles (of 256 rows) that follow one another on a weight panel.  The 32 compute units of an XCD work on 32 consecutive
 // tiles of the order: with 4 to 8 M-tiles side by side these touch 11 to 12 operand panels, with 32 of one weight panel
 // 33 (a weight gradient of 8192 x 2048, or the head's).  Tall problems are cut into equal groups of at most 8: one product of
 // 8192^3 1.24 -> 1.38 PFLOP/s, 8 weight gradients of 8192 x 2048 x 8704 1.13 -> 1.31.
-inline int mfma_m_group(const GemmShape& s) {
-  const int tm = (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256, n = (tm + 7) / 8;
+constexpr int mfma_m_group(const GemmShape& s) {
+  const int tm = mfma_m_tiles(s), n = (tm + 7) / 8;
   return (tm + n - 1) / n;
 }
 
 // Part of a launch's work, so that two tile sizes can share it: units [begin, end), a unit being the tiles of one M-group
 // on one panel of unit_cols output columns, in the order of the tiles.  unit_cols = 0: everything.
 struct TileRange { int unit_cols = 0, begin = 0, end = 0; };
+constexpr int mfma_units(const GemmShape& s, int g, int panels) { return g * ((mfma_m_tiles(s) + mfma_m_group(s) - 1) / mfma_m_group(s)) * panels; }
 
 // First tile of unit u (counted over the groups) for tiles of BM rows of which `tiles_m` cover M, m_group (of BM rows) and
 // tiles_n N-tiles per group, cols_per_unit of them in a unit.
-inline int mfma_unit_tile(int u, int tiles_m, int m_group, int tiles_n, int cols_per_unit) {
+constexpr int mfma_unit_tile(int u, int tiles_m, int m_group, int tiles_n, int cols_per_unit) {
   const int panels = tiles_n / cols_per_unit, n_mg = (tiles_m + m_group - 1) / m_group;
   const int grp = u / (n_mg * panels), r = u % (n_mg * panels), mg = r / panels, p = r % panels;
   const int rows = tiles_m - mg * m_group < m_group ? tiles_m - mg * m_group : m_group;
@@ -688,7 +692,7 @@ inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, Gem
 // Shapes that the persistent 256 x 256 tile takes, of the regular ones: at least three k-tiles, rows that can be stored in 16-byte pieces and reached by
 // 32-bit offsets from a tile's first row, heads of 64 or 128 columns (a wave's columns hold whole ones).
 template <int EPI>
-inline bool tile256_shape(const GemmShape& s) {
+constexpr bool tile256_shape(const GemmShape& s) {
   constexpr int LD = 1 << 21;
   // its copies are two k-tiles ahead, but never more than one tile
   if (s.K < 3 * MF_BK || (s.k_slot > 0 && (s.k_min > 0 ? s.k_min : s.k_slot) < 3)) return false;
@@ -739,7 +743,7 @@ inline hipError_t launch_tile256(const GemmGroup* table, int first, int g, GemmS
 // M = tiles * BM + 16 (a cell: seg_len rows + 16 memory rows) takes the tail variant.
 // shapes the copy-wave variant addresses with one lane offset per operand
 template <int BM, int BN, int EPI>
-inline bool mfma_regular_shape(const GemmShape& s) {
+constexpr bool mfma_regular_shape(const GemmShape& s) {
   constexpr int BN_OUT = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   const bool m_ok = s.M % BM == 0 || (s.M > BM && s.M % BM == 16 && !(s.dbg & 32)) || s.a_rows >= (s.M + BM - 1) / BM * BM;
   const int e0 = s.n0, e1 = s.n0 + s.n1;      // ends of weight blocks 0 and 1
@@ -779,13 +783,30 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
   if (s.epi != EPI_DPFP_READ && tiles_of(64) <= MF_CUS) return s.K > 2 * MF_BK ? 7 : 2;
   if (s.M < 96 || s.N < 96) return 2;
   if (s.epi != EPI_DPFP_READ && tiles_of(128) <= MF_CUS) return 8;
-  const int tm = (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256;
   const int bn_out = (s.epi == EPI_SWIGLU) ? 128 : 256;
-  const long tiles = (long)g * tm * ((s.N + bn_out - 1) / bn_out);
+  const long tiles = (long)g * mfma_m_tiles(s) * ((s.N + bn_out - 1) / bn_out);
   // measured crossover (1040- and 528-row cells, N = 768 ... 3072, K = 768 ... 8192): 128x128 tiles win up to 128 tiles of
   // 256x256 (they still fit the chip in one round of two workgroups per CU; 2048 x 2048 at 128 tiles 39.4 us against 48.3), 256x256 tiles
   // beyond (132 tiles: 768 x 768 29.0 us against 24.4, K 3072 81.1 against 66.8)
   return (s.M >= 192 && s.N >= 192 && tiles > MF_CUS / 2) ? 5 : 6;
+}
+
+// Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs as 128 x 128 tiles (four
+// times as many, two workgroups per CU: one short round instead of a long one that leaves most CUs idle).  The units (TileRange) that keep
+// 256 x 256 tiles, 0: all of them.  Both tile sizes give the same bits (same order of the k-steps, row sums of squares at a fixed
+// granularity), so where the cut falls does not show in the result.  The kernel that takes the whole rounds has no say in it; us per launch of those that the
+// persistent tile leaves, one launch / cut: 9 x (272 x 8192, K 2048) 134 / 117, 32 x (272 x 3072, K 2048) 147 / 138, 12 x (1040 x 3072, K 128)
+// 34.6 / 33.3, 9 x (1040 x 2048, K 64) 22.4 / 21.0.
+template <int EPI>
+constexpr int mfma_round_cut(const GemmShape& s, int g, int force_cfg) {
+  if (EPI == EPI_SWIGLU || EPI == EPI_DPFP_READ || force_cfg >= 0 || s.spread || !mfma_regular_shape<256, 256, EPI>(s) ||
+      !mfma_regular_shape<128, 128, EPI>(s))
+    return 0;
+  const int tm = mfma_m_tiles(s), mg = mfma_m_group(s), panels = s.N / 256, tiles = g * tm * panels, rem = tiles % MF_CUS;
+  if (tiles <= MF_CUS || rem == 0 || rem > MF_CUS / 2) return 0;
+  int cut = mfma_units(s, g, panels);                 // the last units that hold at least the tiles of the partial round
+  while (cut > 0 && tiles - mfma_unit_tile(cut, tm, mg, panels, 1) < rem) --cut;
+  return cut;
 }
 
 // Tile configuration by problem shape: big square tiles for the block's linears, small tiles for
@@ -818,31 +839,26 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
               // launch, eight waves in four phases per k-tile (what was here) / four: gate/up of twelve cells of 1040 x 6144, K 768 107.0 / 94.3, of
               // the 3B model (mean of its launches) 907 / 824, of the 1B model 346 / 315; QKV 56.7 / 50.1, 325 / 310, 70.5 / 66.5; attention
               // output, down and read of K 3072 and 8192 275 / 272, of the 768-wide model, whose launches are at most one tile per CU, 57.6 / 60.9
-      if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s) && tile256_shape<EPI>(s)) {
+      // Regular shapes that the persistent tile leaves (one M-tile and a strip of 16 rows, two k-tiles): the same 16 waves without the address
+      // arithmetic of ragged ones.  us of one launch, general / regular: 32 x (272 x 768, K 3072) 60.0 / 52.5, 32 x (272 x 3072, K 2048)
+      // 148.0 / 147.7, 16 x (272 x 8192, K 2048) 157.1 / 156.8; eight waves of it 55.1 / 149.7 / 160.3
+      if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) {
+        auto tiles_256 = [&](const TileRange& rng) {
+          return tile256_shape<EPI>(s) ? launch_tile256<EPI>(table, first, g, s, st, rng) : launch_mfma_cfg<256, 256, 4, 4, EPI, true>(table, first, g, s, st, rng);
+        };
         if constexpr (EPI != EPI_SWIGLU) {
-          // Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs
-          // as 128 x 128 tiles (four times as many, two workgroups per CU: one short round instead of a long one
-          // that leaves most CUs idle).  Both tile sizes give the same bits (same order of the k-steps, row sums
-          // of squares at a fixed granularity), so where the cut falls does not show in the result.
-          const int tm = (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256, mg = mfma_m_group(s), panels = s.N / 256;
-          const int tiles = g * tm * panels, rem = tiles % MF_CUS, units = g * ((tm + mg - 1) / mg) * panels;
-          int cut = units;                 // the last units that hold at least the tiles of the partial round
-          while (cut > 0 && tiles - mfma_unit_tile(cut, tm, mg, panels, 1) < rem) --cut;
-          if (force_cfg < 0 && !s.spread && tiles > MF_CUS && rem != 0 && rem <= MF_CUS / 2 && cut > 0 && mfma_regular_shape<128, 128, EPI>(s)) {
+          const int cut = mfma_round_cut<EPI>(s, g, force_cfg);
+          if (cut > 0) {
             TileRange big, rest;
             big.unit_cols = rest.unit_cols = 256;
-            big.begin = 0; big.end = rest.begin = cut; rest.end = units;
-            hipError_t e = launch_tile256<EPI>(table, first, g, s, st, big);
+            big.begin = 0; big.end = rest.begin = cut; rest.end = mfma_units(s, g, s.N / 256);
+            hipError_t e = tiles_256(big);
             if (e != hipSuccess) return e;
             return launch_mfma_cfg<128, 128, 4, 2, EPI, true>(table, first, g, s, st, rest);
           }
         }
-        return launch_tile256<EPI>(table, first, g, s, st);
+        return tiles_256(TileRange());
       }
-      // Regular shapes that the persistent tile leaves (one M-tile and a strip of 16 rows, two k-tiles): the same 16 waves without the address
-      // arithmetic of ragged ones.  us per launch, general / regular: 32 x (272 x 768, K 3072) 60.0 / 52.5, 32 x (272 x 3072, K 2048)
-      // 148.0 / 147.7, 16 x (272 x 8192, K 2048) 157.1 / 156.8; eight waves of it 55.1 / 149.7 / 160.3
-      if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) return launch_mfma_cfg<256, 256, 4, 4, EPI, true>(table, first, g, s, st);
       return launch_mfma_cfg<256, 256, 4, 4, EPI>(table, first, g, s, st);
     case 6:   // as 1, copies addressed by scalar base + lane offset where the shape allows
       // Eight waves of 32 x 64 instead of four of 64 x 64: two workgroups of four waves leave a SIMD two waves, which wait for their

@@ -1,0 +1,35 @@
+"""Which tiles a launch of the grouped bf16 GEMM takes: the rules are constant expressions, evaluated by the compiler on the host side alone (no GPU)."""
+import os
+import subprocess
+
+import pytest
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_05229_amd", "csrc")
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+
+
+def holds(tmp_path, *facts):
+    """Compiles `facts`, C++ conditions, as static assertions behind the dispatch's source; what fails is in the message."""
+    source = tmp_path / "facts.hip"
+    source.write_text('#include "gemm_mfma.h"\nusing namespace armt;\n'
+                      "constexpr GemmShape product(int M, int N, int K) {\n"
+                      "  GemmShape s{};\n"
+                      "  s.M = M; s.N = N; s.K = K; s.lda = s.ldb = K; s.ldc = N; s.n0 = N;\n"
+                      "  return s;\n}\n" + "".join(f'static_assert({f}, "");\n' for f in facts))
+    done = subprocess.run([HIPCC, "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-fsyntax-only", "-I", CSRC, str(source)],
+                          capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
+
+
+def test_partial_round(tmp_path):
+    """Up to half a round of 256 x 256 tiles behind whole ones runs as 128 x 128 tiles, whatever kernel the whole ones take."""
+    cut = "mfma_round_cut<EPI_STORE_ACT>"
+    holds(tmp_path,
+          f"{cut}(product(272, 3072, 2048), 32, -1) == 256",      # 384 tiles, a strip behind a single M-tile: units of one tile
+          f"{cut}(product(1040, 3072, 128), 12, -1) == 128",      # 576 tiles, two k-tiles: units of four
+          f"{cut}(product(4352, 4352, 192), 1, -1) == 44",        # 289 tiles, M-groups of 6, 6 and 5 M-tiles: seven panels of the last one are cut off
+          f"{cut}(product(4352, 4352, 128), 1, -1) == 44",
+          f"{cut}(product(1040, 2048, 2048), 8, -1) == 0",        # one round
+          f"{cut}(product(1040, 2048, 2048), 14, -1) == 0",       # 448 tiles: more than half a round is left
+          f"{cut}(product(4352, 4352, 192), 1, 5) == 0")          # tiles asked for
