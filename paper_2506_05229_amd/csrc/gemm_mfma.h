@@ -697,19 +697,15 @@ constexpr bool tile256_shape(const GemmShape& s) {
   // its copies are two k-tiles ahead, but never more than one tile
   if (s.K < 3 * MF_BK || (s.k_slot > 0 && (s.k_min > 0 ? s.k_min : s.k_slot) < 3)) return false;
   if (((s.N | s.ldc | s.ldr | s.ldc2) & 3) != 0 || s.lda > LD || s.ldb > LD || s.ldc > LD || s.ldr > LD || s.ldc2 > LD) return false;
-  if (s.M > 256 && s.M % 256 == 16 && !(s.dbg & 32)) {      // two M-tiles of the last M-group share the strip
-    const int tm = s.M / 256, mg = mfma_m_group(s);
-    if (tm - (tm - 1) / mg * mg < 2) return false;
-  }
   return EPI != EPI_QKV_ROPE || s.ldr == 64 || s.ldr == 128;
 }
 
 template <int EPI>
 inline hipError_t launch_tile256(const GemmGroup* table, int first, int g, GemmShape s, hipStream_t st, const TileRange& rng = TileRange()) {
   constexpr int BN_OUT = EPI == EPI_SWIGLU ? 128 : 256;
-  const bool tail = s.M > 256 && s.M % 256 == 16 && !(s.dbg & 32);
+  const bool strip = s.M > 256 && s.M % 256 == 16 && !(s.dbg & 32);
   TileWalk w;
-  w.tiles_m = tail ? s.M / 256 : (s.M + 255) / 256;
+  w.tiles_m = strip ? s.M / 256 : (s.M + 255) / 256;
   w.tiles_n = s.N / BN_OUT;
   w.m_group = mfma_m_group(s);
   w.begin = 0;
@@ -723,15 +719,19 @@ inline hipError_t launch_tile256(const GemmGroup* table, int first, int g, GemmS
   w.r_group = t256_recip(w.tiles_m * w.tiles_n);
   w.r_mgroup = t256_recip(w.m_group * w.tiles_n);
   w.r_full = t256_recip(w.m_group < w.tiles_m ? w.m_group : w.tiles_m);
-  w.r_last = t256_recip(w.tiles_m - (w.tiles_m - 1) / w.m_group * w.m_group);
+  const int last_group = w.tiles_m - (w.tiles_m - 1) / w.m_group * w.m_group;      // M-tiles of the last M-group: two share the strip, where there are
+  w.r_last = t256_recip(last_group);
   w.r_share = t256_recip(w.tiles_m * w.tiles_n / 8);
   const int grid = w.total < MF_CUS ? (w.total + 7) / 8 * 8 : MF_CUS;
   constexpr int HB = EPI == EPI_QKV_ROPE ? 2 : 0;
   const bool wide = HB > 0 && s.ldr == 128;
-  auto kern = wide ? (tail ? gemm_tile256_kernel<EPI, true, 2 * HB> : gemm_tile256_kernel<EPI, false, 2 * HB>)
-                   : (tail ? gemm_tile256_kernel<EPI, true, HB> : gemm_tile256_kernel<EPI, false, HB>);
-  static std::atomic<uint64_t> lds_raised[4];
-  const hipError_t e = raise_lds_limit((const void*)kern, T256_LDS, lds_raised[2 * wide + tail]);
+  const int tail = !strip ? 0 : last_group > 1 ? 1 : 2;
+  static const decltype(&gemm_tile256_kernel<EPI, 0, HB>) kernels[2][3] = {
+      {gemm_tile256_kernel<EPI, 0, HB>, gemm_tile256_kernel<EPI, 1, HB>, gemm_tile256_kernel<EPI, 2, HB>},
+      {gemm_tile256_kernel<EPI, 0, 2 * HB>, gemm_tile256_kernel<EPI, 1, 2 * HB>, gemm_tile256_kernel<EPI, 2, 2 * HB>}};
+  auto kern = kernels[wide][tail];
+  static std::atomic<uint64_t> lds_raised[2][3];
+  const hipError_t e = raise_lds_limit((const void*)kern, T256_LDS, lds_raised[wide][tail]);
   if (e != hipSuccess) return e;
 #ifdef ARMT_GEMM_TIMELINE
   if (s.tag == g_tl_kind && g_tl_countdown >= 0 && g_tl_countdown-- == 0) s.dbg |= 1 << 20;
@@ -794,9 +794,9 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
 // Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs as 128 x 128 tiles (four
 // times as many, two workgroups per CU: one short round instead of a long one that leaves most CUs idle).  The units (TileRange) that keep
 // 256 x 256 tiles, 0: all of them.  Both tile sizes give the same bits (same order of the k-steps, row sums of squares at a fixed
-// granularity), so where the cut falls does not show in the result.  The kernel that takes the whole rounds has no say in it; us per launch of those that the
-// persistent tile leaves, one launch / cut: 9 x (272 x 8192, K 2048) 134 / 117, 32 x (272 x 3072, K 2048) 147 / 138, 12 x (1040 x 3072, K 128)
-// 34.6 / 33.3, 9 x (1040 x 2048, K 64) 22.4 / 21.0.
+// granularity), so where the cut falls does not show in the result.  The kernel that takes the whole rounds has no say in it; us per launch with 16 waves,
+// one launch / cut: 9 x (272 x 8192, K 2048) 134 / 117, 32 x (272 x 3072, K 2048) 147 / 138, 12 x (1040 x 3072, K 128) 34.6 / 33.3, 9 x (1040 x 2048,
+// K 64) 22.4 / 21.0.
 template <int EPI>
 constexpr int mfma_round_cut(const GemmShape& s, int g, int force_cfg) {
   if (EPI == EPI_SWIGLU || EPI == EPI_DPFP_READ || force_cfg >= 0 || s.spread || !mfma_regular_shape<256, 256, EPI>(s) ||
@@ -839,9 +839,8 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
               // launch, eight waves in four phases per k-tile (what was here) / four: gate/up of twelve cells of 1040 x 6144, K 768 107.0 / 94.3, of
               // the 3B model (mean of its launches) 907 / 824, of the 1B model 346 / 315; QKV 56.7 / 50.1, 325 / 310, 70.5 / 66.5; attention
               // output, down and read of K 3072 and 8192 275 / 272, of the 768-wide model, whose launches are at most one tile per CU, 57.6 / 60.9
-      // Regular shapes that the persistent tile leaves (one M-tile and a strip of 16 rows, two k-tiles): the same 16 waves without the address
-      // arithmetic of ragged ones.  us of one launch, general / regular: 32 x (272 x 768, K 3072) 60.0 / 52.5, 32 x (272 x 3072, K 2048)
-      // 148.0 / 147.7, 16 x (272 x 8192, K 2048) 157.1 / 156.8; eight waves of it 55.1 / 149.7 / 160.3
+      // Regular shapes that the persistent tile leaves (one or two k-tiles): the same 16 waves without the address arithmetic of ragged ones.  us per
+      // launch, general / regular: 12 x (1040 x 3072, K 128) 33.6 / 32.5, 8 x (1024 x 8192, K 128) 45.4 / 44.4, 16 x (1040 x 8192, K 64) 77.2 / 78.1
       if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) {
         auto tiles_256 = [&](const TileRange& rng) {
           return tile256_shape<EPI>(s) ? launch_tile256<EPI>(table, first, g, s, st, rng) : launch_mfma_cfg<256, 256, 4, 4, EPI, true>(table, first, g, s, st, rng);

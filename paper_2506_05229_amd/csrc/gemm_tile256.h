@@ -57,12 +57,16 @@ constexpr int T256_KEEP = 2;
 
 constexpr int T256_STAGE = 65536;                             // a k-tile: 256 rows of A, 256 of B
 constexpr int T256_STRIP = 2 * T256_STAGE;                    // two buffers of the 16 strip rows
-constexpr int T256_SSQ = T256_STRIP + 2 * 2048;               // sums of squares: [half][wave column][256], strip [wave][16]
-constexpr int T256_OUT = T256_SSQ + 4 * 256 * 4 + 4 * 16 * 4;      // results on their way out: 4 KB per wave
+constexpr int T256_SSQ = T256_STRIP + 2 * 2048;               // sums of squares: [half][wave column][256], strip [half][wave][16]
+constexpr int T256_OUT = T256_SSQ + 4 * 256 * 4 + 2 * 4 * 16 * 4;      // results on their way out: 4 KB per wave
 constexpr int T256_LDS = T256_OUT + 4 * 4096;
 
+// TAIL: 16 rows behind the last M-tile, the strip.  1: the last M-tile and the one in front of it compute it, half of the columns each.  2: the
+// last M-group has one M-tile only (cells of 256 + 16 rows), which computes both halves: 8 of 136 products a wave and k-tile.  us per launch, 16 waves / so:
+// 16 x (272 x 8192, K 2048) 157 / 145, 24 x (272 x 2048, K 2048) 61.9 / 53.8, 32 x (272 x 2048, K 8192) 291 / 276, 1 x (14608 x 2048, K 2048)
+// 102.5 / 97.3, gate/up of four cells of the 1B model 79.0 / 76.6; its pass over 48 segments 40.1 / 38.6 ms.
 // HB: EPI_QKV_ROPE, blocks of 16 columns in half a head (2 or 4), otherwise 0
-template <int EPI, bool TAIL, int HB>
+template <int EPI, int TAIL, int HB>
 __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __restrict__ table_g, int first, GemmShape s, TileWalk w) {
   constexpr bool ROPE = EPI == EPI_QKV_ROPE, GLU = EPI == EPI_SWIGLU, RESID = EPI == EPI_RESID_F32;
   constexpr int ROWB = 128, BN_OUT = GLU ? 128 : 256;
@@ -73,9 +77,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
   const int m0_strip = w.tiles_m * 256;
   const ConstGroups table = (ConstGroups)table_g + first;
 
-  struct Tile { int r, grp, m0, n0, nk, half; };               // half: of the strip's columns, that it computes; -1 none
-  // The 16 rows behind the last M-tile: the last M-tile and the one in front of it compute them, half of the columns each (tile256_shape: the last
-  // M-group has two).
+  struct Tile { int r, grp, m0, n0, nk, half; };               // half: first of the strip's halves that it computes; -1 none
   // first tile of this workgroup's sequence from number r on that has something to do; r = -1: none
   auto tile_from = [&](int r) __attribute__((always_inline)) {
     Tile t{-1, 0, 0, 0, 0, -1};
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       t.nk = (range ? range[1] * s.k_slot : s.K / MF_BK);
       if (t.nk <= 0) continue;
       t.m0 = tm * 256; t.n0 = tn * BN_OUT; t.r = r;
-      t.half = TAIL && from_end < 2 ? from_end : -1;
+      t.half = from_end < (TAIL == 1 ? 2 : TAIL == 2) ? from_end : -1;
       return t;
     }
   };
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) koff[ks] = ((4 * ks + t_q) ^ mf_swz(l16)) << 4;
   bf16x8 fx[2][8], fy[2][8];
-  f32x4t acc[8][8], tacc[2];
+  f32x4t acc[8][8], tacc[TAIL == 2 ? 2 : 1][2];
   auto transposed = [&](const Tile& t) { return ROPE && s.ldc2 > 0 && t.n0 >= s.n0 + s.n1; };      // V tile
   Tile tile{-1, 0, 0, 0, 0, -1};                               // the one that is multiplied
   int x_base, y_base;
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
     if (q < 16 && (q & 1) == 0) fx[ks][i] = *(const bf16x8*)(p + xb + at);
     else fy[ks][i] = *(const bf16x8*)(p + yb + at);
   };
-  // Strip: a wave computes two blocks of the tile's half, 16 rows x 16 columns at tile rows (of the weights) strip_row(h, 0) and (h, 1): 32
+  // Strip: a wave computes two blocks of a half, 16 rows x 16 columns at tile rows (of the weights) strip_row(h, 0) and (h, 1): 32
   // neighbouring columns, the two that a rotation mixes, or the gate and the up projection of the same columns.  The fragments are read again
   // (an address costs nothing, a choice of registers a branch), the products written as instructions: the accumulators fill one half of the register
   // file, and the compiler does not mix the halves.  It does not look into the text for hazards either: two wait states behind a vector
@@ -189,7 +191,8 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
     if (ROPE && !transposed(t)) return t.half * 128 + (HB == 2 ? (wave >> 1) * 64 + (wave & 1) * 16 + b * 32 : wave * 16 + b * 64);
     return t.half * 128 + wave * 32 + b * 16;
   };
-  auto strip = [&](int buf, int r0, int r1, bool vt) __attribute__((always_inline)) {
+  constexpr int HALF = GLU ? 64 : 128;                        // rows of the weights between the halves
+  auto strip_half = [&](int buf, int r0, int r1, bool vt, f32x4t (&tacc)[2]) __attribute__((always_inline)) {
     const unsigned char* pt = smem + T256_STRIP + buf * 2048 + l16 * ROWB;
     const unsigned char* pb = smem + buf * T256_STAGE + 32768 + l16 * ROWB;
     const bf16x8 a0 = *(const bf16x8*)(pt + koff[0]), a1 = *(const bf16x8*)(pt + koff[1]);
@@ -203,6 +206,10 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %4, %2, %0\n\tv_mfma_f32_16x16x32_bf16 %1, %5, %2, %1\n\t"
                    "v_mfma_f32_16x16x32_bf16 %0, %6, %3, %0\n\tv_mfma_f32_16x16x32_bf16 %1, %7, %3, %1\n\ts_nop 10"
                    : "+v"(tacc[0]), "+v"(tacc[1]) : "v"(a0), "v"(a1), "v"(b0), "v"(c0), "v"(b1), "v"(c1));
+  };
+  auto strip = [&](int buf, int r0, int r1, bool vt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < TAIL; ++h) strip_half(buf, r0 + h * HALF, r1 + h * HALF, vt, tacc[h]);
   };
   // A product, its accumulator held in the accumulation half of the register file: left to choose, the compiler moves accumulators and fragments
   // between the halves in the middle of the loop.  (The fragments are LDS reads, which it waits for; the accumulators are written and read by others only
@@ -262,10 +269,8 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       tl[2] = tl[3] = __builtin_readcyclecounter();
     }
 #endif
-    if (TAIL) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) tacc[t] = f32x4t{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int t = 0; t < 2 * TAIL; ++t) tacc[t >> 1][t & 1] = f32x4t{0.f, 0.f, 0.f, 0.f};
     const int r0 = strip_row(tile, 0), r1 = strip_row(tile, 1);
     int left = tile.nk;
     // second step of a k-tile, with the last N copies of the one after next
@@ -442,9 +447,9 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
         f32x4t r = {1.f, 1.f, 1.f, 1.f};
         if (g.rowscale) r = *(const f32x4t*)(g.rowscale + m0_strip + 4 * t_q);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const f32x4t v = tacc[t] * r;
-          *(u32x2t*)(ts + (size_t)t * 16 * ldc2) = u32x2t{pack(v[0], v[1]), pack(v[2], v[3])};
+        for (int t = 0; t < 2 * TAIL; ++t) {
+          const f32x4t v = tacc[t >> 1][t & 1] * r;
+          *(u32x2t*)(ts + (size_t)((t >> 1) * HALF + (t & 1) * 16) * ldc2) = u32x2t{pack(v[0], v[1]), pack(v[2], v[3])};
         }
       }
     } else if constexpr (GLU) {
@@ -467,10 +472,13 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
       });
       if (TAIL && tile.half >= 0) {
         const float r = strip_scale();
-        f32x4t v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = silu_mul(r * tacc[0][e], r * tacc[1][e]);
-        *(u32x2t*)((bf16*)g.C + (size_t)(m0_strip + l16) * ldc + tile.n0 + r0 + 4 * t_q) = u32x2t{pack(v[0], v[1]), pack(v[2], v[3])};
+        for (int h = 0; h < TAIL; ++h) {
+          f32x4t v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = silu_mul(r * tacc[h][0][e], r * tacc[h][1][e]);
+          *(u32x2t*)((bf16*)g.C + (size_t)(m0_strip + l16) * ldc + tile.n0 + r0 + h * HALF + 4 * t_q) = u32x2t{pack(v[0], v[1]), pack(v[2], v[3])};
+        }
       }
     } else {
       float rs[8];
@@ -493,9 +501,9 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
           const float r = strip_scale();
           bf16* out = (bf16*)g.C + (size_t)(m0_strip + l16) * ldc + tile.n0 + r0 + 4 * t_q;
 #pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            const f32x4t v = tacc[t] * r;
-            *(u32x2t*)(out + 16 * t) = u32x2t{pack(v[0], v[1]), pack(v[2], v[3])};
+          for (int t = 0; t < 2 * TAIL; ++t) {
+            const f32x4t v = tacc[t >> 1][t & 1] * r;
+            *(u32x2t*)(out + (t >> 1) * HALF + (t & 1) * 16) = u32x2t{pack(v[0], v[1]), pack(v[2], v[3])};
           }
         }
       } else if constexpr (EPI == EPI_STORE_F32) {
@@ -509,7 +517,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
           const float r = strip_scale();
           float* out = (float*)g.C + (size_t)(m0_strip + l16) * ldc + tile.n0 + r0 + 4 * t_q;
 #pragma unroll
-          for (int t = 0; t < 2; ++t) *(f32x4t*)(out + 16 * t) = tacc[t] * r;
+          for (int t = 0; t < 2 * TAIL; ++t) *(f32x4t*)(out + (t >> 1) * HALF + (t & 1) * 16) = tacc[t >> 1][t & 1] * r;
         }
       } else if constexpr (RESID) {
         float* part = (float*)(smem + T256_SSQ);
@@ -603,30 +611,33 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
         if (TAIL && tile.half >= 0) {
           const float r = strip_scale();
           const size_t m = m0_strip + l16;
-          float q[2];
 #pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            const int n = nc + r0 + 16 * b;
-            f32x4t v = {0.f, 0.f, 0.f, 0.f};
-            if (g.R) v = *(const f32x4t*)(g.R + m * ldr + n);
+          for (int h = 0; h < TAIL; ++h) {
+            float q[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaf(tacc[b][e], r, v[e]);
-            *(f32x4t*)((float*)g.C + m * ldc + n) = v;
-            if (copied) {
-              f32x4t c = v;
-              if (g.gain) {
-                const bf16x4 gb = *(const bf16x4*)((const bf16*)g.gain + n);
+            for (int b = 0; b < 2; ++b) {
+              const int n = nc + r0 + h * HALF + 16 * b;
+              f32x4t v = {0.f, 0.f, 0.f, 0.f};
+              if (g.R) v = *(const f32x4t*)(g.R + m * ldr + n);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) c[e] = v[e] * (float)gb[e];
+              for (int e = 0; e < 4; ++e) v[e] = fmaf(tacc[h][b][e], r, v[e]);
+              *(f32x4t*)((float*)g.C + m * ldc + n) = v;
+              if (copied) {
+                f32x4t c = v;
+                if (g.gain) {
+                  const bf16x4 gb = *(const bf16x4*)((const bf16*)g.gain + n);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) c[e] = v[e] * (float)gb[e];
+                }
+                *(u32x2t*)((bf16*)g.C2 + m * ldc2 + n) = u32x2t{pack(c[0], c[1]), pack(c[2], c[3])};
               }
-              *(u32x2t*)((bf16*)g.C2 + m * ldc2 + n) = u32x2t{pack(c[0], c[1]), pack(c[2], c[3])};
+              q[b] = ssq4(v);
             }
-            q[b] = ssq4(v);
-          }
-          if (summed) {
-            const float z4[4] = {q[0], q[1], 0.f, 0.f};        // (+ 0 leaves the bits of a sum of squares)
-            const float sum = sum64(z4);
-            if (t_q == 0) tpart[wave * 16 + l16] = sum;
+            if (summed) {
+              const float z4[4] = {q[0], q[1], 0.f, 0.f};        // (+ 0 leaves the bits of a sum of squares)
+              const float sum = sum64(z4);
+              if (t_q == 0) tpart[h * 64 + wave * 16 + l16] = sum;
+            }
           }
         }
         if (summed) {
@@ -637,8 +648,13 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
 #pragma unroll
             for (int h = 0; h < 2; ++h) g.ssq_out[(size_t)(tile.m0 + tid) * parts + (tile.n0 >> 7) + h] = part[h * 2 * 256 + tid] + part[(h * 2 + 1) * 256 + tid];
           }
-          if (TAIL && tid < 16 && tile.half >= 0)
-            g.ssq_out[(size_t)(m0_strip + tid) * parts + (tile.n0 >> 7) + tile.half] = (tpart[tid] + tpart[tid + 16]) + (tpart[tid + 32] + tpart[tid + 48]);
+          if (TAIL && tid < 16 && tile.half >= 0) {
+#pragma unroll
+            for (int h = 0; h < TAIL; ++h) {
+              const float* p = tpart + h * 64 + tid;
+              g.ssq_out[(size_t)(m0_strip + tid) * parts + (tile.n0 >> 7) + tile.half + h] = (p[0] + p[16]) + (p[32] + p[48]);
+            }
+          }
         }
       } else if constexpr (ROPE) {
         auto o = rsrc((bf16*)g.C + (size_t)tile.m0 * ldc, (size_t)rows * ldc * 2);
@@ -691,14 +707,17 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
           if (TAIL && tile.half >= 0) {
             const float r = strip_scale();
             const size_t m = m0_strip + l16;
-            f32x4t a = tacc[0] * r, b = tacc[1] * r;
-            if (turn) {
-              const float* t = g.R + 2 * (m * (DH / 2) + r0 % DH + 4 * t_q);
-              rotate(a, b, *(const f32x4t*)t, *(const f32x4t*)(t + 4));
+#pragma unroll
+            for (int h = 0; h < TAIL; ++h) {
+              f32x4t a = tacc[h][0] * r, b = tacc[h][1] * r;
+              if (turn) {
+                const float* t = g.R + 2 * (m * (DH / 2) + r0 % DH + 4 * t_q);      // (a half holds whole heads)
+                rotate(a, b, *(const f32x4t*)t, *(const f32x4t*)(t + 4));
+              }
+              bf16* out = (bf16*)g.C + m * ldc + tile.n0 + r0 + h * HALF + 4 * t_q;
+              *(u32x2t*)out = u32x2t{pack(a[0], a[1]), pack(a[2], a[3])};
+              *(u32x2t*)(out + HB * 16) = u32x2t{pack(b[0], b[1]), pack(b[2], b[3])};
             }
-            bf16* out = (bf16*)g.C + m * ldc + tile.n0 + r0 + 4 * t_q;
-            *(u32x2t*)out = u32x2t{pack(a[0], a[1]), pack(a[2], a[3])};
-            *(u32x2t*)(out + HB * 16) = u32x2t{pack(b[0], b[1]), pack(b[2], b[3])};
           }
         }
       }

@@ -33,3 +33,12 @@ def test_partial_round(tmp_path):
           f"{cut}(product(1040, 2048, 2048), 8, -1) == 0",        # one round
           f"{cut}(product(1040, 2048, 2048), 14, -1) == 0",       # 448 tiles: more than half a round is left
           f"{cut}(product(4352, 4352, 192), 1, 5) == 0")          # tiles asked for
+
+
+def test_persistent_tile(tmp_path):
+    """Rows that end in a strip of 16 take the persistent 256 x 256 tile also where one M-tile is all that the strip has in front of it."""
+    holds(tmp_path,
+          "tile256_shape<EPI_SWIGLU>(product(272, 8192, 2048))",
+          "tile256_shape<EPI_STORE_ACT>(product(57 * 256 + 16, 2048, 2048))",      # M-groups of eight, the last of one
+          "tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 192))",
+          "!tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 128))")               # its copies are two k-tiles ahead
