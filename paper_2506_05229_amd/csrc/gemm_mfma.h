@@ -697,6 +697,7 @@ constexpr bool tile256_shape(const GemmShape& s) {
   // its copies are two k-tiles ahead, but never more than one tile
   if (s.K < 3 * MF_BK || (s.k_slot > 0 && (s.k_min > 0 ? s.k_min : s.k_slot) < 3)) return false;
   if (((s.N | s.ldc | s.ldr | s.ldc2) & 3) != 0 || s.lda > LD || s.ldb > LD || s.ldc > LD || s.ldr > LD || s.ldc2 > LD) return false;
+  if (EPI == EPI_QKV_ROPE && s.ldc2 > 0 && s.M % 8 != 0) return false;      // V^T leaves in pieces of eight rows, of which it looks at the first
   return EPI != EPI_QKV_ROPE || s.ldr == 64 || s.ldr == 128;
 }
 

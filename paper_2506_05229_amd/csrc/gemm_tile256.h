@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
     auto silu_mul = [](float gt, float up) { return gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * up; };
 
     if (vt) {
-      // columns n0 + .. of the V block transposed: C2[column][row], eight rows of a column per lane (M is a multiple of 8 here)
+      // columns n0 + .. of the V block transposed: C2[column][row], eight rows of a column per lane (M is a multiple of 8: tile256_shape)
       bf16* out = (bf16*)g.C2 + (size_t)(tile.n0 - (s.n0 + s.n1)) * ldc2 + tile.m0;
       auto o = rsrc(out, (size_t)256 * ldc2 * 2);
       f32x4t rs[8];

@@ -16,6 +16,10 @@ def holds(tmp_path, *facts):
                       "constexpr GemmShape product(int M, int N, int K) {\n"
                       "  GemmShape s{};\n"
                       "  s.M = M; s.N = N; s.K = K; s.lda = s.ldb = K; s.ldc = N; s.n0 = N;\n"
+                      "  return s;\n}\n"
+                      "constexpr GemmShape qkv(int M, int ldc2) {\n"
+                      "  GemmShape s = product(M, 3072, 2048);\n"
+                      "  s.n0 = 2048; s.n1 = 512; s.ldr = 64; s.ldc2 = ldc2; s.a_rows = (M + 255) / 256 * 256;\n"
                       "  return s;\n}\n" + "".join(f'static_assert({f}, "");\n' for f in facts))
     done = subprocess.run([HIPCC, "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-fsyntax-only", "-I", CSRC, str(source)],
                           capture_output=True, text=True)
@@ -42,3 +46,10 @@ def test_persistent_tile(tmp_path):
           "tile256_shape<EPI_STORE_ACT>(product(57 * 256 + 16, 2048, 2048))",      # M-groups of eight, the last of one
           "tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 192))",
           "!tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 128))")               # its copies are two k-tiles ahead
+
+
+def test_transposed_v(tmp_path):
+    """The persistent tile stores V^T eight rows at a time, looking at the first: rows that are no multiple of eight stay with the tiles that look at each."""
+    tile = "tile256_shape<EPI_QKV_ROPE>"
+    holds(tmp_path, "mfma_regular_shape<256, 256, EPI_QKV_ROPE>(qkv(1036, 1152))", f"!{tile}(qkv(1036, 1152))", f"!{tile}(qkv(1047, 1152))",
+          f"{tile}(qkv(1048, 1152))", f"{tile}(qkv(1040, 1152))", f"{tile}(qkv(1036, 0))")
