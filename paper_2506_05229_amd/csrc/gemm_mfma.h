@@ -727,9 +727,9 @@ inline hipError_t launch_tile256(const GemmGroup* table, int first, int g, GemmS
   constexpr int HB = EPI == EPI_QKV_ROPE ? 2 : 0;
   const bool wide = HB > 0 && s.ldr == 128;
   const int tail = !strip ? 0 : last_group > 1 ? 1 : 2;
-  static const decltype(&gemm_tile256_kernel<EPI, 0, HB>) kernels[2][3] = {
-      {gemm_tile256_kernel<EPI, 0, HB>, gemm_tile256_kernel<EPI, 1, HB>, gemm_tile256_kernel<EPI, 2, HB>},
-      {gemm_tile256_kernel<EPI, 0, 2 * HB>, gemm_tile256_kernel<EPI, 1, 2 * HB>, gemm_tile256_kernel<EPI, 2, 2 * HB>}};
+  static const decltype(&gemm_tile256_kernel<EPI, false, HB>) kernels[2][3] = {
+      {gemm_tile256_kernel<EPI, false, HB>, gemm_tile256_kernel<EPI, true, HB>, gemm_tile272_kernel<EPI, HB>},
+      {gemm_tile256_kernel<EPI, false, 2 * HB>, gemm_tile256_kernel<EPI, true, 2 * HB>, gemm_tile272_kernel<EPI, 2 * HB>}};
   auto kern = kernels[wide][tail];
   static std::atomic<uint64_t> lds_raised[2][3];
   const hipError_t e = raise_lds_limit((const void*)kern, T256_LDS, lds_raised[wide][tail]);

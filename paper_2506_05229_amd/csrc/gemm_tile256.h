@@ -67,7 +67,7 @@ constexpr int T256_LDS = T256_OUT + 4 * 4096;
 // 102.5 / 97.3, gate/up of four cells of the 1B model 79.0 / 76.6; its pass over 48 segments 40.1 / 38.6 ms.
 // HB: EPI_QKV_ROPE, blocks of 16 columns in half a head (2 or 4), otherwise 0
 template <int EPI, int TAIL, int HB>
-__global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __restrict__ table_g, int first, GemmShape s, TileWalk w) {
+__device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, int first, const GemmShape& s, const TileWalk& w) {
   constexpr bool ROPE = EPI == EPI_QKV_ROPE, GLU = EPI == EPI_SWIGLU, RESID = EPI == EPI_RESID_F32;
   constexpr int ROWB = 128, BN_OUT = GLU ? 128 : 256;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -735,6 +735,16 @@ __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __re
     behind_epilogue = 1;
   }
   mf_wait_vmcnt<0>();                                          // the copies behind the last k-tile write LDS of this workgroup
+}
+
+template <int EPI, bool TAIL, int HB>
+__global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s, TileWalk w) {
+  tile256<EPI, TAIL, HB>(table, first, s, w);
+}
+// TAIL 2
+template <int EPI, int HB>
+__global__ __launch_bounds__(256) void gemm_tile272_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s, TileWalk w) {
+  tile256<EPI, 2, HB>(table, first, s, w);
 }
 
 }  // namespace armt

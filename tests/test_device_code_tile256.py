@@ -22,7 +22,7 @@ def kernels(code_object):       # noqa: F811
         instruction = re.match(r"\s+(\S.*?)\s*// ([0-9A-F]+):", line)
         if instruction and name and "gemm_tile256" in name:
             found.setdefault(name, []).append((int(instruction.group(2), 16), instruction.group(1)))
-    assert len(found) == 18      # five epilogues, the rotation for two head sizes; without the strip, with one half of it, with both
+    assert len(found) == 12      # five epilogues, the rotation for two head sizes, with and without the strip
     return found
 
 
@@ -47,7 +47,7 @@ def test_main_loop(kernels):
     a reload that it believes in flight) drains the copies once per k-tile, moves between the halves of the register file stand in front of products."""
     for name, code in kernels.items():
         body = main_loop(code)
-        assert sum("v_mfma" in t for t in body) in (128, 132, 136, 144), name      # the strip: four a half, twice that where a V tile swaps the operands
+        assert sum("v_mfma" in t for t in body) in (128, 132, 136), name
         assert not [t for t in body if re.match(r"scratch_|buffer_|v_accvgpr", t)], name
         assert sum("s_waitcnt" in t and "vmcnt" in t for t in body) == 1, name
         assert sum("load_lds" in t for t in body) in (16, 17), name

@@ -20,9 +20,7 @@ def tile_config():
     (3, 2064, 4096, 192),       # 384 tiles on 256 workgroups, strip on two M-tiles of each group
     (2, 768, 97 * 256, 448),    # 582 tiles, seven k-tiles
     (1, 33 * 256, 8 * 256, 256),        # 33 M-tiles in five M-groups, the last of five
-    (20, 272, 7 * 256, 320),    # a strip behind a single M-tile
-    (50, 272, 7 * 256, 320),    # the same, 350 tiles
-    (1, 57 * 256 + 16, 512, 192),       # M-groups of eight, the last of one
+    (20, 272, 7 * 256, 320),    # 16 waves: a strip behind a single M-tile
     (3, 2064, 4096, 128),       # 16 waves: two k-tiles
 ])
 def test_store(tile_config, g, M, N, K):
@@ -57,7 +55,7 @@ def test_head(tile_config, rows):
         assert torch.isfinite(a).all() and torch.equal(a, b)
 
 
-@pytest.mark.parametrize("seg_len, segments", [(240, 3), (256, 3), (512, 3), (1000, 2)])
+@pytest.mark.parametrize("seg_len, segments", [(240, 3), (512, 3), (1000, 2)])
 def test_gradients(tile_config, seg_len, segments):
     """Weight gradients over the slots that a layer has (ranges of the reduction, groups of unequal length), activation gradients with the strip."""
     shape = S.get_shape("tiny").replace(n_layers=3, d_model=256, n_heads=4, n_kv_heads=2, head_dim=64, d_ff=512, seg_len=seg_len, n_mem=16, d_mem=32,
@@ -73,23 +71,5 @@ def test_gradients(tile_config, seg_len, segments):
         *_, tape = model.forward_train(x)
         out = model.backward(tape, shape.n_tokens, d_hidden)
         got[cfg] = [t.clone() for layer in out["layers"] for t in layer.values()] + [out["mem_emb"].clone(), out["x"].clone()]
-    for a, b in zip(got[5], got[6]):
-        assert torch.isfinite(a.float()).all() and torch.equal(a, b)
-
-
-@pytest.mark.parametrize("seg_len, heads, dh", [(256, 16, 64), (256, 8, 128), (512, 16, 64), (512, 8, 128), (752, 16, 64)])
-def test_epilogues(tile_config, seg_len, heads, dh):
-    """80 cells a launch at full steps, 320 to 960 tiles: every epilogue of the forward pass with the next tile's products under it; a strip of one M-tile's own, a
-    shared one and none."""
-    shape = S.get_shape("tiny").replace(n_layers=4, d_model=1024, n_heads=heads, n_kv_heads=heads // 4, head_dim=dh, d_ff=1024, seg_len=seg_len, n_mem=16,
-                                        d_mem=32, n_tokens=seg_len * 4, dtype="bf16", mem_k_scale=2.0 ** -6)
-    layers, mem_emb = S.make_weights(shape, seed=1)
-    model = P.Armt(shape, layers, mem_emb, device="cuda:0")
-    gen = torch.Generator(device="cuda").manual_seed(seg_len + dh)
-    x = torch.randn(20, shape.n_tokens, 1024, device="cuda", generator=gen).bfloat16()
-    got = {}
-    for cfg in (6, 5):
-        tile_config(cfg)
-        got[cfg] = [t.clone() for t in model.forward_batched(x)]
     for a, b in zip(got[5], got[6]):
         assert torch.isfinite(a.float()).all() and torch.equal(a, b)
