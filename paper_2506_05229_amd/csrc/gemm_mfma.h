@@ -629,8 +629,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
 #endif
 }
 
-// M-tiles of 256 rows, of which the last takes a strip of 16 rows behind it along
-constexpr int mfma_m_tiles(const GemmShape& s) { return (s.M > 256 && s.M % 256 == 16) ? s.M / 256 : (s.M + 255) / 256; }
+// M-tiles of 256 rows, of which the last takes a strip of 16 rows behind it along (not with switch 32, as in the launches: a cut launch counts by both)
+constexpr int mfma_m_tiles(const GemmShape& s) { return (s.M > 256 && s.M % 256 == 16 && !(s.dbg & 32)) ? s.M / 256 : (s.M + 255) / 256; }
 
 // M-tiles (of 256 rows) that follow one another on a weight panel.  The 32 compute units of an XCD work on 32 consecutive
 // tiles of the order: with 4 to 8 M-tiles side by side these touch 11 to 12 operand panels, with 32 of one weight panel

@@ -17,6 +17,10 @@ def holds(tmp_path, *facts):
                       "  GemmShape s{};\n"
                       "  s.M = M; s.N = N; s.K = K; s.lda = s.ldb = K; s.ldc = N; s.n0 = N;\n"
                       "  return s;\n}\n"
+                      "constexpr GemmShape without_strip(int M) {\n"
+                      "  GemmShape s = product(M, 2048, 2048);\n"
+                      "  s.dbg = 32; s.a_rows = (M + 255) / 256 * 256;\n"
+                      "  return s;\n}\n"
                       "constexpr GemmShape qkv(int M, int ldc2) {\n"
                       "  GemmShape s = product(M, 3072, 2048);\n"
                       "  s.n0 = 2048; s.n1 = 512; s.ldr = 64; s.ldc2 = ldc2; s.a_rows = (M + 255) / 256 * 256;\n"
@@ -53,3 +57,14 @@ def test_transposed_v(tmp_path):
     tile = "tile256_shape<EPI_QKV_ROPE>"
     holds(tmp_path, "mfma_regular_shape<256, 256, EPI_QKV_ROPE>(qkv(1036, 1152))", f"!{tile}(qkv(1036, 1152))", f"!{tile}(qkv(1047, 1152))",
           f"{tile}(qkv(1048, 1152))", f"{tile}(qkv(1040, 1152))", f"{tile}(qkv(1036, 0))")
+
+
+def test_cut_without_strip(tmp_path):
+    """Memory rows in an M-tile of their own (a switch of the tile configuration): the units of a cut launch still hold every tile."""
+    facts = []
+    for rows in (272, 1040, 2064, 2320, 14608):
+        tiles = (rows + 255) // 256
+        facts += [f"mfma_m_tiles(without_strip({rows})) == {tiles}",
+                  f"mfma_unit_tile(mfma_units(without_strip({rows}), 9, 8), {tiles}, mfma_m_group(without_strip({rows})), 8, 1) == {9 * tiles * 8}",
+                  f"mfma_m_tiles(product({rows}, 2048, 2048)) == {tiles - 1}"]
+    holds(tmp_path, "mfma_round_cut<EPI_RESID_F32>(without_strip(1040), 15, -1) > 0", *facts)
