@@ -68,3 +68,10 @@ def test_cut_without_strip(tmp_path):
                   f"mfma_unit_tile(mfma_units(without_strip({rows}), 9, 8), {tiles}, mfma_m_group(without_strip({rows})), 8, 1) == {9 * tiles * 8}",
                   f"mfma_m_tiles(product({rows}, 2048, 2048)) == {tiles - 1}"]
     holds(tmp_path, "mfma_round_cut<EPI_RESID_F32>(without_strip(1040), 15, -1) > 0", *facts)
+
+
+def test_cut_inside_m_group(tmp_path):
+    """The launches that tests on the device mean to cut inside an M-group: units per M-group are the panels."""
+    residual = "mfma_round_cut<EPI_RESID_F32>(product(2320, 1280, 1024), 6, -1)"
+    holds(tmp_path, f"{residual} == 56 && {residual} % 5 != 0",
+          "mfma_round_cut<EPI_STORE_F32>(product(4352, 4096, 4352), 1, -1) % 16 != 0", "mfma_round_cut<EPI_RESID_F32>(product(4352, 4096, 4352), 1, -1) % 16 != 0")
