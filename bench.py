@@ -23,7 +23,7 @@ HBM_PEAK_GBPS = 8000.0             # MI355X HBM3E peak (published)
 # a line "hbm_bytes_per_cell = <number>" in this file (FETCH_SIZE + WRITE_SIZE per dispatch, each scaled by what the
 # same counter reads for a plain copy kernel of known size, divided by the cells of the dispatch).
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "gate_up_gemm_1b_128k_hbm_traffic.md")
-# the other configurations the benchmark spec names, reported in `configs` next to the headline workload
+# the other configurations, reported in `configs` next to the headline workload
 OTHER_CONFIGS = ("1b_8k", "1b_32k", "1b_128k_s512", "1b_128k_s2048", "3b_128k")
 
 

@@ -53,9 +53,11 @@ __device__ __forceinline__ void mf_wait_vmcnt_if(int left) {
 }
 
 #ifdef ARMT_GEMM_TIMELINE
-// Probe build (paper_2506_05229_amd.build.build_timeline, never the product library): one armed launch records, per
-// workgroup, where its time goes: [0] hardware id, [1] / [6] wall clock (100 MHz) at start / end, [2] .. [5] shader
-// clock at start, after the first k-tile has landed, after the main loop, after the epilogue.
+// Probe build (build(timeline=True) of paper_2506_05229_amd.build, never the product library): one armed launch records, per
+// tile, where its time goes: [0] hardware id, [1] / [6] wall clock (100 MHz) at start / end, [2] .. [5] shader
+// clock at start, after the first k-tile has landed, after the main loop, after the epilogue.  A workgroup of the persistent tile (gemm_tile256.h) writes a
+// record for each of its tiles: [2] and [3] are the same there (a tile starts on what the one before it fetched), and the products of a tile's
+// first k-step that run under the epilogue of the one before count in that epilogue.
 __device__ unsigned long long armt_timeline[8 * 65536];
 inline int g_tl_kind = -2, g_tl_countdown = -1;      // host: the n-th next launch of this kind is the armed one
 #define TL_STAMP(i)                                                     \
@@ -830,6 +832,7 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
       // and 64 x 64 tiles wait longer in the epilogue.  us per launch, 32 x 128 / 32 x 64 (means of a pass): 1B model, one cell 23.5 / 21.3,
       // 1 - 8 cells 29.7 / 23.5, 16 cells of 528 rows 31.7 / 25.4, twelve of width 768 18.6 / 17.4
       if constexpr (EPI == EPI_DPFP_READ) {
+        // (narrower d_mem are not regular: these copies would read rows that the weight does not have)
         if (mfma_regular_shape<32, 64, EPI>(s) && s.N == 64) return launch_mfma_cfg<32, 64, 2, 2, EPI, true, 4>(table, first, g, s, st);
         // else 32 x 128, waves side by side, three k-tiles in LDS (two workgroups still fit on a CU)
         // (six do not pay, also not for at most one workgroup per CU: 25.7 us with either for one cell of d 2048)
@@ -837,9 +840,9 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
       }
       break;
     case 5:   // 256 x 256: the persistent tile of four waves (gemm_tile256.h), for other shapes 16 waves and one barrier per k-tile.  us per
-              // launch, eight waves in four phases per k-tile (what was here) / four: gate/up of twelve cells of 1040 x 6144, K 768 107.0 / 94.3, of
-              // the 3B model (mean of its launches) 907 / 824, of the 1B model 346 / 315; QKV 56.7 / 50.1, 325 / 310, 70.5 / 66.5; attention
-              // output, down and read of K 3072 and 8192 275 / 272, of the 768-wide model, whose launches are at most one tile per CU, 57.6 / 60.9
+              // launch of bf16 results, 16 waves / persistent: 12 x (1040 x 768, K 768) 27.8 / 25.6, K 3072 68.3 / 67.4 (at most one tile per CU), 12 x (1040 x
+              // 6144, K 768) 140 / 114, 16 x (1040 x 3072, K 2048) 191 / 166, 16 x (1040 x 2048, K 8192) 453 / 437, 16 x (1040 x 16384, K 2048) 996 / 884,
+              // 8192^3 831 / 713
       // Regular shapes that the persistent tile leaves (one or two k-tiles): the same 16 waves without the address arithmetic of ragged ones.  us per
       // launch, general / regular: 12 x (1040 x 3072, K 128) 33.6 / 32.5, 8 x (1024 x 8192, K 128) 45.4 / 44.4, 16 x (1040 x 8192, K 64) 77.2 / 78.1
       if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) {

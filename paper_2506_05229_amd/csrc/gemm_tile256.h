@@ -7,7 +7,7 @@
 // closely they hold the wave up, which has no second one beside it: 8192^3 1.01 PFLOP/s with a copy every third MFMA, 1.48 with
 // every sixth.)  Four waves read 128 KB of LDS per k-tile where eight of 128 x 64 read 192.
 // Tiles.  The copies run two k-tiles ahead through ALL tiles of the workgroup: the last two k-tiles of a tile fetch the first two of the next, whose
-// start costs no latency, and the epilogue, which uses registers and global memory only, runs while they land.
+// start costs no latency, and the epilogue runs while they land: the LDS that it uses (T256_SSQ, T256_OUT) is none of theirs.
 // Epilogue.  A 16 x 16 block is multiplied with the weights as first operand: a lane then holds four consecutive columns of one row.  Whole rows of
 // 64 columns leave through LDS of the wave's own.  Buffer stores drop what lies past M.
 #pragma once
@@ -50,10 +50,10 @@ constexpr T256Ones t256_ones_value() {
 }
 static __device__ const T256Ones t256_ones = t256_ones_value();
 
-// Cache policy of the result stores: not kept in the L2 (nt).  A round of tiles writes as much as the L2 holds, and what it displaces are the
+// Cache policy of the result stores: nt, not kept in the L2.  A round of tiles writes as much as the L2 holds, and what it displaces are the
 // operands of the next one.  us per launch, kept / not: gate/up of the 3B model 837 / 824, of twelve cells of width 768 96.8 / 94.3, fp32 results
 // of 16 x (1024 x 2048, K 2048) 132 / 118, 8192^3 754 / 736
-constexpr int T256_KEEP = 2;
+constexpr int T256_NT = 2;
 
 constexpr int T256_STAGE = 65536;                             // a k-tile: 256 rows of A, 256 of B
 constexpr int T256_STRIP = 2 * T256_STAGE;                    // two buffers of the 16 strip rows
@@ -405,7 +405,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
     };
     using N8 = std::integral_constant<int, 8>;
     using N16 = std::integral_constant<int, 16>;
-    auto take = [&](int y, int x) __attribute__((always_inline)) {       // a result block; its accumulators start the next tile at zero
+    auto take = [&](int y, int x) __attribute__((always_inline)) {       // a result block; next_products overwrites its accumulators
       f32x4t v;
       // (where it is needed: the compiler would copy them all out at the end of the loop)
       asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\tv_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7"
@@ -439,7 +439,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
           const unsigned off = ((unsigned)(at16(wy, i >> 1) + 8 * k + r8) * (unsigned)ldc2 + m) * 2u;
-          __builtin_amdgcn_raw_buffer_store_b128(r[k], o, m < rows ? off : 0xfffffff0u, 0, T256_KEEP);
+          __builtin_amdgcn_raw_buffer_store_b128(r[k], o, m < rows ? off : 0xfffffff0u, 0, T256_NT);
         }
       });
       if (TAIL && tile.half >= 0) {
@@ -467,8 +467,8 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
         next_products(y, 0, 8);
       }, [&](int y, const u32x4t (&r)[2]) __attribute__((always_inline)) {
         const unsigned at = (unsigned)(at16(wy, y) + r8) * (unsigned)ldc + tile.n0 + wx * 64 + 8 * c8;
-        __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_KEEP);
-        __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
+        __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_NT);
+        __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_NT);
       });
       if (TAIL && tile.half >= 0) {
         const float r = strip_scale();
@@ -494,8 +494,8 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
         auto o = rsrc((bf16*)g.C + (size_t)tile.m0 * ldc, (size_t)rows * ldc * 2);
         out16(N16{}, scaled, [&](int i, const u32x4t (&r)[2]) __attribute__((always_inline)) {
           const unsigned at = (unsigned)(at16(wy, i >> 1) + r8) * (unsigned)ldc + tile.n0 + at16(wx, 4 * (i & 1)) + 8 * c8;
-          __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_KEEP);
-          __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
+          __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_NT);
+          __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_NT);
         });
         if (TAIL && tile.half >= 0) {
           const float r = strip_scale();
@@ -511,7 +511,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
         out32(N16{}, scaled, [&](int i, const f32x4t (&r)[4]) __attribute__((always_inline)) {
           const unsigned at = (unsigned)(at16(wy, i >> 1) + r4) * (unsigned)ldc + tile.n0 + at16(wx, 4 * (i & 1)) + 4 * c4;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4t, r[k]), o, (at + 4 * k * ldc) * 4u, 0, T256_KEEP);
+          for (int k = 0; k < 4; ++k) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4t, r[k]), o, (at + 4 * k * ldc) * 4u, 0, T256_NT);
         });
         if (TAIL && tile.half >= 0) {
           const float r = strip_scale();
@@ -588,7 +588,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
           for (int k = 0; k < 4; ++k) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[k][e] = fmaf(r[k][e], rr[y % 3][k], pre[i % RING][k][e]);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4t, v[k]), o, ((row + 4 * k) * (unsigned)ldc + col) * 4u, 0, T256_KEEP);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4t, v[k]), o, ((row + 4 * k) * (unsigned)ldc + col) * 4u, 0, T256_NT);
           }
           if (copied) {
 #pragma unroll
@@ -596,7 +596,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
               f32x4t c = v[k];
 #pragma unroll
               for (int e = 0; e < 4; ++e) c[e] *= (float)gq[h][e];
-              __builtin_amdgcn_raw_buffer_store_b64(u32x2t{pack(c[0], c[1]), pack(c[2], c[3])}, o2, ((row + 4 * k) * (unsigned)ldc2 + col) * 2u, 0, T256_KEEP);
+              __builtin_amdgcn_raw_buffer_store_b64(u32x2t{pack(c[0], c[1]), pack(c[2], c[3])}, o2, ((row + 4 * k) * (unsigned)ldc2 + col) * 2u, 0, T256_NT);
             }
           }
           if (summed) {
@@ -701,8 +701,8 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
             for (int x = 0; x < 4; ++x) out[x] = v[4 * h + x];
           }, [&](int i, const u32x4t (&r)[2]) __attribute__((always_inline)) {
             const unsigned at = (unsigned)(at16(wy, i >> 1) + r8) * (unsigned)ldc + col + 64 * (i & 1) + 8 * c8;
-            __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_KEEP);
-            __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_KEEP);
+            __builtin_amdgcn_raw_buffer_store_b128(r[0], o, at * 2u, 0, T256_NT);
+            __builtin_amdgcn_raw_buffer_store_b128(r[1], o, (at + 8 * ldc) * 2u, 0, T256_NT);
           });
           if (TAIL && tile.half >= 0) {
             const float r = strip_scale();

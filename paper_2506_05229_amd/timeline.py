@@ -1,12 +1,16 @@
-"""Where the time of a grouped-GEMM workgroup goes: a probe, not part of the product path.
+"""Where the time of a grouped-GEMM tile goes: a probe, not part of the product path.
 
     python -m paper_2506_05229_amd.build --timeline            # builds libarmt_hip_timeline.so (-DARMT_GEMM_TIMELINE)
     python -m paper_2506_05229_amd.timeline 1b_32k gate_up     # kinds: qkv, attn_out, gate_up, down, mem_read, ...
 
-The probe library records, for every workgroup of ONE launch of the chosen GEMM kind in the middle of a forward pass
+The probe library records, for every tile of ONE launch of the chosen GEMM kind in the middle of a forward pass
 (a step with the full group), the shader clock at its start, after its first k-tile has landed, after its main loop
 and after its epilogue, the wall clock at start and end, and the compute unit it ran on.  Printed: cycles per phase,
-the gap between consecutive workgroups of a compute unit, and the span of the launch.
+the gap between consecutive tiles of a compute unit, and the span of the launch.
+
+A tile is a workgroup, except in the persistent 256 x 256 tile, whose workgroups walk several.  There a tile starts on copies that
+landed during the one before it, so it has no phase in front of its main loop (the line is left out), and its first products run under
+the epilogue of the tile before it, where they are counted.
 """
 import ctypes as C
 import os
@@ -40,14 +44,15 @@ def main(argv):
     assert lib.armt_timeline_read(buf.ctypes.data, buf.size) == 0
     r = buf.reshape(-1, 8)
     r = r[r[:, 2] != 0]
-    print(f"{name} {kind}: {len(r)} workgroups recorded")
+    print(f"{name} {kind}: {len(r)} tiles recorded")
     pro, main_, epi = ((r[:, b] - r[:, a]).astype(np.int64) for a, b in ((2, 3), (3, 4), (4, 5)))
     wall = (r[:, 6] - r[:, 1]).astype(np.int64) * 10          # ns
     q = lambda a: f"mean {a.mean():9.0f}  p10 {np.percentile(a, 10):9.0f}  p50 {np.percentile(a, 50):9.0f}  p90 {np.percentile(a, 90):9.0f}"
-    print("  cycles  start -> first k-tile landed:", q(pro))
+    if pro.any():
+        print("  cycles  start -> first k-tile landed:", q(pro))
     print("  cycles  main loop                   :", q(main_))
     print("  cycles  epilogue                    :", q(epi))
-    print("  ns      workgroup wall time         :", q(wall), f" (shader clock {(pro + main_ + epi).mean() / wall.mean():.2f} GHz)")
+    print("  ns      wall time of a tile         :", q(wall), f" (shader clock {(pro + main_ + epi).mean() / wall.mean():.2f} GHz)")
     cu = (r[:, 0] >> np.uint64(32)) * np.uint64(65536) + ((r[:, 0] >> np.uint64(8)) & np.uint64(0xFF))
     gaps, per_cu = [], []
     for c in np.unique(cu):
@@ -55,9 +60,9 @@ def main(argv):
         st, en = np.sort(r[m, 1].astype(np.int64)), np.sort(r[m, 6].astype(np.int64))
         per_cu.append(int(m.sum()))
         gaps += list((st[1:] - en[:-1]) * 10)
-    print(f"  {len(per_cu)} compute units, workgroups per unit {min(per_cu)} .. {max(per_cu)}")
+    print(f"  {len(per_cu)} compute units, tiles per unit {min(per_cu)} .. {max(per_cu)}")
     if gaps:
-        print("  ns      gap between workgroups of a unit:", q(np.array(gaps)))
+        print("  ns      gap between tiles of a unit :", q(np.array(gaps)))
     print(f"  launch span {(int(r[:, 6].max()) - int(r[:, 1].min())) * 10 / 1e3:.1f} us")
 
 
