@@ -554,7 +554,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_mfma_kernel(const GemmGrou
         // are fixed, not tied to the tile width, so that every tile configuration produces the same partials bit for bit.
         static_assert(EPI != EPI_RESID_F32 || BN_OUT % 128 == 0, "partials cover 128 columns = 32 lanes");
         const float part = sum32(o[0] * o[0] + o[1] * o[1] + o[2] * o[2] + o[3] * o[3]);
-        if ((c4 & 31) == 0 && sr < NROWS && m < s.M)
+        if ((c4 & 31) == 0 && sr < NROWS && m < s.M && n < s.N)      // (a wide tile's columns past N: the next row's partial stands there)
           g.ssq_out[(size_t)m * ((s.N + 127) >> 7) + tn * (BN_OUT / 128) + (c4 >> 5)] = part;
       }
     }
