@@ -336,8 +336,7 @@ armt_status armt_lm_head_static(const armt_config *cfg, const void *hidden, int6
 /* Force the tile configuration of the bf16 grouped GEMM for all later calls of this process (1: 128x128 tile, 4 waves;
  * 2: 64x128, 4 waves; 3: 64x64, 4 waves, for the plain fp32 store only, and 4: 32x128 (d_mem 64: 32x64), 4 waves, for the feature-map
  * epilogue of the W_Q projection only (other epilogues run 2 instead);
- * 5: 256x256, persistent workgroups of 4 waves where the shape lets its copies be addressed by scalar base + lane offset (and has three
- * k-tiles), else 16;
+ * 5: 256x256, persistent workgroups of 4 waves where the shape lets its copies be addressed by scalar base + lane offset, else 16;
  * 6: 128x128, 8 waves with copies addressed that way where the shape allows, else as 1; 7: 64x128, 8 waves (SwiGLU 4), and
  * 8: 128x128, 16 waves (SwiGLU and irregular shapes 8), four k-tiles in LDS,
  * for launches of at most one workgroup per CU; anything else below 100: choose by shape and tile count, the default).  config = 100 *

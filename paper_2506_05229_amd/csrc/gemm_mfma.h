@@ -691,14 +691,17 @@ inline hipError_t launch_mfma_tail(const GemmGroup* table, int first, int g, Gem
   return hipGetLastError();
 }
 
-// Shapes that the persistent 256 x 256 tile takes, of the regular ones: at least three k-tiles, rows that can be stored in 16-byte pieces and reached by
-// 32-bit offsets from a tile's first row, heads of 64 or 128 columns (a wave's columns hold whole ones).
+// Groups of one or two k-tiles, or some of them
+constexpr bool tile256_short(const GemmShape& s) { return s.K < 3 * MF_BK || (s.k_slot > 0 && (s.k_min > 0 ? s.k_min : s.k_slot) < 3); }
+
+// Shapes that the persistent 256 x 256 tile takes, of the regular ones: rows that can be stored in 16-byte pieces and reached by 32-bit offsets from a tile's
+// first row, heads of 64 or 128 columns (a wave's columns hold whole ones).
 template <int EPI>
 constexpr bool tile256_shape(const GemmShape& s) {
   constexpr int LD = 1 << 21;
-  // its copies are two k-tiles ahead, but never more than one tile
-  if (s.K < 3 * MF_BK || (s.k_slot > 0 && (s.k_min > 0 ? s.k_min : s.k_slot) < 3)) return false;
+  if (s.K < MF_BK) return false;                            // a group without products is not stored
   if (((s.N | s.ldc | s.ldr | s.ldc2) & 3) != 0 || s.lda > LD || s.ldb > LD || s.ldc > LD || s.ldr > LD || s.ldc2 > LD) return false;
+  if (EPI == EPI_QKV_ROPE && tile256_short(s)) return false;      // (none is regular: its first weight block has K columns)
   if (EPI == EPI_QKV_ROPE && s.ldc2 > 0 && s.M % 8 != 0) return false;      // V^T leaves in pieces of eight rows, of which it looks at the first
   return EPI != EPI_QKV_ROPE || s.ldr == 64 || s.ldr == 128;
 }
@@ -727,14 +730,20 @@ inline hipError_t launch_tile256(const GemmGroup* table, int first, int g, GemmS
   w.r_share = t256_recip(w.tiles_m * w.tiles_n / 8);
   const int grid = w.total < MF_CUS ? (w.total + 7) / 8 * 8 : MF_CUS;
   constexpr int HB = EPI == EPI_QKV_ROPE ? 2 : 0;
-  const bool wide = HB > 0 && s.ldr == 128;
   const int tail = !strip ? 0 : last_group > 1 ? 1 : 2;
-  static const decltype(&gemm_tile256_kernel<EPI, false, HB>) kernels[2][3] = {
-      {gemm_tile256_kernel<EPI, false, HB>, gemm_tile256_kernel<EPI, true, HB>, gemm_tile272_kernel<EPI, HB>},
-      {gemm_tile256_kernel<EPI, false, 2 * HB>, gemm_tile256_kernel<EPI, true, 2 * HB>, gemm_tile272_kernel<EPI, 2 * HB>}};
-  auto kern = kernels[wide][tail];
+  typedef decltype(&gemm_tile256_kernel<EPI, false, HB>) Kernel;
+  static const Kernel plain[3] = {gemm_tile256_kernel<EPI, false, HB>, gemm_tile256_kernel<EPI, true, HB>, gemm_tile272_kernel<EPI, HB>};
+  Kernel kern = plain[tail];
+  bool other = false;                                       // heads of 128 columns, or fewer than three k-tiles
+  if constexpr (EPI == EPI_QKV_ROPE) {
+    static const Kernel wide[3] = {gemm_tile256_kernel<EPI, false, 2 * HB>, gemm_tile256_kernel<EPI, true, 2 * HB>, gemm_tile272_kernel<EPI, 2 * HB>};
+    if ((other = s.ldr == 128)) kern = wide[tail];
+  } else {
+    static const Kernel brief[3] = {gemm_short256_kernel<EPI, 0>, gemm_short256_kernel<EPI, 1>, gemm_short256_kernel<EPI, 2>};
+    if ((other = tile256_short(s))) kern = brief[tail];
+  }
   static std::atomic<uint64_t> lds_raised[2][3];
-  const hipError_t e = raise_lds_limit((const void*)kern, T256_LDS, lds_raised[wide][tail]);
+  const hipError_t e = raise_lds_limit((const void*)kern, T256_LDS, lds_raised[other][tail]);
   if (e != hipSuccess) return e;
 #ifdef ARMT_GEMM_TIMELINE
   if (s.tag == g_tl_kind && g_tl_countdown >= 0 && g_tl_countdown-- == 0) s.dbg |= 1 << 20;
@@ -797,9 +806,9 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
 // Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs as 128 x 128 tiles (four
 // times as many, two workgroups per CU: one short round instead of a long one that leaves most CUs idle).  The units (TileRange) that keep
 // 256 x 256 tiles, 0: all of them.  Both tile sizes give the same bits (same order of the k-steps, row sums of squares at a fixed
-// granularity), so where the cut falls does not show in the result.  The kernel that takes the whole rounds has no say in it; us per launch with 16 waves,
-// one launch / cut: 9 x (272 x 8192, K 2048) 134 / 117, 32 x (272 x 3072, K 2048) 147 / 138, 12 x (1040 x 3072, K 128) 34.6 / 33.3, 9 x (1040 x 2048,
-// K 64) 22.4 / 21.0.
+// granularity), so where the cut falls does not show in the result.  The kernel that takes the whole rounds has no say in it.  us per launch, one launch / cut:
+// 9 x (1040 x 2048, K 8192) 360 / 318, K 2048 96 / 81, 12 x (1040 x 2048, K 8192) 386 / 362, 4352^3 173 / 150, 9 x (272 x 8192, K 2048) 120 / 107, 32 x (272 x
+// 3072, K 2048) 135 / 133; with one or two k-tiles, where the second launch is most of the difference, 17.9 / 18.7 and (12 x (1040 x 3072)) 28.7 / 29.8.
 template <int EPI>
 constexpr int mfma_round_cut(const GemmShape& s, int g, int force_cfg) {
   if (EPI == EPI_SWIGLU || EPI == EPI_DPFP_READ || force_cfg >= 0 || s.spread || !mfma_regular_shape<256, 256, EPI>(s) ||
@@ -843,11 +852,9 @@ inline hipError_t launch_gemm_mfma_epi(const GemmGroup* table, int first, int g,
               // launch of bf16 results, 16 waves / persistent: 12 x (1040 x 768, K 768) 27.8 / 25.6, K 3072 68.3 / 67.4 (at most one tile per CU), 12 x (1040 x
               // 6144, K 768) 140 / 114, 16 x (1040 x 3072, K 2048) 191 / 166, 16 x (1040 x 2048, K 8192) 453 / 437, 16 x (1040 x 16384, K 2048) 996 / 884,
               // 8192^3 831 / 713
-      // Regular shapes that the persistent tile leaves (one or two k-tiles): the same 16 waves without the address arithmetic of ragged ones.  us per
-      // launch, general / regular: 12 x (1040 x 3072, K 128) 33.6 / 32.5, 8 x (1024 x 8192, K 128) 45.4 / 44.4, 16 x (1040 x 8192, K 64) 77.2 / 78.1
       if constexpr (EPI != EPI_DPFP_READ) if (mfma_regular_shape<256, 256, EPI>(s)) {
         auto tiles_256 = [&](const TileRange& rng) {
-          return tile256_shape<EPI>(s) ? launch_tile256<EPI>(table, first, g, s, st, rng) : launch_mfma_cfg<256, 256, 4, 4, EPI, true>(table, first, g, s, st, rng);
+          return tile256_shape<EPI>(s) ? launch_tile256<EPI>(table, first, g, s, st, rng) : launch_mfma_cfg<256, 256, 4, 4, EPI>(table, first, g, s, st, rng);
         };
         if constexpr (EPI != EPI_SWIGLU) {
           const int cut = mfma_round_cut<EPI>(s, g, force_cfg);

@@ -66,7 +66,10 @@ constexpr int T256_LDS = T256_OUT + 4 * 4096;
 // 16 x (272 x 8192, K 2048) 157 / 145, 24 x (272 x 2048, K 2048) 61.9 / 53.8, 32 x (272 x 2048, K 8192) 291 / 276, 1 x (14608 x 2048, K 2048)
 // 102.5 / 97.3, gate/up of four cells of the 1B model 79.0 / 76.6; its pass over 48 segments 40.1 / 38.6 ms.
 // HB: EPI_QKV_ROPE, blocks of 16 columns in half a head (2 or 4), otherwise 0
-template <int EPI, int TAIL, int HB>
+// SHORT: tiles of any number of k-tiles.  Otherwise they have three at least, and the copies, two k-tiles ahead, never more than one tile; what it takes to follow
+// them over more costs long products 0.2 - 0.5 % (their registers for scalars are all in use).  us per launch, 16 waves / so: the read of 16 cells of 1040 x 2048 with 64
+// features 58.5 / 52, with 128 60.4 / 54.5, 16 x (1024 x 8192, K 64) 76.5 / 59, K 128 93 / 66, the head's weight gradient over 124 rows (46027 x 768) 56 / 53.5.
+template <int EPI, int TAIL, int HB, bool SHORT>
 __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, int first, const GemmShape& s, const TileWalk& w) {
   constexpr bool ROPE = EPI == EPI_QKV_ROPE, GLU = EPI == EPI_SWIGLU, RESID = EPI == EPI_RESID_F32;
   constexpr int ROWB = 128, BN_OUT = GLU ? 128 : 256;
@@ -112,6 +115,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
   // ---- copies: cursor over the k-tiles of all tiles.  Slab wave + 4 j (8 rows) of an operand: base of its half, lane offset j & 3
   const char *cA0, *cA1, *cB0, *cB1, *cT;
   int c_left = 1, c_step = ROWB;
+  int before_ct = -1;                                          // SHORT: number of the tile in front of the cursor's
   Tile ct{(int)(blockIdx.x >> 3) - stride, 0, 0, 0, 0, -1};
   auto advance = [&]() __attribute__((always_inline)) {
     if (--c_left > 0) {
@@ -119,6 +123,7 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
       return;
     }
     const Tile t = tile_from(ct.r + stride);
+    if (SHORT) before_ct = ct.r;
     if (t.r < 0) { c_left = 0x7fffffff; c_step = 0; ct.r = -1; return; }      // behind the last k-tile: that one again (nobody reads it)
     ct = t;
     c_left = t.nk;
@@ -273,10 +278,12 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
     for (int t = 0; t < 2 * TAIL; ++t) tacc[t >> 1][t & 1] = f32x4t{0.f, 0.f, 0.f, 0.f};
     const int r0 = strip_row(tile, 0), r1 = strip_row(tile, 1);
     int left = tile.nk;
+    int next = -1;                                             // SHORT: number of the tile behind this one, -1 none
     // second step of a k-tile, with the last N copies of the one after next
     auto second_step = [&](auto n_c) __attribute__((always_inline)) {
       constexpr int N = decltype(n_c)::value, GAP = 64 / N;
       if (ROPE && left == 1) orient(transposed(ct));             // the cursor stands in the next tile
+      if (SHORT && left == 1) next = before_ct == tile.r ? ct.r : before_ct;      // ... or, if that has one k-tile, in the one behind it
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < 64; ++q) {
@@ -730,8 +737,13 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
 #ifdef ARMT_GEMM_TIMELINE
     if (tl_on && tid == 0) tl[6] = __builtin_amdgcn_s_memrealtime();
 #endif
-    if (ct.r < 0) break;
-    tile = ct;                                                 // (at its third k-tile)
+    if (SHORT) {
+      if (next < 0) break;
+      tile = next == ct.r ? ct : tile_from(next);
+    } else {
+      if (ct.r < 0) break;
+      tile = ct;                                               // (at its third k-tile)
+    }
     behind_epilogue = 1;
   }
   mf_wait_vmcnt<0>();                                          // the copies behind the last k-tile write LDS of this workgroup
@@ -739,12 +751,16 @@ __device__ __forceinline__ void tile256(const GemmGroup* __restrict__ table_g, i
 
 template <int EPI, bool TAIL, int HB>
 __global__ __launch_bounds__(256) void gemm_tile256_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s, TileWalk w) {
-  tile256<EPI, TAIL, HB>(table, first, s, w);
+  tile256<EPI, TAIL, HB, false>(table, first, s, w);
 }
 // TAIL 2
 template <int EPI, int HB>
 __global__ __launch_bounds__(256) void gemm_tile272_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s, TileWalk w) {
-  tile256<EPI, 2, HB>(table, first, s, w);
+  tile256<EPI, 2, HB, false>(table, first, s, w);
+}
+template <int EPI, int TAIL>
+__global__ __launch_bounds__(256) void gemm_short256_kernel(const GemmGroup* __restrict__ table, int first, GemmShape s, TileWalk w) {
+  tile256<EPI, TAIL, 0, true>(table, first, s, w);
 }
 
 }  // namespace armt

@@ -44,12 +44,16 @@ def test_partial_round(tmp_path):
 
 
 def test_persistent_tile(tmp_path):
-    """Rows that end in a strip of 16 take the persistent 256 x 256 tile also where one M-tile is all that the strip has in front of it."""
+    """Rows that end in a strip of 16 take the persistent 256 x 256 tile also where one M-tile is all that the strip has in front of it, and so do products of
+    one or two k-tiles, fewer than its copies are ahead."""
     holds(tmp_path,
           "tile256_shape<EPI_SWIGLU>(product(272, 8192, 2048))",
           "tile256_shape<EPI_STORE_ACT>(product(57 * 256 + 16, 2048, 2048))",      # M-groups of eight, the last of one
           "tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 192))",
-          "!tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 128))")               # its copies are two k-tiles ahead
+          "tile256_shape<EPI_RESID_F32>(product(1040, 2048, 128))",
+          "tile256_shape<EPI_RESID_F32>(product(46080, 768, 64))",
+          "tile256_short(product(1040, 2048, 128)) && !tile256_short(product(1040, 2048, 192))",
+          "!tile256_shape<EPI_STORE_ACT>(product(1040, 2048, 0))")
 
 
 def test_transposed_v(tmp_path):
