@@ -775,7 +775,7 @@ inline hipError_t launch_mfma_cfg(const GemmGroup* table, int first, int g, cons
 
 // Big tiles move the fewest bytes per flop, but a launch needs about one tile per CU to use the chip: a single
 // cell (sequential order, or the first and last steps of the diagonal order) has too few 256x256 tiles.
-inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
+constexpr int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
   if (force_cfg >= 0 && force_cfg < MF_NUM_CONFIGS) return force_cfg;
   // a few rows against wide weights (W_K | W_V on the memory rows): the launch streams the weights once and is bound
   // by how many bytes a CU has in flight, so narrow tiles that give every CU two workgroups
@@ -795,12 +795,10 @@ inline int mfma_pick_config(const GemmShape& s, int g, int force_cfg) {
   if (s.epi != EPI_DPFP_READ && tiles_of(64) <= MF_CUS) return s.K > 2 * MF_BK ? 7 : 2;
   if (s.M < 96 || s.N < 96) return 2;
   if (s.epi != EPI_DPFP_READ && tiles_of(128) <= MF_CUS) return 8;
-  const int bn_out = (s.epi == EPI_SWIGLU) ? 128 : 256;
-  const long tiles = (long)g * mfma_m_tiles(s) * ((s.N + bn_out - 1) / bn_out);
-  // measured crossover (1040- and 528-row cells, N = 768 ... 3072, K = 768 ... 8192): 128x128 tiles win up to 128 tiles of
-  // 256x256 (they still fit the chip in one round of two workgroups per CU; 2048 x 2048 at 128 tiles 39.4 us against 48.3), 256x256 tiles
-  // beyond (132 tiles: 768 x 768 29.0 us against 24.4, K 3072 81.1 against 66.8)
-  return (s.M >= 192 && s.N >= 192 && tiles > MF_CUS / 2) ? 5 : 6;
+  // 128x128 tiles as long as all of them are on the chip at once, two workgroups per CU; us per launch, 256 x 256 / 128 x 128 (N = 256 ... 3072, K = 768 ...
+  // 8192): 512 of them (4 x (1040 x 2048, K 2048)) 48.3 / 39.4, 486 ragged ones (135 of 256 x 256: 3 x (1100 x 2300, K 2048)) 47.6 / 41.6, 510 (5 x (2100 x 768),
+  // K 768) 23.9 / 22.0, K 4096 78 / 71; 528 (11 x (1040 x 768), K 768) 24.4 / 28.6, K 3072 66.8 / 81.1, ragged (13 x (500 x 1280), K 1024) 28.0 / 35.6
+  return (s.M >= 192 && s.N >= 192 && tiles_of(128) > 2 * MF_CUS) ? 5 : 6;
 }
 
 // Whole rounds of the chip with 256 x 256 tiles; if what is left fills at most half of another round, it runs as 128 x 128 tiles (four

@@ -43,6 +43,15 @@ def test_partial_round(tmp_path):
           f"{cut}(product(4352, 4352, 192), 1, 5) == 0")          # tiles asked for
 
 
+def test_small_or_big_tiles(tmp_path):
+    """128 x 128 tiles (6) as long as they fit the chip in one round, also where ragged edges make more than a quarter as many of 256 x 256."""
+    pick = lambda g, *dims: f"mfma_pick_config(product({', '.join(map(str, dims))}), {g}, -1)"
+    holds(tmp_path,
+          f"{pick(4, 1040, 2048, 2048)} == 6 && {pick(11, 1040, 768, 768)} == 5",      # 512, 528
+          f"{pick(3, 1100, 2300, 2048)} == 6 && {pick(5, 2100, 768, 768)} == 6",       # 486 and 510: 135 tiles of 256 x 256
+          f"{pick(13, 500, 1280, 1024)} == 5")
+
+
 def test_persistent_tile(tmp_path):
     """Rows that end in a strip of 16 take the persistent 256 x 256 tile also where one M-tile is all that the strip has in front of it, and so do products of
     one or two k-tiles, fewer than its copies are ahead."""

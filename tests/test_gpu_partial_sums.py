@@ -16,7 +16,7 @@ def tile_config():
     P.set_gemm_tile_config(-1)
 
 
-@pytest.mark.parametrize("d_model, seg_len", [(128, 512), (320, 512), (384, 1000), (640, 752), (576, 256)])
+@pytest.mark.parametrize("d_model, seg_len", [(128, 512), (320, 512), (384, 1000), (640, 752), (576, 512)])
 def test_same_bits(tile_config, d_model, seg_len):
     """Twelve sequences in four layers, 48 cells a launch: the default takes 256 x 256 tiles from 320 columns on, 5 everywhere, 6 takes 128 x 128."""
     shape = S.get_shape("tiny").replace(n_layers=4, d_model=d_model, n_heads=d_model // 64, n_kv_heads=d_model // 64, head_dim=64, d_ff=256, seg_len=seg_len,
@@ -41,6 +41,6 @@ def test_oracle():
     want, _, _ = O.armt_forward_sequential(shape, layers, mem_emb, x)
     model = P.Armt(shape, layers, mem_emb, device="cuda:0")
     xd = model.embed(x)
-    hidden, _, _ = model.forward_batched(xd.expand(40, *xd.shape).contiguous())
-    err = [float(np.linalg.norm(h.float().cpu().numpy() - want) / np.linalg.norm(want)) for h in (hidden[0], hidden[39])]
+    hidden, _, _ = model.forward_batched(xd.expand(60, *xd.shape).contiguous())
+    err = [float(np.linalg.norm(h.float().cpu().numpy() - want) / np.linalg.norm(want)) for h in (hidden[0], hidden[59])]
     assert max(err) <= 2e-2, err      # the bound of a bf16 pass
